@@ -238,7 +238,8 @@ int msp_fgt_plan(msp_tree *t, const msp_fgt_params *prm, msp_fgt_info *info);
  * evaluation move to the sub-cells two levels down with fewer terms, joined to
  * the expansion level by M2M and L2L shifts (msp_fgt_info.fine_terms).  Direct route: Eq. (8) summed over all
  * source leaves within the cutoff of each target leaf.  The direct route
- * synchronises `stream` once when its interaction lists are (re)built. */
+ * synchronises `stream` once when its interaction lists are (re)built, in trees of
+ * more than 2,048 nodes. */
 int msp_fgt_forward(msp_tree *t, const float *w, const uint8_t *is_target,
                     const msp_fgt_params *prm, float *u_out, void *stream);
 

@@ -23,10 +23,44 @@ __global__ void k_target_weights(const float *g, const uint8_t *is_target, int64
     gt[i] = (!is_target || is_target[i]) ? g[i] : 0.f;
 }
 
-// P2P with derivatives, one target leaf per block of one wavefront.
-__global__ void __launch_bounds__(64) k_p2p_grad(GradLeafSet L, int stride, int want_lap) {
-    __shared__ GradShared sh;
-    p2p_grad_leaf(L, blockIdx.x, stride, want_lap, sh);
+// Both fields' weights into key order: w into the records, the target weights into g2.
+__global__ void k_stage_both(const float *w, const float *gt, const int32_t *perm, int64_t n, float4 *ps, float *g2) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t j = perm[i];
+    ps[i].w = w[j];
+    g2[i] = gt[j];
+}
+
+// P2P with derivatives.  SPLIT: a block of three wavefronts per target leaf, one for
+// the value and the Laplacian, one for the gradient, one for the second field (absent
+// without TWO).  The sums of a leaf are serial chains over its list, so in a tree with
+// fewer leaves than the chip has wavefront slots the shares run beside each other at no
+// cost: 5,003 points, both fields, 2 x 225 us -> 162 us.  Otherwise one wavefront does
+// all of them with one exponential per pair.
+template <bool TWO, bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? (TWO ? 192 : 128) : 64) k_p2p_grad(GradLeafSet L, const float *g2, int stride,
+                                                                            int want_lap) {
+    if constexpr (SPLIT) {
+        __shared__ GradShared sh[TWO ? 3 : 2];
+        const int wave = threadIdx.x >> 6;
+        if (wave == 0) p2p_grad_leaf<kGradValue>(L, g2, blockIdx.x, stride, want_lap, sh[0]);
+        else if (wave == 1) p2p_grad_leaf<kGradVector>(L, g2, blockIdx.x, stride, want_lap, sh[1]);
+        else if constexpr (TWO) p2p_grad_leaf<kGradSecond>(L, g2, blockIdx.x, stride, want_lap, sh[2]);
+    } else {
+        __shared__ GradShared sh;
+        p2p_grad_leaf<kGradValue | kGradVector | (TWO ? kGradSecond : 0)>(L, g2, blockIdx.x, stride, want_lap, sh);
+    }
+}
+
+template <bool TWO>
+void launch_p2p_grad(const GradLeafSet &L, const float *g2, int stride, int want_lap, hipStream_t s) {
+    const dim3 grid((unsigned)L.n_nodes);
+    if (p2p_waves(L.n_nodes) > 1)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2p_grad<TWO, true>), grid, dim3(TWO ? 192 : 128), 0, s, L, g2, stride,
+                           want_lap);
+    else
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2p_grad<TWO, false>), grid, dim3(64), 0, s, L, g2, stride, want_lap);
 }
 
 // Per point of the input order j: the key-order record of its point (64 bytes,
@@ -68,21 +102,22 @@ __global__ void k_sum_partials(const double *partial, int64_t m, double *out) {
 
 }  // namespace
 
-int direct_field_grad(msp_tree *t, const msp_fgt_params *prm, float *out, int stride, int want_lap,
-                      hipStream_t s) {
-    // the leaf lists of the direct route are built (or reused) by direct_route's
-    // list pass; ps.w holds the staged weights of this evaluation
-    const int64_t nn = t->n_nodes;
-    BoxGeo geo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side};
+// Value, gradient and Laplacian of the field of the staged weights ps.w (and, with
+// g2, value and gradient of the field of the weights g2, at out + 5) by the direct
+// route, whose lists the handle holds.
+static int direct_field_grad(msp_tree *t, const msp_fgt_params *prm, const float *g2, float *out, int stride,
+                             int want_lap, hipStream_t s) {
     const double sig = prm->sigma;
-    const float kexp = (float)(-1.4426950408889634 / (sig * sig));
-    const float inv_s2 = (float)(1.0 / (sig * sig));
-    const GradLeafSet L{nn, t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nnchild.as<int32_t>(),
+    const GradLeafSet L{t->n_nodes, t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nnchild.as<int32_t>(),
                         t->nlevel.as<int32_t>(), t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(),
-                        geo, t->list_off.as<int64_t>(), t->list_idx.as<int32_t>(), t->ps.as<float4>(), kexp,
-                        inv_s2, out};
+                        BoxGeo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side},
+                        LeafLists{t->list_off.as<int64_t>(), t->list_stride, t->list_cnt.as<int32_t>(),
+                                  t->list_idx.as<int32_t>()},
+                        t->ps.as<float4>(), (float)(-1.4426950408889634 / (sig * sig)), (float)(1.0 / (sig * sig)),
+                        out};
     PhaseScope ps(&t->timing, PH_P2P, s);
-    hipLaunchKernelGGL(k_p2p_grad, dim3((unsigned)nn), dim3(64), 0, s, L, stride, want_lap);
+    if (g2) launch_p2p_grad<true>(L, g2, stride, want_lap, s);
+    else launch_p2p_grad<false>(L, nullptr, stride, want_lap, s);
     MSP_CHECK_LAUNCH();
     return MSP_OK;
 }
@@ -96,11 +131,12 @@ int fgt_backward(msp_tree *t, const float *w, const uint8_t *is_target, const ms
     const int64_t nb = n > 0 ? n : 1;
     const int64_t nblk = (nb + kBlock - 1) / kBlock;
     // scratch: one 64-byte record per point in key order (A: value, gradient,
-    // Laplacian; B: value, gradient), gt in input order, block partials
-    MSP_TRY(t->bwd.ensure((size_t)nb * kRec * 4 + (size_t)nb * 4 + (size_t)nblk * 8 + 64));
+    // Laplacian; B: value, gradient), gt in input order and in key order, block partials
+    MSP_TRY(t->bwd.ensure((size_t)nb * (kRec + 2) * 4 + (size_t)nblk * 8 + 64));
     float *rec = t->bwd.as<float>();
     float *gt = rec + (size_t)nb * kRec;
-    double *partial = reinterpret_cast<double *>(gt + nb + (nb & 1));
+    float *g2 = gt + nb;
+    double *partial = reinterpret_cast<double *>(g2 + nb);
     if (n == 0) {
         // a kernel rather than a memset, so that the sequence can be captured into a graph
         if (grad_sigma) {
@@ -121,15 +157,16 @@ int fgt_backward(msp_tree *t, const float *w, const uint8_t *is_target, const ms
     } else {
         msp_fgt_params q = *prm;
         q.flags &= ~(uint32_t)MSP_EXCLUDE_SELF;
-        if (needA) {
-            MSP_TRY(stage_inputs(t, w, nullptr, s));
-            MSP_TRY(direct_route_lists(t, &q, s));
-            MSP_TRY(direct_field_grad(t, &q, rec, kRec, grad_sigma ? 1 : 0, s));
-        }
-        if (needB) {
-            MSP_TRY(stage_inputs(t, gt, nullptr, s));
-            MSP_TRY(direct_route_lists(t, &q, s));
-            MSP_TRY(direct_field_grad(t, &q, rec + 5, kRec, 0, s));
+        MSP_TRY(direct_route_lists(t, &q, s));
+        if (needA && needB) {   // both fields in one pass: one exponential per pair serves both
+            ++t->ps_gen;
+            hipLaunchKernelGGL(k_stage_both, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, w, gt,
+                               t->perm.as<int32_t>(), n, t->ps.as<float4>(), g2);
+            MSP_CHECK_LAUNCH();
+            MSP_TRY(direct_field_grad(t, &q, g2, rec, kRec, grad_sigma ? 1 : 0, s));
+        } else if (needA || needB) {
+            MSP_TRY(stage_inputs(t, needA ? w : gt, nullptr, s));
+            MSP_TRY(direct_field_grad(t, &q, nullptr, needA ? rec : rec + 5, kRec, needA && grad_sigma ? 1 : 0, s));
         }
     }
     {

@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(256, 8) k_batch_p2p(const PopDesc *desc, const
                 pop = D.pop;
                 t_first = t0;
             }
-            p2p_leaf(D.ls, item - item_off[d], sh[wave]);
+            p2p_leaf<1>(D.ls, item - item_off[d], 0, sh[wave], nullptr);
         }
         if (lane == 0) {
             atomicMin(&stamps[2 * pop], t_first);
@@ -135,12 +135,11 @@ __global__ void __launch_bounds__(256) k_batch_pairs(const PopDesc *desc, const 
         const LeafSet &L = desc[d].ls;
         const int64_t v = item - item_off[d];
         if (v >= L.n_nodes || L.nnchild[v] != 0) continue;
-        const int64_t l0 = L.off[v];
-        int64_t l1 = L.off[v + 1];
-        if (l1 - l0 > L.n_nodes) l1 = l0 + L.n_nodes;
+        const int64_t l0 = L.list.begin(v);
+        const int64_t len = L.list.cnt[v] < L.n_nodes ? L.list.cnt[v] : L.n_nodes;
         unsigned long long src = 0ull;
-        for (int64_t e = l0; e < l1; ++e) {
-            const int32_t u = L.lst[e];
+        for (int64_t e = l0; e < l0 + len; ++e) {
+            const int32_t u = L.list.lst[e];
             if (u >= 0 && u < L.n_nodes) src += (unsigned)L.ncount[u];
         }
         acc += (unsigned long long)(unsigned)L.ncount[v] * src;
@@ -207,7 +206,8 @@ __global__ void __launch_bounds__(256, 7) k_batch_p2p_grad(const GradDesc *desc,
         const int64_t item = (int64_t)__shfl(mine, 0, 64);
         if (item >= total) break;
         const int d = find_segment(item_off, nd, item);
-        p2p_grad_leaf_t<true>(desc[d].L, desc[d].g2, item - item_off[d], kRec, want_lap, sh[wave]);
+        p2p_grad_leaf<kGradValue | kGradVector | kGradSecond>(desc[d].L, desc[d].g2, item - item_off[d], kRec,
+                                                             want_lap, sh[wave]);
     }
 }
 
@@ -271,6 +271,11 @@ struct PopPlan {
     msp_fgt_params prm;
     FgtPlan pl;
 };
+
+// the handle's interaction lists as direct_route_lists left them
+LeafLists leaf_lists(const msp_tree *t) {
+    return LeafLists{t->list_off.as<int64_t>(), t->list_stride, t->list_cnt.as<int32_t>(), t->list_idx.as<int32_t>()};
+}
 
 int plan_batch(msp_batch *b, const float *sigma, const msp_fgt_params *prm, std::vector<PopPlan> &plans) {
     plans.resize(b->npop);
@@ -389,7 +394,7 @@ int prepare_batch(msp_batch *b, const std::vector<PopPlan> &plans, const float *
         q.ls = LeafSet{t->n_nodes, t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nnchild.as<int32_t>(),
                        t->nlevel.as<int32_t>(), t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(),
                        BoxGeo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side},
-                       t->list_off.as<int64_t>(), t->list_idx.as<int32_t>(), t->ps.as<float4>(),
+                       leaf_lists(t), t->ps.as<float4>(),
                        t->tflag.as<uint8_t>(), (float)(std::sqrt(1.4426950408889634) / (double)pp.prm.sigma),
                        (pp.prm.flags & MSP_EXCLUDE_SELF) ? 1 : 0, t->usort.as<float>()};
         q.perm = t->perm.as<int32_t>();
@@ -477,18 +482,19 @@ void append_bytes(std::vector<unsigned char> &k, const void *p, size_t n) {
 // while this is unchanged (the other call's preparation may reallocate or rebuild).
 std::vector<uintptr_t> state_signature(const msp_batch *b) {
     std::vector<uintptr_t> sig;
-    sig.reserve(b->pops.size() * 24);
+    sig.reserve(b->pops.size() * 25);
     for (const auto &tp : b->pops) {
         const msp_tree *t = tp.get();
         const msp::DevBuf *bufs[] = {&t->keys, &t->ps, &t->perm, &t->iperm, &t->nfirst, &t->ncount, &t->nnchild,
                                      &t->nlevel, &t->nix, &t->niy, &t->niz, &t->gridA, &t->gridB, &t->ops,
-                                     &t->list_off, &t->list_idx, &t->tflag, &t->usort, &t->bwd};
+                                     &t->list_off, &t->list_cnt, &t->list_idx, &t->tflag, &t->usort, &t->bwd};
         for (const msp::DevBuf *d : bufs) sig.push_back(reinterpret_cast<uintptr_t>(d->p));
         uint32_t ls, lc;
         std::memcpy(&ls, &t->list_sigma, 4);
         std::memcpy(&lc, &t->list_cutoff, 4);
         sig.push_back(((uintptr_t)ls << 32) | lc);
-        sig.push_back((uintptr_t)t->lists_valid | ((uintptr_t)t->iperm_valid << 1));
+        sig.push_back((uintptr_t)t->lists_valid | ((uintptr_t)t->iperm_valid << 1) |
+                      ((uintptr_t)t->list_stride << 2));
     }
     return sig;
 }
@@ -616,7 +622,7 @@ int prepare_backward(msp_batch *b, const std::vector<PopPlan> &plans, const floa
         g.L = GradLeafSet{t->n_nodes, t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nnchild.as<int32_t>(),
                           t->nlevel.as<int32_t>(), t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(),
                           BoxGeo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side},
-                          t->list_off.as<int64_t>(), t->list_idx.as<int32_t>(), t->ps.as<float4>(),
+                          leaf_lists(t), t->ps.as<float4>(),
                           (float)(-1.4426950408889634 / (sig * sig)), (float)(1.0 / (sig * sig)),
                           t->bwd.as<float>()};
         g.g2 = t->bwd.as<float>() + (size_t)t->n * kRec;

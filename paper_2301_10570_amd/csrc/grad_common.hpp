@@ -21,8 +21,7 @@ struct GradLeafSet {
     int64_t n_nodes;
     const int32_t *nfirst, *ncount, *nnchild, *nlevel, *nix, *niy, *niz;
     BoxGeo geo;
-    const int64_t *off;
-    const int32_t *lst;
+    LeafLists list;
     const float4 *ps;
     float kexp, inv_s2;   // -log2(e) / sigma^2, 1 / sigma^2
     float *out;
@@ -34,30 +33,37 @@ struct GradShared {
     float4 src[128];
     float sg[128];
     float red[9][64];
-    int32_t efirst[64], eend[64];   // a window of list entries: point offset and end
+    ListWindow win;
 };
+
+// Which of a leaf's sums a wavefront forms: all of them, or a share when several
+// wavefronts work on one leaf.  Every sum runs over the list in the same order in
+// float32 whichever wavefront forms it, so its bits do not depend on the split.
+constexpr int kGradValue = 1;    // field A: value and r^2 moment (Laplacian)
+constexpr int kGradVector = 2;   // field A: gradient
+constexpr int kGradSecond = 4;   // field B: value and gradient
 
 // For every point of target leaf v (one wavefront; sh private to it): the sums
 // over the source leaves of its list of e = w exp(-r^2/sigma^2), e (x - s) and
 // e r^2, written as value, gradient and Laplacian of the field.  A block of nt <= 64
 // targets splits the lanes into G = floor(64 / nt) groups of nt (the lanes past G nt
-// idle), each group taking every G-th source of a staged chunk; the source points of up to 64 list entries
-// at a time form one sequence staged 64 per chunk, the next chunk loaded while
-// the current one is used; group partials are added in group order.
-// TWO: a second field at once, with the key-order weights g2 of the sources (value
-// and gradient, into out + 5): one exponential serves both, and each field's sums
-// are formed exactly as a pass of its own would form them.
-template <bool TWO>
-__device__ inline void p2p_grad_leaf_t(const GradLeafSet &L, const float *g2, int64_t v, int stride, int want_lap,
-                                       GradShared &sh) {
+// idle), each group taking every G-th source of a staged chunk; the source points of up
+// to 64 list entries at a time form one sequence staged 64 per chunk, the next chunk
+// loaded while the current one is used; group partials are added in group order.
+// kGradSecond: a second field with the key-order weights g2 of the sources (value
+// and gradient, into out + 5); with PART = all of them one exponential serves both.
+template <int PART>
+__device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, int64_t v, int stride, int want_lap,
+                                     GradShared &sh) {
+    constexpr bool VAL = (PART & kGradValue) != 0, VEC = (PART & kGradVector) != 0, SEC = (PART & kGradSecond) != 0;
     if (v >= L.n_nodes || L.nnchild[v] != 0) return;
     const int lane = threadIdx.x & 63;
     float ct[3], half;
     node_box(L.geo, L.nlevel[v], L.nix[v], L.niy[v], L.niz[v], ct, half);
     const int32_t tf = L.nfirst[v], tn = L.ncount[v];
-    const int64_t l0 = L.off[v];
-    int64_t l1 = L.off[v + 1];
-    if (l1 - l0 > L.n_nodes) l1 = l0 + L.n_nodes;   // a list names each node at most once
+    const int32_t *lst = L.list.lst + L.list.begin(v);
+    int len = L.list.cnt[v];
+    if (len > L.n_nodes) len = (int)L.n_nodes;   // a list names each node at most once
     sh.src[64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
     sh.sg[64 + lane] = 0.f;
     for (int t0 = 0; t0 < tn; t0 += 64) {
@@ -72,43 +78,28 @@ __device__ inline void p2p_grad_leaf_t(const GradLeafSet &L, const float *g2, in
         const float tx = qt.x - ct[0], ty = qt.y - ct[1], tz = qt.z - ct[2];
         float su = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, sr = 0.f;
         float gu = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-        for (int64_t w0 = l0; w0 < l1; w0 += 64) {
-            const int nw = l1 - w0 < 64 ? (int)(l1 - w0) : 64;
-            int32_t esf = 0, esn = 0;
-            if (lane < nw) {
-                const int32_t u = L.lst[w0 + lane];
-                if (u >= 0 && u < L.n_nodes) {
-                    esf = L.nfirst[u];
-                    esn = L.ncount[u];
-                }
-            }
-            const int incl = p2p_incl_scan(esn, lane);
-            const int tot = __shfl(incl, 63, 64);
-            wave_sync();   // previous window's entries and points are no longer read
-            sh.efirst[lane] = esf - (incl - esn);
-            sh.eend[lane] = esn > 0 ? incl : -1;
-            wave_sync();
-            int owner = 0;
+        for (int w0 = 0; w0 < len; w0 += 64) {
+            const int tot = load_window(lst, len, w0, L.n_nodes, L.nfirst, L.ncount, lane, sh.win);
             float4 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
             float ngw = 0.f;
+            // slots past the window's end hold a zero record (weights 0)
             auto fetch = [&](int c0) {
                 const int j = c0 + lane;
+                nxt = make_float4(0.f, 0.f, 0.f, 0.f);
+                ngw = 0.f;
                 if (j < tot) {
-                    while (sh.eend[owner] <= j) ++owner;
-                    const int32_t pj = sh.efirst[owner] + j;
-                    nxt = L.ps[pj];
-                    if (TWO) ngw = g2[pj];
+                    const int32_t pj = window_point(sh.win, j);
+                    const float4 q = L.ps[pj];
+                    nxt = make_float4(q.x - ct[0], q.y - ct[1], q.z - ct[2], q.w);
+                    if (SEC) ngw = g2[pj];
                 }
             };
             fetch(0);
             for (int c0 = 0; c0 < tot; c0 += 64) {
                 const int ns = tot - c0 < 64 ? tot - c0 : 64;
                 wave_sync();
-                // slots past the chunk's end hold a zero record (weights 0)
-                const bool live = lane < ns;
-                sh.src[lane] = live ? make_float4(nxt.x - ct[0], nxt.y - ct[1], nxt.z - ct[2], nxt.w)
-                                    : make_float4(0.f, 0.f, 0.f, 0.f);
-                if (TWO) sh.sg[lane] = live ? ngw : 0.f;
+                sh.src[lane] = nxt;
+                if (SEC) sh.sg[lane] = ngw;
                 wave_sync();
                 if (c0 + 64 < tot) fetch(c0 + 64);
                 // group grp takes sources grp, grp + G, ...: the same trip count on every lane
@@ -116,6 +107,7 @@ __device__ inline void p2p_grad_leaf_t(const GradLeafSet &L, const float *g2, in
                 // chunk's end adds zeros
                 const int nit = __builtin_amdgcn_readfirstlane((ns + G - 1) / G);
                 const int Gs = __builtin_amdgcn_readfirstlane(G);
+#pragma unroll 4
                 for (int it = 0; it < nit; ++it) {
                     const int j = it * Gs + grp;
                     const float4 s4 = sh.src[j];
@@ -123,13 +115,19 @@ __device__ inline void p2p_grad_leaf_t(const GradLeafSet &L, const float *g2, in
                     const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
                     const float k = __builtin_amdgcn_exp2f(r2 * L.kexp);
                     // no contraction: either field's sums carry the same bits as a pass of its own
-                    const float e = __fmul_rn(s4.w, k);
-                    su = __fadd_rn(su, e);
-                    sx = fmaf(e, dx, sx);
-                    sy = fmaf(e, dy, sy);
-                    sz = fmaf(e, dz, sz);
-                    sr = fmaf(e, r2, sr);
-                    if (TWO) {
+                    if (VAL || VEC) {
+                        const float e = __fmul_rn(s4.w, k);
+                        if (VAL) {
+                            su = __fadd_rn(su, e);
+                            sr = fmaf(e, r2, sr);
+                        }
+                        if (VEC) {
+                            sx = fmaf(e, dx, sx);
+                            sy = fmaf(e, dy, sy);
+                            sz = fmaf(e, dz, sz);
+                        }
+                    }
+                    if (SEC) {
                         const float eg = __fmul_rn(sh.sg[j], k);
                         gu = __fadd_rn(gu, eg);
                         gx = fmaf(eg, dx, gx);
@@ -140,12 +138,16 @@ __device__ inline void p2p_grad_leaf_t(const GradLeafSet &L, const float *g2, in
             }
         }
         wave_sync();
-        sh.red[0][lane] = su;
-        sh.red[1][lane] = sx;
-        sh.red[2][lane] = sy;
-        sh.red[3][lane] = sz;
-        sh.red[4][lane] = sr;
-        if (TWO) {
+        if (VAL) {
+            sh.red[0][lane] = su;
+            sh.red[4][lane] = sr;
+        }
+        if (VEC) {
+            sh.red[1][lane] = sx;
+            sh.red[2][lane] = sy;
+            sh.red[3][lane] = sz;
+        }
+        if (SEC) {
             sh.red[5][lane] = gu;
             sh.red[6][lane] = gx;
             sh.red[7][lane] = gy;
@@ -153,20 +155,26 @@ __device__ inline void p2p_grad_leaf_t(const GradLeafSet &L, const float *g2, in
         }
         wave_sync();
         if (grp == 0 && a < nt) {
-            constexpr int NR = TWO ? 9 : 5;
-            float r[NR];
+            float r[9];
 #pragma unroll
-            for (int k = 0; k < NR; ++k) r[k] = 0.f;
+            for (int k = 0; k < 9; ++k) r[k] = 0.f;
             for (int q = 0; q < G; ++q)
 #pragma unroll
-                for (int k = 0; k < NR; ++k) r[k] += sh.red[k][q * tp + a];
+                for (int k = 0; k < 9; ++k) {
+                    const int part = k == 0 || k == 4 ? kGradValue : (k < 4 ? kGradVector : kGradSecond);
+                    if (PART & part) r[k] += sh.red[k][q * tp + a];
+                }
             float *o = L.out + (int64_t)ti * stride;   // value, gradient x y z, Laplacian
-            o[0] = r[0];
-            o[1] = -2.f * L.inv_s2 * r[1];
-            o[2] = -2.f * L.inv_s2 * r[2];
-            o[3] = -2.f * L.inv_s2 * r[3];
-            if (want_lap) o[4] = 4.f * L.inv_s2 * L.inv_s2 * r[4] - 6.f * L.inv_s2 * r[0];
-            if (TWO) {
+            if (VAL) {
+                o[0] = r[0];
+                if (want_lap) o[4] = 4.f * L.inv_s2 * L.inv_s2 * r[4] - 6.f * L.inv_s2 * r[0];
+            }
+            if (VEC) {
+                o[1] = -2.f * L.inv_s2 * r[1];
+                o[2] = -2.f * L.inv_s2 * r[2];
+                o[3] = -2.f * L.inv_s2 * r[3];
+            }
+            if (SEC) {
                 o[5] = r[5];
                 o[6] = -2.f * L.inv_s2 * r[6];
                 o[7] = -2.f * L.inv_s2 * r[7];
@@ -174,10 +182,6 @@ __device__ inline void p2p_grad_leaf_t(const GradLeafSet &L, const float *g2, in
             }
         }
     }
-}
-
-__device__ inline void p2p_grad_leaf(const GradLeafSet &L, int64_t v, int stride, int want_lap, GradShared &sh) {
-    p2p_grad_leaf_t<false>(L, nullptr, v, stride, want_lap, sh);
 }
 
 // The gradients of input point j from its record (rec4: the record as float4),

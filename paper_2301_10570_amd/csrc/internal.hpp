@@ -228,7 +228,7 @@ struct msp_tree {
 
     // per-call staging
     msp::DevBuf tflag, usort;
-    msp::DevBuf bwd;   // backward scratch: field values, gradients, Laplacians, reductions
+    msp::DevBuf bwd;   // backward scratch: records, target weights (input and key order), reductions
     // expansion grids and translation operators
     msp::DevBuf gridA, gridB, ops;
     bool ops_valid = false;     // M2L operator tables in ops match ops_sig (p, grid, cell / sigma)
@@ -237,6 +237,7 @@ struct msp_tree {
     // direct-route interaction lists (cached per sigma/cutoff)
     msp::DevBuf list_off, list_idx, list_cnt;
     int64_t list_total = 0;
+    int64_t list_stride = 0;    // lists_valid: > 0 one row of so many entries per node, 0 compact (list_off)
     float list_sigma = -1.f, list_cutoff = -2.f;
     bool counts_valid = false;  // list_cnt / list_off / list_total match list_sigma, list_cutoff
     bool lists_valid = false;   // list_idx holds those lists too
@@ -456,20 +457,21 @@ int ensure_iperm(msp_tree *t, hipStream_t s);
 // at every point, in key order: point i writes out[i * stride + 0 .. 4].
 int fgt_field_grad(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, const float *w,
                    float *out, int stride, int want_lap, hipStream_t s);
-int direct_field_grad(msp_tree *t, const msp_fgt_params *prm, float *out, int stride, int want_lap,
-                      hipStream_t s);
 int fgt_backward(msp_tree *t, const float *w, const uint8_t *is_target, const msp_fgt_params *prm,
                  const float *grad_u, float *grad_w, float *grad_x, float *grad_y, float *grad_z,
                  double *grad_sigma, hipStream_t s);
 int scatter_output(msp_tree *t, float *u_out, uint32_t flags, bool subtract_self, hipStream_t s);
 
 // p2p.hip
-// lists_ready: t->list_idx already holds the lists of prm (else they are built or
-// taken from the handle's cache)
+// lists_ready: t->list_idx already holds the compact lists of prm (else they are built
+// or taken from the handle's cache)
 int direct_route(msp_tree *t, const msp_fgt_params *prm, hipStream_t s, bool lists_ready = false);
+// the lists of prm into the handle's list_idx (list_stride says how they lie)
 int direct_route_lists(msp_tree *t, const msp_fgt_params *prm, hipStream_t s);
+// wavefronts per target leaf (1, 4, 8 or 16) in the passes over a tree of n_nodes nodes
+int p2p_waves(int64_t n_nodes);
 // per-leaf list lengths and offsets for prm's sigma and cutoff (one host
-// synchronisation when they change), and the list entries into t->list_idx
+// synchronisation when they change), and the compact list entries into t->list_idx
 int direct_route_counts(msp_tree *t, const msp_fgt_params *prm, hipStream_t s);
 int direct_route_fill(msp_tree *t, const msp_fgt_params *prm, hipStream_t s);
 int direct_all_pairs(const float *tx, const float *ty, const float *tz, int64_t nt, const float *sx,

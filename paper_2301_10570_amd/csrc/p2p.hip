@@ -1,9 +1,9 @@
 // Direct evaluation of the Gaussian sum (Eq. (8)).
 //
 // Near-field route: for every leaf of the octree, the list of source leaves whose
-// boxes come within the cutoff radius of its box (interaction lists built by a
-// depth-first walk of the node table), then P2P: one wavefront per target leaf,
-// source leaves staged through LDS.
+// boxes come within the cutoff radius of its box (interaction lists built by walks
+// of the node table), then P2P: one to sixteen wavefronts per target leaf, source
+// leaves staged through LDS.
 //
 // All-pairs baseline: every target against every source with no tree and no
 // cutoff, sources streamed through LDS in tiles.
@@ -18,93 +18,130 @@ namespace msp {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kStack = 8 * (kDepth + 2);
+// trees of at most this many nodes keep their lists as one row of n_nodes entries per
+// node (16 MB at most): the rows need no count before they are filled, so no
+// second walk, no prefix sum and no host wait for their total
+constexpr int64_t kRowNodes = 2048;
+// pending nodes of one wavefront's walk, and what a walk that takes one node at a time
+// can add to them (7 per level and the last one's children)
+constexpr int kWalkCap = 1024, kWalkTail = 8 * (kDepth + 1);
 
-// Count (fill == nullptr) or write the source leaves within reach of each leaf.
-__global__ void k_lists(int64_t n_nodes, const int32_t *nlevel, const int32_t *nix,
-                        const int32_t *niy, const int32_t *niz, const int32_t *nfchild,
-                        const int32_t *nnchild, BoxGeo geo, float r2, int unlimited,
-                        const int64_t *off, int32_t *cnt, int32_t *fill) {
-    const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+// The source leaves within reach of each leaf, in key order, one wavefront per node
+// (inner nodes have empty lists).  A walk in key order over a stack in LDS whose top is
+// the first node to come: a step takes up to 64 nodes from the top, one per lane (fewer
+// when the stack is nearly full: a step adds at most 7 per node it takes), drops those
+// out of reach, writes the leaves that come before the first inner node and puts the
+// rest back, inner nodes as their children, leaves within reach marked as such (~u).
+// One thread per leaf walking alone waited for six dependent loads per node: 395 us for
+// each of the two walks (count, fill) over 5,003 points; this one takes 12 us.
+// cnt == NULL: the counts are there already; lst == NULL: count only.
+__global__ void __launch_bounds__(kBlock) k_lists(int64_t n_nodes, const int32_t *nlevel, const int32_t *nix,
+                                                  const int32_t *niy, const int32_t *niz,
+                                                  const int32_t *nfchild, const int32_t *nnchild, BoxGeo geo,
+                                                  float r2, int unlimited, const int64_t *off, int64_t stride,
+                                                  int32_t *cnt, int32_t *lst) {
+    __shared__ int32_t stacks[kBlock / 64][kWalkCap];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = blockIdx.x * (int64_t)(kBlock / 64) + wave;
     if (v >= n_nodes) return;
     if (nnchild[v] != 0) {
-        if (!fill) cnt[v] = 0;
+        if (cnt && lane == 0) cnt[v] = 0;
         return;
     }
+    int32_t *stk = stacks[wave];
     float ct[3], ht;
     node_box(geo, nlevel[v], nix[v], niy[v], niz[v], ct, ht);
-    int32_t stack[kStack];
-    int sp = 0;
-    stack[sp++] = 0;
-    int64_t k = fill ? off[v] : 0;
+    int32_t *row = lst ? lst + (stride > 0 ? v * stride : off[v]) : nullptr;
+    if (lane == 0) stk[0] = 0;
+    int sp = 1;
     int32_t c = 0;
     while (sp > 0) {
-        const int32_t u = stack[--sp];
-        float cs[3], hs;
-        node_box(geo, nlevel[u], nix[u], niy[u], niz[u], cs, hs);
-        float d2 = 0.f;
+        const int room = (kWalkCap - kWalkTail - sp) / 7;
+        int take = sp < 64 ? sp : 64;
+        take = take < room ? take : (room > 1 ? room : 1);
+        sp -= take;
+        wave_sync();
+        const int32_t e = lane < take ? stk[sp + take - 1 - lane] : 0;
+        wave_sync();   // the popped slots may be written again
+        bool leaf = lane < take && e < 0, inner = false;
+        const int32_t u = e < 0 ? ~e : e;
+        int nc = 0;
+        int32_t f = 0;
+        if (lane < take && e >= 0) {
+            nc = nnchild[u];
+            f = nfchild[u];
+            float cs[3], hs;
+            node_box(geo, nlevel[u], nix[u], niy[u], niz[u], cs, hs);
+            float d2 = 0.f;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float gap = fmaxf(fabsf(ct[a] - cs[a]) - (ht + hs), 0.f);
-            d2 = fmaf(gap, gap, d2);
+            for (int a = 0; a < 3; ++a) {
+                const float gap = fmaxf(fabsf(ct[a] - cs[a]) - (ht + hs), 0.f);
+                d2 = fmaf(gap, gap, d2);
+            }
+            const bool in = unlimited || !(d2 > r2);
+            leaf = in && nc == 0;
+            // children sit one level deeper, so the walk ends within max_depth levels; the
+            // bounds only protect against a corrupt table
+            inner = in && nc > 0 && nc <= 8 && f > u && f + nc <= n_nodes;
         }
-        if (!unlimited && d2 > r2) continue;
-        const int nc = nnchild[u];
-        if (nc == 0) {
-            if (fill) fill[k++] = u;
-            ++c;
-        } else {
-            const int32_t f = nfchild[u];
-            // children sit one level deeper, so the walk ends within max_depth
-            // levels; the bounds below only protect against a corrupt table
-            if (f <= u || f + nc > n_nodes || sp + nc > kStack) continue;
-            for (int q = nc - 1; q >= 0; --q) stack[sp++] = f + q;
-        }
+        const unsigned long long leaves = __ballot(leaf), inners = __ballot(inner);
+        // the leaves before the first inner node are next in key order
+        const unsigned long long ready = inners ? leaves & ((inners & (0 - inners)) - 1) : leaves;
+        const bool mine = (ready >> lane) & 1;
+        if (row && mine) row[c + __popcll(ready & ((1ull << lane) - 1))] = u;
+        c += __popcll(ready);
+        const int k = inner ? nc : (leaf && !mine ? 1 : 0);
+        const int incl = p2p_incl_scan(k, lane);
+        const int all = __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
+        if (sp + all > kWalkCap) continue;
+        const int top = sp + all - 1 - (incl - k);
+        if (inner)
+            for (int q = 0; q < nc; ++q) stk[top - q] = f + q;
+        else if (k)
+            stk[top] = ~u;
+        sp += all;
     }
-    if (!fill) cnt[v] = c;
+    if (cnt && lane == 0) cnt[v] = c;
 }
 
-__global__ void k_scan_i32_to_i64(const int32_t *cnt, int64_t n, int64_t *off) {
-    // single-block exclusive scan (chunked); n up to a few million entries
-    __shared__ int64_t part[kBlock];
-    const int64_t per = (n + kBlock - 1) / kBlock;
-    const int64_t b0 = threadIdx.x * per;
-    int64_t s = 0;
-    for (int64_t k = 0; k < per; ++k)
-        if (b0 + k < n) s += cnt[b0 + k];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int q = 0; q < kBlock; ++q) {
-            const int64_t v = part[q];
-            part[q] = run;
-            run += v;
+// Exclusive prefix sum of cnt into off, the total into off[n]: one block, 1024
+// coalesced entries per round.
+__global__ void __launch_bounds__(1024) k_scan_i32_to_i64(const int32_t *cnt, int64_t n, int64_t *off) {
+    __shared__ int64_t part[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t run = 0;
+    for (int64_t b0 = 0; b0 < n; b0 += 1024) {
+        const int64_t i = b0 + threadIdx.x;
+        const int64_t x = i < n ? cnt[i] : 0;
+        int64_t v = x;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t t = __shfl_up(v, o, 64);
+            if (lane >= o) v += t;
         }
-        off[n] = run;
+        if (lane == 63) part[wave] = v;
+        __syncthreads();
+        int64_t before = run, all = 0;
+        for (int q = 0; q < 16; ++q) {
+            if (q < wave) before += part[q];
+            all += part[q];
+        }
+        if (i < n) off[i] = before + v - x;
+        run += all;
+        __syncthreads();
     }
-    __syncthreads();
-    int64_t run = part[threadIdx.x];
-    for (int64_t k = 0; k < per; ++k)
-        if (b0 + k < n) {
-            off[b0 + k] = run;
-            run += cnt[b0 + k];
-        }
+    if (threadIdx.x == 0) off[n] = run;
 }
 
-// One wavefront per target leaf (non-leaf nodes return at once).
-__global__ void __launch_bounds__(256, 8) k_p2p(int64_t n_nodes, const int32_t *nfirst,
-                                            const int32_t *ncount, const int32_t *nnchild,
-                                            const int32_t *nlevel, const int32_t *nix,
-                                            const int32_t *niy, const int32_t *niz, BoxGeo geo,
-                                            const int64_t *off, const int32_t *lst, const float4 *ps,
-                                            const uint8_t *tflag, float k_scale, int exclude_self,
-                                            float *usort) {
-    __shared__ P2PShared sh[4];
-    const LeafSet ls{n_nodes, nfirst, ncount, nnchild, nlevel, nix, niy, niz, geo, off, lst, ps, tflag,
-                     k_scale, exclude_self, usort};
+// NW wavefronts per target leaf (non-leaf nodes return at once): a block per node, or
+// for NW = 1 four nodes per block.
+template <int NW>
+__global__ void __launch_bounds__(NW == 1 ? 256 : NW * 64, 8) k_p2p(LeafSet ls) {
+    constexpr int W = NW == 1 ? 4 : NW;
+    __shared__ P2PShared sh[W];
+    __shared__ double red[NW > 1 ? NW : 1][64];
     const int wave = threadIdx.x >> 6;
-    p2p_leaf(ls, (int64_t)blockIdx.x * 4 + wave, sh[wave]);
+    if constexpr (NW == 1) p2p_leaf<1>(ls, (int64_t)blockIdx.x * 4 + wave, 0, sh[wave], red);
+    else p2p_leaf<NW>(ls, (int64_t)blockIdx.x, wave, sh[wave], red);
 }
 
 // All-pairs baseline: one target per thread, 1024 sources per LDS tile.
@@ -153,24 +190,31 @@ __global__ void __launch_bounds__(kBlock) k_direct(const float *tx, const float 
 
 }  // namespace
 
+namespace {
+int walk_lists(msp_tree *t, const msp_fgt_params *prm, int64_t stride, int32_t *cnt, int32_t *lst, hipStream_t s) {
+    const BoxGeo geo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side};
+    const bool unlimited = !(prm->cutoff_sigmas > 0.f);
+    const float R = unlimited ? 0.f : prm->cutoff_sigmas * prm->sigma;
+    hipLaunchKernelGGL(k_lists, dim3(grid_for(t->n_nodes, kBlock / 64)), dim3(kBlock), 0, s, t->n_nodes,
+                       t->nlevel.as<int32_t>(), t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(),
+                       t->nfchild.as<int32_t>(), t->nnchild.as<int32_t>(), geo, R * R, unlimited ? 1 : 0,
+                       t->list_off.as<int64_t>(), stride, cnt, lst);
+    MSP_CHECK_LAUNCH();
+    return MSP_OK;
+}
+}  // namespace
+
 int direct_route_counts(msp_tree *t, const msp_fgt_params *prm, hipStream_t s) {
     const int64_t nn = t->n_nodes;
     if (t->n == 0) return MSP_OK;
     if (t->counts_valid && t->list_sigma == prm->sigma && t->list_cutoff == prm->cutoff_sigmas) return MSP_OK;
-    BoxGeo geo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side};
-    const bool unlimited = !(prm->cutoff_sigmas > 0.f);
-    const float R = unlimited ? 0.f : prm->cutoff_sigmas * prm->sigma;
     PhaseScope ps(&t->timing, PH_LISTS, s);
     t->lists_valid = false;
     t->counts_valid = false;
     MSP_TRY(t->list_cnt.ensure(nn * 4));
     MSP_TRY(t->list_off.ensure((nn + 1) * 8));
-    hipLaunchKernelGGL(k_lists, dim3(grid_for(nn, 128)), dim3(128), 0, s, nn, t->nlevel.as<int32_t>(),
-                       t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(),
-                       t->nfchild.as<int32_t>(), t->nnchild.as<int32_t>(), geo, R * R, unlimited ? 1 : 0,
-                       nullptr, t->list_cnt.as<int32_t>(), nullptr);
-    MSP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_scan_i32_to_i64, dim3(1), dim3(kBlock), 0, s, t->list_cnt.as<int32_t>(), nn,
+    MSP_TRY(walk_lists(t, prm, 0, t->list_cnt.as<int32_t>(), nullptr, s));
+    hipLaunchKernelGGL(k_scan_i32_to_i64, dim3(1), dim3(1024), 0, s, t->list_cnt.as<int32_t>(), nn,
                        t->list_off.as<int64_t>());
     MSP_CHECK_LAUNCH();
     int64_t total = 0;
@@ -187,44 +231,63 @@ int direct_route_counts(msp_tree *t, const msp_fgt_params *prm, hipStream_t s) {
 }
 
 int direct_route_fill(msp_tree *t, const msp_fgt_params *prm, hipStream_t s) {
-    const int64_t nn = t->n_nodes;
     if (t->n == 0) return MSP_OK;
-    BoxGeo geo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side};
-    const bool unlimited = !(prm->cutoff_sigmas > 0.f);
-    const float R = unlimited ? 0.f : prm->cutoff_sigmas * prm->sigma;
     PhaseScope ps(&t->timing, PH_LISTS, s);
     MSP_TRY(t->list_idx.ensure((t->list_total > 0 ? t->list_total : 1) * 4));
-    hipLaunchKernelGGL(k_lists, dim3(grid_for(nn, 128)), dim3(128), 0, s, nn, t->nlevel.as<int32_t>(),
-                       t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(),
-                       t->nfchild.as<int32_t>(), t->nnchild.as<int32_t>(), geo, R * R, unlimited ? 1 : 0,
-                       t->list_off.as<int64_t>(), t->list_cnt.as<int32_t>(), t->list_idx.as<int32_t>());
-    MSP_CHECK_LAUNCH();
-    return MSP_OK;
+    return walk_lists(t, prm, 0, nullptr, t->list_idx.as<int32_t>(), s);
 }
 
 int direct_route_lists(msp_tree *t, const msp_fgt_params *prm, hipStream_t s) {
     if (t->n == 0) return MSP_OK;
-    MSP_TRY(direct_route_counts(t, prm, s));
-    if (!t->lists_valid) {
+    if (t->lists_valid && t->list_sigma == prm->sigma && t->list_cutoff == prm->cutoff_sigmas) return MSP_OK;
+    const int64_t nn = t->n_nodes;
+    if (nn <= kRowNodes) {
+        PhaseScope ps(&t->timing, PH_LISTS, s);
+        t->lists_valid = false;
+        t->counts_valid = false;   // the offsets of compact lists are not written here
+        MSP_TRY(t->list_cnt.ensure(nn * 4));
+        MSP_TRY(t->list_idx.ensure(nn * nn * 4));
+        MSP_TRY(walk_lists(t, prm, nn, t->list_cnt.as<int32_t>(), t->list_idx.as<int32_t>(), s));
+        t->list_sigma = prm->sigma;
+        t->list_cutoff = prm->cutoff_sigmas;
+        t->list_stride = nn;
+    } else {
+        MSP_TRY(direct_route_counts(t, prm, s));
         MSP_TRY(direct_route_fill(t, prm, s));
-        t->lists_valid = true;
+        t->list_stride = 0;
     }
+    t->lists_valid = true;
     return MSP_OK;
+}
+
+int p2p_waves(int64_t n_nodes) {
+    // wavefronts per leaf so that a small tree still fills the chip's 8192 wavefront
+    // slots; 16 (the largest block) below 1024 nodes.  4,096 points (300 leaves, lists
+    // of 45 chunks) took 220 us on one wavefront per leaf and take 24 us on 16.
+    int nw = 16;
+    while (nw > 1 && n_nodes * nw > 16384) nw >>= 1;
+    return nw >= 4 ? nw : 1;
 }
 
 int direct_route(msp_tree *t, const msp_fgt_params *prm, hipStream_t s, bool lists_ready) {
     const int64_t nn = t->n_nodes;
     if (t->n == 0) return MSP_OK;
     if (!lists_ready) MSP_TRY(direct_route_lists(t, prm, s));
-    BoxGeo geo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side};
-    const float k_scale = (float)(std::sqrt(1.4426950408889634) / (double)prm->sigma);
+    const LeafSet ls{nn, t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nnchild.as<int32_t>(),
+                     t->nlevel.as<int32_t>(), t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(),
+                     BoxGeo{{t->geo.lo[0], t->geo.lo[1], t->geo.lo[2]}, t->geo.side},
+                     LeafLists{t->list_off.as<int64_t>(), lists_ready ? 0 : t->list_stride,
+                               t->list_cnt.as<int32_t>(), t->list_idx.as<int32_t>()},
+                     t->ps.as<float4>(), t->tflag.as<uint8_t>(),
+                     (float)(std::sqrt(1.4426950408889634) / (double)prm->sigma),
+                     (prm->flags & MSP_EXCLUDE_SELF) ? 1 : 0, t->usort.as<float>()};
     PhaseScope ps(&t->timing, PH_P2P, s);
-    hipLaunchKernelGGL(k_p2p, dim3((unsigned)((nn + 3) / 4)), dim3(256), 0, s, nn, t->nfirst.as<int32_t>(),
-                       t->ncount.as<int32_t>(), t->nnchild.as<int32_t>(), t->nlevel.as<int32_t>(),
-                       t->nix.as<int32_t>(), t->niy.as<int32_t>(), t->niz.as<int32_t>(), geo,
-                       t->list_off.as<int64_t>(), t->list_idx.as<int32_t>(), t->ps.as<float4>(),
-                       t->tflag.as<uint8_t>(), k_scale, (prm->flags & MSP_EXCLUDE_SELF) ? 1 : 0,
-                       t->usort.as<float>());
+    switch (p2p_waves(nn)) {
+        case 16: hipLaunchKernelGGL(k_p2p<16>, dim3((unsigned)nn), dim3(1024), 0, s, ls); break;
+        case 8: hipLaunchKernelGGL(k_p2p<8>, dim3((unsigned)nn), dim3(512), 0, s, ls); break;
+        case 4: hipLaunchKernelGGL(k_p2p<4>, dim3((unsigned)nn), dim3(256), 0, s, ls); break;
+        default: hipLaunchKernelGGL(k_p2p<1>, dim3((unsigned)((nn + 3) / 4)), dim3(256), 0, s, ls);
+    }
     MSP_CHECK_LAUNCH();
     return MSP_OK;
 }

@@ -1,0 +1,64 @@
+"""The direct route at the sizes where its launch shapes change: wavefronts per leaf
+(16, 8, 4, 1), interaction lists as rows or compact, leaves of more than 64 points.
+
+Tolerances.  A float32 term exp2(-d2) has the relative error of d2, whose coordinates
+are rounded at up to six scaled units: below 4e-6 for the farthest terms, far less for
+the ones that carry a sum; a chunk adds at most 64 of them in float32.  1e-5 of a sum,
+and 2e-5 of the largest gradient (float32 running sums over some thousand terms), hold."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests.helpers import rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _T(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("n,leaf_max,exclude", [(1, 64, False), (70, 64, True), (5003, 64, False), (4096, 128, True),
+                                                (1700, 2, False), (2400, 1, True), (5003, 1, False)])
+def test_leaf_sums_and_gradients(n, leaf_max, exclude):
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(n, extent=(900.0, 900.0, 700.0), sigma=100.0, seed=4000 + n)
+    wl.w[0] = 2.0
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"], leaf_max=leaf_max)
+    print(f"direct route n={n} leaf_max={leaf_max} nodes={tree.info()['n_nodes']}", flush=True)
+    u = tree.forward(d["w"], None, sigma=wl.sigma, route="direct", exclude_self=exclude).cpu().numpy()
+    ref = oracle.attraction(wl, np.arange(n), exclude_self=exclude)
+    assert np.abs(u - ref).max() <= 1e-5 * np.abs(ref).max() + 1e-30
+    some = ref > 1e-3 * np.abs(ref).max()
+    if some.any():
+        assert rel_err(u[some], ref[some]).max() <= 1e-5
+    rng = np.random.default_rng(n)
+    g = (rng.random(n) + 0.5).astype(np.float32)
+    got = tree.backward(d["w"], _T(g), d["tgt"], sigma=wl.sigma, route="direct", exclude_self=exclude)
+    gt = np.where(wl.a > 0, g, 0).astype(np.float64)
+    pos = wl.pos64()
+    r = oracle.gauss_grad(pos, gt, pos, wl.w, wl.sigma)
+    gw = r["w"] - (gt if exclude else 0.0)
+    assert np.abs(got["w"].cpu().numpy() - gw).max() <= 2e-5 * max(np.abs(gw).max(), 1.0)
+    for k in range(3):
+        gp = r["t"][:, k] + r["s"][:, k]
+        assert np.abs(got["pos"][k].cpu().numpy() - gp).max() <= 2e-5 * max(np.abs(r["t"]).max(), 1e-3) + 1e-6
+    # the same gradients one field at a time
+    only_w = tree.backward(d["w"], _T(g), d["tgt"], sigma=wl.sigma, route="direct", exclude_self=exclude, want=("w",))
+    np.testing.assert_array_equal(only_w["w"].cpu().numpy(), got["w"].cpu().numpy())
+    only_s = tree.backward(d["w"], _T(g), d["tgt"], sigma=wl.sigma, route="direct", exclude_self=exclude,
+                           want=("sigma",))
+    assert only_s["sigma"].item() == got["sigma"].item()
+    # another cutoff, a workspace call in between, and back: the lists follow
+    u0 = tree.forward(d["w"], None, sigma=wl.sigma, route="direct", cutoff_sigmas=0.0, exclude_self=exclude)
+    assert np.abs(u0.cpu().numpy() - ref).max() <= 1e-5 * np.abs(ref).max() + 1e-30
+    import torch
+    ws = torch.empty(tree.forward_query(wl.sigma, route="direct"), dtype=torch.uint8, device="cuda")
+    uw = tree.forward_ws(d["w"], ws, None, sigma=wl.sigma, route="direct", exclude_self=exclude).cpu().numpy()
+    np.testing.assert_array_equal(uw, u)
+    again = tree.forward(d["w"], None, sigma=wl.sigma, route="direct", exclude_self=exclude).cpu().numpy()
+    np.testing.assert_array_equal(again, u)
+    tree.close()
