@@ -144,48 +144,74 @@ __global__ void __launch_bounds__(NW == 1 ? 256 : NW * 64, 8) k_p2p(LeafSet ls) 
     else p2p_leaf<NW>(ls, (int64_t)blockIdx.x, wave, sh[wave], red);
 }
 
-// All-pairs baseline: one target per thread, 1024 sources per LDS tile.
-constexpr int kDirTile = 1024;
-__global__ void __launch_bounds__(kBlock) k_direct(const float *tx, const float *ty, const float *tz,
-                                                   int64_t nt, const float *sx, const float *sy,
-                                                   const float *sz, const float *w, int64_t ns,
-                                                   float neg_c, float *u) {
-    __shared__ float4 tile[kDirTile];
-    const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+// All-pairs baseline.  A block of sixteen wavefronts takes T targets; a wavefront's
+// lanes split into 64 / T groups, and the sources go round the wavefronts in chunks of
+// 128, staged in LDS by the wavefront that uses them (no block barrier until the end).
+// Bound by the vector units (ten issues and one exponential per pair).  With one target
+// per thread and every source in each block, 16,384 targets made 64 blocks on 256
+// compute units: 7.38 ms against 262,144 sources (5.8e11 pairs/s).
+constexpr int kDirWaves = 16, kDirChunk = 128;
+template <int T>
+__global__ void __launch_bounds__(kDirWaves * 64, 8) k_direct(const float *tx, const float *ty, const float *tz,
+                                                              int64_t nt, const float *sx, const float *sy,
+                                                              const float *sz, const float *w, int64_t ns,
+                                                              float neg_c, float *u) {
+    constexpr int G = 64 / T;                        // source groups of a wavefront
+    constexpr int STEPS = kDirChunk / G;             // sources of a group in a chunk
+    constexpr int U = STEPS < 4 ? STEPS : 4;         // independent partial sums
+    __shared__ float4 tile[kDirWaves][kDirChunk];
+    __shared__ double red[kDirWaves][T];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int grp = lane / T;
+    const int64_t i = blockIdx.x * (int64_t)T + lane % T;
     const bool valid = i < nt;
     const float x = valid ? tx[i] : 0.f, y = valid ? ty[i] : 0.f, z = valid ? tz[i] : 0.f;
-    float total = 0.f, comp = 0.f;
-    for (int64_t s0 = 0; s0 < ns; s0 += kDirTile) {
-        const int cnt = ns - s0 < kDirTile ? (int)(ns - s0) : kDirTile;
-        __syncthreads();
-        for (int e = threadIdx.x; e < kDirTile; e += kBlock) {
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (e < cnt) v = make_float4(sx[s0 + e], sy[s0 + e], sz[s0 + e], w[s0 + e]);
-            tile[e] = v;
+    double total = 0.0;
+    float4 nxt[2];
+    // records past the last source have w = 0, so a full chunk can be summed
+    auto fetch = [&](int64_t s0) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int64_t j = s0 + k * 64 + lane;
+            nxt[k] = j < ns ? make_float4(sx[j], sy[j], sz[j], w[j]) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        __syncthreads();
-        float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
-        // the padded tail has w = 0, so the full tile can be summed
-#pragma unroll 4
-        for (int j = 0; j < kDirTile; j += 4) {
-            float4 a = tile[j], b = tile[j + 1], c = tile[j + 2], d = tile[j + 3];
-            float dx, dy, dz;
-            dx = x - a.x; dy = y - a.y; dz = z - a.z;
-            p0 = fmaf(a.w, __builtin_amdgcn_exp2f(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) * neg_c), p0);
-            dx = x - b.x; dy = y - b.y; dz = z - b.z;
-            p1 = fmaf(b.w, __builtin_amdgcn_exp2f(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) * neg_c), p1);
-            dx = x - c.x; dy = y - c.y; dz = z - c.z;
-            p2 = fmaf(c.w, __builtin_amdgcn_exp2f(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) * neg_c), p2);
-            dx = x - d.x; dy = y - d.y; dz = z - d.z;
-            p3 = fmaf(d.w, __builtin_amdgcn_exp2f(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) * neg_c), p3);
+    };
+    const int64_t step = (int64_t)kDirWaves * kDirChunk;
+    int64_t s0 = (int64_t)wave * kDirChunk;
+    if (s0 < ns) fetch(s0);
+    for (; s0 < ns; s0 += step) {
+        wave_sync();
+        tile[wave][lane] = nxt[0];
+        tile[wave][64 + lane] = nxt[1];
+        wave_sync();
+        if (s0 + step < ns) fetch(s0 + step);
+        float part[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) part[k] = 0.f;
+#pragma unroll(STEPS / U < 4 ? STEPS / U : 4)
+        for (int it = 0; it < STEPS; it += U) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const float4 q = tile[wave][(it + k) * G + grp];
+                const float dx = x - q.x, dy = y - q.y, dz = z - q.z;
+                part[k] = fmaf(q.w, __builtin_amdgcn_exp2f(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) * neg_c), part[k]);
+            }
         }
-        const float part = (p0 + p1) + (p2 + p3);
-        const float yk = part - comp;
-        const float t = total + yk;
-        comp = (t - total) - yk;
-        total = t;
+        float sum = part[0];
+        if constexpr (U == 4) sum = (part[0] + part[1]) + (part[2] + part[3]);
+        else if constexpr (U == 2) sum = part[0] + part[1];
+        total += (double)sum;
     }
-    if (valid) u[i] = total;
+    // groups, then wavefronts, in a fixed order
+    for (int o = T; o < 64; o <<= 1) total += __shfl_xor(total, o, 64);
+    if (lane < T) red[wave][lane] = total;
+    __syncthreads();
+    if (threadIdx.x < T && valid) {
+        double sum = 0.0;
+#pragma unroll
+        for (int k = 0; k < kDirWaves; ++k) sum += red[k][lane];
+        u[i] = (float)sum;
+    }
 }
 
 }  // namespace
@@ -297,8 +323,16 @@ int direct_all_pairs(const float *tx, const float *ty, const float *tz, int64_t 
                      float *u, hipStream_t s) {
     if (nt == 0) return MSP_OK;
     const float neg_c = (float)(-1.4426950408889634 / ((double)sigma * sigma));
-    hipLaunchKernelGGL(k_direct, dim3(grid_for(nt, kBlock)), dim3(kBlock), 0, s, tx, ty, tz, nt, sx,
-                       sy, sz, w, ns, neg_c, u);
+    // targets per block: 64 once they make four blocks per compute unit, fewer below
+    // (down to 2: 200 targets are then still 100 blocks), so that few targets against
+    // many sources spread over the chip
+#define MSP_DIRECT(T) hipLaunchKernelGGL(k_direct<T>, dim3(grid_for(nt, T)), dim3(kDirWaves * 64), 0, s, tx, ty, \
+                                         tz, nt, sx, sy, sz, w, ns, neg_c, u)
+    if (nt >= 64 * 1024) MSP_DIRECT(64);
+    else if (nt >= 32 * 512) MSP_DIRECT(32);
+    else if (nt >= 8 * 512) MSP_DIRECT(8);
+    else MSP_DIRECT(2);
+#undef MSP_DIRECT
     MSP_CHECK_LAUNCH();
     return MSP_OK;
 }

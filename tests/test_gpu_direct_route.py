@@ -1,5 +1,6 @@
-"""The direct route at the sizes where its launch shapes change: wavefronts per leaf
-(16, 8, 4, 1), interaction lists as rows or compact, leaves of more than 64 points.
+"""The direct route and the all-pairs sum at the sizes where their launch shapes change:
+wavefronts per leaf (16, 8, 4, 1), interaction lists as rows or compact, leaves of more
+than 64 points, and targets per block of the all-pairs sum (2, 8, 32, 64).
 
 Tolerances.  A float32 term exp2(-d2) has the relative error of d2, whose coordinates
 are rounded at up to six scaled units: below 4e-6 for the farthest terms, far less for
@@ -62,3 +63,21 @@ def test_leaf_sums_and_gradients(n, leaf_max, exclude):
     again = tree.forward(d["w"], None, sigma=wl.sigma, route="direct", exclude_self=exclude).cpu().numpy()
     np.testing.assert_array_equal(again, u)
     tree.close()
+
+
+@pytest.mark.parametrize("nt,ns", [(1, 1), (3, 127), (50, 4097), (4095, 129), (4096, 2048), (16383, 130), (16385, 2049),
+                                   (65535, 300), (65537, 127), (7, 0)])
+def test_all_pairs(nt, ns):
+    import paper_2301_10570_amd as msp
+    print(f"all-pairs sum {nt} x {ns}", flush=True)
+    rng = np.random.default_rng(nt + ns)
+    t = rng.random((nt, 3)).astype(np.float32) * 300
+    s = rng.random((ns, 3)).astype(np.float32) * 300
+    w = rng.random(ns).astype(np.float32) + 0.1
+    u = msp.direct_sum(*(_T(t[:, k]) for k in range(3)), *(_T(s[:, k]) for k in range(3)), _T(w), 80.0).cpu().numpy()
+    if ns == 0:
+        assert np.all(u == 0)
+        return
+    pick = np.unique(np.concatenate([np.arange(min(nt, 70)), np.arange(max(0, nt - 70), nt)]))
+    assert rel_err(u[pick], oracle.gauss_sum(t[pick], s, w, 80.0)).max() <= 1e-5
+    assert np.all(np.isfinite(u)) and np.all(u > 0)
