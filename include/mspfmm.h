@@ -363,7 +363,7 @@ int msp_partner_probabilities(msp_tree *t, const float *w, const msp_fgt_params 
  * elements, both device float32[n] in input order (>= 0).  prm: sigma, p and
  * cutoff; self pairs are always skipped.  The frontier stays in device memory and
  * every step runs in kernels; the call synchronises `stream` while it sets up
- * (tree topology, box pairs) and at the end, and waits for step k - 2 before it
+ * (numbers of axons, boxes and box pairs) and at the end, and waits for step k - 2 before it
  * launches step k. */
 
 /* One step of msp_partner_descent from the frontier (S_in[k], T_in[k]), k < m

@@ -70,6 +70,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 namespace msp {
@@ -127,6 +128,7 @@ enum Ctr : int {
     C_STEPS,     // steps that started with a non-empty frontier
     C_ERR,       // a table would have exceeded its capacity, or an absent octant was chosen
     C_LIVE,      // units of the step whose choice kept their pair
+    C_TICKET,    // blocks of the step's last kernel that are done
     C_COUNT = 16
 };
 
@@ -155,15 +157,45 @@ __global__ void __launch_bounds__(256) k_desc_direct(const int64_t *ntask, const
     }
 }
 
-// value of candidate k of a K_LEAF or K_SRC unit (FP64, fixed summation order)
-__device__ inline double unit_value(const UnitDesc &U, int k, const double *raw, const float *qa,
-                                    const double *dv, const int64_t *toff, const float *ta, const int64_t *crng) {
+// Value of candidate k of a K_LEAF or K_SRC unit (float64, fixed summation order).  The
+// terms of a unit's tasks lie one after another from dv on (task r0 first; each task
+// ncand terms for K_LEAF, one for K_SRC), so their addresses need no table and the loads
+// of several tasks are in flight together.  K_LEAF: tasks r0 + t0, r0 + t0 + step, ...
+__device__ inline double unit_value(const UnitDesc &U, int k, int t0, int step, const double *dv, const float *ta,
+                                    const int64_t *crng) {
     double v = 0.0;
     if (U.kind == K_LEAF) {
-        for (int64_t t = U.r0; t < U.r1; ++t) v += (double)ta[t] * dv[toff[t] + k];
+        const int64_t n = U.r1 - U.r0;
+        const float *tr = ta + U.r0;
+        const double *dk = dv + k;
+        int64_t t = t0;
+        for (; t + 3 * (int64_t)step < n; t += 4 * (int64_t)step) {
+            double a[4], x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[q] = (double)tr[t + q * (int64_t)step];
+                x[q] = dk[(t + q * (int64_t)step) * U.ncand];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v += a[q] * x[q];
+        }
+#pragma unroll 1
+        for (; t < n; t += step) v += (double)tr[t] * dk[t * U.ncand];
     } else {
         const int64_t b = crng[2 * (U.c0 + k)], e = crng[2 * (U.c0 + k) + 1];
-        for (int64_t t = b; t < e; ++t) v += (double)ta[t] * dv[toff[t]];
+        int64_t t = b;
+        for (; t + 4 <= e; t += 4) {
+            double a[4], x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[q] = (double)ta[t + q];
+                x[q] = dv[t + q - U.r0];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v += a[q] * x[q];
+        }
+#pragma unroll 1
+        for (; t < e; ++t) v += (double)ta[t] * dv[t - U.r0];
     }
     return v;
 }
@@ -182,27 +214,56 @@ __global__ void k_req_count(int64_t nr, const int32_t *rd, int32_t *cnt) {
     if (g < nr) atomicAdd(&cnt[rd[g]], 1);
 }
 
-// exclusive prefix sum of cnt[0 .. n) into off (one block, chunks of 1024)
-__global__ void __launch_bounds__(1024) k_req_scan(int64_t n, const int32_t *cnt, int32_t *off) {
-    __shared__ int32_t part[1024];
-    __shared__ int32_t carry;
-    if (threadIdx.x == 0) carry = 0;
+// Exclusive prefix sum over a block of kScanBlock threads; all: the block's total.
+constexpr int kScanBlock = 1024;
+template <class T>
+__device__ inline T block_scan(T v, T &all) {
+    __shared__ T part[kScanBlock / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    T x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const T t = __shfl_up(x, o, 64);
+        if (lane >= o) x += t;
+    }
+    if (lane == 63) part[wave] = x;
     __syncthreads();
-    for (int64_t c0 = 0; c0 < n; c0 += 1024) {
-        const int64_t g = c0 + threadIdx.x;
-        const int32_t v = g < n ? cnt[g] : 0;
-        part[threadIdx.x] = v;
-        __syncthreads();
-        for (int o = 1; o < 1024; o <<= 1) {
-            const int32_t t = threadIdx.x >= (unsigned)o ? part[threadIdx.x - o] : 0;
-            __syncthreads();
-            part[threadIdx.x] += t;
-            __syncthreads();
-        }
-        if (g < n) off[g] = carry + part[threadIdx.x] - v;
-        __syncthreads();
-        if (threadIdx.x == 0) carry += part[1023];
-        __syncthreads();
+    T before = 0;
+    all = 0;
+#pragma unroll
+    for (int q = 0; q < kScanBlock / 64; ++q) {
+        before += q < wave ? part[q] : 0;
+        all += part[q];
+    }
+    __syncthreads();   // part may be written again
+    return before + x - v;
+}
+
+// Exclusive prefix sum of cnt[0 .. n) into off: kReqParts parts at most, the sum of
+// each first, then every block adds the sums before its part (one block in chunks of
+// 1024 took 440 us over 262,144 neurons, these two take 9 us).
+constexpr int64_t kReqParts = 1024;
+inline int64_t req_part(int64_t n) {   // entries of a part
+    const int64_t per = (n + kReqParts - 1) / kReqParts;
+    return (per + kScanBlock - 1) / kScanBlock * kScanBlock;
+}
+__global__ void __launch_bounds__(kScanBlock) k_req_sums(int64_t n, int64_t per, const int32_t *cnt, int32_t *sums) {
+    const int64_t b0 = blockIdx.x * per;
+    int32_t v = 0, all = 0;
+    for (int64_t k = threadIdx.x; k < per; k += kScanBlock) v += b0 + k < n ? cnt[b0 + k] : 0;
+    block_scan(v, all);
+    if (threadIdx.x == 0) sums[blockIdx.x] = all;
+}
+__global__ void __launch_bounds__(kScanBlock) k_req_scan(int64_t n, int64_t per, const int32_t *cnt,
+                                                         const int32_t *sums, int32_t *off) {
+    const int64_t b0 = blockIdx.x * per;
+    int32_t run = 0, all = 0;
+    block_scan(threadIdx.x < blockIdx.x ? sums[threadIdx.x] : 0, run);   // (at most kReqParts blocks)
+    for (int64_t k = threadIdx.x; k < per; k += kScanBlock) {
+        const int64_t i = b0 + k;
+        const int32_t v = i < n ? cnt[i] : 0;
+        const int32_t before = block_scan(v, all);
+        if (i < n) off[i] = run + before;
+        run += all;
     }
 }
 
@@ -244,6 +305,9 @@ struct BoxArgs {
     const int64_t *pair_off;                      // pairs of axon box s: pair_off[s] .. pair_off[s + 1]
     int32_t *pair_s, *pair_c;                     // axon box, dendrite box of each pair
     double *F;                                    // Att(s, c) of each pair
+    const int64_t *large_off;                     // pairs of s that take a wavefront of their own: their
+    int64_t *large;                               // indices at large_off[s] ..
+    const int64_t *nlarge;                        // and their number over all boxes
     float *A, *M;                                 // per box: A_alpha, Mt_beta (p^3 each)
     const int32_t *nlevel, *nix, *niy, *niz, *nfirst, *ncount, *nfchild, *nnchild;
     double lox, loy, loz, side;
@@ -265,13 +329,37 @@ __device__ inline void box_geom(const BoxArgs &g, int32_t u, double &cx, double 
     half = 0.5 * h;
 }
 
+constexpr int kSmallBox = 64;   // dendrite boxes of up to this many points share wavefronts
+
+// How the pair (s, c) is evaluated: by the expansions, or directly with a wavefront
+// of its own (a dendrite box of more than kSmallBox points), or directly beside other
+// pairs of s.
+__device__ inline bool pair_by_series(const BoxArgs &g, int32_t vs, int32_t vc, int32_t na, int32_t nd,
+                                      const double4 &gs, const double4 &gc) {
+    const double dx = (gs.x - gc.x) * g.inv_sigma, dy = (gs.y - gc.y) * g.inv_sigma, dz = (gs.z - gc.z) * g.inv_sigma;
+    return g.nlevel[vs] >= g.level && g.nlevel[vc] >= g.level && na > kC2 && nd > kC1 &&
+           dx * dx + dy * dy + dz * dz <= kBoxAdmitR * kBoxAdmitR;
+}
+__device__ inline bool pair_is_large(const BoxArgs &g, int32_t s, int32_t c) {
+    const int32_t vs = g.box_node[s], vc = g.box_node[c];
+    return g.ncount[vc] > kSmallBox ||
+           pair_by_series(g, vs, vc, g.box_na[s], g.box_nd[c], g.box_geo[s], g.box_geo[c]);
+}
+
+// a box's pairs and large pairs into the two columns that are scanned into offsets
+__device__ inline void put_counts(const BoxArgs &g, int64_t s, int64_t *cnt, int64_t n, int64_t nl) {
+    cnt[s] = n;
+    cnt[g.nbox + 1 + s] = nl;
+    if (s == 0) cnt[g.nbox] = cnt[2 * g.nbox + 1] = 0;
+}
+
 // One thread per axon box: the dendrite boxes within the cutoff, by a walk from
 // the root (children in key order, so the list of a box is in key order).  With
 // cnt: counts only; otherwise the pairs go to pair_off[s] ...
 __global__ void __launch_bounds__(256) k_box_lists(BoxArgs g, int64_t *cnt) {
     const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (s >= g.nbox) return;
-    int64_t n = 0;
+    int64_t n = 0, nl = 0;
     if (g.box_na[s] > 0) {
         double sx, sy, sz, sh;
         box_geom(g, g.box_node[s], sx, sy, sz, sh);
@@ -292,11 +380,14 @@ __global__ void __launch_bounds__(256) k_box_lists(BoxArgs g, int64_t *cnt) {
             const int32_t bu = g.node_box[u];
             if (bu >= 0) {
                 if (g.box_nd[bu] > 0) {
+                    const bool big = pair_is_large(g, (int32_t)s, bu);
                     if (!cnt) {
                         g.pair_s[base + n] = (int32_t)s;
                         g.pair_c[base + n] = bu;
+                        if (big) g.large[g.large_off[s] + nl] = base + n;
                     }
                     ++n;
+                    nl += big;
                 }
                 continue;
             }
@@ -304,7 +395,7 @@ __global__ void __launch_bounds__(256) k_box_lists(BoxArgs g, int64_t *cnt) {
             for (int k = nc - 1; k >= 0 && sp < kBoxStack; --k) stk[sp++] = fc + k;
         }
     }
-    if (cnt) cnt[s] = n;
+    if (cnt) put_counts(g, s, cnt, n, nl);
 }
 
 // One wavefront per axon box: every dendrite box within the cutoff, tested 64 at
@@ -314,7 +405,7 @@ __global__ void __launch_bounds__(256) k_box_lists_all(BoxArgs g, int64_t *cnt) 
     const int lane = threadIdx.x & 63;
     const int64_t s = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (s >= g.nbox) return;
-    int64_t n = 0;
+    int64_t n = 0, nl = 0;
     if (g.box_na[s] > 0) {
         const double4 gs = g.box_geo[s];
         const int64_t base = cnt ? 0 : g.pair_off[s];
@@ -330,15 +421,19 @@ __global__ void __launch_bounds__(256) k_box_lists_all(BoxArgs g, int64_t *cnt) 
                 ok = gx * gx + gy * gy + gz * gz <= g.cut * g.cut;
             }
             const uint64_t mask = __ballot(ok);
+            const bool big = ok && pair_is_large(g, (int32_t)s, (int32_t)c);
+            const uint64_t bigs = __ballot(big);
             if (!cnt && ok) {
                 const int64_t pos = base + n + __popcll(mask & below);
                 g.pair_s[pos] = (int32_t)s;
                 g.pair_c[pos] = (int32_t)c;
+                if (big) g.large[g.large_off[s] + nl + __popcll(bigs & below)] = pos;
             }
             n += __popcll(mask);
+            nl += __popcll(bigs);
         }
     }
-    if (cnt && lane == 0) cnt[s] = n;
+    if (cnt && lane == 0) put_counts(g, s, cnt, n, nl);
 }
 
 // One wavefront per box whose unit this step is a K_BOX unit (box_stamp): its
@@ -379,13 +474,15 @@ __global__ void __launch_bounds__(256) k_box_partials(BoxArgs g, const uint64_t 
     }
 }
 
-// One wavefront per box at or below the box level: A_alpha (weights w) when the
+// One block per box at or below the box level: A_alpha (weights w) when the
 // box holds more than c1 dendrites, Mt_beta (weights a) when it holds more than
 // c2 axons, both about the box centre; the points pass through LDS 64 at a time
-// as their powers per axis.
+// as their powers per axis, and the coefficients are spread over four wavefronts
+// (each a serial sum over the box's points: one wavefront per box took 171 us on boxes
+// of up to 600 points).
 template <int P>
-__global__ void __launch_bounds__(64) k_box_moments(BoxArgs g) {
-    constexpr int P3 = P * P * P, PER = (P3 + 63) / 64, ROW = 3 * P + 2;
+__global__ void __launch_bounds__(256) k_box_moments(BoxArgs g) {
+    constexpr int P3 = P * P * P, PER = (P3 + 255) / 256, ROW = 3 * P + 2;
     const int64_t b = blockIdx.x;
     const int lane = threadIdx.x;
     const int32_t v = g.box_node[b];
@@ -400,7 +497,7 @@ __global__ void __launch_bounds__(64) k_box_moments(BoxArgs g) {
     float accA[PER], accM[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int m = lane + 64 * k < P3 ? lane + 64 * k : 0;
+        const int m = lane + 256 * k < P3 ? lane + 256 * k : 0;
         ia[k] = m % P;
         ib[k] = P + (m / P) % P;
         ic[k] = 2 * P + m / (P * P);
@@ -410,25 +507,27 @@ __global__ void __launch_bounds__(64) k_box_moments(BoxArgs g) {
     const int32_t f = g.nfirst[v], cnt = g.ncount[v];
     for (int32_t c0 = 0; c0 < cnt; c0 += 64) {
         const int32_t j = c0 + lane;
-        float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-        float aj = 0.f;
-        if (j < cnt) {
-            q = g.ps[f + j];
-            aj = g.akey[f + j];
-        }
-        float *r = pw + lane * ROW;
-        const float y[3] = {(q.x - fx) * is, (q.y - fy) * is, (q.z - fz) * is};
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            float t = 1.f;
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                r[d * P + k] = t;
-                t *= y[d];
+        if (lane < 64) {
+            float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+            float aj = 0.f;
+            if (j < cnt) {
+                q = g.ps[f + j];
+                aj = g.akey[f + j];
             }
+            float *r = pw + lane * ROW;
+            const float y[3] = {(q.x - fx) * is, (q.y - fy) * is, (q.z - fz) * is};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                float t = 1.f;
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    r[d * P + k] = t;
+                    t *= y[d];
+                }
+            }
+            r[3 * P] = q.w;
+            r[3 * P + 1] = aj;
         }
-        r[3 * P] = q.w;
-        r[3 * P + 1] = aj;
         __syncthreads();
         const int m = cnt - c0 < 64 ? cnt - c0 : 64;
         for (int jj = 0; jj < m; ++jj) {
@@ -445,7 +544,7 @@ __global__ void __launch_bounds__(64) k_box_moments(BoxArgs g) {
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int m = lane + 64 * k;
+        const int m = lane + 256 * k;
         if (m >= P3) continue;
         const int ax = ia[k], ay = ib[k] - P, az = ic[k] - 2 * P;
         float fact = 1.f;
@@ -462,131 +561,314 @@ __device__ inline double wave_sum_d(double x) {
     return x;
 }
 
-// One wavefront per box pair: Att(s, c) by the expansions (the double series,
-// contracted one axis at a time in LDS) or directly (float32 terms relative to
-// the pair's closest approach, float64 sums).
-template <int P>
-__global__ void __launch_bounds__(64) k_box_pair_values(BoxArgs g, int64_t npair) {
-    constexpr int P2 = P * P, P3 = P2 * P, NH = 2 * P - 1;
-    const int64_t k = blockIdx.x;
-    const int lane = threadIdx.x;
-    if (k >= npair) return;
-    const int32_t s = g.pair_s[k], c = g.pair_c[k];
-    const int32_t vs = g.box_node[s], vc = g.box_node[c];
-    double sx, sy, sz, sh, cx, cy, cz, ch;
-    box_geom(g, vs, sx, sy, sz, sh);
-    box_geom(g, vc, cx, cy, cz, ch);
-    const double dx = (sx - cx) * g.inv_sigma, dy = (sy - cy) * g.inv_sigma, dz = (sz - cz) * g.inv_sigma;
-    const bool expo = g.nlevel[vs] >= g.level && g.nlevel[vc] >= g.level && g.box_na[s] > kC2 &&
-                      g.box_nd[c] > kC1 && dx * dx + dy * dy + dz * dz <= kBoxAdmitR * kBoxAdmitR;
-    const int32_t fs = g.nfirst[vs], ns = g.ncount[vs];
-    double val = 0.0;
-    if (expo) {
-        __shared__ float sA[P3], sM[P3], sX[P3];
-        __shared__ float hh[3][NH + 1];
-        for (int m = lane; m < P3; m += 64) {
-            sA[m] = g.A[(int64_t)c * P3 + m];
-            sM[m] = g.M[(int64_t)s * P3 + m];
+// The direct sum of a pair: exp(-d^2 / sigma^2) = exp(-g^2 / sigma^2)
+// exp(-(d^2 - g^2) / sigma^2) with g the gap between the boxes (d >= g): the second
+// factor in float32 (each term to about 1e-5 at |d| = 6 sigma), the first once per pair
+// in float64.
+__device__ inline double pair_gap2(const double4 &gs, const double4 &gc) {
+    const double gx = fmax(fabs(gs.x - gc.x) - gs.w - gc.w, 0.0), gy = fmax(fabs(gs.y - gc.y) - gs.w - gc.w, 0.0),
+                 gz = fmax(fabs(gs.z - gc.z) - gs.w - gc.w, 0.0);
+    return gx * gx + gy * gy + gz * gz;
+}
+__device__ inline float pair_exp(const float4 &t, const float4 &q, float g2, float ks) {
+    const float ex = t.x - q.x, ey = t.y - q.y, ez = t.z - q.z;
+    return __builtin_amdgcn_exp2f((g2 - (ex * ex + ey * ey + ez * ez)) * ks);
+}
+
+// row + w e, the product rounded before the addition
+__device__ inline float add_term(float row, float w, float e) {
+#pragma clang fp contract(off)
+    const float r = w * e;
+    return row + r;
+}
+
+// The axon points [i0, min(i0 + cap, ns)) of the node at fs with a > 0, in order, into
+// ax (position, a) and key (key-order index); returns how many.  One wavefront.
+__device__ inline int stage_axons(const BoxArgs &g, int32_t fs, int32_t ns, int32_t i0, int cap, int lane, float4 *ax,
+                                  int32_t *key) {
+    int n = 0;
+    for (int32_t c0 = i0; c0 < ns && c0 < i0 + cap; c0 += 64) {
+        const int32_t i = c0 + lane;
+        const float a = i < ns && i < i0 + cap ? g.akey[fs + i] : 0.f;
+        const uint64_t mask = __ballot(a != 0.f);
+        if (a != 0.f) {
+            const int at = n + __popcll(mask & ((1ull << lane) - 1));
+            const float4 t = g.ps[fs + i];
+            ax[at] = make_float4(t.x, t.y, t.z, a);
+            key[at] = fs + i;
         }
-        if (lane < 3) {   // h_0 .. h_{2p-2} at the centre offset, by the recurrence in FP64
-            const double y = lane == 0 ? dx : lane == 1 ? dy : dz;
-            double h0 = exp(-y * y), h1 = 2.0 * y * h0;
-            hh[lane][0] = (float)h0;
-            if (NH > 1) hh[lane][1] = (float)h1;
-            for (int n = 1; n + 1 < NH; ++n) {
-                const double h2 = 2.0 * y * h1 - 2.0 * n * h0;
-                hh[lane][n + 1] = (float)h2;
-                h0 = h1;
-                h1 = h2;
-            }
-        }
-        __syncthreads();
-        // X[az][ay][bx] = sum_ax A[az][ay][ax] h(ax + bx, dx)
-        for (int m = lane; m < P3; m += 64) {
-            const int bx = m % P, row = m / P;
-            float acc = 0.f;
-#pragma unroll
-            for (int ax = 0; ax < P; ++ax) acc = fmaf(sA[row * P + ax], hh[0][ax + bx], acc);
-            sX[m] = acc;
-        }
-        __syncthreads();
-        // Y[az][by][bx] = sum_ay X[az][ay][bx] h(ay + by, dy), into sA
-        for (int m = lane; m < P3; m += 64) {
-            const int bx = m % P, by = (m / P) % P, az = m / P2;
-            float acc = 0.f;
-#pragma unroll
-            for (int ay = 0; ay < P; ++ay) acc = fmaf(sX[(az * P + ay) * P + bx], hh[1][ay + by], acc);
-            sA[m] = acc;
-        }
-        __syncthreads();
-        // sum_beta Mt[bz][by][bx] sum_az Y[az][by][bx] h(az + bz, dz)
-        float part = 0.f;
-        for (int m = lane; m < P3; m += 64) {
-            const int bx = m % P, by = (m / P) % P, bz = m / P2;
-            float z = 0.f;
-#pragma unroll
-            for (int az = 0; az < P; ++az) z = fmaf(sA[(az * P + by) * P + bx], hh[2][az + bz], z);
-            part = fmaf(z, sM[m], part);
-        }
-        val = wave_sum_d((double)part);
-        if (s == c) {   // the series includes the pairs j = i: a_i w_i K(0) each
-            double self = 0.0;
-            for (int32_t i = lane; i < ns; i += 64) self += (double)g.akey[fs + i] * (double)g.ps[fs + i].w;
-            val -= wave_sum_d(self);
-        }
-    } else {
-        // exp(-d^2 / sigma^2) = exp(-g^2 / sigma^2) exp(-(d^2 - g^2) / sigma^2) with g the
-        // gap between the boxes (d >= g): the second factor in float32 (each term
-        // to about 1e-5 at |d| = 6 sigma), the first once per pair in float64
-        const int32_t fc = g.nfirst[vc], nc = g.ncount[vc];
-        const double gx = fmax(fabs(sx - cx) - sh - ch, 0.0), gy = fmax(fabs(sy - cy) - sh - ch, 0.0),
-                     gz = fmax(fabs(sz - cz) - sh - ch, 0.0);
-        const double gap2 = gx * gx + gy * gy + gz * gz;
-        const float g2 = (float)gap2, ks = (float)(g.inv_sigma * g.inv_sigma * 1.4426950408889634);
-        double part = 0.0;
-        for (int32_t j0 = 0; j0 < nc; j0 += 256) {
-            // up to four dendrite points per lane (as many as the box needs), held while
-            // the axon points pass
-            const int nb = nc - j0 >= 256 ? 4 : (nc - j0 + 63) / 64;
-            float4 q[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int32_t j = j0 + lane + 64 * u;
-                q[u] = j < nc ? g.ps[fc + j] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-            for (int32_t i = 0; i < ns; ++i) {
-                const float ai = g.akey[fs + i];
-                if (ai == 0.f) continue;
-                const float4 ti = g.ps[fs + i];
-                float row = 0.f;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (u >= nb) break;
-                    const int32_t j = j0 + lane + 64 * u;
-                    const float ex = ti.x - q[u].x, ey = ti.y - q[u].y, ez = ti.z - q[u].z;
-                    const float e = __builtin_amdgcn_exp2f((g2 - (ex * ex + ey * ey + ez * ez)) * ks);
-                    // (padding lanes hold no point: their e is not a term and may overflow)
-                    row += j < nc && fc + j != fs + i ? q[u].w * e : 0.f;
-                }
-                part += (double)ai * (double)row;
-            }
-        }
-        val = wave_sum_d(part) * exp(-gap2 * g.inv_sigma * g.inv_sigma);
+        n += __popcll(mask);
     }
-    if (lane == 0) g.F[k] = val;
+    return n;
+}
+
+// Direct pairs whose dendrite box holds at most kSmallBox points.  The pairs of axon
+// box s go in windows round the wavefronts of its blocks; the dendrite points of a
+// window's pairs form one sequence, 64 at a time, one per lane, held while the axon
+// points of s pass from LDS; a lane's sum is float64, and the sums of a box's lanes are
+// added by a segmented scan.  A window holds 64 pairs, 16 when s has many axons (its
+// windows are the longest to run).  With one block per pair, most of the time went to
+// starting 1.4 million wavefronts that each set up two boxes for some hundred terms
+// (64 blobs of 4,096 neurons, 3.2e9 terms: 3.89 ms; 0.70 ms here for 0.8e9 of them and
+// 1.28 ms below for the others).
+constexpr int kPairWaves = 4, kAxTile = 512, kPairBlocks = 4;
+__global__ void __launch_bounds__(kPairWaves * 64, 6) k_box_pairs_small(BoxArgs g) {
+    __shared__ float4 ax[kAxTile];
+    __shared__ int32_t axkey[kAxTile];
+    __shared__ int nax;
+    __shared__ int32_t efirst[kPairWaves][64], incl[kPairWaves][64];
+    __shared__ float eg2[kPairWaves][64];
+    __shared__ double sum[kPairWaves][64];
+    const int64_t s = blockIdx.x;
+    if (g.box_na[s] == 0) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t vs = g.box_node[s], fs = g.nfirst[vs], ns = g.ncount[vs];
+    const int32_t na = g.box_na[s];
+    const double4 gs = g.box_geo[s];
+    const float ks = (float)(g.inv_sigma * g.inv_sigma * 1.4426950408889634);
+    const int64_t p0 = g.pair_off[s], p1 = g.pair_off[s + 1];
+    const int W = na > 64 ? 16 : 64;
+    for (int32_t i0 = 0; i0 < ns; i0 += kAxTile) {
+        __syncthreads();
+        if (wave == 0) {
+            const int n = stage_axons(g, fs, ns, i0, kAxTile, lane, ax, axkey);
+            if (lane == 0) nax = n;
+        }
+        __syncthreads();
+        const int n = nax;
+        for (int64_t k0 = p0 + (int64_t)W * (wave + kPairWaves * (int)blockIdx.y); k0 < p1;
+             k0 += (int64_t)W * kPairWaves * gridDim.y) {
+            // this lane's pair of the window
+            const int64_t k = k0 + lane;
+            bool mine = lane < W && k < p1;
+            int32_t c = -1, fc = 0, nc = 0;
+            double gap2 = 0.0;
+            if (mine) {
+                c = g.pair_c[k];
+                const int32_t vc = g.box_node[c];
+                const double4 gc = g.box_geo[c];
+                nc = g.ncount[vc];
+                mine = nc <= kSmallBox && !pair_by_series(g, vs, vc, na, g.box_nd[c], gs, gc);
+                if (mine) {
+                    fc = g.nfirst[vc];
+                    gap2 = pair_gap2(gs, gc);
+                } else {
+                    nc = 0;
+                }
+            }
+            int in = nc;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(in, o, 64);
+                if (lane >= o) in += t;
+            }
+            const int tot = __builtin_amdgcn_readfirstlane(__shfl(in, 63, 64));
+            if (tot == 0) continue;
+            wave_sync();
+            efirst[wave][lane] = fc - (in - nc);
+            incl[wave][lane] = in;
+            eg2[wave][lane] = (float)gap2;
+            sum[wave][lane] = 0.0;
+            wave_sync();
+            const uint64_t self = __ballot(mine && c == (int32_t)s);
+            const int es = self ? __ffsll((unsigned long long)self) - 1 : -1;   // the window's entry for s itself
+            for (int c0 = 0; c0 < tot; c0 += 64) {
+                const int j = c0 + lane;
+                int e = 0;
+                float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+                int32_t jk = -1;
+                if (j < tot) {
+#pragma unroll
+                    for (int st = 32; st > 0; st >>= 1) e = incl[wave][e + st - 1] <= j ? e + st : e;
+                    jk = efirst[wave][e] + j;
+                    q = g.ps[jk];
+                } else {
+                    // idle lanes repeat a point of the chunk with no weight (their terms stay finite)
+                    e = 64;
+                    const int j1 = tot - 1;
+                    int e1 = 0;
+#pragma unroll
+                    for (int st = 32; st > 0; st >>= 1) e1 = incl[wave][e1 + st - 1] <= j1 ? e1 + st : e1;
+                    q = g.ps[efirst[wave][e1] + j1];
+                    q.w = 0.f;
+                    jk = e1;   // (its gap)
+                }
+                const float g2 = eg2[wave][e < 64 ? e : jk];
+                double part = 0.0;
+                if (__ballot(e == es) != 0) {
+#pragma unroll 2
+                    for (int i = 0; i < n; ++i) {
+                        const float4 t = ax[i];
+                        const float r = q.w * pair_exp(t, q, g2, ks);
+                        part += (double)t.w * (double)(axkey[i] != jk || e != es ? r : 0.f);
+                    }
+                } else {
+#pragma unroll 4
+                    for (int i = 0; i < n; ++i) {
+                        const float4 t = ax[i];
+                        part += (double)t.w * (double)(q.w * pair_exp(t, q, g2, ks));
+                    }
+                }
+                // sums over the lanes of each box; its last lane adds them
+                for (int o = 1; o < 64; o <<= 1) {
+                    const double pv = __shfl_up(part, o, 64);
+                    const int pe = __shfl_up(e, o, 64);
+                    if (lane >= o && pe == e) part += pv;
+                }
+                const int ne = __shfl_down(e, 1, 64);
+                if (j < tot && (lane == 63 || ne != e)) sum[wave][e] += part;
+                wave_sync();
+            }
+            if (mine) {
+                const double v = sum[wave][lane] * exp(-gap2 * g.inv_sigma * g.inv_sigma);
+                g.F[k] = i0 == 0 ? v : g.F[k] + v;
+            }
+        }
+    }
+}
+
+// The other pairs, one wavefront each (the wavefronts stride over their list): by the
+// expansions (the double series, contracted one axis at a time in LDS), or directly with
+// up to four dendrite points per lane held while the axon points pass from LDS.
+template <int P>
+__global__ void __launch_bounds__(64, 6) k_box_pairs_large(BoxArgs g) {
+    constexpr int P2 = P * P, P3 = P2 * P, NH = 2 * P - 1;
+    constexpr int SH = 3 * P3 > 320 ? 3 * P3 : 320;   // series operands, or 64 axon points and their keys
+    __shared__ __align__(16) float sh[SH];
+    __shared__ float hh[3][NH + 1];
+    float *sA = sh, *sM = sh + P3, *sX = sh + 2 * P3;
+    float4 *ax = reinterpret_cast<float4 *>(sh);
+    int32_t *axkey = reinterpret_cast<int32_t *>(sh + 256);
+    const int lane = threadIdx.x;
+    const int64_t nl = *g.nlarge;
+    const float ks = (float)(g.inv_sigma * g.inv_sigma * 1.4426950408889634);
+    for (int64_t m0 = blockIdx.x; m0 < nl; m0 += gridDim.x) {
+        const int64_t k = g.large[m0];
+        const int32_t s = g.pair_s[k], c = g.pair_c[k];
+        const int32_t vs = g.box_node[s], vc = g.box_node[c];
+        const double4 gs = g.box_geo[s], gc = g.box_geo[c];
+        const int32_t fs = g.nfirst[vs], ns = g.ncount[vs];
+        double val = 0.0;
+        __syncthreads();   // the previous pair's LDS is no longer read
+        if (pair_by_series(g, vs, vc, g.box_na[s], g.box_nd[c], gs, gc)) {
+            const double dx = (gs.x - gc.x) * g.inv_sigma, dy = (gs.y - gc.y) * g.inv_sigma,
+                         dz = (gs.z - gc.z) * g.inv_sigma;
+            for (int m = lane; m < P3; m += 64) {
+                sA[m] = g.A[(int64_t)c * P3 + m];
+                sM[m] = g.M[(int64_t)s * P3 + m];
+            }
+            if (lane < 3) {   // h_0 .. h_{2p-2} at the centre offset, by the recurrence in FP64
+                const double y = lane == 0 ? dx : lane == 1 ? dy : dz;
+                double h0 = exp(-y * y), h1 = 2.0 * y * h0;
+                hh[lane][0] = (float)h0;
+                if (NH > 1) hh[lane][1] = (float)h1;
+                for (int n = 1; n + 1 < NH; ++n) {
+                    const double h2 = 2.0 * y * h1 - 2.0 * n * h0;
+                    hh[lane][n + 1] = (float)h2;
+                    h0 = h1;
+                    h1 = h2;
+                }
+            }
+            __syncthreads();
+            // X[az][ay][bx] = sum_ax A[az][ay][ax] h(ax + bx, dx)
+            for (int m = lane; m < P3; m += 64) {
+                const int bx = m % P, row = m / P;
+                float acc = 0.f;
+#pragma unroll
+                for (int ax_ = 0; ax_ < P; ++ax_) acc = fmaf(sA[row * P + ax_], hh[0][ax_ + bx], acc);
+                sX[m] = acc;
+            }
+            __syncthreads();
+            // Y[az][by][bx] = sum_ay X[az][ay][bx] h(ay + by, dy), into sA
+            for (int m = lane; m < P3; m += 64) {
+                const int bx = m % P, by = (m / P) % P, az = m / P2;
+                float acc = 0.f;
+#pragma unroll
+                for (int ay = 0; ay < P; ++ay) acc = fmaf(sX[(az * P + ay) * P + bx], hh[1][ay + by], acc);
+                sA[m] = acc;
+            }
+            __syncthreads();
+            // sum_beta Mt[bz][by][bx] sum_az Y[az][by][bx] h(az + bz, dz)
+            float part = 0.f;
+            for (int m = lane; m < P3; m += 64) {
+                const int bx = m % P, by = (m / P) % P, bz = m / P2;
+                float z = 0.f;
+#pragma unroll
+                for (int az = 0; az < P; ++az) z = fmaf(sA[(az * P + by) * P + bx], hh[2][az + bz], z);
+                part = fmaf(z, sM[m], part);
+            }
+            val = wave_sum_d((double)part);
+            if (s == c) {   // the series includes the pairs j = i: a_i w_i K(0) each
+                double self = 0.0;
+                for (int32_t i = lane; i < ns; i += 64) self += (double)g.akey[fs + i] * (double)g.ps[fs + i].w;
+                val -= wave_sum_d(self);
+            }
+        } else {
+            const int32_t fc = g.nfirst[vc], nc = g.ncount[vc];
+            const double gap2 = pair_gap2(gs, gc);
+            const float g2 = (float)gap2;
+            double part = 0.0;
+            for (int32_t i0 = 0; i0 < ns; i0 += 64) {
+                wave_sync();
+                const int n = stage_axons(g, fs, ns, i0, 64, lane, ax, axkey);
+                wave_sync();
+                for (int32_t j0 = 0; j0 < nc; j0 += 256) {
+                    // up to four dendrite points per lane; lanes past the box repeat its first
+                    // point with no weight (their terms stay finite and add 0)
+                    const int nb = nc - j0 >= 256 ? 4 : (nc - j0 + 63) / 64;
+                    float4 q[4];
+                    int32_t jk[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int32_t j = j0 + lane + 64 * u;
+                        jk[u] = j < nc ? fc + j : -1;
+                        q[u] = g.ps[j < nc ? fc + j : fc];
+                        q[u].w = j < nc ? q[u].w : 0.f;
+                    }
+                    // a lane's terms of one axon point are added in float32, u = 0 .. nb - 1
+                    auto pass = [&](auto NB, auto SELF) {
+#pragma unroll 2
+                        for (int i = 0; i < n; ++i) {
+                            const float4 t = ax[i];
+                            float row = 0.f;
+#pragma unroll
+                            for (int u = 0; u < decltype(NB)::value; ++u) {
+                                const float r = add_term(row, q[u].w, pair_exp(t, q[u], g2, ks));
+                                if constexpr (decltype(SELF)::value) row = jk[u] == axkey[i] ? row : r;
+                                else row = r;
+                            }
+                            part += (double)t.w * (double)row;
+                        }
+                    };
+                    auto by_count = [&](auto SELF) {
+                        if (nb == 1) pass(std::integral_constant<int, 1>{}, SELF);
+                        else if (nb == 2) pass(std::integral_constant<int, 2>{}, SELF);
+                        else if (nb == 3) pass(std::integral_constant<int, 3>{}, SELF);
+                        else pass(std::integral_constant<int, 4>{}, SELF);
+                    };
+                    if (s == c) by_count(std::true_type{});
+                    else by_count(std::false_type{});
+                }
+            }
+            val = wave_sum_d(part) * exp(-gap2 * g.inv_sigma * g.inv_sigma);
+        }
+        if (lane == 0) g.F[k] = val;
+    }
 }
 
 // one wavefront per unit (the units of the step counted in *nunit).  K_OCT: the
 // lanes split the queries; K_BOX: the lanes split the axon node's boxes (their
 // per-octant sums from k_box_partials); both end in a butterfly sum (every lane
-// ends with all eight values).  Otherwise candidate values 64 at a time (lane per candidate),
-// total and running sums in candidate order by lane 0.
+// ends with all eight values).  Otherwise candidate values 64 at a time (lane per
+// candidate; up to 32 candidates leave lanes that share a leaf's tasks), and a running
+// sum over the lanes.  (One lane per candidate over a table of addresses, twice, took
+// 670 us in a step where nodes of some hundred axons choose in a leaf.)
 __global__ void __launch_bounds__(256) k_desc_choose(const int64_t *nunit, const UnitDesc *units, const double *raw,
                                                      const float *qa, const double *dv, const int64_t *toff,
                                                      const float *ta, const int64_t *crng, BoxArgs g,
                                                      uint64_t seed, int step, int32_t *out) {
     __shared__ double sv[4][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // (the wavefront's index in a scalar register: its unit is read by scalar loads)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t nu = *nunit;
     for (int64_t u = (int64_t)blockIdx.x * 4 + wave; u < nu; u += (int64_t)gridDim.x * 4) {
         const UnitDesc U = units[u];
@@ -595,10 +877,12 @@ __global__ void __launch_bounds__(256) k_desc_choose(const int64_t *nunit, const
 #pragma unroll
             for (int d = 0; d < 8; ++d) acc[d] = 0.0;
             if (U.kind == K_BOX) {   // the boxes [r0, r1) of the axon node, summed per octant
+#pragma unroll 1
                 for (int64_t b = U.r0 + lane; b < U.r1; b += 64)
 #pragma unroll
                     for (int d = 0; d < 8; ++d) acc[d] += g.part[b * 8 + d];
             } else {
+#pragma unroll 1
                 for (int64_t q = U.r0 + lane; q < U.r1; q += 64) {
                     const double aq = (double)qa[q];
 #pragma unroll
@@ -630,41 +914,52 @@ __global__ void __launch_bounds__(256) k_desc_choose(const int64_t *nunit, const
             continue;
         }
         const int nc = U.ncand;
-        double total = 0.0;
-        for (int k0 = 0; k0 < nc; k0 += 64) {
-            const int k = k0 + lane;
-            const double v = k < nc ? unit_value(U, k, raw, qa, dv, toff, ta, crng) : 0.0;
-            sv[wave][lane] = v;
-            wave_sync();
-            if (lane == 0)
-                for (int m = 0; m < 64 && k0 + m < nc; ++m) total += sv[wave][m];
-            wave_sync();
-        }
-        total = __shfl(total, 0, 64);
-        int pick = -1;
-        if (total > 0.0) {
-            const double target = desc_uniform(seed, step, U.item) * total;
-            double run = 0.0;
-            int last = -1;
-            for (int k0 = 0; k0 < nc && pick < 0; k0 += 64) {
-                const int k = k0 + lane;
-                const double v = k < nc ? unit_value(U, k, raw, qa, dv, toff, ta, crng) : 0.0;
-                sv[wave][lane] = v;
+        const double *du = dv + (U.r1 > U.r0 ? toff[U.r0] : 0);
+        // the value of candidate k0 + lane, and its sum over the lanes up to this one
+        auto values = [&](int k0, double &run) {
+            const int m = nc - k0 < 64 ? nc - k0 : 64;
+            double v = 0.0;
+            if (U.kind == K_LEAF && nc <= 32) {
+                const int G = 64 / nc, grp = lane / nc, k = lane - grp * nc;
+                const double x = grp < G ? unit_value(U, k, grp, G, du, ta, crng) : 0.0;
                 wave_sync();
-                if (lane == 0)
-                    for (int m = 0; m < 64 && k0 + m < nc && pick < 0; ++m) {
-                        const double x = sv[wave][m];
-                        if (x > 0.0) last = k0 + m;
-                        run += x;
-                        if (run > target && x > 0.0) pick = k0 + m;
-                    }
-                pick = __shfl(pick, 0, 64);
-                last = __shfl(last, 0, 64);
-                run = __shfl(run, 0, 64);
+                sv[wave][lane] = x;
                 wave_sync();
+                if (lane < nc)
+    #pragma unroll 2
+                    for (int q = 0; q < G; ++q) v += sv[wave][q * nc + lane];
+            } else if (lane < m) {
+                v = unit_value(U, k0 + lane, 0, 1, du, ta, crng);
             }
-            if (pick < 0) pick = last;
+            run = v;
+            for (int o = 1; o < 64; o <<= 1) {
+                const double t = __shfl_up(run, o, 64);
+                if (lane >= o) run += t;
+            }
+            return v;
+        };
+        // first the total, then the choice (up to 64 candidates: their values are still there)
+        double total = 0.0, target = 0.0, v = 0.0, run = 0.0;
+        int pick = -1, last = -1;
+        for (int pass = 0; pass < 2 && pick < 0; ++pass) {
+            double before = 0.0;
+            for (int k0 = 0; k0 < nc && pick < 0; k0 += 64) {
+                if (pass == 0 || nc > 64) v = values(k0, run);
+                if (pass == 1) {
+                    const uint64_t some = __ballot(v > 0.0);
+                    const uint64_t past = __ballot(before + run > target && v > 0.0);
+                    if (past) pick = k0 + __ffsll((unsigned long long)past) - 1;
+                    if (some) last = k0 + 63 - __clzll((long long)some);
+                }
+                before += __shfl(run, 63, 64);
+            }
+            if (pass == 0) {
+                total = before;
+                if (!(total > 0.0)) break;
+                target = desc_uniform(seed, step, U.item) * total;
+            }
         }
+        if (pick < 0) pick = last;
         if (lane == 0) out[u] = pick;
     }
 }
@@ -672,60 +967,71 @@ __global__ void __launch_bounds__(256) k_desc_choose(const int64_t *nunit, const
 // ---- device frontier ---------------------------------------------------------
 
 // Exclusive prefix sums, in place, of C int64 columns (column c at data + c *
-// stride) over the first *count entries; the column totals go to totals[0 .. C).
-// Three launches: per block of kScanBlock entries, over the block sums (one
-// block), and the block offsets added back.
-constexpr int kScanBlock = 1024;
-
+// stride) over the first *count entries, in two launches: within blocks of kScanBlock
+// entries, and over the block sums (one block; it also leaves the column totals in
+// totals[0 .. C)).  An entry's prefix is its own value plus that of its block
+// (scan_at); the consumers add the two.
 template <int C>
 __global__ void __launch_bounds__(kScanBlock) k_scan_blocks(const int64_t *count, int64_t stride, int64_t *data,
                                                             int64_t *bsum) {
-    __shared__ int64_t sh[kScanBlock];
     const int64_t n = *count;
     const int64_t nb = gridDim.x;
     const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
     for (int c = 0; c < C; ++c) {
-        const int64_t v = i < n ? data[c * stride + i] : 0;
-        sh[threadIdx.x] = v;
-        __syncthreads();
-        for (int o = 1; o < kScanBlock; o <<= 1) {
-            const int64_t t = threadIdx.x >= (unsigned)o ? sh[threadIdx.x - o] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += t;
-            __syncthreads();
-        }
-        if (i < n) data[c * stride + i] = sh[threadIdx.x] - v;
-        if (threadIdx.x == kScanBlock - 1) bsum[c * nb + blockIdx.x] = sh[threadIdx.x];
-        __syncthreads();
+        int64_t all = 0;
+        const int64_t before = block_scan(i < n ? data[c * stride + i] : (int64_t)0, all);
+        if (i < n) data[c * stride + i] = before;
+        if (threadIdx.x == 0) bsum[c * nb + blockIdx.x] = all;
     }
 }
 
-template <int C>
-__global__ void __launch_bounds__(kScanBlock) k_scan_top(int64_t nb, int64_t *bsum, int64_t *totals) {
-    __shared__ int64_t sh[kScanBlock];
-    __shared__ int64_t carry;
+__device__ inline int64_t scan_at(const int64_t *col, const int64_t *bsum, int64_t i) {
+    return col[i] + bsum[i / kScanBlock];
+}
+
+// What may not exceed its capacity after a scan: a step whose tables would not fit
+// stops the descent (the error flag is set and the step's counts are cleared, so that
+// the later kernels of the step do nothing).
+struct NoClamp {
+    __device__ void operator()() const {}
+};
+struct ClampPairs {
+    int64_t *ctr;
+    int64_t ucap, rcap;
+    __device__ void operator()() const {
+        if (ctr[C_NU] > ucap || ctr[C_NR] + ctr[C_SNR] > rcap) {
+            ctr[C_ERR] = 1;
+            ctr[C_NU] = 0;
+            ctr[C_SNR] = 0;
+        }
+    }
+};
+struct ClampUnits {
+    int64_t *ctr;
+    int64_t qcap, tcap, dvcap, crcap;
+    __device__ void operator()() const {
+        if (ctr[C_NQ] > qcap || ctr[C_NT] > tcap || ctr[C_NDV] > dvcap || ctr[C_NCR] > crcap) {
+            ctr[C_ERR] = 1;
+            ctr[C_NU] = 0;
+            ctr[C_NQ] = ctr[C_NT] = ctr[C_NDV] = ctr[C_NCR] = 0;
+        }
+    }
+};
+
+template <int C, class Clamp>
+__global__ void __launch_bounds__(kScanBlock) k_scan_top(int64_t nb, int64_t *bsum, int64_t *totals, Clamp clamp) {
     for (int c = 0; c < C; ++c) {
-        if (threadIdx.x == 0) carry = 0;
-        __syncthreads();
+        int64_t run = 0;
         for (int64_t c0 = 0; c0 < nb; c0 += kScanBlock) {
             const int64_t g = c0 + threadIdx.x;
-            const int64_t v = g < nb ? bsum[c * nb + g] : 0;
-            sh[threadIdx.x] = v;
-            __syncthreads();
-            for (int o = 1; o < kScanBlock; o <<= 1) {
-                const int64_t t = threadIdx.x >= (unsigned)o ? sh[threadIdx.x - o] : 0;
-                __syncthreads();
-                sh[threadIdx.x] += t;
-                __syncthreads();
-            }
-            if (g < nb) bsum[c * nb + g] = carry + sh[threadIdx.x] - v;
-            __syncthreads();
-            if (threadIdx.x == 0) carry += sh[kScanBlock - 1];
-            __syncthreads();
+            int64_t all = 0;
+            const int64_t before = block_scan(g < nb ? bsum[c * nb + g] : (int64_t)0, all);
+            if (g < nb) bsum[c * nb + g] = run + before;
+            run += all;
         }
-        if (threadIdx.x == 0) totals[c] = carry;
-        __syncthreads();
+        if (threadIdx.x == 0) totals[c] = run;
     }
+    if (threadIdx.x == 0) clamp();
 }
 
 template <int C>
@@ -761,9 +1067,13 @@ struct DescArgs {
     int64_t *ctr;
     const int64_t *S, *T;       // frontier
     int64_t *S2, *T2;           // next frontier (one entry per unit; kNoItem: dropped)
-    int64_t *pcnt;              // per pair: units, requests (2 columns, stride fcap), then their offsets
+    int64_t *pcnt;              // per pair: units, requests before it in its scan block (2 columns, stride fcap)
+    int64_t *bsumF, *bsumU;     // scan block offsets of pcnt and ucnt (nbF, nbU blocks a column)
+    int64_t nbF, nbU;
+    int64_t *host_m;            // page-locked: the frontier's size after the step (or NULL)
     UnitSpec *spec;
-    int64_t *ucnt;              // per unit: queries, tasks, terms, range entries (4 columns, stride ucap)
+    int64_t *ucnt;              // per unit: queries, tasks, terms, range entries (4 columns, stride ucap),
+                                // then what comes before it in its scan block
     UnitDesc *units;
     int32_t *qt, *qs, *qn;      // queries: target input index, key position, node
     float *qa;
@@ -797,13 +1107,15 @@ __global__ void k_desc_init(int64_t *ctr, int64_t *S, int64_t *T, int64_t m0) {
     }
 }
 
-// per pair: how many units and requests it makes
-__global__ void __launch_bounds__(256) k_pairs_count(DescArgs d) {
+// per pair: how many units and requests it makes, with the first launch of their
+// prefix sums (blocks of kScanBlock pairs)
+__global__ void __launch_bounds__(kScanBlock) k_pairs_count(DescArgs d) {
     const int64_t m = d.ctr[C_M];
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < m && k < d.fcap;
-         k += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t k = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
+    const bool live = k < m && k < d.fcap;
+    int64_t nu = 0, nr = 0;
+    if (live) {
         const int64_t Si = d.S[k], Ti = d.T[k];
-        int64_t nu = 0, nr = 0;
         if (Si == kNoItem) {
         } else if (Si < 0 && Ti < 0) {
             nr = 1;
@@ -818,31 +1130,42 @@ __global__ void __launch_bounds__(256) k_pairs_count(DescArgs d) {
                 nu = axons_in(d, d.nfirst[Si], d.ncount[Si]);   // its neurons with axons
             }
         }
-        d.pcnt[k] = nu;
-        d.pcnt[d.fcap + k] = nr;
+    }
+    int64_t allu = 0, allr = 0;
+    const int64_t bu = block_scan(nu, allu), br = block_scan(nr, allr);
+    if (live) {
+        d.pcnt[k] = bu;
+        d.pcnt[d.fcap + k] = br;
+    }
+    if (threadIdx.x == 0) {
+        d.bsumF[blockIdx.x] = allu;
+        d.bsumF[d.nbF + blockIdx.x] = allr;
     }
 }
 
-// per pair: its requests, and its units' kinds and list sizes
+// per pair: its requests, and its units' kinds and list sizes; eight lanes per pair
+// split the children or neurons of its axon item (one thread per pair walked up to 64 of
+// them through dependent loads: 60 us a step)
 __global__ void __launch_bounds__(256) k_pairs_fill(DescArgs d) {
     const int64_t m = d.ctr[C_M];
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < m && k < d.fcap;
-         k += (int64_t)gridDim.x * blockDim.x) {
+    const int sub = threadIdx.x & 7, shift = threadIdx.x & 56;
+    for (int64_t k = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 3; k < m && k < d.fcap;
+         k += ((int64_t)gridDim.x * blockDim.x) >> 3) {
         const int64_t Si = d.S[k], Ti = d.T[k];
         if (Si == kNoItem) continue;
         if (Si < 0 && Ti < 0) {
-            const int64_t pos = d.ctr[C_NR] + d.pcnt[d.fcap + k];
+            const int64_t pos = d.ctr[C_NR] + scan_at(d.pcnt + d.fcap, d.bsumF + d.nbF, k);
             if (pos >= d.rcap) {
                 flag_error(d);
-                continue;
+            } else if (sub == 0) {
+                d.req_a[pos] = (int32_t)(-Si - 1);
+                d.req_d[pos] = (int32_t)(-Ti - 1);
             }
-            d.req_a[pos] = (int32_t)(-Si - 1);
-            d.req_d[pos] = (int32_t)(-Ti - 1);
             continue;
         }
-        int64_t u = d.pcnt[k];
+        const int64_t u0 = scan_at(d.pcnt, d.bsumF, k);
         // kind K_OCT here stands for "over the children of Tn": K_OCT or K_LEAF by Tn
-        auto emit = [&](int64_t X, int64_t Tn, int32_t kind, int32_t side) {
+        auto emit = [&](int64_t u, int64_t X, int64_t Tn, int32_t kind, int32_t side) {
             if (u >= d.ucap) {
                 flag_error(d);
                 return;
@@ -871,25 +1194,26 @@ __global__ void __launch_bounds__(256) k_pairs_fill(DescArgs d) {
             d.ucnt[d.ucap + u] = nt;
             d.ucnt[2 * d.ucap + u] = ndv;
             d.ucnt[3 * d.ucap + u] = ncr;
-            ++u;
         };
         if (Si < 0) {
-            emit(Si, Ti, K_OCT, 0);
+            if (sub == 0) emit(u0, Si, Ti, K_OCT, 0);
         } else if (Ti < 0) {
-            emit(Si, Ti, K_SRC, 1);
+            if (sub == 0) emit(u0, Si, Ti, K_SRC, 1);
         } else {
             const int32_t nc = d.nnchild[Si];
             // both above the box level, both with child nodes: box pairs
             const bool boxes = d.box_level >= 0 && nc > 0 && d.nnchild[Ti] > 0 && d.nlevel[Si] < d.box_level &&
                                d.nlevel[Ti] < d.box_level;
-            if (nc > 0) {
-                const int32_t fc = d.nfchild[Si];
-                for (int32_t c = 0; c < nc; ++c)
-                    if (axons_in(d, d.nfirst[fc + c], d.ncount[fc + c]) > 0) emit(fc + c, Ti, boxes ? K_BOX : K_OCT, 0);
-            } else {
-                const int32_t f = d.nfirst[Si], e = f + d.ncount[Si];
-                for (int32_t p = f; p < e; ++p)
-                    if (d.akey[p] > 0.f) emit(-(int64_t)d.perm[p] - 1, Ti, K_OCT, 0);
+            const int32_t f = nc > 0 ? d.nfchild[Si] : d.nfirst[Si], cnt = nc > 0 ? nc : d.ncount[Si];
+            int64_t u = u0;
+            for (int32_t b = 0; b < cnt; b += 8) {   // in order: the lanes of the group that hold axons
+                const int32_t x = f + b + sub;
+                const bool has = b + sub < cnt &&
+                                 (nc > 0 ? axons_in(d, d.nfirst[x], d.ncount[x]) > 0 : d.akey[x] > 0.f);
+                const unsigned mask = (unsigned)(__ballot(has) >> shift) & 0xffu;
+                const int64_t at = u + __popc(mask & ((1u << sub) - 1));
+                if (has) emit(at, nc > 0 ? (int64_t)x : -(int64_t)d.perm[x] - 1, Ti, boxes ? K_BOX : K_OCT, 0);
+                u += __popc(mask);
             }
         }
     }
@@ -921,23 +1245,21 @@ __device__ inline int64_t lower_bound_i32(const int32_t *a, int64_t n, int32_t k
     return lo;
 }
 
-// one wavefront per unit: its queries or tasks and its descriptor
-__global__ void __launch_bounds__(256) k_units_fill(DescArgs d) {
+// Unit u's queries or tasks and its descriptor, by one wavefront.
+__device__ inline void unit_fill(const DescArgs &d, int64_t u, int64_t nu, const UnitSpec &sp) {
     const int lane = threadIdx.x & 63;
-    const int64_t nu = d.ctr[C_NU];
-    for (int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); u < nu && u < d.ucap;
-         u += (int64_t)gridDim.x * 4) {
-        const UnitSpec sp = d.spec[u];
+    {
         int64_t off[4], cnt[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            off[c] = d.ucnt[c * d.ucap + u];
-            cnt[c] = (u + 1 < nu ? d.ucnt[c * d.ucap + u + 1] : d.ctr[C_NQ + c]) - off[c];
+            const int64_t *col = d.ucnt + c * d.ucap, *bs = d.bsumU + c * d.nbU;
+            off[c] = scan_at(col, bs, u);
+            cnt[c] = (u + 1 < nu ? scan_at(col, bs, u + 1) : d.ctr[C_NQ + c]) - off[c];
         }
         if (off[0] + cnt[0] > d.qcap || off[1] + cnt[1] > d.tcap || off[2] + cnt[2] > d.dvcap ||
             off[3] + cnt[3] > d.crcap) {
             if (lane == 0) flag_error(d);
-            continue;
+            return;
         }
         const int64_t X = sp.X, Tn = sp.Tn;
         UnitDesc U{X, 0, 0, 0, sp.kind, 8};
@@ -1014,6 +1336,46 @@ __global__ void __launch_bounds__(256) k_units_fill(DescArgs d) {
     }
 }
 
+// The units that choose for one neuron over a node's octants or a leaf's neurons (most
+// of them, late in a descent) a lane each: they have one query or task.  Then one
+// wavefront per unit for the others.
+__global__ void __launch_bounds__(256) k_units_fill(DescArgs d) {
+    const int64_t nu = d.ctr[C_NU] < d.ucap ? d.ctr[C_NU] : d.ucap;
+    for (int64_t u = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; u < nu; u += (int64_t)gridDim.x * blockDim.x) {
+        const UnitSpec sp = d.spec[u];
+        if (sp.X >= 0 || sp.kind == K_SRC) continue;
+        const bool oct = sp.kind == K_OCT;
+        const int64_t at = scan_at(d.ucnt + (oct ? 0 : 1) * d.ucap, d.bsumU + (oct ? 0 : 1) * d.nbU, u),
+                      dvo = scan_at(d.ucnt + 2 * d.ucap, d.bsumU + 2 * d.nbU, u);
+        const int32_t p = d.iperm[-sp.X - 1], tc = oct ? 0 : d.ncount[sp.Tn];
+        const float ap = d.akey[p];
+        const bool has = ap > 0.f;   // (a neuron without axons has no query or task)
+        if (has && (at >= (oct ? d.qcap : d.tcap) || dvo + tc > d.dvcap)) {
+            flag_error(d);
+            continue;
+        }
+        if (!has) {
+        } else if (oct) {
+            d.qt[at] = (int32_t)(-sp.X - 1);
+            d.qs[at] = p;
+            d.qn[at] = (int32_t)sp.Tn;
+            d.qa[at] = ap;
+        } else {
+            d.ti[at] = p;
+            d.tcf[at] = d.nfirst[sp.Tn];
+            d.tnc[at] = tc;
+            d.toff[at] = dvo;
+            d.ta[at] = ap;
+        }
+        d.units[u] = UnitDesc{sp.X, at, at + has, 0, sp.kind, oct ? 8 : tc};
+    }
+    for (int64_t u = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < nu;
+         u += (int64_t)gridDim.x * 4) {
+        const UnitSpec sp = d.spec[u];
+        if (sp.X >= 0 || sp.kind == K_SRC) unit_fill(d, u, nu, sp);
+    }
+}
+
 // per unit: the next pair from the choice (candidate k of the unit: the child of
 // Tn in octant k for K_OCT and K_BOX, neuron k of the leaf Tn for K_LEAF, child k
 // of X for K_SRC), or kNoItem when the choice dropped it
@@ -1052,46 +1414,41 @@ __global__ void __launch_bounds__(256) k_next(DescArgs d) {
         live += s2 != kNoItem;
     }
     for (int o = 32; o > 0; o >>= 1) live += __shfl_xor(live, o, 64);
-    if ((threadIdx.x & 63) == 0 && live > 0)
-        atomicAdd(reinterpret_cast<unsigned long long *>(d.ctr + C_LIVE), live);
-}
-
-// After the prefix sums: a step whose tables would not fit stops the descent
-// (the error flag is set and the step's counts are cleared, so that the later
-// kernels of the step do nothing).
-__global__ void k_clamp_pairs(int64_t *ctr, int64_t ucap, int64_t rcap) {
+    __shared__ unsigned long long part[4];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = live;
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    if (ctr[C_NU] > ucap || ctr[C_NR] + ctr[C_SNR] > rcap) {
-        ctr[C_ERR] = 1;
-        ctr[C_NU] = 0;
-        ctr[C_SNR] = 0;
+    // the last block ends the step: the next frontier holds one entry per unit, or none
+    // when every choice dropped its pair.  A block takes its ticket after its count has
+    // arrived (the ticket's operand needs the count's return value)
+    auto *ctr = reinterpret_cast<unsigned long long *>(d.ctr);
+    live = part[0] + part[1] + part[2] + part[3];
+    const unsigned long long seen = live > 0 ? atomicAdd(ctr + C_LIVE, live) : 0ull;
+    if (atomicAdd(ctr + C_TICKET, 1ull + (seen >> 63)) != gridDim.x - 1) return;
+    const int64_t any = (int64_t)atomicAdd(ctr + C_LIVE, 0ull);
+    if (d.ctr[C_M] > 0) d.ctr[C_STEPS] += 1;
+    d.ctr[C_NR] += d.ctr[C_SNR];
+    const int64_t m = any > 0 ? d.ctr[C_NU] : 0;
+    d.ctr[C_M] = m;
+    d.ctr[C_LIVE] = 0;
+    d.ctr[C_TICKET] = 0;
+    if (d.host_m) {
+        *d.host_m = m;
+        __threadfence_system();
     }
 }
 
-__global__ void k_clamp_units(int64_t *ctr, int64_t qcap, int64_t tcap, int64_t dvcap, int64_t crcap) {
-    if (threadIdx.x != 0) return;
-    if (ctr[C_NQ] > qcap || ctr[C_NT] > tcap || ctr[C_NDV] > dvcap || ctr[C_NCR] > crcap) {
-        ctr[C_ERR] = 1;
-        ctr[C_NU] = 0;
-        ctr[C_NQ] = ctr[C_NT] = ctr[C_NDV] = ctr[C_NCR] = 0;
-    }
-}
+// What the set-up reads back (int64 slots): neurons with axons, boxes, the largest
+// leaf; without a cutoff the boxes with axons and with dendrites; pairs and large pairs.
+enum Stat : int { S_NAX = 0, S_NBOX, S_MAXLEAF, S_NAB, S_NDB, S_NPAIR, S_NLARGE, S_COUNT = 8 };
 
-// the next frontier holds one entry per unit, or none when every choice dropped
-// its pair
-__global__ void k_step_end(int64_t *ctr) {
-    if (threadIdx.x != 0) return;
-    if (ctr[C_M] > 0) ctr[C_STEPS] += 1;
-    ctr[C_NR] += ctr[C_SNR];
-    ctr[C_M] = ctr[C_LIVE] > 0 ? ctr[C_NU] : 0;
-    ctr[C_LIVE] = 0;
-}
-
-// key order: a gathered, and the prefix counts of neurons with a > 0 (as 0/1 then
-// scanned)
-__global__ void k_desc_akey(int64_t n, const int32_t *perm, const float *a, float *akey, int64_t *flag) {
+// key order: a gathered, and two columns of n + 1 flags to be scanned: neurons with
+// a > 0, and (set by k_box_mark) the first points of boxes
+__global__ void k_desc_akey(int64_t n, const int32_t *perm, const float *a, float *akey, int64_t *flag, int64_t *stat) {
     const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (p < S_COUNT) stat[p] = 0;
     if (p > n) return;
+    flag[n + 1 + p] = 0;
     if (p == n) {
         flag[p] = 0;
         return;
@@ -1101,40 +1458,96 @@ __global__ void k_desc_akey(int64_t n, const int32_t *perm, const float *a, floa
     flag[p] = v > 0.f ? 1 : 0;
 }
 
+// The boxes: the nodes at or below the box level whose parent lies above it, and the
+// leaves above it.
+__device__ inline bool is_box(int32_t v, int level, const int32_t *nlevel, const int32_t *nnchild,
+                              const int32_t *nparent) {
+    return (nlevel[v] >= level || nnchild[v] == 0) && (v == 0 || nlevel[nparent[v]] < level);
+}
+// marks the boxes' first points (box == NULL: none) and finds the largest leaf
+__global__ void __launch_bounds__(256) k_box_mark(int64_t nn, int level, const int32_t *nlevel, const int32_t *nfirst,
+                                                  const int32_t *ncount, const int32_t *nnchild,
+                                                  const int32_t *nparent, int64_t *box, int64_t *stat) {
+    const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    int32_t leaf = 0;
+    if (v < nn) {
+        if (nnchild[v] == 0) leaf = ncount[v];
+        if (box && is_box((int32_t)v, level, nlevel, nnchild, nparent)) box[nfirst[v]] = 1;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const int32_t t = __shfl_xor(leaf, o, 64);
+        leaf = t > leaf ? t : leaf;
+    }
+    __shared__ int32_t part[4];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = leaf;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int q = 1; q < 4; ++q) leaf = part[q] > leaf ? part[q] : leaf;
+    if (leaf > 0) atomicMax(reinterpret_cast<unsigned long long *>(stat + S_MAXLEAF), (unsigned long long)leaf);
+}
+// node -> box (-1: none), box -> node and first point; `rank` holds the boxes before
+// each point
+__global__ void __launch_bounds__(256) k_box_table(int64_t nn, int level, const int32_t *nlevel, const int32_t *nfirst,
+                                                   const int32_t *nnchild, const int32_t *nparent,
+                                                   const int64_t *rank, int32_t *node_box, int32_t *box_node,
+                                                   int32_t *box_first) {
+    const int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (v >= nn) return;
+    int32_t b = -1;
+    if (is_box((int32_t)v, level, nlevel, nnchild, nparent)) {
+        b = (int32_t)rank[nfirst[v]];
+        box_node[b] = (int32_t)v;
+        box_first[b] = nfirst[v];
+    }
+    node_box[v] = b;
+}
+
 // per box: neurons with a > 0 and with staged w > 0, the key of its first point,
-// its centre and half side; no unit yet (stamp -1)
-__global__ void k_box_counts(BoxArgs g, const int64_t *axc, const uint64_t *keys, int32_t *na, int32_t *nd,
-                             uint64_t *key, double4 *geo) {
-    const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+// its centre and half side; no unit yet (stamp -1); one wavefront per box
+__global__ void __launch_bounds__(256) k_box_counts(BoxArgs g, const int64_t *axc, const uint64_t *keys, int32_t *na,
+                                                    int32_t *nd, uint64_t *key, double4 *geo, int64_t *sides) {
+    const int lane = threadIdx.x & 63;
+    const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (b >= g.nbox) return;
     const int32_t v = g.box_node[b], f = g.nfirst[v], e = f + g.ncount[v];
-    na[b] = (int32_t)(axc[e] - axc[f]);
     int32_t c = 0;
-    for (int32_t p = f; p < e; ++p) c += g.ps[p].w > 0.f;
+    for (int32_t p = f; p < e; p += 64) c += __popcll(__ballot(p + lane < e && g.ps[p + lane].w > 0.f));
+    if (lane != 0) return;
+    na[b] = (int32_t)(axc[e] - axc[f]);
     nd[b] = c;
     key[b] = keys[f];
     double cx, cy, cz, half;
     box_geom(g, v, cx, cy, cz, half);
     geo[b] = make_double4(cx, cy, cz, half);
     g.box_stamp[b] = -1;
+    if (sides) {   // (without a cutoff: boxes with axons, with dendrites)
+        auto *st = reinterpret_cast<unsigned long long *>(sides);
+        if (axc[e] > axc[f]) atomicAdd(st + S_NAB, 1ull);
+        if (c > 0) atomicAdd(st + S_NDB, 1ull);
+    }
 }
 
 __global__ void k_set_i64(int64_t *p, int64_t v) {
     if (threadIdx.x == 0) *p = v;
 }
 
-// Exclusive scan of C columns of `stride` entries each (see k_scan_blocks); count
-// in device memory, at most stride; bsum: C * ceil(stride / kScanBlock) entries.
-template <int C>
-int scan_cols(const int64_t *count, int64_t stride, int64_t *data, int64_t *bsum, int64_t *totals, hipStream_t s) {
+// The scan of k_scan_blocks, whose second launch also runs `clamp`; count in device
+// memory, at most stride; bsum: C * ceil(stride / kScanBlock) entries.  add: the block
+// offsets are added back to the entries.
+template <int C, class Clamp>
+int scan_cols(const int64_t *count, int64_t stride, int64_t *data, int64_t *bsum, int64_t *totals, bool add,
+              Clamp clamp, hipStream_t s) {
     const int64_t nb = (stride + kScanBlock - 1) / kScanBlock;
     const unsigned g = (unsigned)(nb > 0 ? nb : 1);
     hipLaunchKernelGGL(k_scan_blocks<C>, dim3(g), dim3(kScanBlock), 0, s, count, stride, data, bsum);
     MSP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_scan_top<C>, dim3(1), dim3(kScanBlock), 0, s, (int64_t)g, bsum, totals);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_scan_top<C, Clamp>), dim3(1), dim3(kScanBlock), 0, s, (int64_t)g, bsum, totals,
+                       clamp);
     MSP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_scan_add<C>, dim3(g), dim3(kScanBlock), 0, s, count, stride, data, bsum);
-    MSP_CHECK_LAUNCH();
+    if (add) {
+        hipLaunchKernelGGL(k_scan_add<C>, dim3(g), dim3(kScanBlock), 0, s, count, stride, data, bsum);
+        MSP_CHECK_LAUNCH();
+    }
     return MSP_OK;
 }
 
@@ -1151,7 +1564,6 @@ int to_host(std::vector<T> &v, const void *dev, int64_t count) {
 struct Descent {
     msp_tree *t = nullptr;
     int64_t n = 0, nn = 0, nax = 0, maxleaf = 1;
-    std::vector<int32_t> nfirst, ncount, nfchild, nnchild, nlevel;   // host copies (setup, caps)
     BoxArgs box{};
     int box_level = -1;
     const int32_t *box_first = nullptr;
@@ -1160,8 +1572,7 @@ struct Descent {
 
 // Staged weights and node moments, a in key order with its prefix counts, the
 // inverse permutation, and the box table with every box pair's attraction.
-// Synchronises `s` (the topology for the box table, the axon count, the pair
-// counts).  No box pairs (box_level -1) when p is beyond kBoxPMax, when the root
+// Synchronises `s` (the numbers of axons and boxes, of pairs).  No box pairs (box_level -1) when p is beyond kBoxPMax, when the root
 // is a leaf, or, without a cutoff, when the axon boxes times the dendrite boxes
 // exceed kBoxPairsNoCutoff.
 int desc_setup(Descent &D, msp_tree *t, const float *w, const float *a, const msp_fgt_params *prm, hipStream_t s) {
@@ -1173,75 +1584,63 @@ int desc_setup(Descent &D, msp_tree *t, const float *w, const float *a, const ms
     MSP_TRY(partner_prepare(t, w, prm, s));   // staged w, node moments
     MSP_TRY(ensure_iperm(t, s));
     const int64_t n = D.n;
-    // a in key order and the prefix counts of neurons with a > 0
+    // the box level, when the box path can apply
+    const int p = prm->p;
+    const double sigma = prm->sigma;
+    int L = -1;
+    if (p >= 1 && p <= kBoxPMax && D.nn > 1) {
+        const double rmax = rho_max_for_p(p);
+        int lm = kDepth;
+        for (int l = 0; l <= kDepth; ++l)
+            if (t->geo.side / std::ldexp(1.0, l + 1) / sigma <= rmax) {
+                lm = l;
+                break;
+            }
+        L = lm + 1;
+    }
+    // a in key order; the neurons with a > 0 and the boxes before each key-order position
+    // (two columns); what the host needs to know comes back in one copy
     MSP_TRY(t->desc_akey.ensure((size_t)(n > 0 ? n : 1) * 4));
+    MSP_TRY(t->desc_stage.ensure((size_t)(S_COUNT + 2 * (t->depth + 2) + 2) * 8));
+    int64_t *seen = static_cast<int64_t *>(t->desc_stage.p);
     const int64_t nbp = scan_blocks(n + 1);
-    MSP_TRY(t->desc_prefix.ensure((size_t)(n + 1 + nbp + 2) * 8));
+    MSP_TRY(t->desc_prefix.ensure((size_t)(2 * (n + 1) + 2 * nbp + S_COUNT + 1) * 8));
     int64_t *axc = t->desc_prefix.as<int64_t>();
-    int64_t *bsum = axc + n + 1, *cnt = bsum + nbp;
-    hipLaunchKernelGGL(k_desc_akey, dim3(grid_for(n + 1, kBlock)), dim3(kBlock), 0, s, n, t->perm.as<int32_t>(), a,
-                       t->desc_akey.as<float>(), axc);
+    int64_t *rank = axc + n + 1, *bsum = rank + n + 1, *stat = bsum + 2 * nbp, *cnt = stat + S_COUNT;
+    hipLaunchKernelGGL(k_desc_akey, dim3(grid_for(n + S_COUNT, kBlock)), dim3(kBlock), 0, s, n, t->perm.as<int32_t>(), a,
+                       t->desc_akey.as<float>(), axc, stat);
+    MSP_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_box_mark, dim3(grid_for(D.nn, kBlock)), dim3(kBlock), 0, s, D.nn, L, t->nlevel.as<int32_t>(),
+                       t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nnchild.as<int32_t>(),
+                       t->nparent.as<int32_t>(), L >= 0 ? rank : nullptr, stat);
     MSP_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(64), 0, s, cnt, n + 1);
     MSP_CHECK_LAUNCH();
-    MSP_TRY(scan_cols<1>(cnt, n + 1, axc, bsum, cnt + 1, s));
+    MSP_TRY(scan_cols<2>(cnt, n + 1, axc, bsum, stat + S_NAX, true, NoClamp{}, s));
     D.axc = axc;
+    MSP_HIP(hipMemcpyAsync(seen, stat, S_COUNT * 8, hipMemcpyDeviceToHost, s));
     MSP_HIP(hipStreamSynchronize(s));
-    // topology on the host: the box table's walk and the largest leaf
-    MSP_TRY(to_host(D.nfirst, t->nfirst.p, D.nn));
-    MSP_TRY(to_host(D.ncount, t->ncount.p, D.nn));
-    MSP_TRY(to_host(D.nfchild, t->nfchild.p, D.nn));
-    MSP_TRY(to_host(D.nnchild, t->nnchild.p, D.nn));
-    MSP_TRY(to_host(D.nlevel, t->nlevel.p, D.nn));
-    D.maxleaf = 1;
-    for (int64_t v = 0; v < D.nn; ++v)
-        if (D.nnchild[v] == 0 && D.ncount[v] > D.maxleaf) D.maxleaf = D.ncount[v];
-    int64_t nax = 0;
-    MSP_HIP(hipMemcpy(&nax, axc + n, 8, hipMemcpyDeviceToHost));
+    const int64_t nax = seen[S_NAX], nbox = seen[S_NBOX];
+    D.maxleaf = seen[S_MAXLEAF] > 1 ? seen[S_MAXLEAF] : 1;
     D.nax = nax;
-    // the box table
     D.box_level = -1;
-    const int p = prm->p;
-    if (p < 1 || p > kBoxPMax || D.nn == 0 || D.nnchild[0] == 0 || nax == 0) return MSP_OK;
-    const double rmax = rho_max_for_p(p), sigma = prm->sigma;
-    int lm = kDepth;
-    for (int l = 0; l <= kDepth; ++l)
-        if (t->geo.side / std::ldexp(1.0, l + 1) / sigma <= rmax) {
-            lm = l;
-            break;
-        }
-    const int L = lm + 1;
-    // boxes in key order: a walk from the root that stops at the first node at or
-    // below L and at leaves
-    std::vector<int32_t> node_box((size_t)D.nn, -1), stk{0}, bnode, bfirst;
-    while (!stk.empty()) {
-        const int32_t u = stk.back();
-        stk.pop_back();
-        if (D.nlevel[u] >= L || D.nnchild[u] == 0) {
-            bnode.push_back(u);
-            continue;
-        }
-        for (int32_t k = D.nnchild[u] - 1; k >= 0; --k) stk.push_back(D.nfchild[u] + k);
-    }
-    std::sort(bnode.begin(), bnode.end(), [&](int32_t x, int32_t y) { return D.nfirst[x] < D.nfirst[y]; });
-    const int64_t nbox = (int64_t)bnode.size();
-    bfirst.resize((size_t)nbox);
-    for (int64_t b = 0; b < nbox; ++b) {
-        node_box[bnode[b]] = (int32_t)b;
-        bfirst[b] = D.nfirst[bnode[b]];
-    }
-    // device: node -> box, then per box: node, first point, axons, dendrites, pair
-    // offsets, pair counts, key, geometry, unit node, stamp, octant sums
+    if (L < 0 || nax == 0) return MSP_OK;
+    // device: node -> box, then per box: node, first point, axons, dendrites, pair and
+    // large-pair offsets, key, geometry, unit node, stamp, octant sums
     const size_t nb4 = align_up((size_t)nbox * 4), nb8 = align_up((size_t)nbox * 8);
+    const int64_t nbs = scan_blocks(nbox + 1);
     const size_t o_nb = 0, o_bn = align_up((size_t)D.nn * 4), o_bf = o_bn + nb4, o_na = o_bf + nb4,
-                 o_nd = o_na + nb4, o_off = o_nd + nb4, o_cnt = o_off + align_up((size_t)(nbox + 1) * 8),
-                 o_key = o_cnt + nb8, o_geo = o_key + nb8, o_T = o_geo + align_up((size_t)nbox * 32),
-                 o_st = o_T + nb4, o_part = o_st + nb4, tot = o_part + align_up((size_t)nbox * 64);
+                 o_nd = o_na + nb4, o_off = o_nd + nb4, o_bs = o_off + align_up((size_t)(nbox + 1) * 16),
+                 o_key = o_bs + align_up((size_t)(2 * nbs + 1) * 8), o_geo = o_key + nb8,
+                 o_T = o_geo + align_up((size_t)nbox * 32), o_st = o_T + nb4, o_part = o_st + nb4,
+                 tot = o_part + align_up((size_t)nbox * 64);
     MSP_TRY(t->desc_box.ensure(tot));
     char *db = t->desc_box.as<char>();
-    MSP_HIP(hipMemcpyAsync(db + o_nb, node_box.data(), (size_t)D.nn * 4, hipMemcpyHostToDevice, s));
-    MSP_HIP(hipMemcpyAsync(db + o_bn, bnode.data(), (size_t)nbox * 4, hipMemcpyHostToDevice, s));
-    MSP_HIP(hipMemcpyAsync(db + o_bf, bfirst.data(), (size_t)nbox * 4, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_box_table, dim3(grid_for(D.nn, kBlock)), dim3(kBlock), 0, s, D.nn, L, t->nlevel.as<int32_t>(),
+                       t->nfirst.as<int32_t>(), t->nnchild.as<int32_t>(), t->nparent.as<int32_t>(), rank,
+                       reinterpret_cast<int32_t *>(db + o_nb), reinterpret_cast<int32_t *>(db + o_bn),
+                       reinterpret_cast<int32_t *>(db + o_bf));
+    MSP_CHECK_LAUNCH();
     int32_t *dna = reinterpret_cast<int32_t *>(db + o_na), *dnd = reinterpret_cast<int32_t *>(db + o_nd);
     BoxArgs &g = D.box;
     g = BoxArgs{};
@@ -1270,48 +1669,45 @@ int desc_setup(Descent &D, msp_tree *t, const float *w, const float *a, const ms
     g.box_T = reinterpret_cast<int32_t *>(db + o_T);
     g.box_stamp = reinterpret_cast<int32_t *>(db + o_st);
     g.part = reinterpret_cast<double *>(db + o_part);
-    hipLaunchKernelGGL(k_box_counts, dim3(grid_for(nbox, kBlock)), dim3(kBlock), 0, s, g, axc,
-                       t->keys.as<uint64_t>(), dna, dnd, reinterpret_cast<uint64_t *>(db + o_key),
-                       reinterpret_cast<double4 *>(db + o_geo));
-    MSP_CHECK_LAUNCH();
     const bool unlimited = !(prm->cutoff_sigmas > 0.f);
+    hipLaunchKernelGGL(k_box_counts, dim3(grid_for(nbox, 4)), dim3(256), 0, s, g, axc,
+                       t->keys.as<uint64_t>(), dna, dnd, reinterpret_cast<uint64_t *>(db + o_key),
+                       reinterpret_cast<double4 *>(db + o_geo), unlimited ? stat : nullptr);
+    MSP_CHECK_LAUNCH();
     if (unlimited) {
-        std::vector<int32_t> na((size_t)nbox), nd((size_t)nbox);
-        MSP_HIP(hipMemcpyAsync(na.data(), dna, (size_t)nbox * 4, hipMemcpyDeviceToHost, s));
-        MSP_HIP(hipMemcpyAsync(nd.data(), dnd, (size_t)nbox * 4, hipMemcpyDeviceToHost, s));
+        MSP_HIP(hipMemcpyAsync(seen, stat, S_COUNT * 8, hipMemcpyDeviceToHost, s));
         MSP_HIP(hipStreamSynchronize(s));
-        int64_t nab = 0, ndb = 0;
-        for (int64_t b = 0; b < nbox; ++b) {
-            nab += na[b] > 0;
-            ndb += nd[b] > 0;
-        }
-        if ((double)nab * (double)ndb > (double)kBoxPairsNoCutoff) return MSP_OK;
+        if ((double)seen[S_NAB] * (double)seen[S_NDB] > (double)kBoxPairsNoCutoff) return MSP_OK;
     }
     g.level = L;
     g.inv_sigma = 1.0 / sigma;
     g.cut = unlimited ? -1.0 : (double)prm->cutoff_sigmas * sigma;
-    // pair counts, offsets on the host, pairs
-    int64_t *dcnt = reinterpret_cast<int64_t *>(db + o_cnt);
-    std::vector<int64_t> pc((size_t)nbox), poff((size_t)nbox + 1, 0);
+    // pair counts, their offsets (two columns of nbox + 1 entries), pairs
+    int64_t *dcnt = reinterpret_cast<int64_t *>(db + o_off);
+    int64_t *bs = reinterpret_cast<int64_t *>(db + o_bs), *ncol = bs + 2 * nbs;
     const bool brute = nbox <= kBoxBrute;
     {
         PhaseScope ph(&t->timing, PH_DESC_BOXES, s);
         if (brute) hipLaunchKernelGGL(k_box_lists_all, dim3(grid_for(nbox, 4)), dim3(256), 0, s, g, dcnt);
         else hipLaunchKernelGGL(k_box_lists, dim3(grid_for(nbox, kBlock)), dim3(kBlock), 0, s, g, dcnt);
         MSP_CHECK_LAUNCH();
+        hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(64), 0, s, ncol, nbox + 1);
+        MSP_CHECK_LAUNCH();
+        MSP_TRY(scan_cols<2>(ncol, nbox + 1, dcnt, bs, stat + S_NPAIR, true, NoClamp{}, s));
     }
-    MSP_HIP(hipMemcpyAsync(pc.data(), dcnt, (size_t)nbox * 8, hipMemcpyDeviceToHost, s));
+    MSP_HIP(hipMemcpyAsync(seen, stat, S_COUNT * 8, hipMemcpyDeviceToHost, s));
     MSP_HIP(hipStreamSynchronize(s));
-    for (int64_t b = 0; b < nbox; ++b) poff[b + 1] = poff[b] + pc[b];
-    const int64_t npair = poff[nbox];
-    MSP_HIP(hipMemcpyAsync(db + o_off, poff.data(), (size_t)(nbox + 1) * 8, hipMemcpyHostToDevice, s));
+    const int64_t npair = seen[S_NPAIR], nlarge = seen[S_NLARGE];
+    g.large_off = dcnt + nbox + 1;
+    g.nlarge = g.large_off + nbox;
     const size_t q_s = 0, q_c = align_up((size_t)npair * 4), q_f = q_c + align_up((size_t)npair * 4),
-                 qtot = q_f + align_up((size_t)npair * 8);
+                 q_l = q_f + align_up((size_t)npair * 8), qtot = q_l + align_up((size_t)nlarge * 8);
     MSP_TRY(t->desc_pairs.ensure(qtot > 0 ? qtot : kAlign));
     char *dp = t->desc_pairs.as<char>();
     g.pair_s = reinterpret_cast<int32_t *>(dp + q_s);
     g.pair_c = reinterpret_cast<int32_t *>(dp + q_c);
     g.F = reinterpret_cast<double *>(dp + q_f);
+    g.large = reinterpret_cast<int64_t *>(dp + q_l);
     const int64_t P3 = (int64_t)p * p * p;
     MSP_TRY(t->desc_boxmom.ensure((size_t)nbox * P3 * 8));
     g.A = t->desc_boxmom.as<float>();
@@ -1329,18 +1725,22 @@ int desc_setup(Descent &D, msp_tree *t, const float *w, const float *a, const ms
         switch (p) {
 #define CASE(P)                                                                                           \
     case P:                                                                                               \
-        hipLaunchKernelGGL(k_box_moments<P>, dim3((unsigned)nbox), dim3(64), 0, s, g);                   \
+        hipLaunchKernelGGL(k_box_moments<P>, dim3((unsigned)nbox), dim3(256), 0, s, g);                  \
         MSP_CHECK_LAUNCH();                                                                               \
-        if (npair > 0) {                                                                                  \
-            hipLaunchKernelGGL(k_box_pair_values<P>, dim3((unsigned)npair), dim3(64), 0, s, g, npair);   \
+        if (nlarge > 0) {                                                                                 \
+            hipLaunchKernelGGL(k_box_pairs_large<P>, dim3((unsigned)(nlarge < 16384 ? nlarge : 16384)),   \
+                               dim3(64), 0, s, g);                                                        \
             MSP_CHECK_LAUNCH();                                                                           \
         }                                                                                                 \
         break;
             CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10)
 #undef CASE
         }
+        if (npair > nlarge) {
+            hipLaunchKernelGGL(k_box_pairs_small, dim3((unsigned)nbox, kPairBlocks), dim3(kPairWaves * 64), 0, s, g);
+            MSP_CHECK_LAUNCH();
+        }
     }
-    MSP_HIP(hipStreamSynchronize(s));   // the host vectors above are released on return
     D.box_level = L;
     D.box_first = reinterpret_cast<const int32_t *>(db + o_bf);
     t->desc_box_level = L;
@@ -1438,24 +1838,29 @@ inline unsigned capped_grid(int64_t items, int per_block, unsigned cap) {
 
 // One step, all on the device: units and requests per pair, their offsets, the
 // units' lists, the partner queries and direct terms, the choices, the next
-// frontier (a.S2 / a.T2, one entry per unit) and the counters.
+// frontier (a.S2 / a.T2, one entry per unit) and the counters; host_m (page-locked, or
+// NULL) receives the next frontier's size.
 int launch_step(Descent &D, const DescArgs &a_in, int64_t *bsumF, int64_t *bsumU, const msp_fgt_params *q,
-                uint64_t seed, int step, hipStream_t s) {
+                uint64_t seed, int step, int64_t *host_m, hipStream_t s) {
     msp_tree *t = D.t;
     DescArgs a = a_in;
     a.step = step;
-    const unsigned gF = capped_grid(a.fcap, kBlock, 2048), gU = capped_grid(a.ucap, kBlock, 2048),
+    a.bsumF = bsumF;
+    a.bsumU = bsumU;
+    a.nbF = scan_blocks(a.fcap);
+    a.nbU = scan_blocks(a.ucap);
+    a.host_m = host_m;
+    const unsigned gF = capped_grid(a.fcap, kBlock / 8, 4096), gU = capped_grid(a.ucap, kBlock, 256),
                    gW = capped_grid(a.ucap, 4, 8192), gT = capped_grid(a.tcap, 4, 8192);
-    hipLaunchKernelGGL(k_pairs_count, dim3(gF), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_pairs_count, dim3((unsigned)a.nbF), dim3(kScanBlock), 0, s, a);
     MSP_CHECK_LAUNCH();
-    MSP_TRY(scan_cols<2>(a.ctr + C_M, a.fcap, a.pcnt, bsumF, a.ctr + C_NU, s));
-    hipLaunchKernelGGL(k_clamp_pairs, dim3(1), dim3(64), 0, s, a.ctr, a.ucap, a.rcap);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k_scan_top<2, ClampPairs>), dim3(1), dim3(kScanBlock), 0, s, a.nbF, bsumF,
+                       a.ctr + C_NU, ClampPairs{a.ctr, a.ucap, a.rcap});
     MSP_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_pairs_fill, dim3(gF), dim3(kBlock), 0, s, a);
     MSP_CHECK_LAUNCH();
-    MSP_TRY(scan_cols<4>(a.ctr + C_NU, a.ucap, a.ucnt, bsumU, a.ctr + C_NQ, s));
-    hipLaunchKernelGGL(k_clamp_units, dim3(1), dim3(64), 0, s, a.ctr, a.qcap, a.tcap, a.dvcap, a.crcap);
-    MSP_CHECK_LAUNCH();
+    MSP_TRY((scan_cols<4>(a.ctr + C_NU, a.ucap, a.ucnt, bsumU, a.ctr + C_NQ, false,
+                          ClampUnits{a.ctr, a.qcap, a.tcap, a.dvcap, a.crcap}, s)));
     hipLaunchKernelGGL(k_units_fill, dim3(gW), dim3(256), 0, s, a);
     MSP_CHECK_LAUNCH();
     if (a.qcap > 0)
@@ -1476,8 +1881,6 @@ int launch_step(Descent &D, const DescArgs &a_in, int64_t *bsumF, int64_t *bsumU
         MSP_CHECK_LAUNCH();
     }
     hipLaunchKernelGGL(k_next, dim3(gU), dim3(kBlock), 0, s, a);
-    MSP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, s, a.ctr);
     MSP_CHECK_LAUNCH();
     return MSP_OK;
 }
@@ -1500,15 +1903,18 @@ int descent_step(msp_tree *t, const float *w, const float *a, const msp_fgt_para
     MSP_TRY(desc_setup(D, t, w, a, &q, s));
     MSP_TRY(check_items(D, S_in, m));
     MSP_TRY(check_items(D, T_in, m));
+    std::vector<int32_t> ncount, nnchild;
+    MSP_TRY(to_host(ncount, t->ncount.p, D.nn));
+    MSP_TRY(to_host(nnchild, t->nnchild.p, D.nn));
     // capacities from the given pairs: a pair's units, queries, tasks and range
     // entries stay within its axon item's neurons, its terms within those times
     // the dendrite leaf's neurons
     Caps c{m > 0 ? m : 1, 0, 0, 0, 0, 0, m > 0 ? m : 1};
     for (int64_t k = 0; k < m; ++k) {
         const int64_t Si = S_in[k], Ti = T_in[k];
-        const int64_t ns = Si >= 0 ? D.ncount[Si] : 1;
-        const int64_t nu = Si >= 0 ? (D.nnchild[Si] > 0 ? D.nnchild[Si] : D.ncount[Si]) : 1;
-        const int64_t tl = Ti >= 0 && D.nnchild[Ti] == 0 ? D.ncount[Ti] : 1;
+        const int64_t ns = Si >= 0 ? ncount[Si] : 1;
+        const int64_t nu = Si >= 0 ? (nnchild[Si] > 0 ? nnchild[Si] : ncount[Si]) : 1;
+        const int64_t tl = Ti >= 0 && nnchild[Ti] == 0 ? ncount[Ti] : 1;
         c.u += nu;
         c.q += ns;
         c.dv += ns * tl;
@@ -1530,7 +1936,7 @@ int descent_step(msp_tree *t, const float *w, const float *a, const msp_fgt_para
     }
     hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(64), 0, s, da.ctr + C_M, m);
     MSP_CHECK_LAUNCH();
-    MSP_TRY(launch_step(D, da, bsumF, bsumU, &q, seed, step, s));
+    MSP_TRY(launch_step(D, da, bsumF, bsumU, &q, seed, step, nullptr, s));
     int64_t ctr[C_COUNT];
     MSP_HIP(hipMemcpyAsync(ctr, da.ctr, sizeof(ctr), hipMemcpyDeviceToHost, s));
     MSP_HIP(hipStreamSynchronize(s));
@@ -1584,10 +1990,9 @@ int partner_descent(msp_tree *t, const float *w, const float *a, const msp_fgt_p
     // every step takes at least one side one level down; neurons sit below the
     // deepest level, so 2 (depth + 2) steps empty the frontier.  The host stays at
     // most two steps ahead of the device and stops once a step has emptied the
-    // frontier (the frontier size after each step is copied to page-locked memory).
+    // frontier (each step's last kernel writes the frontier's size to page-locked memory).
     const int max_steps = 2 * (t->depth + 2) + 2;
-    MSP_TRY(t->desc_stage.ensure((size_t)max_steps * 8));
-    volatile int64_t *msize = static_cast<volatile int64_t *>(t->desc_stage.p);
+    volatile int64_t *msize = static_cast<volatile int64_t *>(t->desc_stage.p) + S_COUNT;   // sized by desc_setup
     std::vector<hipEvent_t> ev((size_t)max_steps, nullptr);
     int rc = MSP_OK;
     int launched = 0;
@@ -1610,12 +2015,10 @@ int partner_descent(msp_tree *t, const float *w, const float *a, const msp_fgt_p
             sa.S2 = const_cast<int64_t *>(da.S);
             sa.T2 = const_cast<int64_t *>(da.T);
         }
-        rc = launch_step(D, sa, bsumF, bsumU, &q, seed, step, s);
+        rc = launch_step(D, sa, bsumF, bsumU, &q, seed, step, const_cast<int64_t *>(msize + step), s);
         if (rc != MSP_OK) break;
         ++launched;
-        if (hipMemcpyAsync(const_cast<int64_t *>(msize + step), da.ctr + C_M, 8, hipMemcpyDeviceToHost, s) !=
-                hipSuccess ||
-            hipEventRecord(ev[step], s) != hipSuccess) {
+        if (hipEventRecord(ev[step], s) != hipSuccess) {
             rc = fail(MSP_EHIP, "recording descent step %d", step);
             break;
         }
@@ -1636,7 +2039,8 @@ int partner_descent(msp_tree *t, const float *w, const float *a, const msp_fgt_p
     if (n_steps) *n_steps = (int32_t)ctr[C_STEPS];
     if (nr == 0) return MSP_OK;
     // acceptance at the dendrites (input indices): counts, offsets, buckets, ranks
-    DevBuf cnt, off, fill, bucket;
+    DevBuf cnt, off, fill, bucket, sums;
+    MSP_TRY(sums.ensure((size_t)kReqParts * 4));
     MSP_TRY(cnt.ensure((size_t)D.n * 4));
     MSP_TRY(off.ensure((size_t)D.n * 4));
     MSP_TRY(fill.ensure((size_t)D.n * 4));
@@ -1647,7 +2051,12 @@ int partner_descent(msp_tree *t, const float *w, const float *a, const msp_fgt_p
     hipLaunchKernelGGL(k_req_count, dim3(grid_for(nr, kBlock)), dim3(kBlock), 0, s, nr, req_dendrite,
                        cnt.as<int32_t>());
     MSP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_req_scan, dim3(1), dim3(1024), 0, s, D.n, cnt.as<int32_t>(), off.as<int32_t>());
+    const int64_t per = req_part(D.n);
+    const dim3 parts(grid_for(D.n, (int)per));
+    hipLaunchKernelGGL(k_req_sums, parts, dim3(kScanBlock), 0, s, D.n, per, cnt.as<int32_t>(), sums.as<int32_t>());
+    MSP_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_req_scan, parts, dim3(kScanBlock), 0, s, D.n, per, cnt.as<int32_t>(), sums.as<int32_t>(),
+                       off.as<int32_t>());
     MSP_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_req_fill, dim3(grid_for(nr, kBlock)), dim3(kBlock), 0, s, nr, req_dendrite,
                        off.as<int32_t>(), fill.as<int32_t>(), bucket.as<int32_t>());

@@ -913,6 +913,9 @@ k_partner_direct(int64_t nq, const int64_t *nq_dev, const int32_t *target_idx, c
 // Queries whose node holds more than kSmallNode and at most kDirectPoints
 // points: one wavefront per query sums the node's points directly, lane group g
 // (eight lanes) the points of child g.  Other queries return at once.
+// MANY: more queries than wavefronts, which go round them (a loop that never repeats
+// still cost 13% of the pass in scalar spills).
+template <bool MANY>
 __global__ void __launch_bounds__(256)
 k_partner_wave(int64_t nq, const int64_t *nq_dev, const int32_t *target_idx, const int32_t *node_id,
                const float *uniforms,
@@ -922,149 +925,150 @@ k_partner_wave(int64_t nq, const int64_t *nq_dev, const int32_t *target_idx, con
                double lox, double loy, double loz, double side, const float4 *ps, double sigma,
                float cutoff2, int unlimited, int exclude_self, float *probs, int32_t *choice,
                double *raw, unsigned long long *work) {
-    const int64_t q = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (q >= (nq_dev ? *nq_dev : nq)) return;
-    const int32_t ti = target_idx[q], X = node_id[q];
-    if (!(ti >= 0 && ti < n && X >= 0 && X < n_nodes && qpos[q] >= 0)) return;
-    const int nc = nnchild[X];
-    const int32_t fc = nfchild[X];
-    if (!(nc > 0 && fc > X && fc + nc <= n_nodes)) return;
-    const int32_t cnt = ncount[X];
-    if (cnt <= kSmallNode || cnt > kDirectPoints) return;
-    const int32_t si = qpos[q];
-    const float4 qt = ps[si];
-    const double tx = qt.x, ty = qt.y, tz = qt.z;
-    const double kexp = 1.4426950408889634 / (sigma * sigma);
-    const int lx = nlevel[X];
-    auto box_d2 = [&](int32_t u) {
-        const double h = side / (double)(1ll << nlevel[u]);
-        const double half = 0.5 * h;
-        const double gx = fmax(fabs(tx - (lox + (nix[u] + 0.5) * h)) - half, 0.0);
-        const double gy = fmax(fabs(ty - (loy + (niy[u] + 0.5) * h)) - half, 0.0);
-        const double gz = fmax(fabs(tz - (loz + (niz[u] + 0.5) * h)) - half, 0.0);
-        return gx * gx + gy * gy + gz * gz;
-    };
-    // child k of lane k: point range end, octant, within reach, node id
-    int32_t uend = 0, cid = -1;
-    int dg = 0, in = 0;
-    if (lane < nc) {
-        cid = fc + lane;
-        uend = nfirst[cid] + ncount[cid];
-        const int shf = nlevel[cid] - lx - 1;
-        dg = (((nix[cid] >> shf) & 1) << 2) | (((niy[cid] >> shf) & 1) << 1) | ((niz[cid] >> shf) & 1);
-        in = 1;
-        if (!unlimited) {
-            const double reach = sqrt(box_d2(X)) + sqrt((double)cutoff2);
-            in = box_d2(cid) <= reach * reach;
+    const int64_t total_q = nq_dev ? *nq_dev : nq, wave0 = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6);
+    for (int64_t q = wave0; q < total_q; q = MANY ? q + (int64_t)gridDim.x * (blockDim.x >> 6) : total_q) {
+        const int32_t ti = target_idx[q], X = node_id[q];
+        if (!(ti >= 0 && ti < n && X >= 0 && X < n_nodes && qpos[q] >= 0)) continue;
+        const int nc = nnchild[X];
+        const int32_t fc = nfchild[X];
+        if (!(nc > 0 && fc > X && fc + nc <= n_nodes)) continue;
+        const int32_t cnt = ncount[X];
+        if (cnt <= kSmallNode || cnt > kDirectPoints) continue;
+        const int32_t si = qpos[q];
+        const float4 qt = ps[si];
+        const double tx = qt.x, ty = qt.y, tz = qt.z;
+        const double kexp = 1.4426950408889634 / (sigma * sigma);
+        const int lx = nlevel[X];
+        auto box_d2 = [&](int32_t u) {
+            const double h = side / (double)(1ll << nlevel[u]);
+            const double half = 0.5 * h;
+            const double gx = fmax(fabs(tx - (lox + (nix[u] + 0.5) * h)) - half, 0.0);
+            const double gy = fmax(fabs(ty - (loy + (niy[u] + 0.5) * h)) - half, 0.0);
+            const double gz = fmax(fabs(tz - (loz + (niz[u] + 0.5) * h)) - half, 0.0);
+            return gx * gx + gy * gy + gz * gz;
+        };
+        // child k of lane k: point range end, octant, within reach, node id
+        int32_t uend = 0, cid = -1;
+        int dg = 0, in = 0;
+        if (lane < nc) {
+            cid = fc + lane;
+            uend = nfirst[cid] + ncount[cid];
+            const int shf = nlevel[cid] - lx - 1;
+            dg = (((nix[cid] >> shf) & 1) << 2) | (((niy[cid] >> shf) & 1) << 1) | ((niz[cid] >> shf) & 1);
+            in = 1;
+            if (!unlimited) {
+                const double reach = sqrt(box_d2(X)) + sqrt((double)cutoff2);
+                in = box_d2(cid) <= reach * reach;
+            }
         }
-    }
-    // the lane group g (lanes 8 g .. 8 g + 7) sums the points of child g, lane s of
-    // the group taking every eighth one with eight records in flight (the group
-    // reads whole lines); float32 terms relative to the node's closest approach
-    // when the node is narrow enough (as in the eight-lane pass), float64 otherwise
-    double g0, far2;
-    {
-        const double h = side / (double)(1ll << lx), half = 0.5 * h;
-        const double ax = fabs(tx - (lox + (nix[X] + 0.5) * h)), ay = fabs(ty - (loy + (niy[X] + 0.5) * h)),
-                     az = fabs(tz - (loz + (niz[X] + 0.5) * h));
-        far2 = (ax + half) * (ax + half) + (ay + half) * (ay + half) + (az + half) * (az + half);
-        const double gx = fmax(ax - half, 0.0), gy = fmax(ay - half, 0.0), gz = fmax(az - half, 0.0);
-        g0 = gx * gx + gy * gy + gz * gz;
-    }
-    const bool narrow = (far2 - g0) * kexp <= kSpan32 * 1.4426950408889634;
-    const float g0f = (float)g0, ksf = (float)kexp, txf = qt.x, tyf = qt.y, tzf = qt.z;
-    const int grp = lane >> 3, sl = lane & 7;
-    const int32_t gend = __shfl(uend, grp, 64), gcid = __shfl(cid, grp, 64);
-    const int gin = __shfl(in, grp, 64);
-    double mysum = 0.0;
-    if (gcid >= 0 && gin) {
-        const int32_t cf = nfirst[gcid];
-        if (narrow) {
-            float run = 0.f;
-            int nrun = 0;
-            for (int32_t j0 = cf + sl; j0 < gend; j0 += 64) {
-                float4 qv[8];
+        // the lane group g (lanes 8 g .. 8 g + 7) sums the points of child g, lane s of
+        // the group taking every eighth one with eight records in flight (the group
+        // reads whole lines); float32 terms relative to the node's closest approach
+        // when the node is narrow enough (as in the eight-lane pass), float64 otherwise
+        double g0, far2;
+        {
+            const double h = side / (double)(1ll << lx), half = 0.5 * h;
+            const double ax = fabs(tx - (lox + (nix[X] + 0.5) * h)), ay = fabs(ty - (loy + (niy[X] + 0.5) * h)),
+                         az = fabs(tz - (loz + (niz[X] + 0.5) * h));
+            far2 = (ax + half) * (ax + half) + (ay + half) * (ay + half) + (az + half) * (az + half);
+            const double gx = fmax(ax - half, 0.0), gy = fmax(ay - half, 0.0), gz = fmax(az - half, 0.0);
+            g0 = gx * gx + gy * gy + gz * gz;
+        }
+        const bool narrow = (far2 - g0) * kexp <= kSpan32 * 1.4426950408889634;
+        const float g0f = (float)g0, ksf = (float)kexp, txf = qt.x, tyf = qt.y, tzf = qt.z;
+        const int grp = lane >> 3, sl = lane & 7;
+        const int32_t gend = __shfl(uend, grp, 64), gcid = __shfl(cid, grp, 64);
+        const int gin = __shfl(in, grp, 64);
+        double mysum = 0.0;
+        if (gcid >= 0 && gin) {
+            const int32_t cf = nfirst[gcid];
+            if (narrow) {
+                float run = 0.f;
+                int nrun = 0;
+                for (int32_t j0 = cf + sl; j0 < gend; j0 += 64) {
+                    float4 qv[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) qv[u] = j0 + 8 * u < gend ? ps[j0 + 8 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    for (int u = 0; u < 8; ++u) qv[u] = j0 + 8 * u < gend ? ps[j0 + 8 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int32_t j = j0 + 8 * u;
-                    const float4 qj = qv[u];
-                    if (j >= gend || qj.w == 0.f || (exclude_self && j == si)) continue;
-                    const float ex = txf - qj.x, ey = tyf - qj.y, ez = tzf - qj.z;
-                    run = fmaf(qj.w, __builtin_amdgcn_exp2f((g0f - (ex * ex + ey * ey + ez * ez)) * ksf), run);
+                    for (int u = 0; u < 8; ++u) {
+                        const int32_t j = j0 + 8 * u;
+                        const float4 qj = qv[u];
+                        if (j >= gend || qj.w == 0.f || (exclude_self && j == si)) continue;
+                        const float ex = txf - qj.x, ey = tyf - qj.y, ez = tzf - qj.z;
+                        run = fmaf(qj.w, __builtin_amdgcn_exp2f((g0f - (ex * ex + ey * ey + ez * ez)) * ksf), run);
+                    }
+                    if (++nrun == 4) {
+                        mysum += (double)run;
+                        run = 0.f;
+                        nrun = 0;
+                    }
                 }
-                if (++nrun == 4) {
-                    mysum += (double)run;
-                    run = 0.f;
-                    nrun = 0;
+                mysum += (double)run;
+                mysum *= exp2_neg(g0 * kexp);
+            } else {
+                for (int32_t j = cf + sl; j < gend; j += 8) {
+                    const float4 qj = ps[j];
+                    if (qj.w == 0.f || (exclude_self && j == si)) continue;
+                    const double ex = tx - qj.x, ey = ty - qj.y, ez = tz - qj.z;
+                    mysum += (double)qj.w * exp2_neg((ex * ex + ey * ey + ez * ez) * kexp);
                 }
             }
-            mysum += (double)run;
-            mysum *= exp2_neg(g0 * kexp);
-        } else {
-            for (int32_t j = cf + sl; j < gend; j += 8) {
-                const float4 qj = ps[j];
-                if (qj.w == 0.f || (exclude_self && j == si)) continue;
-                const double ex = tx - qj.x, ey = ty - qj.y, ez = tz - qj.z;
-                mysum += (double)qj.w * exp2_neg((ex * ex + ey * ey + ez * ez) * kexp);
-            }
         }
-    }
-    mysum += __shfl_xor(mysum, 1, 64);
-    mysum += __shfl_xor(mysum, 2, 64);
-    mysum += __shfl_xor(mysum, 4, 64);
-    // per octant: child k's sum sits in lane 8 k
-    double S[8], total = 0.0;
-    int32_t cids[8];
+        mysum += __shfl_xor(mysum, 1, 64);
+        mysum += __shfl_xor(mysum, 2, 64);
+        mysum += __shfl_xor(mysum, 4, 64);
+        // per octant: child k's sum sits in lane 8 k
+        double S[8], total = 0.0;
+        int32_t cids[8];
 #pragma unroll
-    for (int d = 0; d < 8; ++d) {
-        S[d] = 0.0;
-        cids[d] = -1;
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const double sk = __shfl(mysum, 8 * k, 64);
-        const int dk = __shfl(dg, k, 64);
-        const int32_t ck = __shfl(cid, k, 64);
-#pragma unroll
-        for (int d = 0; d < 8; ++d)
-            if (ck >= 0 && d == dk) {
-                S[d] = sk;
-                cids[d] = ck;
-            }
-    }
-#pragma unroll
-    for (int d = 0; d < 8; ++d) total += S[d];
-    if (lane < 8) {
-        double mine = 0.0;
-#pragma unroll
-        for (int d = 0; d < 8; ++d)
-            if (d == lane) mine = S[d];
-        probs[q * 8 + lane] = total > 0.0 ? (float)(mine / total) : 0.f;
-        if (raw) raw[q * 8 + lane] = mine;
-    }
-    if (lane == 0 && work) {
-        atomicAdd(&work[W_WAVE_Q], 1ull);
-        atomicAdd(&work[W_WAVE_PAIRS], (unsigned long long)cnt);
-    }
-    if (lane == 0 && choice) {
-        int32_t pick = -1;
-        if (total > 0.0 && uniforms) {
-            const double target = (double)uniforms[q] * total;
-            double accp = 0.0;
-            int32_t last = -1;
-#pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                if (pick >= 0) continue;
-                if (S[d] > 0.0) last = cids[d];
-                accp += S[d];
-                if (accp > target && S[d] > 0.0) pick = cids[d];
-            }
-            if (pick < 0) pick = last;
+        for (int d = 0; d < 8; ++d) {
+            S[d] = 0.0;
+            cids[d] = -1;
         }
-        choice[q] = pick;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const double sk = __shfl(mysum, 8 * k, 64);
+            const int dk = __shfl(dg, k, 64);
+            const int32_t ck = __shfl(cid, k, 64);
+#pragma unroll
+            for (int d = 0; d < 8; ++d)
+                if (ck >= 0 && d == dk) {
+                    S[d] = sk;
+                    cids[d] = ck;
+                }
+        }
+#pragma unroll
+        for (int d = 0; d < 8; ++d) total += S[d];
+        if (lane < 8) {
+            double mine = 0.0;
+#pragma unroll
+            for (int d = 0; d < 8; ++d)
+                if (d == lane) mine = S[d];
+            probs[q * 8 + lane] = total > 0.0 ? (float)(mine / total) : 0.f;
+            if (raw) raw[q * 8 + lane] = mine;
+        }
+        if (lane == 0 && work) {
+            atomicAdd(&work[W_WAVE_Q], 1ull);
+            atomicAdd(&work[W_WAVE_PAIRS], (unsigned long long)cnt);
+        }
+        if (lane == 0 && choice) {
+            int32_t pick = -1;
+            if (total > 0.0 && uniforms) {
+                const double target = (double)uniforms[q] * total;
+                double accp = 0.0;
+                int32_t last = -1;
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+                    if (pick >= 0) continue;
+                    if (S[d] > 0.0) last = cids[d];
+                    accp += S[d];
+                    if (accp > target && S[d] > 0.0) pick = cids[d];
+                }
+                if (pick < 0) pick = last;
+            }
+            choice[q] = pick;
+        }
     }
 }
 
@@ -1832,7 +1836,11 @@ int launch_direct(msp_tree *t, const QuerySet &q, hipStream_t s) {
     }
     {
         PhaseScope pw(&t->timing, PH_PARTNER_WAVE, s);
-        hipLaunchKernelGGL(k_partner_wave, dim3(grid_for(q.nq, 4)), dim3(256), 0, s, q.nq, q.nq_dev, q.target_idx,
+        // one query per wavefront up to 65,536; beyond (the descent's tables hold as many
+        // as there are neurons with axons, most steps use few), the wavefronts go round
+        const bool many = q.nq > 65536;
+        const unsigned blocks = grid_for(many ? 65536 : q.nq, 4);
+        hipLaunchKernelGGL(many ? k_partner_wave<true> : k_partner_wave<false>, dim3(blocks), dim3(256), 0, s, q.nq, q.nq_dev, q.target_idx,
                            q.node_id, q.uniforms, t->n, t->n_nodes, q.qpos, t->nlevel.as<int32_t>(),
                            t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nfchild.as<int32_t>(),
                            t->nnchild.as<int32_t>(), t->nix.as<int32_t>(), t->niy.as<int32_t>(),

@@ -258,3 +258,30 @@ def test_clustered_steps_match_oracle():
         S = np.array([s for s, _ in onxt], np.int64)
         T = np.array([t for _, t in onxt], np.int64)
     print(f"  {total} choices, {flips} near-tie flips")
+
+
+@pytest.mark.parametrize("n,leaf_max,sigma,cutoff", [(3000, 700, 60.0, 0.0), (2600, 90, 40.0, 1.0), (1300, 8, 90.0, 0.0)])
+def test_box_pairs_by_size(n, leaf_max, sigma, cutoff):
+    """Direct box pairs by the sizes that decide how they are summed: dendrite boxes of up
+    to 64 points (many pairs per wavefront), of 65 to 256 and beyond (one to four points
+    per lane, several rounds), axon boxes of more than 512 points (two tiles), a box
+    paired with itself.  2e-5 of the value: float32 terms relative to the boxes' closest
+    approach, float64 sums."""
+    wl = synth.uniform_box(n, extent=(420.0, 400.0, 380.0), sigma=sigma, seed=60 + n)
+    tree, od, w, a = _setup(wl, leaf_max)
+    print(f"box pairs, {n} neurons, leaf_max {leaf_max}", flush=True)
+    tree.descent_step(w, a, np.array([0]), np.array([0]), 0, 5, sigma, cutoff_sigmas=cutoff)
+    bn, F = tree.debug_buffer(7).cpu().numpy(), tree.debug_buffer(4).cpu().numpy()
+    ps, pc = tree.debug_buffer(5).cpu().numpy(), tree.debug_buffer(6).cpu().numpy()
+    size = od.tree.count[bn]
+    picks = [synth.sample_indices(ps.size, 40, seed=503), np.nonzero(ps == pc)[0][:10],
+             np.argsort(size[pc], kind="stable")[-20:], np.argsort(size[ps], kind="stable")[-20:]]
+    for k in np.unique(np.concatenate(picks)):
+        ref = od.att(int(bn[ps[k]]), int(bn[pc[k]]))
+        assert abs(F[k] - ref) <= 2e-5 * ref, (k, size[ps[k]], size[pc[k]], F[k], ref)
+    # and a whole descent, whose leaves hold up to leaf_max candidates
+    got = tree.partner_descent(w, a, sigma, 8, cutoff_sigmas=0.0)
+    g = sorted(zip(got["axon"].cpu().numpy().tolist(), got["dendrite"].cpu().numpy().tolist()))
+    oreq, mmin = _oracle_run(od, 8)
+    if mmin >= TIE:
+        assert g == oreq
