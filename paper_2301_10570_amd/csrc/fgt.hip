@@ -505,8 +505,10 @@ __device__ inline void split_bf16(const float *src, int stride, bf16x8 &hi, bf16
 // offset, row and column) and sweeps the r columns in 16-wide MFMA tiles
 // (v_mfma_f32_16x16x4f32, same lane layout as above).  LDS: RT x (U + 1) floats of
 // In and (2G - 1) p^2 floats of T (dynamic).
+constexpr int kOpStr = 80;   // floats of an 8 x 8 operator block in LDS (p = 8)
 __host__ __device__ inline size_t m2l_gemm_lds(int U, int G, int p, int RT) {
     // input rows, operator table, and (cell-major modes) row bases and column offsets
+    if (p == 8) return ((size_t)RT * (U + 2) + (size_t)(2 * G - 1) * kOpStr) * 4 + (size_t)RT * 8;
     const size_t nT = (size_t)(2 * G - 1) * p * p;
     return ((size_t)RT * (U + 1) + nT + (nT & 1)) * 4 + (size_t)RT * 8 + (size_t)U * 4;
 }
@@ -649,19 +651,217 @@ __device__ void m2l_gemm_tile_split(const float *In, float *Out, int64_t R, int 
     }
 }
 
+// Which cells of a pass matter, by row of cells (the pass's other two axes, as the
+// rows r lie): the cells along the axis whose inputs can be non-zero, and those whose
+// outputs are read later.  NULL: all of them.  glo: cells along the rows' faster axis.
+struct PassMask {
+    const uint64_t *in = nullptr, *out = nullptr;
+    int glo = 1;
+};
+
+// The OR of the masks of rows r0 .. r0 + rt - 1 (rt <= 64; eight rows per cell), on
+// every lane of the wavefront.
+__device__ inline uint64_t rows_mask(const uint64_t *m, int glo, int64_t r0, int64_t R, int rt) {
+    const int lane = threadIdx.x & 63;
+    const int64_t r = r0 + lane, lo = 8 * (int64_t)glo;
+    uint64_t v = lane < rt && r < R ? m[(r / lo / 8) * glo + (r % lo) / 8] : 0ull;
+    for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, 64);
+    return ((uint64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// The float32 tile for p = 8.  The contraction runs over the source cells (two K steps
+// of four terms each), four at a time, so that cells without moments and cells beyond
+// the band cost nothing.  Input rows are padded by two floats and an operator block is
+// kept transposed (source term, then target term) every 80 floats, so that the 32 lanes
+// served together read 32 banks; with rows padded by one and blocks untransposed the
+// operand reads took four times as long and bound the pass as much as the matrix cores
+// did.
+template <int RT, int MODE>
+__device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, const float *T, int64_t r0, float *sm,
+                               int Ga, int band, PassMask pm) {
+    constexpr int NR = RT / 16;   // 16-wide column tiles per block
+    constexpr int NC = 4;         // source cells per round
+    const int U = G * 8, UP = U + 2;
+    uint64_t kin = ~0ull, kout = ~0ull;
+    if (pm.in) {   // (G <= 64)
+        kin = rows_mask(pm.in, pm.glo, r0, R, RT);
+        kout = rows_mask(pm.out, pm.glo, r0, R, RT);
+        if (kin == 0 || kout == 0) return;   // nothing here is read later
+    }
+    float *sIn = sm, *sT = sm + (size_t)RT * UP;
+    // (both operands are staged with four loads in flight per thread: one at a time, the
+    // loads' latencies took longer than the products)
+    const int nT4 = (2 * G - 1) * 16;
+    for (int e0 = threadIdx.x; e0 < nT4; e0 += 4 * 256) {
+        float4 t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = reinterpret_cast<const float4 *>(T)[e0 + 256 * k < nT4 ? e0 + 256 * k : 0];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int e = e0 + 256 * k;   // block e / 16, target term (e / 2) % 8, source terms 4 (e % 2) ..
+            if (e >= nT4) continue;
+            float *d = sT + (e >> 4) * kOpStr + (e & 1) * 32 + ((e >> 1) & 7);
+            d[0] = t[k].x;
+            d[8] = t[k].y;
+            d[16] = t[k].z;
+            d[24] = t[k].w;
+        }
+    }
+    // U = 8 G: rows in 16-byte chunks, which never straddle a cell
+    const int U4 = U / 4;
+    int64_t *rowbase = reinterpret_cast<int64_t *>(sT + (2 * G - 1) * kOpStr);
+    if constexpr (MODE != 0) {
+        for (int rr = threadIdx.x; rr < RT; rr += 256) {
+            const int64_t r = r0 + rr;
+            int64_t b = -1;
+            if (r < R) {
+                if constexpr (MODE == 1) {   // row r = (z', y') of the cell-major moments
+                    const int Uy = Ga * 8;
+                    const int zq = (int)(r / Uy), yq = (int)(r % Uy);
+                    b = ((int64_t)(zq >> 3) * Ga + (yq >> 3)) * G * 512 + ((zq & 7) * 8 + (yq & 7)) * 8;
+                } else {                     // row q = (ky, kx, ay, ax) in cell-column order
+                    const int c = (int)(r >> 6), rem = (int)(r & 63);
+                    b = ((int64_t)((c / Ga) * 8 + (rem >> 3)) * Ga * 8 + (c % Ga) * 8 + (rem & 7)) * U;
+                }
+            }
+            rowbase[rr] = b;
+        }
+        __syncthreads();
+    }
+    constexpr int NB = RT >= 32 ? 8 : 4;   // loads in flight
+    const int dr = 256 / U4, dc = 256 - dr * U4;
+    int rr = threadIdx.x / U4, c4 = threadIdx.x - rr * U4;
+    while (rr < RT) {
+        float4 v[NB];
+        int at[NB];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            at[k] = rr < RT ? rr * UP + 4 * c4 : -1;
+            if (pm.in && !((kin >> (c4 >> 1)) & 1)) at[k] = -1;   // never read
+            const float *src = nullptr;
+            if constexpr (MODE == 0) {
+                const int64_t r = r0 + rr;
+                if (r < R) src = In + r * U + 4 * c4;
+            } else {
+                const int64_t b = rowbase[rr < RT ? rr : 0];
+                // MODE 1: column u = 4 c4 is (cell u / 8, term u % 8), 512 floats per cell
+                const int64_t col = MODE == 1 ? (int64_t)(c4 >> 1) * 512 + (c4 & 1) * 4 : 4 * c4;
+                if (b >= 0) src = In + b + col;
+            }
+            v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (at[k] >= 0 && src) v[k] = *reinterpret_cast<const float4 *>(src);
+            rr += dr;
+            c4 += dc;
+            if (c4 >= U4) {
+                c4 -= U4;
+                ++rr;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (at[k] < 0) continue;
+            float2 *d = reinterpret_cast<float2 *>(sIn + at[k]);
+            d[0] = make_float2(v[k].x, v[k].y);
+            d[1] = make_float2(v[k].z, v[k].w);
+        }
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = lane >> 4, nv = (U + 15) / 16;
+    // the grid's y index picks a group of four 16-wide column blocks (one group
+    // when the grid is one-dimensional)
+    for (int vc = wave + 4 * (int)blockIdx.y; vc < nv; vc += 4 * (int)gridDim.y) {
+        if (pm.in && !((kout >> (2 * vc)) & 3)) continue;
+        const int v = vc * 16 + (lane & 15);
+        const int tv = v >> 3, b = v & 7;
+        const bool has = v < U;
+        f32x4 acc[NR];
+#pragma unroll
+        for (int j = 0; j < NR; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // source cells within `band` of this column block's two cells (those beyond are
+        // negligible); entry of term 4 h + q of cell s: base - 80 s + 32 h
+        const int s_lo = 2 * vc - band > 0 ? 2 * vc - band : 0;
+        const int s_hi = 2 * vc + 1 + band < G - 1 ? 2 * vc + 1 + band : G - 1;
+        const int base = has ? (tv + G - 1) * kOpStr + q * 8 + b : 0;
+        const float *bcol = sIn + (lane & 15) * UP + q;
+        bool any = !pm.in;
+        auto round = [&](const int (&sc)[NC], int cnt) {
+            float a[2 * NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const float t = sT[has ? base - kOpStr * sc[c] + 32 * h : 0];
+                    a[2 * c + h] = has && c < cnt ? t : 0.f;
+                }
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                float bv[2 * NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) bv[2 * c + h] = bcol[16 * j * UP + 8 * sc[c] + 4 * h];
+#pragma unroll
+                for (int k = 0; k < 2 * NC; ++k)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], bv[k], acc[j], 0, 0, 0);
+            }
+        };
+        if (pm.in) {
+            uint64_t m = kin & (~0ull << s_lo) & (~0ull >> (63 - s_hi));
+            any = m != 0;
+            while (m) {
+                int sc[NC], cnt = 0;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    sc[c] = c == 0 || m ? __ffsll((unsigned long long)m) - 1 : sc[0];   // (past the last: any staged cell)
+                    cnt += m != 0;
+                    m &= m - (m != 0);
+                }
+                round(sc, cnt);
+            }
+        } else {
+            for (int s0 = s_lo; s0 <= s_hi; s0 += NC) {
+                int sc[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) sc[c] = s0 + c <= s_hi ? s0 + c : s0;
+                round(sc, s_hi - s0 + 1);
+            }
+        }
+        if (!any) continue;   // exactly zero, and not read later
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int vo = vc * 16 + 4 * q + i;
+                const int64_t r = r0 + 16 * j + (lane & 15);
+                if (vo < U && r < R) {
+                    if constexpr (MODE == 2) {   // vo = z' = (kz, az); r = q in cell-column order
+                        const int qq = (int)r;
+                        Out[(int64_t)(vo >> 3) * R * 8 + (vo & 7) * 64 + (int64_t)(qq >> 6) * 512 + (qq & 63)] = acc[j][i];
+                    } else {
+                        Out[(int64_t)vo * R + r] = acc[j][i];
+                    }
+                }
+            }
+    }
+}
+
+// The tile for any p (PT = 8: the tiles above, as split bfloat16 products with SPLIT).
 template <int RT, int MODE = 0, int PT = 0, bool SPLIT = false>
-__device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p_rt, int G, const float *T, int64_t r0,
-                              float *sm, int Ga = 0, int band = 1 << 30) {
+__device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p, int G, const float *T, int64_t r0,
+                              float *sm, int Ga = 0, int band = 1 << 30, PassMask pm = PassMask{}) {
     if constexpr (SPLIT) {
         static_assert(PT == 8, "the split bfloat16 tile is built for p = 8");
         m2l_gemm_tile_split<RT, MODE>(In, Out, R, G, T, r0, sm, Ga, band);
         return;
     }
-    // PT = 8: the term count is a compile-time 8, so the tile's index arithmetic
-    // folds into constants and rows are read 16 bytes at a time; PT = 0: any p
+    if constexpr (PT == 8) {
+        m2l_gemm_tile8<RT, MODE>(In, Out, R, G, T, r0, sm, Ga, band, pm);
+        return;
+    }
     constexpr int NR = RT / 16;   // 16-wide column tiles per block
     constexpr int KC = 8;         // K steps (of 4) per operator chunk in registers
-    const int p = PT ? PT : p_rt;
     const int U = G * p;
     const int UP = U + 1;
     float *sIn = sm;
@@ -670,54 +870,7 @@ __device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p_rt, 
     for (int e = threadIdx.x; e < nT; e += 256) sT[e] = T[e];
     const int pp = p * p;
     const int p3 = pp * p;
-    if constexpr (PT == 8) {
-        // U = 8 G: rows in 16-byte chunks, which never straddle a cell
-        const int U4 = U / 4;
-        if constexpr (MODE == 0) {
-            for (int e = threadIdx.x; e < RT * U4; e += 256) {
-                const int rr = e / U4, c4 = e - rr * U4;
-                const int64_t r = r0 + rr;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (r < R) v = *reinterpret_cast<const float4 *>(In + r * U + 4 * c4);
-                float *d = sIn + rr * UP + 4 * c4;
-                d[0] = v.x;
-                d[1] = v.y;
-                d[2] = v.z;
-                d[3] = v.w;
-            }
-        } else {
-            int64_t *rowbase = reinterpret_cast<int64_t *>(sT + nT + (nT & 1));
-            for (int rr = threadIdx.x; rr < RT; rr += 256) {
-                const int64_t r = r0 + rr;
-                int64_t b = -1;
-                if (r < R) {
-                    if constexpr (MODE == 1) {
-                        const int Uy = Ga * 8;
-                        const int zq = (int)(r / Uy), yq = (int)(r % Uy);
-                        b = ((int64_t)(zq >> 3) * Ga + (yq >> 3)) * G * 512 + ((zq & 7) * 8 + (yq & 7)) * 8;
-                    } else {
-                        const int c = (int)(r >> 6), rem = (int)(r & 63);
-                        b = ((int64_t)((c / Ga) * 8 + (rem >> 3)) * Ga * 8 + (c % Ga) * 8 + (rem & 7)) * U;
-                    }
-                }
-                rowbase[rr] = b;
-            }
-            __syncthreads();
-            for (int e = threadIdx.x; e < RT * U4; e += 256) {
-                const int rr = e / U4, c4 = e - rr * U4;
-                const int64_t b = rowbase[rr];
-                // MODE 1: column u = 4 c4 is (cell u / 8, term u % 8), 512 floats per cell
-                const int64_t col = MODE == 1 ? (int64_t)(c4 >> 1) * 512 + (c4 & 1) * 4 : 4 * c4;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (b >= 0) v = *reinterpret_cast<const float4 *>(In + b + col);
-                float *d = sIn + rr * UP + 4 * c4;
-                d[0] = v.x;
-                d[1] = v.y;
-                d[2] = v.z;
-                d[3] = v.w;
-            }
-        }
-    } else if constexpr (MODE == 0) {
+    if constexpr (MODE == 0) {
         for (int e = threadIdx.x; e < RT * U; e += 256) {
             const int rr = e / U, u = e % U;
             const int64_t r = r0 + rr;
@@ -774,24 +927,17 @@ __device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p_rt, 
         }
         const int u0 = 4 * kb + (lane >> 4);
         int s = u0 / p, ai = u0 % p;   // column u = 4 k + lane / 16 as (cell, term)
-        // p = 8: entry of step k at base8 - 64 (k / 2) + 4 (k % 2)
-        const int base8 = ((tv + G - 1) * 8 + b) * 8 + (lane >> 4);
         for (int k0 = kb; k0 < ke; k0 += KC) {
             // this lane's operator entries M[v][u] for KC steps
             float a[KC];
 #pragma unroll
             for (int k = 0; k < KC; ++k) {
-                if constexpr (PT == 8) {
-                    const int kk = k0 + k;
-                    a[k] = (v < U && kk < ke) ? sT[base8 - 64 * (kk >> 1) + 4 * (kk & 1)] : 0.f;
-                } else {
-                    const int u = 4 * (k0 + k) + (lane >> 4);
-                    a[k] = (v < U && u < U && k0 + k < ke) ? sT[((tv - s + G - 1) * p + b) * p + ai] : 0.f;
-                    ai += 4;
-                    while (ai >= p) {
-                        ai -= p;
-                        ++s;
-                    }
+                const int u = 4 * (k0 + k) + (lane >> 4);
+                a[k] = (v < U && u < U && k0 + k < ke) ? sT[((tv - s + G - 1) * p + b) * p + ai] : 0.f;
+                ai += 4;
+                while (ai >= p) {
+                    ai -= p;
+                    ++s;
                 }
             }
 #pragma unroll
@@ -799,13 +945,8 @@ __device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p_rt, 
                 const float *bcol = sIn + (16 * j + (lane & 15)) * UP + (lane >> 4);
 #pragma unroll
                 for (int k = 0; k < KC; ++k) {
-                    float bv;
-                    if constexpr (PT == 8) {
-                        bv = k0 + k < ke ? bcol[4 * (k0 + k)] : 0.f;
-                    } else {
-                        const int u = 4 * (k0 + k) + (lane >> 4);
-                        bv = (u < U && k0 + k < ke) ? bcol[4 * (k0 + k)] : 0.f;
-                    }
+                    const int u = 4 * (k0 + k) + (lane >> 4);
+                    const float bv = (u < U && k0 + k < ke) ? bcol[4 * (k0 + k)] : 0.f;
                     acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], bv, acc[j], 0, 0, 0);
                 }
             }
@@ -830,9 +971,9 @@ __device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p_rt, 
 
 template <int RT>
 __global__ void __launch_bounds__(256) k_m2l_gemm(const float *In, float *Out, int64_t R, int p, int G,
-                                                  const float *T, int band) {
+                                                  const float *T, int band, PassMask pm) {
     extern __shared__ float sm[];
-    if (p == 8) m2l_gemm_tile<RT, 0, 8>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band);
+    if (p == 8) m2l_gemm_tile<RT, 0, 8>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band, pm);
     else m2l_gemm_tile<RT>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band);
 }
 
@@ -2557,6 +2698,7 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
     const bool bf16x3 = (prm->flags & MSP_M2L_BF16X3) != 0;
     for (int k = 0; k < 3; ++k) {
         const Pass &ps = passes[k];
+        const PassMask pm{};
         PhaseScope sc(&t->timing, PH_M2L_X + k, s);
         if (valu) {
             dim3 grid((unsigned)((ps.R + TR - 1) / TR), (unsigned)((ps.U + TV - 1) / TV));
@@ -2599,11 +2741,11 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
                 const dim3 grid((unsigned)rows, (unsigned)cg);
                 const int band = m2l_band(p, step, ps.G);
                 if (RT == 64)
-                    hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
+                    hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm);
                 else if (RT == 32)
-                    hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
+                    hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm);
                 else
-                    hipLaunchKernelGGL(k_m2l_gemm<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
+                    hipLaunchKernelGGL(k_m2l_gemm<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm);
             } else {
                 dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
                 hipLaunchKernelGGL(k_m2l_pass_mfma, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
