@@ -134,6 +134,101 @@ __device__ inline void cell_range(const uint64_t *keys, int64_t n, int level, in
     end = lower_bound_u64(keys, start, n, (prefix + 1ull) << sh);
 }
 
+// Point range of cell g = (kz Gy + ky) Gx + kx from the table, or by search without one.
+__device__ inline void cell_points(const int2 *cells, int64_t g, const uint64_t *keys, int64_t n, int level, int kx,
+                                   int ky, int kz, int64_t &start, int64_t &end) {
+    if (cells) {
+        const int2 r = cells[g];
+        start = r.x;
+        end = r.y;
+    } else {
+        cell_range(keys, n, level, kx, ky, kz, start, end);
+    }
+}
+
+__global__ void __launch_bounds__(kBlock) k_cell_clear(int64_t n16, uint4 *p) {
+    const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+    if (i < n16) p[i] = make_uint4(0, 0, 0, 0);
+}
+
+// The table of the cells' point ranges (cleared before): the first point of a cell
+// writes its start and the previous cell's end.  One pass over the keys, once per tree
+// and level, in place of two searches over all of them (a chain of some twenty loads)
+// in every block of every pass.  With masks: the cell's bit in its x row (inx) and its
+// z column (outz).
+__global__ void __launch_bounds__(kBlock) k_cell_points(const uint64_t *keys, int64_t n, int level, int Gx, int Gy,
+                                                        int Gz, int2 *cells, unsigned long long *inx,
+                                                        unsigned long long *outz) {
+    const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+    if (i >= n) return;
+    const int sh = 3 * (kDepth - level);
+    const uint64_t c = keys[i] >> sh, b = i > 0 ? keys[i - 1] >> sh : ~0ull;
+    auto at = [&](uint64_t m, int &kx, int &ky, int &kz) {
+        kx = (int)compact3(m >> 2);
+        ky = (int)compact3(m >> 1);
+        kz = (int)compact3(m);
+        return ((int64_t)kz * Gy + ky) * Gx + kx;
+    };
+    int kx, ky, kz;
+    if (i == n - 1) cells[at(c, kx, ky, kz)].y = (int)n;
+    if (c == b) return;
+    if (i > 0) cells[at(b, kx, ky, kz)].y = (int)i;
+    cells[at(c, kx, ky, kz)].x = (int)i;
+    if (inx) {
+        atomicOr(&inx[(int64_t)kz * Gy + ky], 1ull << kx);
+        atomicOr(&outz[(int64_t)ky * Gx + kx], 1ull << kz);
+    }
+}
+
+// Cells that a column block of two cells reads: the pair of cell c widened by the band.
+__device__ inline uint64_t mask_range(int lo, int hi) {   // bits max(lo, 0) .. min(hi, 63)
+    lo = lo > 0 ? lo : 0;
+    hi = hi < 63 ? hi : 63;
+    return lo > hi ? 0ull : (~0ull << lo) & (~0ull >> (63 - hi));
+}
+__device__ inline uint64_t reads_of(int c, int band) { return mask_range((c & ~1) - band, (c | 1) + band); }
+// The cells whose column blocks read cell c.
+__device__ inline uint64_t readers_of(int c, int band) {
+    const int lo = c - 1 - band;   // the pairs (2 P, 2 P + 1) with 2 P - band <= c <= 2 P + 1 + band
+    return mask_range(lo > 0 ? (lo + 1) & ~1 : 0, (c + band) | 1);
+}
+
+// The masks of the three passes (one block).  Inputs that can be non-zero: x rows as
+// occupied (inx), then whatever reads a non-zero input (iny, inz).  Outputs that are
+// read: the occupied cells in z (outz), then whatever they read (outy, outx); the others
+// are not written.  Over 64 blobs in 32 x 32 x 32 cells (8% of them occupied) the three
+// passes take 98 us instead of 190.
+__global__ void __launch_bounds__(1024) k_cell_masks(int Gx, int Gy, int Gz, int bx, int by, int bz,
+                                                     const uint64_t *inx, uint64_t *iny, uint64_t *inz,
+                                                     uint64_t *outx, uint64_t *outy, const uint64_t *outz) {
+    for (int e = threadIdx.x; e < Gx * Gz; e += 1024) {
+        const int kx = e / Gz, kz = e % Gz;
+        const uint64_t rx = reads_of(kx, bx), rz = readers_of(kz, bz);
+        uint64_t i = 0, o = 0;
+        for (int ky = 0; ky < Gy; ++ky) {
+            i |= (uint64_t)((inx[kz * Gy + ky] & rx) != 0) << ky;
+            o |= (uint64_t)((outz[ky * Gx + kx] & rz) != 0) << ky;
+        }
+        iny[e] = i;
+        outy[e] = o;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < Gx * Gy; e += 1024) {
+        const int ky = e / Gx, kx = e % Gx;
+        const uint64_t ry = reads_of(ky, by);
+        uint64_t i = 0;
+        for (int kz = 0; kz < Gz; ++kz) i |= (uint64_t)((iny[kx * Gz + kz] & ry) != 0) << kz;
+        inz[e] = i;
+    }
+    for (int e = threadIdx.x; e < Gy * Gz; e += 1024) {
+        const int kz = e / Gy, ky = e % Gy;
+        const uint64_t ry = readers_of(ky, by);
+        uint64_t o = 0;
+        for (int kx = 0; kx < Gx; ++kx) o |= (uint64_t)((outy[kx * Gz + kz] & ry) != 0) << kx;
+        outx[e] = o;
+    }
+}
+
 // One block per cell of the grid; moments written in the grid layout
 // [kz][az][ky][ay][kx][ax].  Lane l of a wave owns az = l % P and handles every
 // (64/P)-th point of the wave's share; it keeps the P x P moments (ax, ay) of its
@@ -234,14 +329,14 @@ __device__ void p2m_cell(const float4 *ps, const int32_t *perm, const float *w, 
 // [kz][az][ky][ay][kx][ax] (empty cells get zeros).
 template <int P>
 __global__ void __launch_bounds__(kBlock) k_p2m(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                const int32_t *perm, const float *w,
+                                                const int32_t *perm, const float *w, const int2 *cells,
                                                 int level, int Gx, int Gy, int Gz, double lox,
                                                 double loy, double loz, double cell,
                                                 double inv_sigma, float *A, float4 *stage) {
     const int64_t g = blockIdx.x;
     const int kx = (int)(g % Gx), ky = (int)((g / Gx) % Gy), kz = (int)(g / ((int64_t)Gx * Gy));
     int64_t start, end;
-    cell_range(keys, n, level, kx, ky, kz, start, end);
+    cell_points(cells, g, keys, n, level, kx, ky, kz, start, end);
     p2m_cell<P>(ps, perm, w, Gx, Gy, lox, loy, loz, cell, inv_sigma, A, kx, ky, kz, start, end, stage);
 }
 
@@ -256,15 +351,24 @@ __global__ void __launch_bounds__(kBlock) k_p2m(const uint64_t *keys, int64_t n,
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPowStr = 25;   // floats per staged point (24 powers, padded)
 __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                      const int32_t *perm, const float *w, int level, int Gx,
-                                                      int Gy, int Gz, double lox, double loy, double loz,
+                                                      const int32_t *perm, const float *w, const int2 *cells,
+                                                      int level, int Gx, int Gy, int Gz, double lox, double loy, double loz,
                                                       double cell, double inv_sigma, float *A, float4 *stage) {
     __shared__ float pw[kBlock * kPowStr];
     __shared__ float red[kBlock / 64][512];
-    const int64_t g = blockIdx.x;
+    // one cell per block, or every gridDim.x-th one in grids of mostly empty cells (32,768
+    // cells, 8% with points: 238 us with a search in every block, 52 us)
+    for (int64_t g = blockIdx.x; g < (int64_t)Gx * Gy * Gz; g += gridDim.x) {
     const int kx = (int)(g % Gx), ky = (int)((g / Gx) % Gy), kz = (int)(g / ((int64_t)Gx * Gy));
     int64_t start, end;
-    cell_range(keys, n, level, kx, ky, kz, start, end);
+    cell_points(cells, g, keys, n, level, kx, ky, kz, start, end);
+    if (start == end) {   // no points: zeros, 16 bytes a thread
+        const int e = threadIdx.x;
+        if (e < 128)
+            *reinterpret_cast<float4 *>(A + (((int64_t)kz * 8 + (e >> 4)) * Gy * 8 + (int64_t)ky * 8 + ((e >> 1) & 7)) *
+                                                Gx * 8 + (int64_t)kx * 8 + 4 * (e & 1)) = make_float4(0.f, 0.f, 0.f, 0.f);
+        continue;
+    }
     const double cx = lox + (kx + 0.5) * cell, cy = loy + (ky + 0.5) * cell, cz = loz + (kz + 0.5) * cell;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     float4 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -350,6 +454,7 @@ __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int6
         for (int k = 2; k <= ey; ++k) f *= (float)k;
         for (int k = 2; k <= ez; ++k) f *= (float)k;
         A[(((int64_t)kz * 8 + ez) * Ry + (int64_t)ky * 8 + ey) * Rx + (int64_t)kx * 8 + ex] = sum / f;
+    }    __syncthreads();   // red and pw may be written again
     }
 }
 
@@ -506,9 +611,12 @@ __device__ inline void split_bf16(const float *src, int stride, bf16x8 &hi, bf16
 // (v_mfma_f32_16x16x4f32, same lane layout as above).  LDS: RT x (U + 1) floats of
 // In and (2G - 1) p^2 floats of T (dynamic).
 constexpr int kOpStr = 80;   // floats of an 8 x 8 operator block in LDS (p = 8)
-__host__ __device__ inline size_t m2l_gemm_lds(int U, int G, int p, int RT) {
+// The largest cell offset that a tile of two-cell column blocks meets (p = 8).
+__host__ __device__ inline int m2l_reach(int G, int band) { return band < G - 2 ? band + 1 : G - 1; }
+__host__ __device__ inline size_t m2l_gemm_lds(int U, int G, int p, int RT, int band) {
     // input rows, operator table, and (cell-major modes) row bases and column offsets
-    if (p == 8) return ((size_t)RT * (U + 2) + (size_t)(2 * G - 1) * kOpStr) * 4 + (size_t)RT * 8;
+    if (p == 8)
+        return ((size_t)RT * (U + 2) + (size_t)(2 * m2l_reach(G, band) + 1) * kOpStr) * 4 + (size_t)RT * 8;
     const size_t nT = (size_t)(2 * G - 1) * p * p;
     return ((size_t)RT * (U + 1) + nT + (nT & 1)) * 4 + (size_t)RT * 8 + (size_t)U * 4;
 }
@@ -687,12 +795,14 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
     if (pm.in) {   // (G <= 64)
         kin = rows_mask(pm.in, pm.glo, r0, R, RT);
         kout = rows_mask(pm.out, pm.glo, r0, R, RT);
-        if (kin == 0 || kout == 0) return;   // nothing here is read later
+        if (kout == 0) return;   // nothing here is read later
     }
     float *sIn = sm, *sT = sm + (size_t)RT * UP;
+    const int ob = m2l_reach(G, band), nop = 2 * ob + 1;   // operator blocks of offsets -ob .. ob
+    T += (size_t)(G - 1 - ob) * 64;
     // (both operands are staged with four loads in flight per thread: one at a time, the
     // loads' latencies took longer than the products)
-    const int nT4 = (2 * G - 1) * 16;
+    const int nT4 = nop * 16;
     for (int e0 = threadIdx.x; e0 < nT4; e0 += 4 * 256) {
         float4 t[4];
 #pragma unroll
@@ -710,7 +820,7 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
     }
     // U = 8 G: rows in 16-byte chunks, which never straddle a cell
     const int U4 = U / 4;
-    int64_t *rowbase = reinterpret_cast<int64_t *>(sT + (2 * G - 1) * kOpStr);
+    int64_t *rowbase = reinterpret_cast<int64_t *>(sT + nop * kOpStr);
     if constexpr (MODE != 0) {
         for (int rr = threadIdx.x; rr < RT; rr += 256) {
             const int64_t r = r0 + rr;
@@ -783,9 +893,8 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
         // negligible); entry of term 4 h + q of cell s: base - 80 s + 32 h
         const int s_lo = 2 * vc - band > 0 ? 2 * vc - band : 0;
         const int s_hi = 2 * vc + 1 + band < G - 1 ? 2 * vc + 1 + band : G - 1;
-        const int base = has ? (tv + G - 1) * kOpStr + q * 8 + b : 0;
+        const int base = has ? (tv + ob) * kOpStr + q * 8 + b : 0;
         const float *bcol = sIn + (lane & 15) * UP + q;
-        bool any = !pm.in;
         auto round = [&](const int (&sc)[NC], int cnt) {
             float a[2 * NC];
 #pragma unroll
@@ -809,7 +918,6 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
         };
         if (pm.in) {
             uint64_t m = kin & (~0ull << s_lo) & (~0ull >> (63 - s_hi));
-            any = m != 0;
             while (m) {
                 int sc[NC], cnt = 0;
 #pragma unroll
@@ -828,7 +936,6 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
                 round(sc, s_hi - s0 + 1);
             }
         }
-        if (!any) continue;   // exactly zero, and not read later
 #pragma unroll
         for (int j = 0; j < NR; ++j)
 #pragma unroll
@@ -1047,117 +1154,156 @@ __global__ void __launch_bounds__(64) k_m2l_pass_bf16x3(const float *In, float *
             }
 }
 
-// One block per cell: evaluate the cell's Taylor series at its targets (Horner
-// in x, then y, then z), two targets per thread so that every coefficient read
-// from LDS feeds two multiply-adds.
-// Taylor series of cell (kx, ky, kz) at its points [start, end) (block-wide).
-// TGT: target flags given; SUB: the self term w_j is subtracted (both fixed per
-// launch, so the gathers through the permutation issue without branches)
-template <int P, bool TGT, bool SUB>
-__device__ void l2p_cell_impl(const float4 *ps, const int32_t *perm, const uint8_t *is_target,
-                              const float *w, int Gx, int Gy, double lox, double loy, double loz,
-                              double cell, double inv_sigma, const float *C, float *u_out, int kx,
-                              int ky, int kz, int64_t start, int64_t end) {
-    constexpr int P3 = P * P * P;
-    __shared__ float sC[P3];
-    const int64_t Rx = (int64_t)Gx * P, Ry = (int64_t)Gy * P;
-    for (int e = threadIdx.x; e < P3; e += kBlock) {
-        const int ax = e % P, ay = (e / P) % P, az = e / (P * P);
-        sC[e] = C[(((int64_t)kz * P + az) * Ry + (int64_t)ky * P + ay) * Rx + (int64_t)kx * P + ax];
+// Orders LDS accesses among the lanes of one wavefront (the lanes run in lockstep;
+// this keeps the compiler from moving LDS reads above the wave's writes and waits
+// for them to land).
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The end of the run of keys that share key i's cell, looked for in (i, e].
+__device__ inline int64_t run_end(const uint64_t *keys, int64_t i, int64_t e, int sh) {
+    const uint64_t c = keys[i] >> sh;
+    int64_t lo = i + 1, hi = e;
+    while (lo < hi) {
+        const int64_t mid = lo + ((hi - lo) >> 1);
+        if ((keys[mid] >> sh) == c) lo = mid + 1;
+        else hi = mid;
     }
-    __syncthreads();
-    const double cx = lox + (kx + 0.5) * cell, cy = loy + (ky + 0.5) * cell, cz = loz + (kz + 0.5) * cell;
-    // four points per thread and pass, so that every coefficient read from LDS serves
-    // four Horner chains (with fewer, the LDS reads bound the loop)
-    constexpr int NPT = 4;
-    for (int64_t i0 = start + threadIdx.x; i0 < end; i0 += NPT * kBlock) {
-        float X[NPT], Y[NPT], Z[NPT], ws[NPT];
+    return lo;
+}
+
+// Taylor series of the cells at their points (Horner in x, then y, then z), every
+// point's sum to input order.  A wavefront takes `chunks` runs of 64 NPT consecutive
+// points in key order (the next run's records loaded while one is evaluated), cell by
+// cell (usually one), with the cell's coefficients in LDS; NPT points per lane, so that
+// a coefficient read from LDS serves NPT chains: with four the vector units bound it
+// (2 p^3 flops a point), but few points then make few wavefronts.  One block per cell
+// left the chip to the fullest cells: 262,144 points in 64 blobs (32,768 cells, 2,600
+// with points, up to 5,000 in one) 198 us, 35 us here; 2,097,152 points in 512 cells
+// 86 us, 60 us here; 4,194,304 points in 1,024 cells 87 us, 89 us here.
+template <int P, int NPT>
+__global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n, const float4 *ps,
+                                                const int32_t *perm, const int2 *cells, int level,
+                                                int Gx, int Gy, int Gz, double lox, double loy, double loz,
+                                                double cell, double inv_sigma, const float *C, int chunks,
+                                                float *u_out) {
+    constexpr int P3 = P * P * P, NW = P <= 12 ? kBlock / 64 : 1;   // (LDS of large p: launched with one wave)
+    constexpr int CPL = (P3 + 63) / 64;                             // coefficients per lane
+    __shared__ __align__(16) float coef[NW][P3];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float *sC = coef[wave];
+    const int sh = 3 * (kDepth - level);
+    const int64_t Rx = (int64_t)Gx * P, Ry = (int64_t)Gy * P;
+    int64_t i0 = (blockIdx.x * (int64_t)(blockDim.x >> 6) + wave) * (64 * NPT) * chunks;
+    const int64_t iend = i0 + (int64_t)chunks * (64 * NPT) < n ? i0 + (int64_t)chunks * (64 * NPT) : n;
+    float4 qn[NPT];
+    int32_t jn[NPT];
+    auto fetch = [&](int64_t c0) {
+#pragma unroll
+        for (int u = 0; u < NPT; ++u) {
+            const int64_t i = c0 + lane + 64 * u, ii = i < n ? i : n - 1;
+            qn[u] = ps[ii];
+            jn[u] = perm[ii];
+        }
+    };
+    if (i0 < iend) fetch(i0);
+    uint64_t staged = ~0ull;   // the cell whose coefficients LDS holds
+    for (; i0 < iend; i0 += 64 * NPT) {
+        const int64_t i1 = i0 + 64 * NPT < iend ? i0 + 64 * NPT : iend;
+        float4 q[NPT];
         int32_t jo[NPT];
-        bool has[NPT], tg[NPT];
 #pragma unroll
         for (int u = 0; u < NPT; ++u) {
-            const int64_t i = i0 + (int64_t)u * kBlock;
-            has[u] = i < end;
-            const float4 q = ps[has[u] ? i : i0];
-            X[u] = (q.x - (float)cx) * (float)inv_sigma;
-            Y[u] = (q.y - (float)cy) * (float)inv_sigma;
-            Z[u] = (q.z - (float)cz) * (float)inv_sigma;
-            jo[u] = perm[has[u] ? i : i0];
+            q[u] = qn[u];
+            jo[u] = jn[u];
         }
-        // the scattered reads of the output step are issued before the evaluation
+        if (i1 < iend) fetch(i1);
+        // one point per lane: the lanes' own keys say where each cell ends, and the next
+        // cell's coefficients are loaded while one is evaluated
+        uint64_t mine = 0;
+        float nc[CPL];
+        if constexpr (NPT == 1) mine = keys[i0 + lane < n ? i0 + lane : n - 1] >> sh;
+        auto lane_cell = [&](int64_t i) {
+            const int l = (int)(i - i0);
+            return ((uint64_t)(uint32_t)__shfl((int)(mine >> 32), l, 64) << 32) | (uint32_t)__shfl((int)mine, l, 64);
+        };
+        auto load_cell = [&](uint64_t m) {
+            const int kx = (int)compact3(m >> 2), ky = (int)compact3(m >> 1), kz = (int)compact3(m);
 #pragma unroll
-        for (int u = 0; u < NPT; ++u) {
-            tg[u] = TGT ? is_target[jo[u]] != 0 : true;
-            ws[u] = SUB ? w[jo[u]] : 0.f;
-        }
-        float uz[NPT];
+            for (int r = 0; r < CPL; ++r) {
+                const int k = lane + 64 * r < P3 ? lane + 64 * r : 0;
+                const int ax = k % P, ay = (k / P) % P, az = k / (P * P);
+                nc[r] = C[(((int64_t)kz * P + az) * Ry + (int64_t)ky * P + ay) * Rx + (int64_t)kx * P + ax];
+            }
+        };
+        if (NPT == 1 && lane_cell(i0) != staged) load_cell(lane_cell(i0));
+        for (int64_t s0 = i0; s0 < i1;) {
+            uint64_t m;
+            int64_t e;
+            if constexpr (NPT == 1) {
+                m = lane_cell(s0);
+                e = s0 + __popcll(__ballot(mine == m && i0 + lane >= s0 && i0 + lane < i1));
+            } else {
+                m = keys[s0] >> sh;
+            }
+            const int kx = (int)compact3(m >> 2), ky = (int)compact3(m >> 1), kz = (int)compact3(m);
+            if constexpr (NPT != 1) {
+                e = cells ? (int64_t)cells[((int64_t)kz * Gy + ky) * Gx + kx].y : run_end(keys, s0, i1, sh);
+                e = e < i1 ? e : i1;
+            }
+            if (m != staged) {
+                if constexpr (NPT != 1) load_cell(m);
+                wave_sync();   // the previous cell's coefficients are no longer read
 #pragma unroll
-        for (int u = 0; u < NPT; ++u) uz[u] = 0.f;
-        for (int az = P - 1; az >= 0; --az) {
-            float uy[NPT];
+                for (int r = 0; r < CPL; ++r)
+                    if (lane + 64 * r < P3) sC[lane + 64 * r] = nc[r];
+                wave_sync();
+                staged = m;
+            }
+            if (NPT == 1 && e < i1) load_cell(lane_cell(e));
+            const float cx = (float)(lox + (kx + 0.5) * cell), cy = (float)(loy + (ky + 0.5) * cell),
+                        cz = (float)(loz + (kz + 0.5) * cell);
+            float X[NPT], Y[NPT], Z[NPT], uz[NPT];
 #pragma unroll
-            for (int u = 0; u < NPT; ++u) uy[u] = 0.f;
+            for (int u = 0; u < NPT; ++u) {
+                X[u] = (q[u].x - cx) * (float)inv_sigma;
+                Y[u] = (q[u].y - cy) * (float)inv_sigma;
+                Z[u] = (q[u].z - cz) * (float)inv_sigma;
+                uz[u] = 0.f;
+            }
+            for (int az = P - 1; az >= 0; --az) {
+                float uy[NPT];
 #pragma unroll
-            for (int ay = P - 1; ay >= 0; --ay) {
-                const float *c = sC + (az * P + ay) * P;
-                float ux[NPT];
+                for (int u = 0; u < NPT; ++u) uy[u] = 0.f;
 #pragma unroll
-                for (int u = 0; u < NPT; ++u) ux[u] = c[P - 1];
+                for (int ay = P - 1; ay >= 0; --ay) {
+                    const float *c = sC + (az * P + ay) * P;
+                    float ux[NPT];
 #pragma unroll
-                for (int ax = P - 2; ax >= 0; --ax) {
-                    const float cv = c[ax];
+                    for (int u = 0; u < NPT; ++u) ux[u] = c[P - 1];
 #pragma unroll
-                    for (int u = 0; u < NPT; ++u) ux[u] = fmaf(ux[u], X[u], cv);
+                    for (int ax = P - 2; ax >= 0; --ax) {
+                        const float cv = c[ax];
+#pragma unroll
+                        for (int u = 0; u < NPT; ++u) ux[u] = fmaf(ux[u], X[u], cv);
+                    }
+#pragma unroll
+                    for (int u = 0; u < NPT; ++u) uy[u] = fmaf(uy[u], Y[u], ux[u]);
                 }
 #pragma unroll
-                for (int u = 0; u < NPT; ++u) uy[u] = fmaf(uy[u], Y[u], ux[u]);
+                for (int u = 0; u < NPT; ++u) uz[u] = fmaf(uz[u], Z[u], uy[u]);
             }
 #pragma unroll
-            for (int u = 0; u < NPT; ++u) uz[u] = fmaf(uz[u], Z[u], uy[u]);
+            for (int u = 0; u < NPT; ++u) {
+                const int64_t i = i0 + lane + 64 * u;
+                if (i >= s0 && i < e) u_out[jo[u]] = uz[u];
+            }
+            s0 = e;
         }
-        // back to input order; non-targets get 0
-#pragma unroll
-        for (int u = 0; u < NPT; ++u)
-            if (has[u]) u_out[jo[u]] = tg[u] ? uz[u] - ws[u] : 0.f;
     }
-}
-
-template <int P>
-__device__ void l2p_cell(const float4 *ps, const int32_t *perm, const uint8_t *is_target, const float *w,
-                         int subtract_self, int Gx, int Gy, double lox, double loy, double loz,
-                         double cell, double inv_sigma, const float *C, float *u_out, int kx, int ky,
-                         int kz, int64_t start, int64_t end) {
-    if (is_target) {
-        if (subtract_self)
-            l2p_cell_impl<P, true, true>(ps, perm, is_target, w, Gx, Gy, lox, loy, loz, cell, inv_sigma, C,
-                                         u_out, kx, ky, kz, start, end);
-        else
-            l2p_cell_impl<P, true, false>(ps, perm, is_target, w, Gx, Gy, lox, loy, loz, cell, inv_sigma, C,
-                                          u_out, kx, ky, kz, start, end);
-    } else {
-        if (subtract_self)
-            l2p_cell_impl<P, false, true>(ps, perm, is_target, w, Gx, Gy, lox, loy, loz, cell, inv_sigma, C,
-                                          u_out, kx, ky, kz, start, end);
-        else
-            l2p_cell_impl<P, false, false>(ps, perm, is_target, w, Gx, Gy, lox, loy, loz, cell, inv_sigma,
-                                           C, u_out, kx, ky, kz, start, end);
-    }
-}
-
-template <int P>
-__global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                const int32_t *perm, const uint8_t *is_target,
-                                                const float *w, int subtract_self, int level, int Gx,
-                                                int Gy, int Gz, double lox, double loy, double loz,
-                                                double cell, double inv_sigma, const float *C,
-                                                float *u_out) {
-    const int64_t g = blockIdx.x;
-    const int kx = (int)(g % Gx), ky = (int)((g / Gx) % Gy), kz = (int)(g / ((int64_t)Gx * Gy));
-    int64_t start, end;
-    cell_range(keys, n, level, kx, ky, kz, start, end);
-    if (start == end) return;
-    l2p_cell<P>(ps, perm, is_target, w, subtract_self, Gx, Gy, lox, loy, loz, cell, inv_sigma, C, u_out,
-                kx, ky, kz, start, end);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1171,15 +1317,6 @@ __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n,
 //   M2M  A[a] = sum_s sum_{g<=a, g<pf} a_s[g] prod_k d_k^(a_k-g_k)/(a_k-g_k)!
 //   L2L  c_s[b] = sum_{g>=b} C[g] prod_k binom(g_k, b_k) d_k^(g_k-b_k),  b < pf
 // ---------------------------------------------------------------------------------
-
-// Orders LDS accesses among the lanes of one wavefront (the lanes run in lockstep;
-// this keeps the compiler from moving LDS reads above the wave's writes and waits
-// for them to land).
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __device__ inline int sub_coord(int s, int axis) {
     const int d1 = s >> 3, d2 = s & 7, sh = 2 - axis;
@@ -1496,7 +1633,7 @@ __device__ inline void l2p_grad_point(const float *sC, float X, float Y, float Z
 // L2P with derivatives at every point of each cell (in key order), one block per cell.
 template <int P>
 __global__ void __launch_bounds__(kBlock) k_l2p_grad(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                     int level, int Gx, int Gy, int Gz, double lox,
+                                                     const int2 *cells, int level, int Gx, int Gy, int Gz, double lox,
                                                      double loy, double loz, double cell,
                                                      double inv_sigma, const float *C, float *out,
                                                      int stride, int want_lap) {
@@ -1505,7 +1642,7 @@ __global__ void __launch_bounds__(kBlock) k_l2p_grad(const uint64_t *keys, int64
     const int64_t g = blockIdx.x;
     const int kx = (int)(g % Gx), ky = (int)((g / Gx) % Gy), kz = (int)(g / ((int64_t)Gx * Gy));
     int64_t start, end;
-    cell_range(keys, n, level, kx, ky, kz, start, end);
+    cell_points(cells, g, keys, n, level, kx, ky, kz, start, end);
     if (start == end) return;
     const int64_t Rx = (int64_t)Gx * P, Ry = (int64_t)Gy * P;
     for (int e = threadIdx.x; e < P3; e += kBlock) {
@@ -1550,6 +1687,8 @@ struct GridArgs {
     int subtract_self;
     float *u_out;
     bool stage;   // P2M writes the gathered weights into the sorted records (MSP_STAGE_WEIGHTS)
+    const int2 *cells = nullptr;   // point range of every cell (NULL: searched for)
+    bool sparse = false;           // many cells may be empty
 };
 
 // Target flags and the self term applied in input order after an L2P that wrote
@@ -1626,21 +1765,31 @@ int launch_p2m_l2p(msp_tree *t, const FgtPlan &pl, double inv_sigma, bool l2p, c
         }
     }
     if (!l2p && P == 8) {
-        hipLaunchKernelGGL(k_p2m_mfma8, dim3((unsigned)ncell), dim3(kBlock), 0, s, t->keys.as<uint64_t>(), t->n,
-                           t->ps.as<float4>(), t->perm.as<int32_t>(), ga.w_gather, pl.level, pl.G[0], pl.G[1], pl.G[2],
+        hipLaunchKernelGGL(k_p2m_mfma8, dim3((unsigned)(ga.sparse && ncell > 8192 ? 8192 : ncell)), dim3(kBlock), 0, s,
+                           t->keys.as<uint64_t>(), t->n,
+                           t->ps.as<float4>(), t->perm.as<int32_t>(), ga.w_gather, ga.cells, pl.level, pl.G[0], pl.G[1], pl.G[2],
                            t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell, inv_sigma, A,
                            ga.stage ? t->ps.as<float4>() : nullptr);
     } else if (!l2p) {
         hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2m<P>), dim3((unsigned)ncell), dim3(kBlock), 0, s,
                            t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), t->perm.as<int32_t>(),
-                           ga.w_gather, pl.level, pl.G[0], pl.G[1], pl.G[2], t->geo.lo[0], t->geo.lo[1],
+                           ga.w_gather, ga.cells, pl.level, pl.G[0], pl.G[1], pl.G[2], t->geo.lo[0], t->geo.lo[1],
                            t->geo.lo[2], pl.cell, inv_sigma, A, ga.stage ? t->ps.as<float4>() : nullptr);
     } else {
-        // every point's sum straight to input order, flags and self term afterwards
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2p<P>), dim3((unsigned)ncell), dim3(kBlock), 0, s,
-                           t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), t->perm.as<int32_t>(),
-                           (const uint8_t *)nullptr, ga.w, 0, pl.level, pl.G[0], pl.G[1], pl.G[2],
-                           t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell, inv_sigma, C, ga.u_out);
+        // every point's sum straight to input order, flags and self term afterwards; four
+        // points per lane once that still makes sixteen wavefronts per compute unit, then
+        // more runs per wavefront while it does
+        const int bw = P <= 12 ? kBlock / 64 : 1;
+        auto launch = [&](auto kern, int npt) {
+            const int64_t most = t->n / (64 * npt * 4096);
+            const int chunks = most < 1 ? 1 : most > 4 ? 4 : (int)most;
+            hipLaunchKernelGGL(kern, dim3(grid_for(t->n, 64 * npt * bw * chunks)), dim3(64 * bw), 0, s,
+                               t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), t->perm.as<int32_t>(), ga.cells,
+                               pl.level, pl.G[0], pl.G[1], pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell,
+                               inv_sigma, C, chunks, ga.u_out);
+        };
+        if (t->n >= 4 * 64 * 4096) launch(k_l2p<P, 4>, 4);
+        else launch(k_l2p<P, 1>, 1);
         // (the target flags and the self term follow in fgt_forward_grid)
     }
     MSP_CHECK_LAUNCH();
@@ -1665,8 +1814,9 @@ template <int P>
 int launch_l2p_grad(msp_tree *t, const FgtPlan &pl, double inv_sigma, const float *C, float *out,
                     int stride, int want_lap, hipStream_t s) {
     const int64_t ncell = (int64_t)pl.G[0] * pl.G[1] * pl.G[2];
+    const int2 *cells = t->cell_level == pl.level ? t->cell_pts.as<int2>() : nullptr;
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2p_grad<P>), dim3((unsigned)ncell), dim3(kBlock), 0, s,
-                       t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), pl.level, pl.G[0], pl.G[1],
+                       t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), cells, pl.level, pl.G[0], pl.G[1],
                        pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell, inv_sigma, C, out,
                        stride, want_lap);
     MSP_CHECK_LAUNCH();
@@ -2571,7 +2721,7 @@ int64_t fgt_pop_tiles(const FgtPop &f, int p, int pass, bool gemm) {
 size_t fgt_pop_gemm_lds(const FgtPop &f, int p, bool split) {
     size_t m = 0;
     for (int k = 0; k < 3; ++k) {
-        const size_t l = split ? m2l_gemm_lds_split(f.G[k] * p, f.G[k], 32) : m2l_gemm_lds(f.G[k] * p, f.G[k], p, 32);
+        const size_t l = split ? m2l_gemm_lds_split(f.G[k] * p, f.G[k], 32) : m2l_gemm_lds(f.G[k] * p, f.G[k], p, 32, f.band[k]);
         m = l > m ? l : m;
     }
     return m;
@@ -2646,10 +2796,56 @@ int stage_inputs(msp_tree *t, const float *w, const uint8_t *is_target, hipStrea
     return MSP_OK;
 }
 
+// The table of the cells' point ranges at pl.level and, with band, the masks of the
+// three translation passes; kept until the next build.
+static int cell_tables(msp_tree *t, const FgtPlan &pl, const int *band, PassMask (&masks)[3], hipStream_t s) {
+    const int Gx = pl.G[0], Gy = pl.G[1], Gz = pl.G[2];
+    const int64_t ncell = (int64_t)Gx * Gy * Gz, nxy = (int64_t)Gx * Gy, nxz = (int64_t)Gx * Gz, nyz = (int64_t)Gy * Gz;
+    const int64_t nmask = 2 * (nxy + nxz + nyz);
+    if (t->cell_level != pl.level) t->cell_band[0] = -1;
+    const bool fresh = t->cell_level != pl.level || (band && t->cell_band[0] < 0);
+    if (fresh) {
+        t->cell_level = -1;
+        MSP_TRY(t->cell_pts.ensure((size_t)(ncell + (ncell & 1)) * 8));
+        if (band) MSP_TRY(t->cell_mask.ensure((size_t)nmask * 8));
+    }
+    uint64_t *inx = t->cell_mask.as<uint64_t>(), *iny = inx + nyz, *inz = iny + nxz, *outx = inz + nxy,
+             *outy = outx + nyz, *outz = outy + nxz;
+    if (fresh) {
+        PhaseScope ps(&t->timing, PH_OPS, s);
+        const int64_t c16 = (ncell + 1) / 2;
+        hipLaunchKernelGGL(k_cell_clear, dim3(grid_for(c16, kBlock)), dim3(kBlock), 0, s, c16, t->cell_pts.as<uint4>());
+        MSP_CHECK_LAUNCH();
+        if (band) {
+            hipLaunchKernelGGL(k_cell_clear, dim3(grid_for(nmask / 2, kBlock)), dim3(kBlock), 0, s, nmask / 2,
+                               t->cell_mask.as<uint4>());
+            MSP_CHECK_LAUNCH();
+        }
+        hipLaunchKernelGGL(k_cell_points, dim3(grid_for(t->n, kBlock)), dim3(kBlock), 0, s, t->keys.as<uint64_t>(),
+                           t->n, pl.level, Gx, Gy, Gz, t->cell_pts.as<int2>(),
+                           reinterpret_cast<unsigned long long *>(band ? inx : nullptr),
+                           reinterpret_cast<unsigned long long *>(outz));
+        MSP_CHECK_LAUNCH();
+        t->cell_level = pl.level;
+    }
+    if (band && !std::equal(band, band + 3, t->cell_band)) {
+        hipLaunchKernelGGL(k_cell_masks, dim3(1), dim3(1024), 0, s, Gx, Gy, Gz, band[0], band[1], band[2], inx, iny,
+                           inz, outx, outy, outz);
+        MSP_CHECK_LAUNCH();
+        std::copy(band, band + 3, t->cell_band);
+    }
+    if (band) {
+        masks[0] = PassMask{inx, outx, Gy};   // rows (z', y')
+        masks[1] = PassMask{iny, outy, Gz};   // rows (x', z')
+        masks[2] = PassMask{inz, outz, Gx};   // rows (y', x')
+    }
+    return MSP_OK;
+}
+
 int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, const float *w,
                      const uint8_t *is_target, float *u_out, hipStream_t s) {
     const bool staged = (prm->flags & MSP_WEIGHTS_STAGED) != 0;
-    const GridArgs ga{w, staged ? nullptr : w, is_target, (prm->flags & MSP_EXCLUDE_SELF) ? 1 : 0, u_out,
+    GridArgs ga{w, staged ? nullptr : w, is_target, (prm->flags & MSP_EXCLUDE_SELF) ? 1 : 0, u_out,
                       !staged && (prm->flags & MSP_STAGE_WEIGHTS) != 0};
     if (ga.stage) ++t->ps_gen;   // its P2M rewrites the weights of the records
     const int p = pl.p;
@@ -2684,6 +2880,21 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
         t->ops_valid = true;
     }
     const double inv_sigma = 1.0 / prm->sigma;
+    const bool valu = (prm->flags & MSP_M2L_VALU) != 0;
+    const bool bf16x3 = (prm->flags & MSP_M2L_BF16X3) != 0;
+    PassMask masks[3];
+    // (the calls that run in a caller's workspace search for the cells: their memory was
+    // counted without the table)
+    if (!t->gridA.fixed) {
+        int band[3];
+        for (int k = 0; k < 3; ++k) band[k] = m2l_band(p, step, pl.G[k]);
+        // cells of few points on average: many may be empty
+        const bool sparse = p == 8 && !valu && !bf16x3 && ncell >= 4096 && t->n < 64 * ncell &&
+                            pl.G[0] <= 64 && pl.G[1] <= 64 && pl.G[2] <= 64;
+        MSP_TRY(cell_tables(t, pl, sparse ? band : nullptr, masks, s));
+        ga.cells = t->cell_pts.as<int2>();
+        ga.sparse = sparse;
+    }
     {
         PhaseScope ps(&t->timing, PH_P2M, s);
         MSP_TRY(dispatch_p2m_l2p(t, pl, inv_sigma, false, nullptr, A, ga, s));
@@ -2694,11 +2905,9 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
     const Pass passes[3] = {{A, B, Uz * Uy, pl.G[0], opsx, Ux},
                             {B, Tmp, Ux * Uz, pl.G[1], opsy, Uy},
                             {Tmp, B, Uy * Ux, pl.G[2], opsz, Uz}};
-    const bool valu = (prm->flags & MSP_M2L_VALU) != 0;
-    const bool bf16x3 = (prm->flags & MSP_M2L_BF16X3) != 0;
     for (int k = 0; k < 3; ++k) {
         const Pass &ps = passes[k];
-        const PassMask pm{};
+        const PassMask &pm = masks[k];
         PhaseScope sc(&t->timing, PH_M2L_X + k, s);
         if (valu) {
             dim3 grid((unsigned)((ps.R + TR - 1) / TR), (unsigned)((ps.U + TV - 1) / TV));
@@ -2726,10 +2935,11 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
         } else {
             // rows per block: enough blocks to fill the chip, at most 64, and fewer
             // when the tile would not fit in LDS
+            const int band = m2l_band(p, step, ps.G);
             int RT = 64;
-            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds((int)ps.U, ps.G, p, RT) > 64 * 1024))
+            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds((int)ps.U, ps.G, p, RT, band) > 64 * 1024))
                 RT >>= 1;
-            const size_t lds = m2l_gemm_lds((int)ps.U, ps.G, p, RT);
+            const size_t lds = m2l_gemm_lds((int)ps.U, ps.G, p, RT, band);
             if (lds <= 64 * 1024) {
                 // column groups of four 16-wide blocks, one per wavefront, as the grid's y,
                 // only while the row tiles alone make fewer than 1024 blocks (every group
@@ -2739,7 +2949,6 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
                 const int64_t want = (1024 + rows - 1) / rows;
                 const int cg = want < ngroup ? (int)want : ngroup;
                 const dim3 grid((unsigned)rows, (unsigned)cg);
-                const int band = m2l_band(p, step, ps.G);
                 if (RT == 64)
                     hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm);
                 else if (RT == 32)

@@ -234,6 +234,11 @@ struct msp_tree {
     bool ops_valid = false;     // M2L operator tables in ops match ops_sig (p, grid, cell / sigma)
     uint64_t ops_sig[5] = {};
     int64_t grid_bytes_valid = 0;
+    // point range of every cell of the expansion level, and which rows of cells the
+    // translation passes need (kept until the next build)
+    msp::DevBuf cell_pts, cell_mask;
+    int cell_level = -1;                         // level of cell_pts (-1: none)
+    int cell_band[3] = {-1, -1, -1};             // bands cell_mask was made for (-1: none)
     // direct-route interaction lists (cached per sigma/cutoff)
     msp::DevBuf list_off, list_idx, list_cnt;
     int64_t list_total = 0;

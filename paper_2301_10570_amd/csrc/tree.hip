@@ -876,6 +876,7 @@ int build_tree(msp_tree *t, const float *x, const float *y, const float *z, int6
     t->iperm_valid = false;
     t->lists_valid = false;
     t->counts_valid = false;
+    t->cell_level = -1;
     t->w_staged = false;
     ++t->ps_gen;   // the records are rewritten
     t->node_moments_level = -1;

@@ -1,0 +1,65 @@
+"""The expansion route with its table of cells, the passes that skip empty cells and the
+point runs of the L2P: the bits of the same call in a caller's workspace, which searches
+for the cells and computes every one of them, and the accuracy bar."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests.helpers import rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _make(kind, n):
+    if kind == "blobs":        # a few per cent of the cells hold points
+        return synth.blobs(n // 512, 512, extent=3000.0, std=30.0, sigma=120.0, seed=900 + n)
+    if kind == "line":         # one row of cells along x, most of the grid empty in y and z
+        return synth.uniform_box(n, extent=(4000.0, 30.0, 20.0), sigma=100.0, seed=901)
+    if kind == "corners":      # two far corners of the cube
+        wl = synth.uniform_box(n, extent=(200.0, 200.0, 200.0), sigma=110.0, seed=902)
+        for v in (wl.x, wl.y, wl.z):
+            v[n // 2:] += np.float32(3800.0)
+        return wl
+    return synth.uniform_box(n, extent=(1500.0, 900.0, 400.0), sigma=150.0, seed=903)
+
+
+@pytest.mark.parametrize("kind,n,p", [("blobs", 16384, 8), ("blobs", 512, 8), ("line", 3001, 8), ("corners", 5000, 8),
+                                      ("box", 63, 8), ("box", 65, 6), ("box", 257, 10), ("box", 30011, 13),
+                                      ("box", 1048576 + 77, 8), ("blobs", 16384, 5)])
+def test_same_bits_as_without_the_table(kind, n, p):
+    import torch
+    import paper_2301_10570_amd as msp
+    wl = _make(kind, n)
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    plan = tree.plan(wl.sigma, p=p, route="fgt")
+    print(f"{kind} n={wl.n} p={p} level {plan['level']} grid {plan['grid']}", flush=True)
+    ws = torch.empty(tree.forward_query(wl.sigma, p=p, route="fgt"), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xff)             # what is not written must not be read: NaN everywhere
+    ref = tree.forward_ws(d["w"], ws, d["tgt"], sigma=wl.sigma, p=p, route="fgt").cpu().numpy()
+    for rep in range(2):       # the table made, then kept
+        u = tree.forward(d["w"], d["tgt"], sigma=wl.sigma, p=p, route="fgt").cpu().numpy()
+        np.testing.assert_array_equal(u, ref)
+    # another sigma at the same level (other bands), then the first again
+    s2 = wl.sigma * 0.97
+    if tree.plan(s2, p=p, route="fgt")["level"] == plan["level"]:
+        u2 = tree.forward(d["w"], d["tgt"], sigma=s2, p=p, route="fgt").cpu().numpy()
+        r2 = tree.forward_ws(d["w"], ws, d["tgt"], sigma=s2, p=p, route="fgt").cpu().numpy()
+        np.testing.assert_array_equal(u2, r2)
+    u = tree.forward(d["w"], d["tgt"], sigma=wl.sigma, p=p, route="fgt").cpu().numpy()
+    np.testing.assert_array_equal(u, ref)
+    # NaN weights leave NaN in every grid entry that is written: none of it is read again
+    tree.forward(torch.full_like(d["w"], float("nan")), d["tgt"], sigma=wl.sigma, p=p, route="fgt")
+    u = tree.forward(d["w"], d["tgt"], sigma=wl.sigma, p=p, route="fgt").cpu().numpy()
+    np.testing.assert_array_equal(u, ref)
+    tgt = np.nonzero(wl.a > 0)[0]
+    sel = tgt[synth.sample_indices(tgt.size, 64, seed=904)]
+    r = oracle.attraction(wl, sel)
+    some = r > 1e-2 * r.max()
+    assert rel_err(u[sel][some], r[some]).max() <= 1e-4
+    # other points in the same handle: the table is made again
+    tree.build(d["y"], d["x"], d["z"])
+    u3 = tree.forward(d["w"], d["tgt"], sigma=wl.sigma, p=p, route="fgt").cpu().numpy()
+    assert rel_err(u3[sel][some], r[some]).max() <= 1e-4
+    tree.close()
