@@ -134,13 +134,21 @@ __device__ inline void cell_range(const uint64_t *keys, int64_t n, int level, in
     end = lower_bound_u64(keys, start, n, (prefix + 1ull) << sh);
 }
 
-// Point range of cell g = (kz Gy + ky) Gx + kx from the table, or by search without one.
-__device__ inline void cell_points(const int2 *cells, int64_t g, const uint64_t *keys, int64_t n, int level, int kx,
-                                   int ky, int kz, int64_t &start, int64_t &end) {
-    if (cells) {
-        const int2 r = cells[g];
-        start = r.x;
-        end = r.y;
+// The table of the cells' point ranges: (start, gen, end, gen) of cell (kz Gy + ky) Gx +
+// kx.  An entry of another generation is an empty cell, so the table is never cleared
+// between trees (a launch of its own).  at == NULL: no table.
+struct CellTable {
+    const int4 *at = nullptr;
+    int gen = 0;
+};
+
+// Point range of cell g from the table, or by search without one.
+__device__ inline void cell_points(const CellTable &cells, int64_t g, const uint64_t *keys, int64_t n, int level,
+                                   int kx, int ky, int kz, int64_t &start, int64_t &end) {
+    if (cells.at) {
+        const int4 r = cells.at[g];
+        start = r.y == cells.gen ? r.x : 0;
+        end = r.y == cells.gen ? r.z : 0;
     } else {
         cell_range(keys, n, level, kx, ky, kz, start, end);
     }
@@ -151,14 +159,15 @@ __global__ void __launch_bounds__(kBlock) k_cell_clear(int64_t n16, uint4 *p) {
     if (i < n16) p[i] = make_uint4(0, 0, 0, 0);
 }
 
-// The table of the cells' point ranges (cleared before): the first point of a cell
-// writes its start and the previous cell's end.  One pass over the keys, once per tree
+// The table of the cells' point ranges: the first point of a cell writes its start and
+// the previous cell's end.  One pass over the keys, once per tree
 // and level, in place of two searches over all of them (a chain of some twenty loads)
 // in every block of every pass.  With masks: the cell's bit in its x row (inx) and its
 // z column (outz).
 __global__ void __launch_bounds__(kBlock) k_cell_points(const uint64_t *keys, int64_t n, int level, int Gx, int Gy,
-                                                        int Gz, int2 *cells, unsigned long long *inx,
+                                                        int Gz, int4 *table, int gen, unsigned long long *inx,
                                                         unsigned long long *outz) {
+    int2 *cells = reinterpret_cast<int2 *>(table);   // (start, gen) and (end, gen) of a cell
     const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
     if (i >= n) return;
     const int sh = 3 * (kDepth - level);
@@ -170,10 +179,10 @@ __global__ void __launch_bounds__(kBlock) k_cell_points(const uint64_t *keys, in
         return ((int64_t)kz * Gy + ky) * Gx + kx;
     };
     int kx, ky, kz;
-    if (i == n - 1) cells[at(c, kx, ky, kz)].y = (int)n;
+    if (i == n - 1) cells[2 * at(c, kx, ky, kz) + 1] = make_int2((int)n, gen);
     if (c == b) return;
-    if (i > 0) cells[at(b, kx, ky, kz)].y = (int)i;
-    cells[at(c, kx, ky, kz)].x = (int)i;
+    if (i > 0) cells[2 * at(b, kx, ky, kz) + 1] = make_int2((int)i, gen);
+    cells[2 * at(c, kx, ky, kz)] = make_int2((int)i, gen);
     if (inx) {
         atomicOr(&inx[(int64_t)kz * Gy + ky], 1ull << kx);
         atomicOr(&outz[(int64_t)ky * Gx + kx], 1ull << kz);
@@ -329,7 +338,7 @@ __device__ void p2m_cell(const float4 *ps, const int32_t *perm, const float *w, 
 // [kz][az][ky][ay][kx][ax] (empty cells get zeros).
 template <int P>
 __global__ void __launch_bounds__(kBlock) k_p2m(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                const int32_t *perm, const float *w, const int2 *cells,
+                                                const int32_t *perm, const float *w, const CellTable cells,
                                                 int level, int Gx, int Gy, int Gz, double lox,
                                                 double loy, double loz, double cell,
                                                 double inv_sigma, float *A, float4 *stage) {
@@ -351,7 +360,7 @@ __global__ void __launch_bounds__(kBlock) k_p2m(const uint64_t *keys, int64_t n,
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPowStr = 25;   // floats per staged point (24 powers, padded)
 __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                      const int32_t *perm, const float *w, const int2 *cells,
+                                                      const int32_t *perm, const float *w, const CellTable cells,
                                                       int level, int Gx, int Gy, int Gz, double lox, double loy, double loz,
                                                       double cell, double inv_sigma, float *A, float4 *stage) {
     __shared__ float pw[kBlock * kPowStr];
@@ -1186,7 +1195,7 @@ __device__ inline int64_t run_end(const uint64_t *keys, int64_t i, int64_t e, in
 // 86 us, 60 us here; 4,194,304 points in 1,024 cells 87 us, 89 us here.
 template <int P, int NPT>
 __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                const int32_t *perm, const int2 *cells, int level,
+                                                const int32_t *perm, const CellTable cells, int level,
                                                 int Gx, int Gy, int Gz, double lox, double loy, double loz,
                                                 double cell, double inv_sigma, const float *C, int chunks,
                                                 float *u_out) {
@@ -1251,7 +1260,7 @@ __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n,
             }
             const int kx = (int)compact3(m >> 2), ky = (int)compact3(m >> 1), kz = (int)compact3(m);
             if constexpr (NPT != 1) {
-                e = cells ? (int64_t)cells[((int64_t)kz * Gy + ky) * Gx + kx].y : run_end(keys, s0, i1, sh);
+                e = cells.at ? (int64_t)cells.at[((int64_t)kz * Gy + ky) * Gx + kx].z : run_end(keys, s0, i1, sh);
                 e = e < i1 ? e : i1;
             }
             if (m != staged) {
@@ -1633,7 +1642,7 @@ __device__ inline void l2p_grad_point(const float *sC, float X, float Y, float Z
 // L2P with derivatives at every point of each cell (in key order), one block per cell.
 template <int P>
 __global__ void __launch_bounds__(kBlock) k_l2p_grad(const uint64_t *keys, int64_t n, const float4 *ps,
-                                                     const int2 *cells, int level, int Gx, int Gy, int Gz, double lox,
+                                                     const CellTable cells, int level, int Gx, int Gy, int Gz, double lox,
                                                      double loy, double loz, double cell,
                                                      double inv_sigma, const float *C, float *out,
                                                      int stride, int want_lap) {
@@ -1687,7 +1696,7 @@ struct GridArgs {
     int subtract_self;
     float *u_out;
     bool stage;   // P2M writes the gathered weights into the sorted records (MSP_STAGE_WEIGHTS)
-    const int2 *cells = nullptr;   // point range of every cell (NULL: searched for)
+    CellTable cells;               // point range of every cell
     bool sparse = false;           // many cells may be empty
 };
 
@@ -1814,7 +1823,7 @@ template <int P>
 int launch_l2p_grad(msp_tree *t, const FgtPlan &pl, double inv_sigma, const float *C, float *out,
                     int stride, int want_lap, hipStream_t s) {
     const int64_t ncell = (int64_t)pl.G[0] * pl.G[1] * pl.G[2];
-    const int2 *cells = t->cell_level == pl.level ? t->cell_pts.as<int2>() : nullptr;
+    const CellTable cells{t->cell_level == pl.level ? t->cell_pts.as<int4>() : nullptr, t->cell_gen};
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2p_grad<P>), dim3((unsigned)ncell), dim3(kBlock), 0, s,
                        t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), cells, pl.level, pl.G[0], pl.G[1],
                        pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell, inv_sigma, C, out,
@@ -2804,25 +2813,33 @@ static int cell_tables(msp_tree *t, const FgtPlan &pl, const int *band, PassMask
     const int64_t nmask = 2 * (nxy + nxz + nyz);
     if (t->cell_level != pl.level) t->cell_band[0] = -1;
     const bool fresh = t->cell_level != pl.level || (band && t->cell_band[0] < 0);
+    bool grown = false;
     if (fresh) {
         t->cell_level = -1;
-        MSP_TRY(t->cell_pts.ensure((size_t)(ncell + (ncell & 1)) * 8));
+        const size_t had = t->cell_pts.bytes;
+        MSP_TRY(t->cell_pts.ensure((size_t)ncell * sizeof(int4)));
+        grown = t->cell_pts.bytes != had;   // new memory: no generation can be told from its contents
         if (band) MSP_TRY(t->cell_mask.ensure((size_t)nmask * 8));
     }
     uint64_t *inx = t->cell_mask.as<uint64_t>(), *iny = inx + nyz, *inz = iny + nxz, *outx = inz + nxy,
              *outy = outx + nyz, *outz = outy + nxz;
     if (fresh) {
         PhaseScope ps(&t->timing, PH_OPS, s);
-        const int64_t c16 = (ncell + 1) / 2;
-        hipLaunchKernelGGL(k_cell_clear, dim3(grid_for(c16, kBlock)), dim3(kBlock), 0, s, c16, t->cell_pts.as<uint4>());
-        MSP_CHECK_LAUNCH();
+        if (grown || t->cell_gen == 0x7fffffff) {
+            const int64_t c16 = (int64_t)(t->cell_pts.bytes / 16);
+            hipLaunchKernelGGL(k_cell_clear, dim3(grid_for(c16, kBlock)), dim3(kBlock), 0, s, c16,
+                               t->cell_pts.as<uint4>());
+            MSP_CHECK_LAUNCH();
+            t->cell_gen = 0;
+        }
+        ++t->cell_gen;
         if (band) {
             hipLaunchKernelGGL(k_cell_clear, dim3(grid_for(nmask / 2, kBlock)), dim3(kBlock), 0, s, nmask / 2,
                                t->cell_mask.as<uint4>());
             MSP_CHECK_LAUNCH();
         }
         hipLaunchKernelGGL(k_cell_points, dim3(grid_for(t->n, kBlock)), dim3(kBlock), 0, s, t->keys.as<uint64_t>(),
-                           t->n, pl.level, Gx, Gy, Gz, t->cell_pts.as<int2>(),
+                           t->n, pl.level, Gx, Gy, Gz, t->cell_pts.as<int4>(), t->cell_gen,
                            reinterpret_cast<unsigned long long *>(band ? inx : nullptr),
                            reinterpret_cast<unsigned long long *>(outz));
         MSP_CHECK_LAUNCH();
@@ -2892,7 +2909,7 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
         const bool sparse = p == 8 && !valu && !bf16x3 && ncell >= 4096 && t->n < 64 * ncell &&
                             pl.G[0] <= 64 && pl.G[1] <= 64 && pl.G[2] <= 64;
         MSP_TRY(cell_tables(t, pl, sparse ? band : nullptr, masks, s));
-        ga.cells = t->cell_pts.as<int2>();
+        ga.cells = CellTable{t->cell_pts.as<int4>(), t->cell_gen};
         ga.sparse = sparse;
     }
     {

@@ -238,6 +238,7 @@ struct msp_tree {
     // translation passes need (kept until the next build)
     msp::DevBuf cell_pts, cell_mask;
     int cell_level = -1;                         // level of cell_pts (-1: none)
+    int cell_gen = 0;                            // its generation (entries of others are empty cells)
     int cell_band[3] = {-1, -1, -1};             // bands cell_mask was made for (-1: none)
     // direct-route interaction lists (cached per sigma/cutoff)
     msp::DevBuf list_off, list_idx, list_cnt;
