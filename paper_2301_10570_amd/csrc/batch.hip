@@ -327,7 +327,9 @@ int prepare_fgt(msp_batch *b, const std::vector<PopPlan> &plans, const float *w,
         gemm_lds = l > gemm_lds ? l : gemm_lds;
     }
     const bool gemm = gemm_lds <= 64 * 1024;
-    if (split && !fp.empty() && (p != 8 || !gemm))
+    bool whole = true;   // every operator table would fit as a whole: the documented limit
+    for (const FgtPop &f : fp) whole = whole && fgt_pop_split_whole(f) <= 64 * 1024;
+    if (split && !fp.empty() && (p != 8 || !gemm || !whole))
         return fail(MSP_ENOTSUP, "split-bfloat16 translation in a batch needs p = 8 and tiles that fit in LDS");
     for (const FgtPop &f : fp)
         for (int pass = 0; pass < 3; ++pass)

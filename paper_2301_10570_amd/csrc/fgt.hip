@@ -623,19 +623,23 @@ constexpr int kOpStr = 80;   // floats of an 8 x 8 operator block in LDS (p = 8)
 // The largest cell offset that a tile of two-cell column blocks meets (p = 8).
 __host__ __device__ inline int m2l_reach(int G, int band) { return band < G - 2 ? band + 1 : G - 1; }
 __host__ __device__ inline size_t m2l_gemm_lds(int U, int G, int p, int RT, int band) {
-    // input rows, operator table, and (cell-major modes) row bases and column offsets
-    if (p == 8)
+    // input rows, operator table, and (cell-major modes) row bases and column offsets;
+    // p = 8, or p < 8 with eight terms per cell (U = 8 G)
+    if (U == 8 * G)
         return ((size_t)RT * (U + 2) + (size_t)(2 * m2l_reach(G, band) + 1) * kOpStr) * 4 + (size_t)RT * 8;
     const size_t nT = (size_t)(2 * G - 1) * p * p;
     return ((size_t)RT * (U + 1) + nT + (nT & 1)) * 4 + (size_t)RT * 8 + (size_t)U * 4;
 }
 
-// The split bfloat16 form of the tile (p = 8): the RT input rows and the operator
-// table as hi and lo bfloat16 planes, rows padded to whole 32-term K steps plus 8.
-__host__ __device__ inline int m2l_split_row(int U) { return ((U + 31) / 32) * 32 + 8; }
-__host__ __device__ inline size_t m2l_gemm_lds_split(int U, int G, int RT) {
-    const size_t nT = (size_t)(2 * G - 1) * 64;
-    size_t b = (size_t)RT * m2l_split_row(U) * 4 + nT * 4;   // two 2-byte planes each
+// The split bfloat16 form of the tile (p <= 8): the RT input rows and the operator
+// blocks as hi and lo bfloat16 planes, eight terms per cell (zeros past p), rows padded
+// to whole 32-term K steps plus 8.  G8: 8 G.
+__host__ __device__ inline int m2l_split_row(int G8) { return ((G8 + 31) / 32) * 32 + 8; }
+// The largest cell offset that column blocks of two cells meet in K steps of four cells.
+__host__ __device__ inline int m2l_split_reach(int G, int band) { return band < G - 5 ? band + 4 : G - 1; }
+__host__ __device__ inline size_t m2l_gemm_lds_split(int G, int RT, int band) {
+    const size_t nT = (size_t)(2 * m2l_split_reach(G, band) + 1) * 64;
+    size_t b = (size_t)RT * m2l_split_row(8 * G) * 4 + nT * 4;   // two 2-byte planes each
     b = (b + 15) & ~(size_t)15;
     return b + (size_t)RT * 8;
 }
@@ -647,33 +651,63 @@ __host__ __device__ inline size_t m2l_gemm_lds_split(int U, int G, int RT) {
 // cell-major moments, and its z pass (MODE 2) takes its rows in cell-column order
 // (ky, kx, ay, ax) and writes the cell-major Taylor grid.  Ga: the grid's cells along
 // y (MODE 1) or x (MODE 2).
-// m2l_gemm_tile with split bfloat16 products (p = 8): every staged input and
+// m2l_gemm_tile with split bfloat16 products (p <= 8): every staged input and
 // operator entry x is split once into hi = bf16(x) and lo = bf16(x - hi), and each
 // 16 x 16 output tile accumulates hi*hi + hi*lo + lo*hi over 32-term K steps with
-// v_mfma_f32_16x16x32_bf16 (four cells of eight terms per step).  Lane l supplies
-// A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j][l % 16], j < 8, and receives
-// D[4 (l / 16) + i][l % 16]: one operator row of one cell and eight consecutive
-// terms of one input row, each one 16-byte read from LDS.
-template <int RT, int MODE>
-__device__ void m2l_gemm_tile_split(const float *In, float *Out, int64_t R, int G, const float *T, int64_t r0,
+// v_mfma_f32_16x16x32_bf16 (four cells of eight terms per step; PAD: p < 8, whose
+// missing terms are zeros, MODE 0 only).  Lane l supplies A[l % 16][8 (l / 16) + j] and
+// B[8 (l / 16) + j][l % 16], j < 8, and receives D[4 (l / 16) + i][l % 16]: one operator
+// row of one cell and eight consecutive terms of one input row, each one 16-byte read
+// from LDS.
+template <int RT, int MODE, bool PAD>
+__device__ void m2l_gemm_tile_split(const float *In, float *Out, int64_t R, int p, int G, const float *T, int64_t r0,
                                     float *sm, int Ga, int band) {
     constexpr int NR = RT / 16;
-    constexpr int p = 8, pp = 64, p3 = 512;
-    const int U = G * p;
+    constexpr int pp = 64, p3 = 512;   // (MODE != 0: p = 8)
+    const int U = G * 8;               // columns with eight terms per cell
     const int UH = m2l_split_row(U);
-    const int nT = (2 * G - 1) * pp;
+    const int ob = m2l_split_reach(G, band), nT = (2 * ob + 1) * 64;
     unsigned short *sInH = reinterpret_cast<unsigned short *>(sm);
     unsigned short *sInL = sInH + (size_t)RT * UH;
     unsigned short *sTH = sInL + (size_t)RT * UH;
     unsigned short *sTL = sTH + nT;
     int64_t *rowbase = reinterpret_cast<int64_t *>(
         reinterpret_cast<char *>(sm) + ((((size_t)RT * UH * 4 + (size_t)nT * 4) + 15) & ~(size_t)15));
-    auto put = [](unsigned short *h, unsigned short *l, float x) {
-        const unsigned short hb = bf16_bits(x);
-        *h = hb;
-        *l = bf16_bits(x - __uint_as_float((uint32_t)hb << 16));
+    // four values to their two planes, as 8-byte stores
+    auto put4 = [](unsigned short *h, unsigned short *l, const float (&x)[4]) {
+        ushort4 hv, lv;
+        unsigned short *hp = &hv.x, *lp = &lv.x;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            hp[k] = bf16_bits(x[k]);
+            lp[k] = bf16_bits(x[k] - __uint_as_float((uint32_t)hp[k] << 16));
+        }
+        *reinterpret_cast<ushort4 *>(h) = hv;
+        *reinterpret_cast<ushort4 *>(l) = lv;
     };
-    for (int e = threadIdx.x; e < nT; e += 256) put(sTH + e, sTL + e, T[e]);
+    // operator blocks of offsets -ob .. ob (both operands with several loads in flight)
+    T += (size_t)(G - 1 - ob) * (PAD ? p * p : 64);
+    for (int e0 = threadIdx.x; e0 < nT / 4; e0 += 4 * 256) {
+        float x[4][4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int e = e0 + 256 * k < nT / 4 ? e0 + 256 * k : 0;
+            if constexpr (PAD) {
+                const int o = e >> 4, b = (e >> 1) & 7, a = 4 * (e & 1);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[k][c] = b < p && a + c < p ? T[(o * p + b) * p + a + c] : 0.f;
+            } else {
+                const float4 v = reinterpret_cast<const float4 *>(T)[e];
+                x[k][0] = v.x;
+                x[k][1] = v.y;
+                x[k][2] = v.z;
+                x[k][3] = v.w;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (e0 + 256 * k < nT / 4) put4(sTH + 4 * (e0 + 256 * k), sTL + 4 * (e0 + 256 * k), x[k]);
+    }
     if constexpr (MODE != 0) {
         for (int rr = threadIdx.x; rr < RT; rr += 256) {
             const int64_t r = r0 + rr;
@@ -692,42 +726,69 @@ __device__ void m2l_gemm_tile_split(const float *In, float *Out, int64_t R, int 
         }
         __syncthreads();
     }
-    // input rows in 16-byte chunks (a chunk never straddles a cell), zeros past U
+    // input rows, four terms at a time (a chunk never straddles a cell), zeros past U
     const int U4 = UH / 4;
-    for (int e = threadIdx.x; e < RT * U4; e += 256) {
-        const int rr = e / U4, c4 = e - rr * U4;
-        const int64_t r = r0 + rr;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (4 * c4 < U) {
-            if constexpr (MODE == 0) {
-                if (r < R) v = *reinterpret_cast<const float4 *>(In + r * U + 4 * c4);
-            } else {
-                const int64_t b = rowbase[rr];
-                const int64_t col = MODE == 1 ? (int64_t)(c4 >> 1) * 512 + (c4 & 1) * 4 : 4 * c4;
-                if (b >= 0) v = *reinterpret_cast<const float4 *>(In + b + col);
+    const int dr = 256 / U4, dc = 256 - dr * U4;
+    int rr = threadIdx.x / U4, c4 = threadIdx.x - rr * U4;
+    while (rr < RT) {
+        float x[4][4];
+        int at[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            at[k] = rr < RT ? rr * UH + 4 * c4 : -1;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[k][c] = 0.f;
+            if (at[k] >= 0 && 4 * c4 < U) {
+                if constexpr (PAD) {
+                    const int64_t r = r0 + rr;
+                    const float *src = In + r * (G * p) + (c4 >> 1) * p + 4 * (c4 & 1);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (r < R && 4 * (c4 & 1) + c < p) x[k][c] = src[c];
+                } else {
+                    const float *src = nullptr;
+                    if constexpr (MODE == 0) {
+                        if (r0 + rr < R) src = In + (r0 + rr) * U + 4 * c4;
+                    } else {
+                        const int64_t b = rowbase[rr];
+                        if (b >= 0) src = In + b + (MODE == 1 ? (int64_t)(c4 >> 1) * 512 + (c4 & 1) * 4 : 4 * c4);
+                    }
+                    if (src) {
+                        const float4 v = *reinterpret_cast<const float4 *>(src);
+                        x[k][0] = v.x;
+                        x[k][1] = v.y;
+                        x[k][2] = v.z;
+                        x[k][3] = v.w;
+                    }
+                }
+            }
+            rr += dr;
+            c4 += dc;
+            if (c4 >= U4) {
+                c4 -= U4;
+                ++rr;
             }
         }
-        unsigned short *dh = sInH + (size_t)rr * UH + 4 * c4, *dl = sInL + (size_t)rr * UH + 4 * c4;
-        put(dh, dl, v.x);
-        put(dh + 1, dl + 1, v.y);
-        put(dh + 2, dl + 2, v.z);
-        put(dh + 3, dl + 3, v.w);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (at[k] >= 0) put4(sInH + at[k], sInL + at[k], x[k]);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nk = (U + 31) / 32;   // 32-term K steps
     const int nv = (U + 15) / 16;
     const bf16x8 zero8 = __builtin_bit_cast(bf16x8, u16x8{0, 0, 0, 0, 0, 0, 0, 0});
-    for (int vc = wave; vc < nv; vc += 4) {
+    // the grid's y index picks a group of four 16-wide column blocks
+    for (int vc = wave + 4 * (int)blockIdx.y; vc < nv; vc += 4 * (int)gridDim.y) {
         const int v = vc * 16 + (lane & 15);
-        const int tv = v / p, b = v % p;
+        const int tv = v >> 3, b = v & 7;
         f32x4 acc[NR];
 #pragma unroll
         for (int j = 0; j < NR; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         int kb = 0, ke = nk;
         if (band < G - 1) {
             const int vlast = vc * 16 + 15 < U ? vc * 16 + 15 : U - 1;
-            const int c_lo = (vc * 16) / p - band, c_hi = vlast / p + band;
+            const int c_lo = 2 * vc - band, c_hi = (vlast >> 3) + band;
             kb = (c_lo > 0 ? c_lo : 0) / 4;
             const int c_end = c_hi + 1 < G ? c_hi + 1 : G;
             ke = (c_end + 3) / 4 < nk ? (c_end + 3) / 4 : nk;
@@ -736,7 +797,7 @@ __device__ void m2l_gemm_tile_split(const float *In, float *Out, int64_t R, int 
             const int sc = 4 * ks + (lane >> 4);   // the cell of this lane's eight terms
             bf16x8 ah = zero8, al = zero8;
             if (v < U && sc < G) {
-                const int row = ((tv - sc + G - 1) * p + b) * p;
+                const int row = ((tv - sc + ob) * 8 + b) * 8;
                 ah = *reinterpret_cast<const bf16x8 *>(sTH + row);
                 al = *reinterpret_cast<const bf16x8 *>(sTL + row);
             }
@@ -759,7 +820,9 @@ __device__ void m2l_gemm_tile_split(const float *In, float *Out, int64_t R, int 
                 if (vo < U && r < R) {
                     if constexpr (MODE == 2) {
                         const int q = (int)r;
-                        Out[(int64_t)(vo / p) * R * p + (vo % p) * pp + (int64_t)(q / pp) * p3 + q % pp] = acc[j][i];
+                        Out[(int64_t)(vo >> 3) * R * 8 + (vo & 7) * pp + (int64_t)(q / pp) * p3 + q % pp] = acc[j][i];
+                    } else if constexpr (PAD) {
+                        if ((vo & 7) < p) Out[((int64_t)(vo >> 3) * p + (vo & 7)) * R + r] = acc[j][i];
                     } else {
                         Out[(int64_t)vo * R + r] = acc[j][i];
                     }
@@ -787,16 +850,17 @@ __device__ inline uint64_t rows_mask(const uint64_t *m, int glo, int64_t r0, int
            (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-// The float32 tile for p = 8.  The contraction runs over the source cells (two K steps
+// The float32 tile for p = 8 (PAD: p < 8, eight terms per cell with zeros past p, MODE
+// 0 only).  The contraction runs over the source cells (two K steps
 // of four terms each), four at a time, so that cells without moments and cells beyond
 // the band cost nothing.  Input rows are padded by two floats and an operator block is
 // kept transposed (source term, then target term) every 80 floats, so that the 32 lanes
 // served together read 32 banks; with rows padded by one and blocks untransposed the
 // operand reads took four times as long and bound the pass as much as the matrix cores
 // did.
-template <int RT, int MODE>
-__device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, const float *T, int64_t r0, float *sm,
-                               int Ga, int band, PassMask pm) {
+template <int RT, int MODE, bool PAD>
+__device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int p, int G, const float *T, int64_t r0,
+                               float *sm, int Ga, int band, PassMask pm) {
     constexpr int NR = RT / 16;   // 16-wide column tiles per block
     constexpr int NC = 4;         // source cells per round
     const int U = G * 8, UP = U + 2;
@@ -808,14 +872,24 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
     }
     float *sIn = sm, *sT = sm + (size_t)RT * UP;
     const int ob = m2l_reach(G, band), nop = 2 * ob + 1;   // operator blocks of offsets -ob .. ob
-    T += (size_t)(G - 1 - ob) * 64;
+    T += (size_t)(G - 1 - ob) * (PAD ? p * p : 64);
     // (both operands are staged with four loads in flight per thread: one at a time, the
     // loads' latencies took longer than the products)
     const int nT4 = nop * 16;
     for (int e0 = threadIdx.x; e0 < nT4; e0 += 4 * 256) {
         float4 t[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) t[k] = reinterpret_cast<const float4 *>(T)[e0 + 256 * k < nT4 ? e0 + 256 * k : 0];
+        for (int k = 0; k < 4; ++k) {
+            const int e = e0 + 256 * k < nT4 ? e0 + 256 * k : 0;
+            if constexpr (PAD) {
+                const int o = e >> 4, b = (e >> 1) & 7, a = 4 * (e & 1);
+                const float *row = T + (o * p + (b < p ? b : 0)) * p;
+                auto at = [&](int c) { return b < p && a + c < p ? row[a + c] : 0.f; };
+                t[k] = make_float4(at(0), at(1), at(2), at(3));
+            } else {
+                t[k] = reinterpret_cast<const float4 *>(T)[e];
+            }
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int e = e0 + 256 * k;   // block e / 16, target term (e / 2) % 8, source terms 4 (e % 2) ..
@@ -859,7 +933,8 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
             at[k] = rr < RT ? rr * UP + 4 * c4 : -1;
             if (pm.in && !((kin >> (c4 >> 1)) & 1)) at[k] = -1;   // never read
             const float *src = nullptr;
-            if constexpr (MODE == 0) {
+            if constexpr (PAD) {
+            } else if constexpr (MODE == 0) {
                 const int64_t r = r0 + rr;
                 if (r < R) src = In + r * U + 4 * c4;
             } else {
@@ -869,7 +944,14 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
                 if (b >= 0) src = In + b + col;
             }
             v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (at[k] >= 0 && src) v[k] = *reinterpret_cast<const float4 *>(src);
+            if constexpr (PAD) {
+                src = In + (r0 + rr) * (G * p) + (c4 >> 1) * p + 4 * (c4 & 1);
+                const int left = at[k] >= 0 && r0 + rr < R ? p - 4 * (c4 & 1) : 0;   // terms of the chunk
+                v[k] = make_float4(left > 0 ? src[0] : 0.f, left > 1 ? src[1] : 0.f, left > 2 ? src[2] : 0.f,
+                                   left > 3 ? src[3] : 0.f);
+            } else if (at[k] >= 0 && src) {
+                v[k] = *reinterpret_cast<const float4 *>(src);
+            }
             rr += dr;
             c4 += dc;
             if (c4 >= U4) {
@@ -955,6 +1037,8 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int G, co
                     if constexpr (MODE == 2) {   // vo = z' = (kz, az); r = q in cell-column order
                         const int qq = (int)r;
                         Out[(int64_t)(vo >> 3) * R * 8 + (vo & 7) * 64 + (int64_t)(qq >> 6) * 512 + (qq & 63)] = acc[j][i];
+                    } else if constexpr (PAD) {
+                        if ((vo & 7) < p) Out[((int64_t)(vo >> 3) * p + (vo & 7)) * R + r] = acc[j][i];
                     } else {
                         Out[(int64_t)vo * R + r] = acc[j][i];
                     }
@@ -969,11 +1053,11 @@ __device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p, int
                               float *sm, int Ga = 0, int band = 1 << 30, PassMask pm = PassMask{}) {
     if constexpr (SPLIT) {
         static_assert(PT == 8, "the split bfloat16 tile is built for p = 8");
-        m2l_gemm_tile_split<RT, MODE>(In, Out, R, G, T, r0, sm, Ga, band);
+        m2l_gemm_tile_split<RT, MODE, false>(In, Out, R, 8, G, T, r0, sm, Ga, band);
         return;
     }
     if constexpr (PT == 8) {
-        m2l_gemm_tile8<RT, MODE>(In, Out, R, G, T, r0, sm, Ga, band, pm);
+        m2l_gemm_tile8<RT, MODE, false>(In, Out, R, 8, G, T, r0, sm, Ga, band, pm);
         return;
     }
     constexpr int NR = RT / 16;   // 16-wide column tiles per block
@@ -1087,24 +1171,28 @@ __device__ void m2l_gemm_tile(const float *In, float *Out, int64_t R, int p, int
 
 template <int RT>
 __global__ void __launch_bounds__(256) k_m2l_gemm(const float *In, float *Out, int64_t R, int p, int G,
-                                                  const float *T, int band, PassMask pm) {
+                                                  const float *T, int band, PassMask pm, int pad) {
     extern __shared__ float sm[];
     if (p == 8) m2l_gemm_tile<RT, 0, 8>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band, pm);
+    else if (pad) m2l_gemm_tile8<RT, 0, true>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band, PassMask{});
     else m2l_gemm_tile<RT>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band);
 }
 
-// The whole-K tile with split bfloat16 products (p = 8).
+// The whole-K tile with split bfloat16 products (p <= 8).
 template <int RT>
-__global__ void __launch_bounds__(256) k_m2l_gemm_bf16x3(const float *In, float *Out, int64_t R, int G,
+__global__ void __launch_bounds__(256) k_m2l_gemm_bf16x3(const float *In, float *Out, int64_t R, int p, int G,
                                                          const float *T, int band) {
     extern __shared__ float sm[];
-    m2l_gemm_tile<RT, 0, 8, true>(In, Out, R, 8, G, T, (int64_t)blockIdx.x * RT, sm, 0, band);
+    const int64_t r0 = (int64_t)blockIdx.x * RT;
+    if (p == 8) m2l_gemm_tile_split<RT, 0, false>(In, Out, R, 8, G, T, r0, sm, 0, band);
+    else m2l_gemm_tile_split<RT, 0, true>(In, Out, R, p, G, T, r0, sm, 0, band);
 }
 
 // The split bfloat16 pass for any p, 32 x 32 output tiles: each K step builds the
 // operator tile from T and splits both operands in registers; a lane supplies
 // eight consecutive k of its row of A and of its column of B (the same k for
-// both).  Used where the whole-K tile does not apply (p != 8, or too little LDS).
+// both).  Used where the whole-K tile does not apply (p > 8, or too little LDS), and for
+// the gradients' fields at p < 8.
 __global__ void __launch_bounds__(64) k_m2l_pass_bf16x3(const float *In, float *Out, int64_t R, int p,
                                                         int G, const float *T) {
     __shared__ float sA[MT][MK2 + 1];   // operator rows v, columns u
@@ -2730,7 +2818,16 @@ int64_t fgt_pop_tiles(const FgtPop &f, int p, int pass, bool gemm) {
 size_t fgt_pop_gemm_lds(const FgtPop &f, int p, bool split) {
     size_t m = 0;
     for (int k = 0; k < 3; ++k) {
-        const size_t l = split ? m2l_gemm_lds_split(f.G[k] * p, f.G[k], 32) : m2l_gemm_lds(f.G[k] * p, f.G[k], p, 32, f.band[k]);
+        const size_t l = split ? m2l_gemm_lds_split(f.G[k], 32, f.band[k]) : m2l_gemm_lds(f.G[k] * p, f.G[k], p, 32, f.band[k]);
+        m = l > m ? l : m;
+    }
+    return m;
+}
+
+size_t fgt_pop_split_whole(const FgtPop &f) {
+    size_t m = 0;
+    for (int k = 0; k < 3; ++k) {
+        const size_t l = (size_t)32 * m2l_split_row(8 * f.G[k]) * 4 + (size_t)(2 * f.G[k] - 1) * 256 + 32 * 8;
         m = l > m ? l : m;
     }
     return m;
@@ -2932,19 +3029,27 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
         } else if (bf16x3) {
             // rows per block: enough blocks to fill the chip, at most 64, and fewer
             // when the tile would not fit in LDS
+            const int band = m2l_band(p, step, ps.G);
             int RT = 64;
-            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds_split((int)ps.U, ps.G, RT) > 64 * 1024))
+            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds_split(ps.G, RT, band) > 64 * 1024))
                 RT >>= 1;
-            const size_t lds = m2l_gemm_lds_split((int)ps.U, ps.G, RT);
-            if (p == 8 && lds <= 64 * 1024) {
-                const dim3 grid((unsigned)((ps.R + RT - 1) / RT));
-                const int band = m2l_band(p, step, ps.G);
+            const size_t lds = m2l_gemm_lds_split(ps.G, RT, band);
+            // p < 8 in forward sums: the tile's sums run in another order than those of the
+            // 32 x 32 tiles, whose bits the gradients keep.  (1,792 cells at p = 6: 378
+            // wavefronts that rebuilt their operands per K step took 73 us for the three
+            // passes, 17 us here.)
+            if ((p == 8 || (p < 8 && u_out)) && lds <= 64 * 1024) {
+                // column groups as in the float32 passes below
+                const int64_t rows = (ps.R + RT - 1) / RT;
+                const int ngroup = ((8 * ps.G + 15) / 16 + 3) / 4;
+                const int64_t want = (1024 + rows - 1) / rows;
+                const dim3 grid((unsigned)rows, (unsigned)(want < ngroup ? want : ngroup));
                 if (RT == 64)
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, ps.G, ps.T, band);
+                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
                 else if (RT == 32)
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, ps.G, ps.T, band);
+                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
                 else
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, ps.G, ps.T, band);
+                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
             } else {
                 dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
                 hipLaunchKernelGGL(k_m2l_pass_bf16x3, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
@@ -2953,25 +3058,29 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
             // rows per block: enough blocks to fill the chip, at most 64, and fewer
             // when the tile would not fit in LDS
             const int band = m2l_band(p, step, ps.G);
+            // p < 8 in forward sums: eight terms per cell (the tile for any p sums in another
+            // order, whose bits the gradients keep)
+            const int pad = p < 8 && u_out ? 1 : 0;
+            const int Ut = pad ? 8 * ps.G : (int)ps.U;
             int RT = 64;
-            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds((int)ps.U, ps.G, p, RT, band) > 64 * 1024))
+            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds(Ut, ps.G, p, RT, band) > 64 * 1024))
                 RT >>= 1;
-            const size_t lds = m2l_gemm_lds((int)ps.U, ps.G, p, RT, band);
+            const size_t lds = m2l_gemm_lds(Ut, ps.G, p, RT, band);
             if (lds <= 64 * 1024) {
                 // column groups of four 16-wide blocks, one per wavefront, as the grid's y,
                 // only while the row tiles alone make fewer than 1024 blocks (every group
                 // stages the whole input rows)
                 const int64_t rows = (ps.R + RT - 1) / RT;
-                const int ngroup = ((int)(ps.U + 15) / 16 + 3) / 4;
+                const int ngroup = ((Ut + 15) / 16 + 3) / 4;
                 const int64_t want = (1024 + rows - 1) / rows;
                 const int cg = want < ngroup ? (int)want : ngroup;
                 const dim3 grid((unsigned)rows, (unsigned)cg);
                 if (RT == 64)
-                    hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm);
+                    hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm, pad);
                 else if (RT == 32)
-                    hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm);
+                    hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm, pad);
                 else
-                    hipLaunchKernelGGL(k_m2l_gemm<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm);
+                    hipLaunchKernelGGL(k_m2l_gemm<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm, pad);
             } else {
                 dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
                 hipLaunchKernelGGL(k_m2l_pass_mfma, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);

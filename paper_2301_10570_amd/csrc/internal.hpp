@@ -446,6 +446,8 @@ struct FgtPlan {
 int fgt_pop_prepare(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, FgtPop *out);
 int64_t fgt_pop_tiles(const FgtPop &f, int p, int pass, bool gemm);
 size_t fgt_pop_gemm_lds(const FgtPop &f, int p, bool split = false);
+// LDS of the split tile with the whole operator table (its limit is the batch's)
+size_t fgt_pop_split_whole(const FgtPop &f);
 int fgt_batch_forward(const FgtBatchPlan &bp, hipStream_t s);
 // value, gradient and (want_lap) Laplacian of every population's field at all its
 // points, into f.rec + i * stride + slot (key order i)

@@ -63,3 +63,25 @@ def test_same_bits_as_without_the_table(kind, n, p):
     u3 = tree.forward(d["w"], d["tgt"], sigma=wl.sigma, p=p, route="fgt").cpu().numpy()
     assert rel_err(u3[sel][some], r[some]).max() <= 1e-4
     tree.close()
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 5, 6, 7])
+@pytest.mark.parametrize("m2l", ["mfma", "bf16x3"])
+def test_padded_translation_tiles(p, m2l):
+    """Orders below eight run on the tiles of eight terms per cell, padded with zeros:
+    against the vector passes, 1e-5 (float32) and 5e-5 (about 2^-16 per product) as for
+    the unpadded tiles, on a grid ragged in every axis."""
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(9001, extent=(1300.0, 700.0, 500.0), sigma=400.0, seed=905)
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    print(f"padded tiles p={p} {m2l} grid {tree.plan(wl.sigma, p=p, level=4, route='fgt')['grid']}", flush=True)
+    kw = dict(sigma=wl.sigma, p=p, level=4, route="fgt")
+    u = tree.forward(d["w"], d["tgt"], m2l=m2l, **kw).cpu().numpy()
+    C = tree.debug_buffer(1).cpu().numpy()
+    v = tree.forward(d["w"], d["tgt"], m2l="valu", **kw).cpu().numpy()
+    Cv = tree.debug_buffer(1).cpu().numpy()
+    tgt = wl.a > 0
+    assert np.abs(C - Cv).max() <= (1e-5 if m2l == "mfma" else 2e-4) * np.abs(Cv).max()
+    assert rel_err(u[tgt], v[tgt]).max() <= (1e-5 if m2l == "mfma" else 5e-5)
+    tree.close()
