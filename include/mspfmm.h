@@ -419,11 +419,10 @@ int msp_fgt_debug_buffer(msp_tree *t, int32_t which, void *dst, size_t dst_bytes
  * is_target, u_out, gradients).  Every population gets its own octree; the
  * kernels of a forward call cover all of them: populations on the expansion
  * route run their own short sequence, and all populations on the direct route
- * share one persistent launch that takes (population, node) work items from a
- * device counter.  The first forward call with a given argument set runs
+ * share one launch with a block per (population, node).  The first forward call with a given argument set runs
  * eagerly and captures the sequence into a hipGraph; later calls with the same
  * pointers, sigmas and parameters replay it on `stream`.  Calls on one batch
- * must not overlap (they share the work counter and scratch).
+ * must not overlap (they share scratch).
  * ------------------------------------------------------------------------- */
 typedef struct msp_batch msp_batch; /* opaque handle */
 
@@ -480,7 +479,7 @@ int msp_batch_backward(msp_batch *b, const float *w, const uint8_t *is_target, c
 /* Per-population latency of the last forward call, from device timestamps
  * (host double[npop], milliseconds; 0 for empty populations).  Waits for the
  * device.  For direct-route populations it spans the first to the last work
- * item of the population inside the shared persistent launch. */
+ * item of the population inside the shared launch. */
 int msp_batch_instance_ms(msp_batch *b, double *ms);
 
 /* Number of populations; launches of the last eager forward call. */
@@ -492,7 +491,7 @@ int msp_batch_info(const msp_batch *b, int32_t *npop, int64_t *launches);
  * point count times the point counts of the leaves its list names, counted on the
  * device on `stream` (one small launch, then a wait for `stream`); *span_ms (or
  * NULL) gets the time from the first to the last work item of the shared
- * persistent launch, from device timestamps (0 without direct-route populations).
+ * launch, from device timestamps (0 without direct-route populations).
  * Both are 0 when no population took the direct route.  MSP_ESTATE before the
  * first forward after a build, or when a later call rebuilt or moved the
  * populations' lists (a backward with other parameters). */

@@ -610,7 +610,7 @@ class Batch:
     def pair_count(self) -> tuple[int, float]:
         """(point pairs, span in ms) of the direct-route populations in the last forward:
         the pairs their P2P pass evaluates and the time from the first to the last work
-        item of the shared persistent launch (msp_batch_pair_count)."""
+        item of the shared launch (msp_batch_pair_count)."""
         pairs, span = _i64(), ctypes.c_double()
         _check(_lib.msp_batch_pair_count(self._h, ctypes.byref(pairs), ctypes.byref(span), _stream()),
                "msp_batch_pair_count")

@@ -8,11 +8,11 @@
 //     L2P straight into the output slices), each pass locating its work units
 //     (population, cell / tile / operator) in prefix sums; they run on a branch
 //     stream that forks from the caller's stream and joins it again;
-//   - all populations on the direct route share ONE persistent P2P launch: a
-//     grid sized to the chip takes work items (population, node) from a global
-//     counter until the queue is empty, so small populations do not each pay
-//     for a launch and the chip stays busy across the uneven sizes.  One staging
-//     launch before it and one scatter launch after it also cover all of them.
+//   - all populations on the direct route share ONE P2P launch with a block per
+//     (population, node), the largest populations first, so small populations do
+//     not each pay for a launch and the chip stays busy across the uneven sizes.
+//     One staging launch before it and one scatter launch after it also cover all
+//     of them.
 // The backward has the same shape: the two fields it needs (weights w, and the
 // upstream gradient at the targets) by the batched expansion passes with an L2P
 // that also gives gradient and Laplacian, or by one persistent P2P-with-derivatives
@@ -20,16 +20,18 @@
 // gradients and one that reduces the sigma derivative of each population.
 // After a first eager call the sequence is captured into a hipGraph on a
 // private stream and later calls with the same arguments replay the graph on
-// the caller's stream.  The capture holds no memset nodes: the work counter and
-// the timestamps are cleared by a kernel.
+// the caller's stream.  The capture holds no memset nodes: what is counted and the
+// timestamps are cleared by kernels.
 //
 // The autotuner times every population at each candidate leaf size on both
 // routes and keeps the fastest pair.
 #include "grad_common.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <memory>
+#include <numeric>
 #include <vector>
 
 namespace msp {
@@ -46,6 +48,8 @@ struct PopDesc {
     int32_t pop;
 };
 
+__device__ inline const LeafSet &leaf_set(const PopDesc &d) { return d.ls; }
+
 __device__ inline int find_segment(const int64_t *off, int nseg, int64_t x) {
     int lo = 0, hi = nseg;   // off[lo] <= x < off[hi]
     while (hi - lo > 1) {
@@ -56,10 +60,8 @@ __device__ inline int find_segment(const int64_t *off, int nseg, int64_t x) {
     return lo;
 }
 
-__global__ void k_batch_reset(const PopDesc *desc, int nd, unsigned long long *counter,
-                              unsigned long long *stamps) {
+__global__ void k_batch_reset(const PopDesc *desc, int nd, unsigned long long *stamps) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) *counter = 0ull;
     if (i < nd) {
         stamps[2 * desc[i].pop] = ~0ull;
         stamps[2 * desc[i].pop + 1] = 0ull;
@@ -79,45 +81,35 @@ __global__ void k_batch_stage(const PopDesc *desc, const int64_t *pt_off, int nd
     const_cast<uint8_t *>(D.ls.tflag)[i] = is_target ? (is_target[j] != 0) : (uint8_t)1;
 }
 
-// Persistent P2P over the nodes of every direct-route population, four independent
-// wavefronts per block.  A wave takes kP2PTake consecutive items per atomic addition
-// on the shared counter (one item balances the load best: leaves differ widely in
-// work) and leaves the loop once the counter passes the last item; population
-// timestamps are recorded once per run of items of one population.
-constexpr int kP2PTake = 1;
-__global__ void __launch_bounds__(256, 8) k_batch_p2p(const PopDesc *desc, const int64_t *item_off, int nd,
-                                                   unsigned long long *counter,
-                                                   unsigned long long *stamps) {
+// The direct-route populations' nodes as tasks, item by item: found once per plan, so
+// that a leaf's block does not start with a chain of a dozen dependent loads.
+template <class DESC>
+__global__ void k_batch_tasks(const DESC *desc, const int64_t *item_off, int nd, LeafTask *tasks) {
+    const int64_t item = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (item >= item_off[nd]) return;
+    const int d = find_segment(item_off, nd, item);
+    tasks[item] = leaf_task(leaf_set(desc[d]), item - item_off[d], d);
+}
+
+// P2P over the nodes of every direct-route population: a block of four wavefronts per
+// node (largest populations first, leaves differ widely in work), which share the leaf's
+// list.  A wavefront per leaf left a tail as long as the largest leaf's list (48
+// populations: 250 us of work per wave slot took 750 us).  The blocks are short-lived on
+// purpose: persistent ones held their wave slots and registers, and the expansion kernels
+// of the other populations, a tenth of the grid's time each, waited for the last of them.
+__global__ void __launch_bounds__(256, 5) k_batch_p2p(const PopDesc *desc, const LeafTask *tasks, int64_t n,
+                                                      unsigned long long *stamps) {
     __shared__ P2PShared sh[4];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t total = item_off[nd];
-    // a wave can take at most `total` batches before the counter passes the end
-    for (int64_t it = 0; it <= total; ++it) {
-        unsigned long long mine = 0ull;
-        if (lane == 0) mine = atomicAdd(counter, (unsigned long long)kP2PTake);
-        const int64_t first = (int64_t)__shfl(mine, 0, 64);
-        if (first >= total) break;
-        const int64_t last = first + kP2PTake < total ? first + kP2PTake : total;
-        int pop = -1;
-        unsigned long long t_first = 0ull;
-        for (int64_t item = first; item < last; ++item) {
-            const int d = find_segment(item_off, nd, item);
-            const PopDesc &D = desc[d];
-            const unsigned long long t0 = wall_clock64();
-            if (D.pop != pop) {
-                if (pop >= 0 && lane == 0) {
-                    atomicMin(&stamps[2 * pop], t_first);
-                    atomicMax(&stamps[2 * pop + 1], (unsigned long long)wall_clock64());
-                }
-                pop = D.pop;
-                t_first = t0;
-            }
-            p2p_leaf<1>(D.ls, item - item_off[d], 0, sh[wave], nullptr);
-        }
-        if (lane == 0) {
-            atomicMin(&stamps[2 * pop], t_first);
-            atomicMax(&stamps[2 * pop + 1], (unsigned long long)wall_clock64());
-        }
+    __shared__ double red[4][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int64_t item = blockIdx.x; item < n; item += gridDim.x) {
+        const LeafTask t = uniform_copy(tasks[item]);
+        if (t.count == 0) continue;
+        const LeafSet ls = uniform_copy(desc[t.owner].ls);
+        const int pop = desc[t.owner].pop;
+        if (threadIdx.x == 0) atomicMin(&stamps[2 * pop], (unsigned long long)wall_clock64());
+        p2p_leaf<4>(ls, t, wave, sh[wave], red);
+        if (threadIdx.x == 0) atomicMax(&stamps[2 * pop + 1], (unsigned long long)wall_clock64());
     }
 }
 
@@ -368,6 +360,14 @@ int prepare_fgt(msp_batch *b, const std::vector<PopPlan> &plans, const float *w,
     return MSP_OK;
 }
 
+// The populations in the order of the direct-route launches: the longest lists first.
+std::vector<int> largest_first(const msp_batch *b) {
+    std::vector<int> o(b->npop);
+    std::iota(o.begin(), o.end(), 0);
+    std::stable_sort(o.begin(), o.end(), [&](int p, int q) { return b->pops[p]->n > b->pops[q]->n; });
+    return o;
+}
+
 // Allocations, interaction lists and the descriptors of the direct-route
 // populations (host synchronisations allowed: never under capture).
 int prepare_batch(msp_batch *b, const std::vector<PopPlan> &plans, const float *w, const uint8_t *is_target,
@@ -384,7 +384,7 @@ int prepare_batch(msp_batch *b, const std::vector<PopPlan> &plans, const float *
         MSP_HIP(hipMemcpy(b->fdesc.p, fp.data(), fp.size() * sizeof(FgtPop), hipMemcpyHostToDevice));
         b->fplan.pops = b->fdesc.as<FgtPop>();
     }
-    for (int k = 0; k < b->npop; ++k) {
+    for (int k : largest_first(b)) {
         msp_tree *t = b->pops[k].get();
         const PopPlan &pp = plans[k];
         if (pp.pl.route == MSP_ROUTE_FGT || t->n == 0) continue;
@@ -422,15 +422,23 @@ int prepare_batch(msp_batch *b, const std::vector<PopPlan> &plans, const float *
     MSP_TRY(b->desc.ensure((d.size() + 1) * sizeof(PopDesc)));
     MSP_TRY(b->pt_off.ensure(poff.size() * 8));
     MSP_TRY(b->item_off.ensure(ioff.size() * 8));
-    MSP_TRY(b->counter.ensure(8));
     MSP_HIP(hipStreamSynchronize(s));
     if (!d.empty()) MSP_HIP(hipMemcpy(b->desc.p, d.data(), d.size() * sizeof(PopDesc), hipMemcpyHostToDevice));
     MSP_HIP(hipMemcpy(b->pt_off.p, poff.data(), poff.size() * 8, hipMemcpyHostToDevice));
     MSP_HIP(hipMemcpy(b->item_off.p, ioff.data(), ioff.size() * 8, hipMemcpyHostToDevice));
+    if (b->direct_items > 0) {
+        MSP_TRY(b->tasks.ensure((size_t)b->direct_items * sizeof(LeafTask)));
+        hipLaunchKernelGGL(k_batch_tasks<PopDesc>, dim3(grid_for(b->direct_items, kBlock)), dim3(kBlock), 0, s,
+                           b->desc.as<PopDesc>(), b->item_off.as<int64_t>(), (int)d.size(), b->tasks.as<LeafTask>());
+        MSP_CHECK_LAUNCH();
+    }
     std::vector<uint64_t> zero((size_t)(b->npop > 0 ? b->npop : 1) * 2, 0);
     MSP_HIP(hipMemcpy(b->stamps.p, zero.data(), zero.size() * 8, hipMemcpyHostToDevice));
     return MSP_OK;
 }
+
+// Blocks of a launch with one per item (the kernels stride over what is past the limit)
+unsigned item_grid(int64_t items) { return (unsigned)(items < (int64_t)1 << 22 ? items : (int64_t)1 << 22); }
 
 // The whole forward as a launch sequence on s (no synchronisation, no allocation
 // once prepare_batch has run for the same plans).
@@ -448,19 +456,15 @@ int enqueue_forward(msp_batch *b, const std::vector<PopPlan> &plans, const float
     const int nd = b->n_direct;
     if (nd > 0) {
         const PopDesc *desc = b->desc.as<PopDesc>();
-        auto *counter = b->counter.as<unsigned long long>();
         auto *st = b->stamps.as<unsigned long long>();
-        hipLaunchKernelGGL(k_batch_reset, dim3(grid_for(nd, 64)), dim3(64), 0, s, desc, nd, counter, st);
+        hipLaunchKernelGGL(k_batch_reset, dim3(grid_for(nd, 64)), dim3(64), 0, s, desc, nd, st);
         MSP_CHECK_LAUNCH();
         hipLaunchKernelGGL(k_batch_stage, dim3(grid_for(b->direct_points, kBlock)), dim3(kBlock), 0, s, desc,
                            b->pt_off.as<int64_t>(), nd, w, is_target);
         MSP_CHECK_LAUNCH();
-        const int64_t waves = (int64_t)b->cus * 32;
-        const int64_t want = b->direct_items < waves ? b->direct_items : waves;
-        const int64_t grid = (want + 3) / 4;
-        if (grid > 0) {
-            hipLaunchKernelGGL(k_batch_p2p, dim3((unsigned)grid), dim3(256), 0, s, desc,
-                               b->item_off.as<int64_t>(), nd, counter, st);
+        if (b->direct_items > 0) {
+            hipLaunchKernelGGL(k_batch_p2p, dim3(item_grid(b->direct_items)), dim3(256), 0, s, desc,
+                               b->tasks.as<LeafTask>(), b->direct_items, st);
             MSP_CHECK_LAUNCH();
         }
         hipLaunchKernelGGL(k_batch_scatter, dim3(grid_for(b->direct_points, kBlock)), dim3(kBlock), 0, s, desc,

@@ -1959,7 +1959,14 @@ __device__ inline int find_pop(const int64_t *off, int npop, int64_t x) {
     return lo;
 }
 
+// The batched expansion kernels run beside the persistent P2P, whose wavefronts are
+// older and keep the vector units busy: at equal priority the few wavefronts of a
+// latency-bound kernel like k_bcells got hardly an issue slot (1.7 ms beside the P2P of
+// 256 populations, 0.1 ms alone).
+__device__ inline void ahead_of_p2p() { __builtin_amdgcn_s_setprio(3); }
+
 __global__ void k_bops(FgtBatchPlan bp) {
+    ahead_of_p2p();
     const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (g >= bp.n_ops) return;
     const int k = find_pop(bp.ops_off, bp.npop, g);
@@ -1971,6 +1978,7 @@ __global__ void k_bops(FgtBatchPlan bp) {
 // the cell counters and the timestamps.  Each population's grid is cleared
 // in 16-byte stores by all threads (grids start at allocation boundaries).
 __global__ void k_bclear(FgtBatchPlan bp) {
+    ahead_of_p2p();
     const int64_t g0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t nth = (int64_t)gridDim.x * blockDim.x;
     if (g0 == 0) {
@@ -2002,6 +2010,7 @@ __global__ void k_bclear(FgtBatchPlan bp) {
 // system).
 constexpr int kCellWin = 16;
 __global__ void __launch_bounds__(256) k_bcells(FgtBatchPlan bp, int cmax) {
+    ahead_of_p2p();
     const int lane = threadIdx.x & 63;
     const int64_t w0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kCellWin;
     if (w0 >= bp.n_pw) return;   // whole wavefronts
@@ -2367,6 +2376,7 @@ __device__ void p2m_cells_group(const FgtBatchPlan &bp, int64_t r0, int64_t nsma
 // wavefront (four wavefronts per block, each on its own cells).
 template <int P>
 __global__ void __launch_bounds__(256) k_bp2m(FgtBatchPlan bp) {
+    ahead_of_p2p();
     __shared__ float4 stage[4][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t wid = (int64_t)blockIdx.x * 4 + wave, nw = (int64_t)gridDim.x * 4;
@@ -2387,6 +2397,7 @@ __global__ void __launch_bounds__(256) k_bp2m(FgtBatchPlan bp) {
 }
 
 __global__ void __launch_bounds__(64) k_bm2l(FgtBatchPlan bp, int pass) {
+    ahead_of_p2p();
     const int64_t g = blockIdx.x;
     const int k = find_pop(bp.tile_off[pass], bp.npop, g);
     const FgtPop &f = bp.pops[k];
@@ -2405,6 +2416,7 @@ __global__ void __launch_bounds__(64) k_bm2l(FgtBatchPlan bp, int pass) {
 // x pass from the cell-major moments, z pass into the cell-major Taylor grid
 template <int PASS>
 __global__ void __launch_bounds__(256) k_bm2l_gemm(FgtBatchPlan bp) {
+    ahead_of_p2p();
     extern __shared__ float sm[];
     const int64_t g = blockIdx.x;
     const int k = find_pop(bp.tile_off[PASS], bp.npop, g);
@@ -2632,6 +2644,7 @@ __device__ void l2p_cells_group(const FgtBatchPlan &bp, int64_t r0, int64_t nsma
 // wavefront (four wavefronts per block, each on its own cells).
 template <int P>
 __global__ void __launch_bounds__(256) k_bl2p(FgtBatchPlan bp) {
+    ahead_of_p2p();
     constexpr int SC = P * (P * P + 4) > 256 ? P * (P * P + 4) : 256;   // slice buffer, or 64 float4
     __shared__ __align__(16) float sC[4][SC];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -2657,6 +2670,7 @@ __global__ void __launch_bounds__(256) k_bl2p(FgtBatchPlan bp) {
 // population's records f.rec + i * stride + slot (key order i).
 template <int P>
 __global__ void __launch_bounds__(64) k_bl2p_grad(FgtBatchPlan bp, int stride, int slot, int want_lap) {
+    ahead_of_p2p();
     constexpr int P3 = P * P * P;
     __shared__ float sC[P3];
     const int lane = threadIdx.x;

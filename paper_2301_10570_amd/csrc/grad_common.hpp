@@ -79,16 +79,17 @@ __device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, int6
         float su = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, sr = 0.f;
         float gu = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
         for (int w0 = 0; w0 < len; w0 += 64) {
-            const int tot = load_window(lst, len, w0, L.n_nodes, L.nfirst, L.ncount, lane, sh.win);
+            int start;
+            const int tot = load_window(lst, w0, len - w0 < 64 ? len - w0 : 64, L.n_nodes, L.nfirst, L.ncount, lane,
+                                        sh.win, start);
             float4 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
             float ngw = 0.f;
             // slots past the window's end hold a zero record (weights 0)
             auto fetch = [&](int c0) {
-                const int j = c0 + lane;
+                const int32_t pj = window_point(sh.win, start, c0 >> 6, lane);
                 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
                 ngw = 0.f;
-                if (j < tot) {
-                    const int32_t pj = window_point(sh.win, j);
+                if (c0 + lane < tot) {
                     const float4 q = L.ps[pj];
                     nxt = make_float4(q.x - ct[0], q.y - ct[1], q.z - ct[2], q.w);
                     if (SEC) ngw = g2[pj];

@@ -326,7 +326,7 @@ struct msp_batch {
     std::vector<std::unique_ptr<msp_tree>> pops;
     std::vector<int32_t> leaf_max, route;
     // batched direct route
-    msp::DevBuf desc, pt_off, item_off, counter, stamps;
+    msp::DevBuf desc, pt_off, item_off, tasks, stamps;
     int32_t n_direct = 0;
     int cus = 256;
     int64_t direct_points = 0, direct_items = 0;

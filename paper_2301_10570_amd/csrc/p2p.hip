@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(kBlock) k_lists(int64_t n_nodes, const int32_t
         if (row && mine) row[c + __popcll(ready & ((1ull << lane) - 1))] = u;
         c += __popcll(ready);
         const int k = inner ? nc : (leaf && !mine ? 1 : 0);
-        const int incl = p2p_incl_scan(k, lane);
+        const int incl = p2p_incl_scan(k);
         const int all = __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
         if (sp + all > kWalkCap) continue;
         const int top = sp + all - 1 - (incl - k);
@@ -135,13 +135,13 @@ __global__ void __launch_bounds__(1024) k_scan_i32_to_i64(const int32_t *cnt, in
 // NW wavefronts per target leaf (non-leaf nodes return at once): a block per node, or
 // for NW = 1 four nodes per block.
 template <int NW>
-__global__ void __launch_bounds__(NW == 1 ? 256 : NW * 64, 8) k_p2p(LeafSet ls) {
+__global__ void __launch_bounds__(NW == 1 ? 256 : NW * 64, 4) k_p2p(LeafSet ls) {
     constexpr int W = NW == 1 ? 4 : NW;
     __shared__ P2PShared sh[W];
     __shared__ double red[NW > 1 ? NW : 1][64];
-    const int wave = threadIdx.x >> 6;
-    if constexpr (NW == 1) p2p_leaf<1>(ls, (int64_t)blockIdx.x * 4 + wave, 0, sh[wave], red);
-    else p2p_leaf<NW>(ls, (int64_t)blockIdx.x, wave, sh[wave], red);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const LeafTask t = uniform_copy(leaf_task(ls, NW == 1 ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x, 0));
+    if (t.count > 0) p2p_leaf<NW>(ls, t, NW == 1 ? 0 : wave, sh[wave], red);
 }
 
 // All-pairs baseline.  A block of sixteen wavefronts takes T targets; a wavefront's

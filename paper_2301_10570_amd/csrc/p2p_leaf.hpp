@@ -1,20 +1,59 @@
 // P2P of one target leaf against its interaction list (Eq. (8)); shared by the
-// single-tree direct route and the batched persistent kernel.
+// single-tree direct route and the batched kernel.
 //
-// NW wavefronts share one target leaf (sh is private to each wave).  The source
-// points of up to 64 list entries at a time form one sequence, cut into chunks of
-// 64; the chunks go round the waves.  Within a chunk a block of nt <= 64 targets
-// splits the lanes into G = floor(64 / nt) groups of nt (the lanes past G nt idle),
-// each group taking every G-th source.  A chunk's partial sums are float32 (at most
-// 64 terms) and are added in float64, so the result does not depend on how many
-// waves share the leaf (the order of the float64 additions moves it by 2^-53).
-// exp(-d^2/sigma^2) is evaluated as exp2(-(k d)^2) with k^2 = log2(e)/sigma^2
-// (k = k_scale); the sources of a chunk sit in LDS as one 16-byte record each.
+// NW wavefronts share one target leaf (sh is private to each wave).  The list is cut
+// into windows of at most 64 entries, about sixteen of them (p2p_window), which go round
+// the waves; the source points of a window form one sequence, staged in LDS in chunks of
+// 128.  Sums of at most 32 terms are float32 and are added in float64, so the result does
+// not depend on how many waves share the leaf (the order of the float64 additions moves
+// it by 2^-53).  exp(-d^2/sigma^2) is evaluated as exp2(-d^2) of coordinates from the
+// leaf centre scaled by k_scale = sqrt(log2(e)) / sigma.
+//
+// Two forms, by the size of the leaf against sigma (see kMatrixReach):
+//   p2p_block_matrix   exp2(-d^2) = exp2(-t^2) exp2(2 t.s) exp2(-s^2): the products t.s of
+//       16 targets and 16 sources come from one matrix instruction, the other two factors
+//       are one value per target and per source, and a pair costs one exponential and
+//       one multiply-add on the vector unit in place of eight instructions.
+//   p2p_block_vector   the differences themselves.  T = 1, 2 or 4 targets per lane (nt up
+//       to 9, 18, 64), the lanes in G = floor(64 / ceil(nt / T)) groups, each taking
+//       every G-th source: nine tenths of the lanes' targets are there (one target per
+//       lane: 84%) and a record read from LDS serves T pairs.
+//
+// The vector unit bounds both.  256 populations of 1,024 to 65,536 points (5.0e9 pairs,
+// half of them of leaves of at most 16 points) took 2.15 ms with one target per lane and a
+// wavefront per leaf, and take 1.74 ms (of which the sums are half, the rest finds and
+// stages the sources).
 #pragma once
 #include "internal.hpp"
 
 namespace msp {
 namespace {
+
+// Loads through pointers that a kernel reads from memory (a batch's descriptors): the
+// compiler does not know that they are global and would make flat loads, which wait on
+// LDS traffic too.
+template <typename T>
+__device__ inline T ld_global(const T *p, int64_t i) {
+    return reinterpret_cast<const __attribute__((address_space(1))) T *>(reinterpret_cast<uintptr_t>(p))[i];
+}
+__device__ inline float4 ld_global4(const float4 *p, int64_t i) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const f32x4 v =
+        reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>(reinterpret_cast<uintptr_t>(p))[i];
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// A descriptor that is the same for the whole wavefront, in scalar registers.
+template <typename T>
+__device__ inline T uniform_copy(const T &from) {
+    int32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &from, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    T to;
+    __builtin_memcpy(&to, w, sizeof(T));
+    return to;
+}
 
 struct BoxGeo {
     double lo[3];
@@ -36,7 +75,7 @@ struct LeafLists {
     const int64_t *off;
     int64_t stride;
     const int32_t *cnt, *lst;
-    __device__ int64_t begin(int64_t v) const { return stride > 0 ? v * stride : off[v]; }
+    __device__ int64_t begin(int64_t v) const { return stride > 0 ? v * stride : ld_global(off, v); }
 };
 
 // One tree's arrays as the P2P pass reads them.
@@ -52,150 +91,373 @@ struct LeafSet {
     float *usort;
 };
 
-// A window of up to 64 list entries: for entry e, the number of source points up to
-// and including it, and its first point minus the points before it.
-struct ListWindow {
-    int32_t efirst[64], incl[64];
+// What a wavefront needs to know of a target leaf before it reads the list: its points,
+// its list, its centre and half side.  No points: not a leaf.
+struct LeafTask {
+    const int32_t *lst;
+    int32_t len, first, count, owner;   // owner: which of a batch's descriptors
+    float ct[3], half;
 };
+
+// Node v of a tree (SET: LeafSet or what the derivatives read).
+template <class SET>
+__device__ inline LeafTask leaf_task(const SET &L, int64_t v, int owner) {
+    LeafTask t{nullptr, 0, 0, 0, owner, {0.f, 0.f, 0.f}, 0.f};
+    if (v >= L.n_nodes || L.nnchild[v] != 0) return t;
+    node_box(L.geo, L.nlevel[v], L.nix[v], L.niy[v], L.niz[v], t.ct, t.half);
+    t.first = L.nfirst[v];
+    t.count = L.ncount[v];
+    t.lst = L.list.lst + L.list.begin(v);
+    t.len = L.list.cnt[v];
+    if (t.len > L.n_nodes) t.len = (int)L.n_nodes;   // a list names each node at most once
+    return t;
+}
+
+// A window of up to 64 list entries as runs of consecutive points (neighbours in key
+// order often follow each other): run e's first point less the points of the window
+// before it (those stay in registers, lane e: run e).
+struct ListWindow {
+    int32_t base[64];
+};
+
+constexpr int kP2PChunk = 128;   // sources staged at a time
+constexpr uint8_t kNoTarget = 255;
 
 struct P2PShared {
-    // staged sources (scaled offsets from the leaf centre, weight) and their point
-    // indices; slots 64..127 hold zero records for the idle lanes' reads
-    float4 sp[128];
-    int32_t sid[128];
+    // staged sources and which target of the block each is (kNoTarget: none); 64 slots
+    // past them hold zero records for the idle lanes' reads
+    float4 sp[kP2PChunk + 64];
+    float sw[kP2PChunk];
     double red[64];
     ListWindow win;
+    uint8_t sid[kP2PChunk + 64];
 };
 
-__device__ inline int p2p_incl_scan(int v, int lane) {
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
+// Inclusive sum over the wavefront (rows of 16 lanes, then the rows' totals).
+__device__ inline int p2p_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return v;
 }
 
-// The window's entries w0 .. w0 + 63 of a list of len entries at lst into win;
-// returns its source points.  One wavefront; win is written after a wave_sync, so
-// the previous window's readers are done.
-__device__ inline int load_window(const int32_t *lst, int len, int w0, int64_t n_nodes, const int32_t *nfirst,
-                                  const int32_t *ncount, int lane, ListWindow &win) {
+// The entries first .. first + n - 1 (n <= 64) of the list at lst into win; start: the
+// window's points before this lane's run (a value past any point on lanes without one).
+// Returns the window's points.  One wavefront; win is written after a wave_sync, so the
+// previous window's readers are done.
+__device__ inline int load_window(const int32_t *lst, int first, int n, int64_t n_nodes, const int32_t *nfirst,
+                                  const int32_t *ncount, int lane, ListWindow &win, int &start) {
     int32_t esf = 0, esn = 0;
-    if (w0 + lane < len) {
-        const int32_t u = lst[w0 + lane];
+    if (lane < n) {
+        const int32_t u = ld_global(lst, first + lane);
         if (u >= 0 && u < n_nodes) {
-            esf = nfirst[u];
-            esn = ncount[u];
+            esf = ld_global(nfirst, u);
+            esn = ld_global(ncount, u);
         }
     }
-    const int incl = p2p_incl_scan(esn, lane);
+    const int incl = p2p_incl_scan(esn);
+    const int32_t before = __shfl_up(esf + esn, 1, 64);
+    const bool begins = esn > 0 && (lane == 0 || esf != before);
+    const uint64_t runs = __ballot(begins);
+    const int e = __popcll(runs & ((1ull << lane) - 1ull));
     wave_sync();
-    win.efirst[lane] = esf - (incl - esn);
-    win.incl[lane] = incl;
+    if (begins) win.base[e] = esf - (incl - esn);
+    const int moved = __builtin_amdgcn_ds_permute((begins ? e : 63) * 4, incl - esn);
+    start = lane < __popcll(runs) ? moved : 0x7fffffff;
     wave_sync();
-    return __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
+    return __builtin_amdgcn_readlane(incl, 63);
 }
 
-// Point index of source j of the window (j < its source points): the first entry
-// whose inclusive count exceeds j, by six halvings.
-__device__ inline int32_t window_point(const ListWindow &win, int j) {
-    int e = 0;
-#pragma unroll
-    for (int st = 32; st > 0; st >>= 1) e = win.incl[e + st - 1] <= j ? e + st : e;
-    return win.efirst[e] + j;
+// Point index of source c * 64 + lane of the window (of no meaning past its points):
+// the runs that start inside block c of 64 are marked in a scalar mask (a few lane reads
+// in place of six dependent halvings per lane).  The whole wavefront calls it.
+__device__ inline int32_t window_point(const ListWindow &win, int start, int c, int lane) {
+    const int e0 = __popcll(__ballot(start < c * 64));
+    const int e1 = __popcll(__ballot(start < c * 64 + 64));
+    if (e0 == e1) return win.base[e0 - 1] + c * 64 + lane;
+    uint64_t mark = 0ull;
+    for (int e = e0; e < e1; ++e) mark |= 1ull << (__builtin_amdgcn_readlane(start, e) - c * 64);
+    // runs that start at or before this lane's source, less one (at least one does)
+    const uint64_t upto = mark & (lane < 63 ? (2ull << lane) - 1ull : ~0ull);
+    return win.base[e0 + (int)__popcll(upto) - 1] + c * 64 + lane;
 }
 
-// Wave `wave` of the NW that share target leaf v; red: one row of 64 per wave (NW > 1).
-template <int NW>
-__device__ inline void p2p_leaf(const LeafSet &L, int64_t v, int wave, P2PShared &sh, double (*red)[64]) {
-    if (v >= L.n_nodes || L.nnchild[v] != 0) return;
+// Entries per window of a list of len: sixteen windows for the sixteen wavefronts that
+// may share a leaf, of 8 to 64 entries.
+__device__ inline int p2p_window(int len) {
+    const int w = (len + 15) >> 4;
+    return w < 8 ? 8 : (w > 64 ? 64 : w);
+}
+
+// The wave's walk over its windows and their chunks: stage(nxt, nid, own) puts a chunk's
+// points (as they lie in memory) and their indices (-1: none) into sh, lane l holding
+// sources l and 64 + l; use(sources, own, flush) forms the sums over it, flush: the
+// fourth chunk since the last one or the window's last.  own: the chunk holds
+// points of the block tf .. tf + nt - 1 and self pairs are excluded.  The next chunk is
+// loaded while one is used: nothing waits for it before it is staged.
+template <int NW, class Stage, class Use>
+__device__ inline void p2p_sources(const LeafSet &L, const int32_t *lst, int len, int32_t tf, int nt, int wave,
+                                   P2PShared &sh, Stage stage, Use use) {
+    constexpr int PER = kP2PChunk / 64;
     const int lane = threadIdx.x & 63;
-    float ct[3], ht;
-    node_box(L.geo, L.nlevel[v], L.nix[v], L.niy[v], L.niz[v], ct, ht);
-    const int32_t tf = L.nfirst[v], tn = L.ncount[v];
-    const int32_t *lst = L.list.lst + L.list.begin(v);
-    int len = L.list.cnt[v];
-    if (len > L.n_nodes) len = (int)L.n_nodes;   // a list names each node at most once
-    sh.sp[64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-    sh.sid[64 + lane] = -1;
-    for (int t0 = 0; t0 < tn; t0 += 64) {
-        const int nt = tn - t0 < 64 ? tn - t0 : 64;
-        const int tp = __builtin_amdgcn_readfirstlane(nt);
-        const int G = 64 / tp;
-        // lane / tp as a multiply by ceil(2^16 / tp): exact for lane < 64, tp <= 64
-        const int grp = (lane * ((65536 + tp - 1) / tp)) >> 16;   // grp == G: an idle lane
-        const int a = lane - grp * tp;
-        const int32_t ti = tf + t0 + a;
-        const float4 qt = L.ps[ti];
-        const float tx = (qt.x - ct[0]) * L.k_scale;
-        const float ty = (qt.y - ct[1]) * L.k_scale;
-        const float tz = (qt.z - ct[2]) * L.k_scale;
-        double total = 0.0;
-        int turn = NW > 1 ? wave : 0;   // this wave's next chunk, counted from the window's first
-        for (int w0 = 0; w0 < len; w0 += 64) {
-            const int tot = load_window(lst, len, w0, L.n_nodes, L.nfirst, L.ncount, lane, sh.win);
-            const int nch = (tot + 63) >> 6;
-            float4 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
-            int32_t nid = -1;
-            // slots past the window's end hold a zero record (weight 0, no point)
-            auto fetch = [&](int c) {
-                const int j = c * 64 + lane;
-                nxt = make_float4(0.f, 0.f, 0.f, 0.f);
-                nid = -1;
-                if (j < tot) {
-                    nid = window_point(sh.win, j);
-                    const float4 q = L.ps[nid];
-                    nxt = make_float4((q.x - ct[0]) * L.k_scale, (q.y - ct[1]) * L.k_scale,
-                                      (q.z - ct[2]) * L.k_scale, q.w);
+    const int W = __builtin_amdgcn_readfirstlane(p2p_window(len));
+    for (int w0 = wave * W; w0 < len; w0 += NW * W) {
+        int start;
+        const int tot = load_window(lst, w0, len - w0 < W ? len - w0 : W, L.n_nodes, L.nfirst, L.ncount, lane, sh.win,
+                                    start);
+        float4 nxt[PER];
+        int32_t nid[PER];
+        auto fetch = [&](int c0) {
+#pragma unroll
+            for (int h = 0; h < PER; ++h) {
+                // lanes past the window's end take a target's, with index -1
+                nid[h] = -1;
+                int32_t i = tf;
+                if (c0 + 64 * h < tot) {
+                    const int32_t at = window_point(sh.win, start, (c0 >> 6) + h, lane);
+                    if (c0 + 64 * h + lane < tot) nid[h] = i = at;
                 }
-            };
-            if (turn < nch) fetch(turn);
-            for (; turn < nch; turn += NW) {
-                const int ns = tot - turn * 64 < 64 ? tot - turn * 64 : 64;
-                wave_sync();
-                sh.sp[lane] = nxt;
-                sh.sid[lane] = nid;
-                wave_sync();
-                // the wave's next chunk is loaded while this one is used
-                if (turn + NW < nch) fetch(turn + NW);
-                // a group takes sources grp, grp + G, ... of the chunk.  The trip count is the
-                // same for every lane (a scalar loop that unrolls); the slots read stay below
-                // ns + G <= 128, and a slot past the chunk's end adds exactly 0
-                float part = 0.f;
-                const int nit = __builtin_amdgcn_readfirstlane((ns + G - 1) / G);
-                const float4 *sp = sh.sp + grp;
-                const int32_t *sid = sh.sid + grp;
-                const int Gs = __builtin_amdgcn_readfirstlane(G);
-                if (L.exclude_self) {
-#pragma unroll 4
-                    for (int it = 0; it < nit; ++it) {
-                        const float4 q = sp[it * Gs];
-                        const float dx = tx - q.x, dy = ty - q.y, dz = tz - q.z;
-                        const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                        const float e = q.w * __builtin_amdgcn_exp2f(-d2);
-                        part += sid[it * Gs] == ti ? 0.f : e;
-                    }
-                } else {
-#pragma unroll 4
-                    for (int it = 0; it < nit; ++it) {
-                        const float4 q = sp[it * Gs];
-                        const float dx = tx - q.x, dy = ty - q.y, dz = tz - q.z;
-                        const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                        part = fmaf(q.w, __builtin_amdgcn_exp2f(-d2), part);
-                    }
-                }
-                total += (double)part;
+                nxt[h] = ld_global4(L.ps, i);
             }
-            turn -= nch;
+        };
+        if (tot > 0) fetch(0);
+        for (int c0 = 0; c0 < tot; c0 += kP2PChunk) {
+            bool own = false;
+            if (L.exclude_self) {
+#pragma unroll
+                for (int h = 0; h < PER; ++h) own |= __ballot((unsigned)(nid[h] - tf) < (unsigned)nt) != 0;
+            }
+            wave_sync();
+            stage(nxt, nid);
+            if (own) {
+#pragma unroll
+                for (int h = 0; h < PER; ++h)
+                    sh.sid[64 * h + lane] =
+                        (unsigned)(nid[h] - tf) < (unsigned)nt ? (uint8_t)(nid[h] - tf) : kNoTarget;
+            }
+            wave_sync();
+            if (c0 + kP2PChunk < tot) fetch(c0 + kP2PChunk);
+            use(tot - c0, own, c0 + kP2PChunk >= tot || (c0 / kP2PChunk & 3) == 3);
         }
-        // the groups of a wave in order, then the waves in order
+    }
+}
+
+// Targets tf .. tf + nt - 1 (T per lane): this wave's windows of the list, into its share
+// of the sums (lane l: target l, for l < nt).
+template <int NW, int T>
+__device__ inline double p2p_block_vector(const LeafSet &L, const int32_t *lst, int len, const float ct[3], int32_t tf,
+                                          int nt, int wave, P2PShared &sh) {
+    const int lane = threadIdx.x & 63;
+    const int tp = __builtin_amdgcn_readfirstlane((nt + T - 1) / T);
+    const int G = __builtin_amdgcn_readfirstlane(64 / tp), nfull = __builtin_amdgcn_readfirstlane((kP2PChunk + G - 1) / G);
+    // lane / tp as a multiply by ceil(2^16 / tp): exact for lane < 64, tp <= 64
+    const int grp = (lane * ((65536 + tp - 1) / tp)) >> 16;   // grp == G: an idle lane
+    const int a = lane - grp * tp;
+    float tx[T], ty[T], tz[T];
+    double total[T];
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+        const float4 qt = ld_global4(L.ps, tf + (a + k * tp < nt ? a + k * tp : nt - 1));
+        tx[k] = (qt.x - ct[0]) * L.k_scale;
+        ty[k] = (qt.y - ct[1]) * L.k_scale;
+        tz[k] = (qt.z - ct[2]) * L.k_scale;
+        total[k] = 0.0;
+    }
+    auto stage = [&](const float4 *nxt, const int32_t *nid) {
+#pragma unroll
+        for (int h = 0; h < kP2PChunk / 64; ++h)
+            sh.sp[64 * h + lane] =
+                make_float4((nxt[h].x - ct[0]) * L.k_scale, (nxt[h].y - ct[1]) * L.k_scale,
+                            (nxt[h].z - ct[2]) * L.k_scale, nid[h] < 0 ? 0.f : nxt[h].w);
+    };
+    // a group takes sources grp, grp + G, ... of the chunk.  The trip count is the same for
+    // every lane (a scalar loop); the slots read stay below the chunk's sources + G, and a
+    // slot past them adds exactly 0
+    auto use = [&](int left, bool own, bool) {
+        float part[T];
+#pragma unroll
+        for (int k = 0; k < T; ++k) part[k] = 0.f;
+        const int nit = left >= kP2PChunk ? nfull : __builtin_amdgcn_readfirstlane((left + G - 1) / G);
+        const float4 *sp = sh.sp + grp;
+        if (own) {
+            const uint8_t *sid = sh.sid + grp;
+            for (int it = 0; it < nit; ++it) {
+                const float4 q = sp[it * G];
+                const int id = sid[it * G];
+#pragma unroll
+                for (int k = 0; k < T; ++k) {
+                    const float dx = tx[k] - q.x, dy = ty[k] - q.y, dz = tz[k] - q.z;
+                    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                    part[k] = fmaf(id == a + k * tp ? 0.f : q.w, __builtin_amdgcn_exp2f(-d2), part[k]);
+                }
+            }
+        } else {
+#pragma unroll 4 / T
+            for (int it = 0; it < nit; ++it) {
+                const float4 q = sp[it * G];
+#pragma unroll
+                for (int k = 0; k < T; ++k) {
+                    const float dx = tx[k] - q.x, dy = ty[k] - q.y, dz = tz[k] - q.z;
+                    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                    part[k] = fmaf(q.w, __builtin_amdgcn_exp2f(-d2), part[k]);
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < T; ++k) total[k] += (double)part[k];
+    };
+    p2p_sources<NW>(L, lst, len, tf, nt, wave, sh, stage, use);
+    // the groups of the wave in order; lane l gathers target l = (l / tp) tp + l % tp
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
         wave_sync();
-        sh.red[lane] = total;
+        sh.red[lane] = total[k];
         wave_sync();
-        double s = 0.0;
-        if (a < nt && grp == 0)
+        if (grp == k)   // T <= G: the group exists
             for (int q = 0; q < G; ++q) s += sh.red[q * tp + a];
+    }
+    return s;
+}
+
+// Largest scaled distance of a target from its leaf's centre for the matrix form.  Its
+// error grows with the size of 2 t.s against d^2.  Measured against float64 over leaves
+// of 10 and 40 points, root mean square (largest) relative error of a sum, vector form ->
+// matrix form: reach 1: 3.6e-8 (8.5e-8) -> 3.5e-8 (7.2e-8); 1.5: 4.2e-8 (1.1e-7) ->
+// 4.2e-8 (1.2e-7); 2: 4.8e-8 (1.2e-7) -> 4.7e-8 (1.9e-7); 3: 6.5e-8 (2.7e-7) -> 8.8e-8
+// (3.4e-7).
+constexpr float kMatrixReach = 1.5f;
+
+// 2^x for a small x (|x| below 127; to 1e-11): the nearest whole power, and the Taylor
+// series of the rest's exponential.
+__device__ inline double exp2_near(double x) {
+    const double n = rint(x), y = 0.69314718055994531 * (x - n);
+    double e = 1.0;
+#pragma unroll
+    for (int k = 10; k > 0; --k) e = fma(e, y * (1.0 / k), 1.0);
+    return ldexp(e, (int)n);
+}
+
+template <int CTRL>
+__device__ inline float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
+// The same by matrix products, M = ceil(nt / 16) tiles of 16 targets; the sums lack the
+// factors exp2(-t^2).  Lane l holds of a tile (v_mfma_f32_16x16x4f32): operand A target
+// l % 16, operand B source l % 16, both their component l / 16; result source l % 16 and
+// targets 4 (l / 16) .. + 3.  The fourth component takes what of a far source's s^2 would
+// underflow: its weight carries exp2(-min(s^2, 100)), the product -(s^2 - 100).
+template <int NW, int M>
+__device__ inline double p2p_block_matrix(const LeafSet &L, const int32_t *lst, int len, const float ct[3], int32_t tf,
+                                          int nt, int wave, P2PShared &sh) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, col = lane & 15, comp = lane >> 4;
+    float A[M], part[M][4];
+    double total[M];   // lane l: target 4 (l / 16) + l % 4 of each tile
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const float4 q = ld_global4(L.ps, tf + (16 * m + col < nt ? 16 * m + col : nt - 1));
+        const float c = comp == 0 ? q.x - ct[0] : comp == 1 ? q.y - ct[1] : q.z - ct[2];
+        A[m] = comp == 3 ? -1.f : 2.f * (c * L.k_scale);
+        total[m] = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[m][r] = 0.f;
+    }
+    auto stage = [&](const float4 *nxt, const int32_t *nid) {
+#pragma unroll
+        for (int h = 0; h < kP2PChunk / 64; ++h) {
+            const float x = (nxt[h].x - ct[0]) * L.k_scale, y = (nxt[h].y - ct[1]) * L.k_scale,
+                        z = (nxt[h].z - ct[2]) * L.k_scale;
+            const float s2 = fmaf(x, x, fmaf(y, y, z * z)), near = fminf(s2, 100.f);
+            sh.sp[64 * h + lane] = make_float4(x, y, z, s2 - near);
+            sh.sw[64 * h + lane] = nid[h] < 0 ? 0.f : nxt[h].w * __builtin_amdgcn_exp2f(-near);
+        }
+    };
+    auto use = [&](int left, bool own, bool flush) {
+        const float *B = reinterpret_cast<const float *>(sh.sp) + 4 * col + comp;
+        const int n16 = __builtin_amdgcn_readfirstlane(left >= kP2PChunk ? kP2PChunk / 16 : (left + 15) >> 4);
+        if (own) {
+            for (int g = 0; g < n16; ++g) {
+                const float b = B[64 * g], w = sh.sw[16 * g + col];
+                const int id = (int)sh.sid[16 * g + col] - 4 * comp;
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(A[m], b, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        part[m][r] = fmaf(id == 16 * m + r ? 0.f : w, __builtin_amdgcn_exp2f(d[r]), part[m][r]);
+                }
+            }
+        } else {
+#pragma unroll(M < 3 ? 2 : 1)
+            for (int g = 0; g < n16; ++g) {
+                const float b = B[64 * g], w = sh.sw[16 * g + col];
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(A[m], b, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) part[m][r] = fmaf(w, __builtin_amdgcn_exp2f(d[r]), part[m][r]);
+                }
+            }
+        }
+        if (!flush) return;
+        // at most 32 terms a value; the 16 source columns, halving the columns and the
+        // values together, then the other columns
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const bool hi2 = (lane & 2) != 0, hi1 = (lane & 1) != 0;
+            const float a = (hi2 ? part[m][2] : part[m][0]) + dpp<0x4e>(hi2 ? part[m][0] : part[m][2]);   // lane ^ 2
+            const float b = (hi2 ? part[m][3] : part[m][1]) + dpp<0x4e>(hi2 ? part[m][1] : part[m][3]);
+            float v = (hi1 ? b : a) + dpp<0xb1>(hi1 ? a : b);   // lane ^ 1
+            v += dpp<0x124>(v);                                 // row_ror 4, 8
+            v += dpp<0x128>(v);
+            total[m] += (double)v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[m][r] = 0.f;
+        }
+    };
+    p2p_sources<NW>(L, lst, len, tf, nt, wave, sh, stage, use);
+    // target 16 m + 4 c + q from lane 16 c + q to lane 16 m + 4 c + q
+    double s = 0.0;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const double to = __shfl(total[m], ((lane & 12) << 2) | (lane & 3), 64);
+        if (comp == m) s = to;
+    }
+    return s;
+}
+
+// Wave `wave` of the NW that share the target leaf of task t (the same for all of them);
+// red: one row of 64 per wave (NW > 1).
+template <int NW>
+__device__ inline void p2p_leaf(const LeafSet &L, const LeafTask &t, int wave, P2PShared &sh, double (*red)[64]) {
+    const int lane = threadIdx.x & 63, len = t.len;
+    const int32_t tf = t.first, tn = t.count, *lst = t.lst;
+    const float *ct = t.ct;
+    const bool matrix = __builtin_amdgcn_readfirstlane((int)(1.7320508f * t.half * L.k_scale <= kMatrixReach));
+    sh.sp[kP2PChunk + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+    sh.sid[kP2PChunk + lane] = kNoTarget;
+    for (int t0 = 0; t0 < tn; t0 += 64) {
+        const int nt = __builtin_amdgcn_readfirstlane(tn - t0 < 64 ? tn - t0 : 64);
+        double s;
+#define MSP_P2P(F, K) F<NW, K>(L, lst, len, ct, tf + t0, nt, wave, sh)
+        if (matrix) {
+            if (nt <= 16) s = MSP_P2P(p2p_block_matrix, 1);
+            else if (nt <= 32) s = MSP_P2P(p2p_block_matrix, 2);
+            else if (nt <= 48) s = MSP_P2P(p2p_block_matrix, 3);
+            else s = MSP_P2P(p2p_block_matrix, 4);
+        } else {
+            if (nt <= 9) s = MSP_P2P(p2p_block_vector, 1);
+            else if (nt <= 18) s = MSP_P2P(p2p_block_vector, 2);
+            else s = MSP_P2P(p2p_block_vector, 4);
+        }
+#undef MSP_P2P
         if constexpr (NW > 1) {
+            // the waves in order
             red[wave][lane] = s;
             __syncthreads();
             if (wave == 0 && lane < nt) {
@@ -204,7 +466,15 @@ __device__ inline void p2p_leaf(const LeafSet &L, int64_t v, int wave, P2PShared
                 for (int q = 0; q < NW; ++q) s += red[q][lane];
             }
         }
-        if (wave == 0 && grp == 0 && a < nt) L.usort[ti] = L.tflag[ti] ? (float)s : 0.f;
+        if (wave == 0 && lane < nt) {
+            const int32_t ti = tf + t0 + lane;
+            if (matrix) {
+                const float4 q = ld_global4(L.ps, ti);
+                const double x = (q.x - ct[0]) * L.k_scale, y = (q.y - ct[1]) * L.k_scale, z = (q.z - ct[2]) * L.k_scale;
+                s *= exp2_near(-(x * x + y * y + z * z));
+            }
+            L.usort[ti] = ld_global(L.tflag, ti) ? (float)s : 0.f;
+        }
         if constexpr (NW > 1) __syncthreads();   // red is free again
     }
 }

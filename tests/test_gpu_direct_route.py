@@ -65,6 +65,35 @@ def test_leaf_sums_and_gradients(n, leaf_max, exclude):
     tree.close()
 
 
+@pytest.mark.parametrize("m", [1, 2, 9, 10, 16, 17, 18, 19, 32, 33, 48, 49, 63, 64, 130])
+@pytest.mark.parametrize("sigma", [24.0, 60.0, 500.0])
+@pytest.mark.parametrize("exclude", [False, True])
+def test_leaf_forms(m, sigma, exclude):
+    """Leaves of m targets (every count of tiles and of targets per lane) of half side 25,
+    scaled reach 2.2, 0.87 and 0.1: differences, and matrix products near and far from the
+    bound; a list of some hundred leaves, consecutive or not; a far cluster whose terms
+    all underflow.  A sum's relative error: three roundings of 2 t.s, at most 2 x 1.5 x 7
+    scaled units squared in the terms of 2^-30 and 2 x 1.5 x 2.5 in those that carry a
+    sum, 9e-7, with the factors' and the float32 additions' 5e-7: 2e-6."""
+    import paper_2301_10570_amd as msp
+    rng = np.random.default_rng(m)
+    cells = np.array([(i, j, k) for i in range(8) for j in range(8) for k in range(8)])
+    keep = cells[np.sort(rng.permutation(512)[: 512 if m < 20 else 100])]
+    pts = (keep[:, None, :] * 50.0 + 1.0 + rng.random((len(keep), m, 3)) * 48.0).reshape(-1, 3)
+    pts = np.concatenate([pts, [[0.0, 0.0, 0.0], [399.99, 399.99, 399.99]]]).astype(np.float32)
+    n = len(pts)
+    w = rng.integers(0, 4, n).astype(np.float32)
+    w[0] = 3.0
+    tree = msp.build_tree(*(_T(pts[:, k]) for k in range(3)), leaf_max=max(m, 2), max_depth=3)
+    print(f"leaf forms m={m} sigma={sigma} exclude={exclude} nodes={tree.info()['n_nodes']}", flush=True)
+    u = tree.forward(_T(w), None, sigma=sigma, route="direct", cutoff_sigmas=6.5, exclude_self=exclude).cpu().numpy()
+    pick = rng.permutation(n)[:300]
+    ref = oracle.gauss_sum(pts[pick], pts, w, sigma) - (w[pick].astype(np.float64) if exclude else 0.0)
+    far = w.astype(np.float64).sum() * np.exp(-6.5 ** 2)   # what the cutoff may drop
+    assert np.all(np.abs(u[pick] - ref) <= 2e-6 * np.abs(ref) + far)
+    tree.close()
+
+
 @pytest.mark.parametrize("nt,ns", [(1, 1), (3, 127), (50, 4097), (4095, 129), (4096, 2048), (16383, 130), (16385, 2049),
                                    (65535, 300), (65537, 127), (7, 0)])
 def test_all_pairs(nt, ns):
