@@ -462,7 +462,7 @@ int msp_batch_forward(msp_batch *b, const float *w, const uint8_t *is_target, co
  * the two fields (weights w, and the upstream gradient at the targets) of the
  * expansion-route populations as batched P2M / M2L / L2P-with-derivatives passes
  * on an internal stream that forks from `stream` and joins it again, beside one
- * persistent P2P-with-derivatives launch per field for the direct-route
+ * P2P-with-derivatives launch for both fields of the direct-route
  * populations, then one combination launch and one sigma-reduction launch.  The
  * direct route gives the bits of msp_fgt_backward; the expansion route agrees with
  * it to float32 rounding (moments and translations summed in another order).  The

@@ -32,35 +32,25 @@ __global__ void k_stage_both(const float *w, const float *gt, const int32_t *per
     g2[i] = gt[j];
 }
 
-// P2P with derivatives.  SPLIT: a block of three wavefronts per target leaf, one for
-// the value and the Laplacian, one for the gradient, one for the second field (absent
-// without TWO).  The sums of a leaf are serial chains over its list, so in a tree with
-// fewer leaves than the chip has wavefront slots the shares run beside each other at no
-// cost: 5,003 points, both fields, 2 x 225 us -> 162 us.  Otherwise one wavefront does
-// all of them with one exponential per pair.
-template <bool TWO, bool SPLIT>
-__global__ void __launch_bounds__(SPLIT ? (TWO ? 192 : 128) : 64) k_p2p_grad(GradLeafSet L, const float *g2, int stride,
-                                                                            int want_lap) {
-    if constexpr (SPLIT) {
-        __shared__ GradShared sh[TWO ? 3 : 2];
-        const int wave = threadIdx.x >> 6;
-        if (wave == 0) p2p_grad_leaf<kGradValue>(L, g2, blockIdx.x, stride, want_lap, sh[0]);
-        else if (wave == 1) p2p_grad_leaf<kGradVector>(L, g2, blockIdx.x, stride, want_lap, sh[1]);
-        else if constexpr (TWO) p2p_grad_leaf<kGradSecond>(L, g2, blockIdx.x, stride, want_lap, sh[2]);
-    } else {
-        __shared__ GradShared sh;
-        p2p_grad_leaf<kGradValue | kGradVector | (TWO ? kGradSecond : 0)>(L, g2, blockIdx.x, stride, want_lap, sh);
-    }
+// P2P with derivatives, NW wavefronts per target leaf.
+template <int NW, bool TWO>
+__global__ void __launch_bounds__(NW * 64, NW > 1 ? 4 : 6) k_p2p_grad(GradLeafSet L, const float *g2, int stride, int want_lap) {
+    __shared__ GradShared sh[NW];
+    __shared__ GradBlock bk;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const LeafTask t = uniform_copy(leaf_task(L, (int64_t)blockIdx.x, 0));
+    if (t.count > 0) p2p_grad_leaf<NW, TWO>(L, g2, t, stride, want_lap, wave, sh[wave], bk);
 }
 
+// Eight wavefronts per leaf while the tree has fewer leaves than the chip has wavefront
+// slots, one beyond.
 template <bool TWO>
 void launch_p2p_grad(const GradLeafSet &L, const float *g2, int stride, int want_lap, hipStream_t s) {
     const dim3 grid((unsigned)L.n_nodes);
     if (p2p_waves(L.n_nodes) > 1)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2p_grad<TWO, true>), grid, dim3(TWO ? 192 : 128), 0, s, L, g2, stride,
-                           want_lap);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2p_grad<8, TWO>), grid, dim3(512), 0, s, L, g2, stride, want_lap);
     else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2p_grad<TWO, false>), grid, dim3(64), 0, s, L, g2, stride, want_lap);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_p2p_grad<1, TWO>), grid, dim3(64), 0, s, L, g2, stride, want_lap);
 }
 
 // Per point of the input order j: the key-order record of its point (64 bytes,

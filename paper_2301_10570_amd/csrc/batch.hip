@@ -15,8 +15,8 @@
 //     of them.
 // The backward has the same shape: the two fields it needs (weights w, and the
 // upstream gradient at the targets) by the batched expansion passes with an L2P
-// that also gives gradient and Laplacian, or by one persistent P2P-with-derivatives
-// launch per field, then one launch that combines every point's records into its
+// that also gives gradient and Laplacian, or by one P2P-with-derivatives launch for
+// both, then one launch that combines every point's records into its
 // gradients and one that reduces the sigma derivative of each population.
 // After a first eager call the sequence is captured into a hipGraph on a
 // private stream and later calls with the same arguments replay the graph on
@@ -48,7 +48,14 @@ struct PopDesc {
     int32_t pop;
 };
 
-__device__ inline const LeafSet &leaf_set(const PopDesc &d) { return d.ls; }
+
+// The same for the backward.
+struct GradDesc {
+    GradLeafSet L;          // tree arrays, staged weights w (L.ps.w), records L.out
+    float *g2;              // staged target weights g in key order
+    const int32_t *perm;    // key order -> index inside the population
+    int64_t base, n;
+};
 
 __device__ inline int find_segment(const int64_t *off, int nseg, int64_t x) {
     int lo = 0, hi = nseg;   // off[lo] <= x < off[hi]
@@ -80,6 +87,9 @@ __global__ void k_batch_stage(const PopDesc *desc, const int64_t *pt_off, int nd
     ps[i].w = w[j];
     const_cast<uint8_t *>(D.ls.tflag)[i] = is_target ? (is_target[j] != 0) : (uint8_t)1;
 }
+
+__device__ inline const LeafSet &leaf_set(const PopDesc &d) { return d.ls; }
+__device__ inline const GradLeafSet &leaf_set(const GradDesc &d) { return d.L; }
 
 // The direct-route populations' nodes as tasks, item by item: found once per plan, so
 // that a leaf's block does not start with a chain of a dozen dependent loads.
@@ -152,13 +162,7 @@ __global__ void k_batch_scatter(const PopDesc *desc, const int64_t *pt_off, int 
 }
 
 // ---------------------------------------------------------------------------------
-// Batched backward.  One direct-route population as its kernels read it.
-struct GradDesc {
-    GradLeafSet L;          // tree arrays, staged weights w (L.ps.w), records L.out
-    float *g2;              // staged target weights g in key order
-    const int32_t *perm;    // key order -> index inside the population
-    int64_t base, n;
-};
+// Batched backward.
 
 // One population as the combination reads it.
 struct CombDesc {
@@ -182,24 +186,19 @@ __global__ void k_bw_stage(const GradDesc *desc, const int64_t *pt_off, int nd, 
     D.g2[i] = gt[j];
 }
 
-__global__ void k_bw_reset(unsigned long long *counter) { *counter = 0ull; }
-
-// Persistent P2P with derivatives of both fields over the nodes of every
-// direct-route population (four independent wavefronts per block, one item per
-// counter addition).
-__global__ void __launch_bounds__(256, 7) k_batch_p2p_grad(const GradDesc *desc, const int64_t *item_off, int nd,
-                                                        unsigned long long *counter, int want_lap) {
+// P2P with derivatives of both fields over the nodes of every direct-route population:
+// a block of four wavefronts per node, as in the forward's launch.
+__global__ void __launch_bounds__(256, 4) k_batch_p2p_grad(const GradDesc *desc, const LeafTask *tasks, int64_t n,
+                                                           int want_lap) {
     __shared__ GradShared sh[4];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t total = item_off[nd];
-    for (int64_t it = 0; it <= total; ++it) {
-        unsigned long long mine = 0ull;
-        if (lane == 0) mine = atomicAdd(counter, 1ull);
-        const int64_t item = (int64_t)__shfl(mine, 0, 64);
-        if (item >= total) break;
-        const int d = find_segment(item_off, nd, item);
-        p2p_grad_leaf<kGradValue | kGradVector | kGradSecond>(desc[d].L, desc[d].g2, item - item_off[d], kRec,
-                                                             want_lap, sh[wave]);
+    __shared__ GradBlock bk;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int64_t item = blockIdx.x; item < n; item += gridDim.x) {
+        const LeafTask t = uniform_copy(tasks[item]);
+        if (t.count == 0) continue;
+        const GradLeafSet L = uniform_copy(desc[t.owner].L);
+        const float *g2 = uniform_copy(desc[t.owner].g2);
+        p2p_grad_leaf<4, true>(L, g2, t, kRec, want_lap, wave, sh[wave], bk);
     }
 }
 
@@ -618,7 +617,7 @@ int prepare_backward(msp_batch *b, const std::vector<PopPlan> &plans, const floa
     // direct route
     std::vector<GradDesc> gd;
     std::vector<int64_t> poff{0}, ioff{0};
-    for (int k = 0; k < b->npop; ++k) {
+    for (int k : largest_first(b)) {
         msp_tree *t = b->pops[k].get();
         const PopPlan &pp = plans[k];
         if (pp.pl.route == MSP_ROUTE_FGT || t->n == 0) continue;
@@ -646,7 +645,6 @@ int prepare_backward(msp_batch *b, const std::vector<PopPlan> &plans, const floa
     MSP_TRY(b->bw_desc.ensure((gd.size() + 1) * sizeof(GradDesc)));
     MSP_TRY(b->bw_pt_off.ensure(poff.size() * 8));
     MSP_TRY(b->bw_item_off.ensure(ioff.size() * 8));
-    MSP_TRY(b->bw_counter.ensure(8));
     MSP_TRY(b->bw_comb.ensure((cd.size() + 1) * sizeof(CombDesc)));
     MSP_TRY(b->bw_boff.ensure(boff.size() * 8));
     MSP_TRY(b->bw_partial.ensure((size_t)(b->bw_nblk > 0 ? b->bw_nblk : 1) * 8));
@@ -654,6 +652,13 @@ int prepare_backward(msp_batch *b, const std::vector<PopPlan> &plans, const floa
     if (!gd.empty()) MSP_HIP(hipMemcpy(b->bw_desc.p, gd.data(), gd.size() * sizeof(GradDesc), hipMemcpyHostToDevice));
     MSP_HIP(hipMemcpy(b->bw_pt_off.p, poff.data(), poff.size() * 8, hipMemcpyHostToDevice));
     MSP_HIP(hipMemcpy(b->bw_item_off.p, ioff.data(), ioff.size() * 8, hipMemcpyHostToDevice));
+    if (b->bw_items > 0) {
+        MSP_TRY(b->bw_tasks.ensure((size_t)b->bw_items * sizeof(LeafTask)));
+        hipLaunchKernelGGL(k_batch_tasks<GradDesc>, dim3(grid_for(b->bw_items, kBlock)), dim3(kBlock), 0, s,
+                           b->bw_desc.as<GradDesc>(), b->bw_item_off.as<int64_t>(), (int)gd.size(),
+                           b->bw_tasks.as<LeafTask>());
+        MSP_CHECK_LAUNCH();
+    }
     if (!cd.empty()) MSP_HIP(hipMemcpy(b->bw_comb.p, cd.data(), cd.size() * sizeof(CombDesc), hipMemcpyHostToDevice));
     MSP_HIP(hipMemcpy(b->bw_boff.p, boff.data(), boff.size() * 8, hipMemcpyHostToDevice));
     if (!b->bfork) {
@@ -687,19 +692,13 @@ int enqueue_backward(msp_batch *b, const float *w, const uint8_t *is_target, con
     const int nd = b->bw_nd;
     if (nd > 0) {
         const GradDesc *desc = b->bw_desc.as<GradDesc>();
-        auto *counter = b->bw_counter.as<unsigned long long>();
-        const int64_t waves = (int64_t)b->cus * 32;
-        const int64_t want = b->bw_items < waves ? b->bw_items : waves;
-        const unsigned grid = (unsigned)((want + 3) / 4);
         // both fields in one pass: one exponential per pair serves both
         hipLaunchKernelGGL(k_bw_stage, dim3(grid_for(b->bw_points, kBlock)), dim3(kBlock), 0, s, desc,
                            b->bw_pt_off.as<int64_t>(), nd, w, gt);
         MSP_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_bw_reset, dim3(1), dim3(1), 0, s, counter);
-        MSP_CHECK_LAUNCH();
-        if (grid > 0) {
-            hipLaunchKernelGGL(k_batch_p2p_grad, dim3(grid), dim3(256), 0, s, desc, b->bw_item_off.as<int64_t>(),
-                               nd, counter, grad_sigma ? 1 : 0);
+        if (b->bw_items > 0) {
+            hipLaunchKernelGGL(k_batch_p2p_grad, dim3(item_grid(b->bw_items)), dim3(256), 0, s, desc,
+                               b->bw_tasks.as<LeafTask>(), b->bw_items, grad_sigma ? 1 : 0);
             MSP_CHECK_LAUNCH();
         }
     }

@@ -27,161 +27,225 @@ struct GradLeafSet {
     float *out;
 };
 
+// One wavefront's staging: sources (offsets from the leaf centre, weight) and their
+// second weights; the slots from 64 on hold zeros for the idle lanes' reads.
 struct GradShared {
-    // staged sources (offsets from the leaf centre, weight) and their second weights
-    // (two fields at once); slots 64..127 hold zeros for the idle lanes' reads
-    float4 src[128];
-    float sg[128];
-    float red[9][64];
+    float4 src[256];
+    float sg[256];
     ListWindow win;
 };
 
-// Which of a leaf's sums a wavefront forms: all of them, or a share when several
-// wavefronts work on one leaf.  Every sum runs over the list in the same order in
-// float32 whichever wavefront forms it, so its bits do not depend on the split.
-constexpr int kGradValue = 1;    // field A: value and r^2 moment (Laplacian)
-constexpr int kGradVector = 2;   // field A: gradient
-constexpr int kGradSecond = 4;   // field B: value and gradient
+// What the wavefronts of a leaf share: the ordered running sums and whose turn it is to
+// add to them, and the other sums.
+struct GradBlock {
+    float run[3][64];
+    double sum[6][64];
+    int turn;
+};
 
-// For every point of target leaf v (one wavefront; sh private to it): the sums
-// over the source leaves of its list of e = w exp(-r^2/sigma^2), e (x - s) and
-// e r^2, written as value, gradient and Laplacian of the field.  A block of nt <= 64
+// A scalar whose uses stay where they are: the slots' addresses, kept in registers across
+// the units, would spill.
+__device__ inline int not_hoisted(int x) {
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
+// For every point of the target leaf of task t: the sums over the source leaves of its
+// list of e = w exp(-r^2/sigma^2), e (x - s) and e r^2, written as value, gradient and
+// Laplacian of the field; TWO: also of a second field with the key-order weights g2 of the
+// sources (value and gradient, into out + 5), one exponential serving both.
+//
+// NW wavefronts share the leaf (sh is private to each, bk common).  A block of nt <= 64
 // targets splits the lanes into G = floor(64 / nt) groups of nt (the lanes past G nt
-// idle), each group taking every G-th source of a staged chunk; the source points of up
-// to 64 list entries at a time form one sequence staged 64 per chunk, the next chunk
-// loaded while the current one is used; group partials are added in group order.
-// kGradSecond: a second field with the key-order weights g2 of the sources (value
-// and gradient, into out + 5); with PART = all of them one exponential serves both.
-template <int PART>
-__device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, int64_t v, int stride, int want_lap,
-                                     GradShared &sh) {
-    constexpr bool VAL = (PART & kGradValue) != 0, VEC = (PART & kGradVector) != 0, SEC = (PART & kGradSecond) != 0;
-    if (v >= L.n_nodes || L.nnchild[v] != 0) return;
-    const int lane = threadIdx.x & 63;
-    float ct[3], half;
-    node_box(L.geo, L.nlevel[v], L.nix[v], L.niy[v], L.niz[v], ct, half);
-    const int32_t tf = L.nfirst[v], tn = L.ncount[v];
-    const int32_t *lst = L.list.lst + L.list.begin(v);
-    int len = L.list.cnt[v];
-    if (len > L.n_nodes) len = (int)L.n_nodes;   // a list names each node at most once
-    sh.src[64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-    sh.sg[64 + lane] = 0.f;
-    for (int t0 = 0; t0 < tn; t0 += 64) {
-        const int nt = tn - t0 < 64 ? tn - t0 : 64;
-        const int tp = __builtin_amdgcn_readfirstlane(nt);
-        const int G = 64 / tp;
-        // lane / tp as a multiply by ceil(2^16 / tp): exact for lane < 64, tp <= 64
-        const int grp = (lane * ((65536 + tp - 1) / tp)) >> 16;   // grp == G: an idle lane
-        const int a = lane - grp * tp;
-        const int32_t ti = tf + t0 + a;
-        const float4 qt = L.ps[ti];
-        const float tx = qt.x - ct[0], ty = qt.y - ct[1], tz = qt.z - ct[2];
-        float su = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, sr = 0.f;
-        float gu = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
+// idle), each group taking every G-th source of a 64-source chunk of a window of 64 list
+// entries.  The values and the Laplacian are float32 running sums over the whole list in
+// its order, which is a serial chain however many wavefronts share the leaf.  So each
+// wavefront evaluates units of at most 16 sources a group (the chunk, or a part of it
+// where G < 4), keeps the weights, exp and r^2 of every pair in registers, and adds them
+// when its turn comes: four instructions a pair in the chain in place of some 25, and no
+// load.  The
+// gradients are float32 per unit and float64 over the units.  5,003 points, both fields:
+// 162 us with a wavefront per kind of sum, 72 us with eight per leaf; 48 populations of
+// 1,024 to 32,768 points: 1.61 ms with a wavefront per leaf, whose largest leaves were the
+// launch's tail, 1.0 ms with four.
+template <int NW, bool TWO>
+__device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, const LeafTask &t, int stride, int want_lap,
+                                     int wave, GradShared &sh, GradBlock &bk) {
+    const int lane = threadIdx.x & 63, len = t.len;
+#pragma unroll
+    for (int c = 64; c < 256; c += 64) {
+        sh.src[c + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+        sh.sg[c + lane] = 0.f;
+    }
+    for (int t0 = 0; t0 < t.count; t0 += 64) {
+        const int nt = __builtin_amdgcn_readfirstlane(t.count - t0 < 64 ? t.count - t0 : 64);
+        const int G = __builtin_amdgcn_readfirstlane(64 / nt);
+        // lane / nt as a multiply by ceil(2^16 / nt): exact for lane < 64, nt <= 64
+        const int grp = (lane * ((65536 + nt - 1) / nt)) >> 16;   // grp == G: an idle lane
+        const int a = lane - grp * nt;
+        const int32_t ti = t.first + t0 + a;
+        const float4 qt = ld_global4(L.ps, a < nt ? ti : t.first);
+        const float tx = qt.x - t.ct[0], ty = qt.y - t.ct[1], tz = qt.z - t.ct[2];
+        const int unit = G < 4 ? 16 * G : 64;
+        float su = 0.f, sr = 0.f, gu = 0.f;
+        double total[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        if constexpr (NW > 1) {
+            if (wave == 0) {
+                bk.run[0][lane] = bk.run[1][lane] = bk.run[2][lane] = 0.f;
+                if (lane == 0) bk.turn = 0;
+            }
+            __syncthreads();
+        }
+        int mine = NW > 1 ? wave : 0;   // this wave's next unit, counted from the window's first
+        int before = 0;                 // units of the windows before
         for (int w0 = 0; w0 < len; w0 += 64) {
             int start;
-            const int tot = load_window(lst, w0, len - w0 < 64 ? len - w0 : 64, L.n_nodes, L.nfirst, L.ncount, lane,
+            const int tot = load_window(t.lst, w0, len - w0 < 64 ? len - w0 : 64, L.n_nodes, L.nfirst, L.ncount, lane,
                                         sh.win, start);
+            const int units = __builtin_amdgcn_readfirstlane(G == 3 ? 2 * (tot >> 6) + ((tot & 63) + 47) / 48
+                                                                    : (tot + unit - 1) / unit);
+            // the next unit's points as they lie in memory (nothing waits for them before they
+            // are staged); lanes past the unit or the window take a target's, with weights 0
             float4 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
             float ngw = 0.f;
-            // slots past the window's end hold a zero record (weights 0)
-            auto fetch = [&](int c0) {
-                const int32_t pj = window_point(sh.win, start, c0 >> 6, lane);
-                nxt = make_float4(0.f, 0.f, 0.f, 0.f);
-                ngw = 0.f;
-                if (c0 + lane < tot) {
-                    const float4 q = L.ps[pj];
-                    nxt = make_float4(q.x - ct[0], q.y - ct[1], q.z - ct[2], q.w);
-                    if (SEC) ngw = g2[pj];
-                }
+            bool valid = false;
+            auto fetch = [&](int u) {
+                // (G = 3: units of 48, 16 sources of a chunk of 64)
+                const int c = G == 3 ? u >> 1 : (u * unit) >> 6, o = G == 3 ? 48 * (u & 1) : (u * unit) & 63;
+                const int32_t pj = window_point(sh.win, start, c, o + lane < 63 ? o + lane : 63);
+                valid = lane < unit && o + lane < 64 && c * 64 + o + lane < tot;
+                const int32_t i = valid ? pj : t.first;
+                nxt = ld_global4(L.ps, i);
+                if constexpr (TWO) ngw = ld_global(g2, i);
             };
-            fetch(0);
-            for (int c0 = 0; c0 < tot; c0 += 64) {
-                const int ns = tot - c0 < 64 ? tot - c0 : 64;
+            if (mine < units) fetch(mine);
+            for (; mine < units; mine += NW) {
+                const int ns = __popcll(__ballot(valid));
                 wave_sync();
-                sh.src[lane] = nxt;
-                if (SEC) sh.sg[lane] = ngw;
+                sh.src[lane] = make_float4(nxt.x - t.ct[0], nxt.y - t.ct[1], nxt.z - t.ct[2], valid ? nxt.w : 0.f);
+                if constexpr (TWO) sh.sg[lane] = valid ? ngw : 0.f;
                 wave_sync();
-                if (c0 + 64 < tot) fetch(c0 + 64);
-                // group grp takes sources grp, grp + G, ...: the same trip count on every lane
-                // (a scalar loop); the slots read stay below ns + G <= 128, and a slot past the
-                // chunk's end adds zeros
+                if (mine + NW < units) fetch(mine + NW);
+                // group grp takes sources grp, grp + G, ...: the same trip count on every lane,
+                // in fours; the slots read stay below 3 G + ns + G <= 256 (G = 64) or 128, and a
+                // slot past the unit's end adds zeros
                 const int nit = __builtin_amdgcn_readfirstlane((ns + G - 1) / G);
-                const int Gs = __builtin_amdgcn_readfirstlane(G);
-#pragma unroll 4
-                for (int it = 0; it < nit; ++it) {
-                    const int j = it * Gs + grp;
-                    const float4 s4 = sh.src[j];
-                    const float dx = tx - s4.x, dy = ty - s4.y, dz = tz - s4.z;
-                    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    const float k = __builtin_amdgcn_exp2f(r2 * L.kexp);
-                    // no contraction: either field's sums carry the same bits as a pass of its own
-                    if (VAL || VEC) {
-                        const float e = __fmul_rn(s4.w, k);
-                        if (VAL) {
-                            su = __fadd_rn(su, e);
-                            sr = fmaf(e, r2, sr);
+                const float4 *src = sh.src + grp;
+                const float *sg = sh.sg + grp;
+                float ke[16], r2[16];
+                float px = 0.f, py = 0.f, pz = 0.f, qx = 0.f, qy = 0.f, qz = 0.f;
+#pragma unroll
+                for (int b = 0; b < 16; b += 4) {
+                    if (b >= nit) continue;
+                    const int Gs = not_hoisted(G);
+#pragma unroll
+                    for (int i = b; i < b + 4; ++i) {
+                        const float4 s4 = src[i * Gs];
+                        const float dx = tx - s4.x, dy = ty - s4.y, dz = tz - s4.z;
+                        r2[i] = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                        ke[i] = __builtin_amdgcn_exp2f(r2[i] * L.kexp);
+                        const float e = s4.w * ke[i];
+                        px = fmaf(e, dx, px);
+                        py = fmaf(e, dy, py);
+                        pz = fmaf(e, dz, pz);
+                        if constexpr (TWO) {
+                            const float g = sg[i * Gs], eg = g * ke[i];
+                            if constexpr (NW == 1) gu = fmaf(g, ke[i], gu);
+                            qx = fmaf(eg, dx, qx);
+                            qy = fmaf(eg, dy, qy);
+                            qz = fmaf(eg, dz, qz);
                         }
-                        if (VEC) {
-                            sx = fmaf(e, dx, sx);
-                            sy = fmaf(e, dy, sy);
-                            sz = fmaf(e, dz, sz);
+                        if constexpr (NW == 1) {
+                            sr = fmaf(e, r2[i], sr);
+                            su = fmaf(s4.w, ke[i], su);
                         }
                     }
-                    if (SEC) {
-                        const float eg = __fmul_rn(sh.sg[j], k);
-                        gu = __fadd_rn(gu, eg);
-                        gx = fmaf(eg, dx, gx);
-                        gy = fmaf(eg, dy, gy);
-                        gz = fmaf(eg, dz, gz);
+                }
+                total[0] += (double)px;
+                total[1] += (double)py;
+                total[2] += (double)pz;
+                if constexpr (TWO) {
+                    total[3] += (double)qx;
+                    total[4] += (double)qy;
+                    total[5] += (double)qz;
+                }
+                if constexpr (NW == 1) continue;
+                // (the weights again, before the turn: they need not be live above)
+                float wt[16], gw[16];
+#pragma unroll
+                for (int b = 0; b < 16; b += 4) {
+                    if (b >= nit) continue;
+                    const int Gs = not_hoisted(G);
+#pragma unroll
+                    for (int i = b; i < b + 4; ++i) {
+                        wt[i] = src[i * Gs].w;
+                        if constexpr (TWO) gw[i] = sg[i * Gs];
                     }
+                }
+                // the turns come round: every earlier unit belongs to a wave of this block that
+                // is at it or will be without waiting for this one
+                while (__hip_atomic_load(&bk.turn, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != before + mine)
+                    __builtin_amdgcn_s_sleep(1);
+                su = bk.run[0][lane];
+                sr = bk.run[1][lane];
+                if constexpr (TWO) gu = bk.run[2][lane];
+#pragma unroll
+                for (int b = 0; b < 16; b += 4) {
+                    if (b >= nit) continue;
+#pragma unroll
+                    for (int i = b; i < b + 4; ++i) {
+                        sr = fmaf(wt[i] * ke[i], r2[i], sr);
+                        su = fmaf(wt[i], ke[i], su);
+                        if constexpr (TWO) gu = fmaf(gw[i], ke[i], gu);
+                    }
+                }
+                bk.run[0][lane] = su;
+                bk.run[1][lane] = sr;
+                if constexpr (TWO) bk.run[2][lane] = gu;
+                __hip_atomic_store(&bk.turn, before + mine + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            mine -= units;
+            before += units;
+        }
+        // the other sums, wave by wave
+        for (int q = 0; q < NW; ++q) {
+            if (wave == q) {
+#pragma unroll
+                for (int c = 0; c < (TWO ? 6 : 3); ++c) bk.sum[c][lane] = (q > 0 ? bk.sum[c][lane] : 0.0) + total[c];
+                if constexpr (NW == 1) {
+                    bk.run[0][lane] = su;
+                    bk.run[1][lane] = sr;
+                    bk.run[2][lane] = gu;
                 }
             }
+            if constexpr (NW > 1) __syncthreads();
+            else wave_sync();
         }
-        wave_sync();
-        if (VAL) {
-            sh.red[0][lane] = su;
-            sh.red[4][lane] = sr;
-        }
-        if (VEC) {
-            sh.red[1][lane] = sx;
-            sh.red[2][lane] = sy;
-            sh.red[3][lane] = sz;
-        }
-        if (SEC) {
-            sh.red[5][lane] = gu;
-            sh.red[6][lane] = gx;
-            sh.red[7][lane] = gy;
-            sh.red[8][lane] = gz;
-        }
-        wave_sync();
-        if (grp == 0 && a < nt) {
-            float r[9];
+        if (wave == 0 && grp == 0 && a < nt) {
+            float r[3] = {0.f, 0.f, 0.f};
+            double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            for (int q = 0; q < G; ++q) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) r[k] = 0.f;
-            for (int q = 0; q < G; ++q)
+                for (int c = 0; c < 3; ++c) r[c] += bk.run[c][q * nt + a];
 #pragma unroll
-                for (int k = 0; k < 9; ++k) {
-                    const int part = k == 0 || k == 4 ? kGradValue : (k < 4 ? kGradVector : kGradSecond);
-                    if (PART & part) r[k] += sh.red[k][q * tp + a];
-                }
+                for (int c = 0; c < (TWO ? 6 : 3); ++c) v[c] += bk.sum[c][q * nt + a];
+            }
             float *o = L.out + (int64_t)ti * stride;   // value, gradient x y z, Laplacian
-            if (VAL) {
-                o[0] = r[0];
-                if (want_lap) o[4] = 4.f * L.inv_s2 * L.inv_s2 * r[4] - 6.f * L.inv_s2 * r[0];
-            }
-            if (VEC) {
-                o[1] = -2.f * L.inv_s2 * r[1];
-                o[2] = -2.f * L.inv_s2 * r[2];
-                o[3] = -2.f * L.inv_s2 * r[3];
-            }
-            if (SEC) {
-                o[5] = r[5];
-                o[6] = -2.f * L.inv_s2 * r[6];
-                o[7] = -2.f * L.inv_s2 * r[7];
-                o[8] = -2.f * L.inv_s2 * r[8];
+            const double m2 = -2.0 * (double)L.inv_s2;
+            o[0] = r[0];
+            o[1] = (float)(m2 * v[0]);
+            o[2] = (float)(m2 * v[1]);
+            o[3] = (float)(m2 * v[2]);
+            if (want_lap) o[4] = 4.f * L.inv_s2 * L.inv_s2 * r[1] - 6.f * L.inv_s2 * r[0];
+            if constexpr (TWO) {
+                o[5] = r[2];
+                o[6] = (float)(m2 * v[3]);
+                o[7] = (float)(m2 * v[4]);
+                o[8] = (float)(m2 * v[5]);
             }
         }
+        if constexpr (NW > 1) __syncthreads();   // the block's sums are free again
+        else wave_sync();
     }
 }
 

@@ -345,7 +345,7 @@ struct msp_batch {
     hipEvent_t fork = nullptr, join[kBranches] = {};
     // batched backward: its own descriptors, offsets and scratch (target weights gt,
     // block partials of the sigma derivative), and one plan per field (weights w, g)
-    msp::DevBuf bw_fdesc, bw_foff, bw_franges, bw_stamps, bw_desc, bw_pt_off, bw_item_off, bw_counter,
+    msp::DevBuf bw_fdesc, bw_foff, bw_franges, bw_stamps, bw_desc, bw_pt_off, bw_item_off, bw_tasks,
         bw_comb, bw_boff, bw_partial, bw_gt;
     msp::FgtBatchPlan bw_plan[2]{};
     int32_t bw_nd = 0;

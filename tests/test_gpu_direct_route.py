@@ -94,6 +94,46 @@ def test_leaf_forms(m, sigma, exclude):
     tree.close()
 
 
+@pytest.mark.parametrize("m", [1, 2, 3, 15, 16, 17, 21, 22, 32, 33, 64, 100])
+@pytest.mark.parametrize("cells", [100, 4000])
+def test_gradient_units(m, cells):
+    """Leaves of m targets: units of the running sums of every length (64 / m groups), eight
+    wavefronts a leaf (100 leaves), one (4,000), four (the batch), the same bits from each
+    of them where the sums run in order; the oracle on some points, 2e-5 of the largest."""
+    import paper_2301_10570_amd as msp
+    if cells * m > 150000:
+        pytest.skip("the same units as with 33 targets")
+    rng = np.random.default_rng(m + cells)
+    grid = np.stack(np.meshgrid(*[np.arange(16)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    keep = grid[np.sort(rng.permutation(4096)[:cells])]
+    pts = (keep[:, None, :] * 20.0 + 0.5 + rng.random((cells, m, 3)) * 19.0).reshape(-1, 3)
+    pts = np.concatenate([pts, [[0.0, 0.0, 0.0], [319.99, 319.99, 319.99]]]).astype(np.float32)
+    n, sigma = len(pts), 8.0 if cells > 100 else 80.0   # lists of some thousand points
+    w = rng.integers(0, 4, n).astype(np.float32)
+    g = (rng.random(n) + 0.5).astype(np.float32)
+    x = [_T(pts[:, k]) for k in range(3)]
+    tree = msp.build_tree(*x, leaf_max=max(m, 2), max_depth=4)
+    print(f"gradient units m={m} cells={cells} nodes={tree.info()['n_nodes']}", flush=True)
+    got = tree.backward(_T(w), _T(g), None, sigma=sigma, route="direct")
+    pick = rng.permutation(n)[:60]
+    pos = pts.astype(np.float64)
+    u = oracle.gauss_sum(pts[pick], pts, g, sigma)
+    assert np.abs(got["w"].cpu().numpy()[pick] - u).max() <= 2e-5 * np.abs(u).max()
+    d = pos[pick][:, None, :] - pos[None]
+    e = np.exp(-(d ** 2).sum(-1) / sigma ** 2)
+    both = e * (g[pick][:, None].astype(np.float64) * w + w[pick][:, None].astype(np.float64) * g)
+    gp = -2.0 / sigma ** 2 * (both[..., None] * d).sum(1)
+    for k in range(3):
+        assert np.abs(got["pos"][k].cpu().numpy()[pick] - gp[:, k]).max() <= 2e-5 * np.abs(gp).max()
+    b = msp.Batch().build(*x, np.array([0, n], dtype=np.int64), leaf_max=np.array([max(m, 2)], dtype=np.int32),
+                          max_depth=4)
+    gb = b.backward(_T(w), _T(g), np.array([sigma], dtype=np.float32), route="direct")
+    np.testing.assert_array_equal(gb["w"].cpu().numpy(), got["w"].cpu().numpy())
+    assert abs(gb["sigma"].cpu().numpy()[0] - got["sigma"].item()) <= 1e-12 * abs(got["sigma"].item())
+    b.close()
+    tree.close()
+
+
 @pytest.mark.parametrize("nt,ns", [(1, 1), (3, 127), (50, 4097), (4095, 129), (4096, 2048), (16383, 130), (16385, 2049),
                                    (65535, 300), (65537, 127), (7, 0)])
 def test_all_pairs(nt, ns):
