@@ -3,9 +3,9 @@
 // Every population keeps its own octree (built from its slice of the caller's
 // concatenated arrays) and its own sigma.  A forward call evaluates all of them
 // with a fixed, short launch sequence whatever the number of populations:
-//   - the expansion-route populations share one launch per pass (translation
-//     operators, grid clearing, the occupied-cell list, P2M, three M2L passes,
-//     L2P straight into the output slices), each pass locating its work units
+//   - the expansion-route populations share one launch per pass (P2M, three M2L
+//     passes, L2P straight into the output slices; translation operators, the cleared
+//     cells without points and the list of the others are made with the plan), each pass locating its work units
 //     (population, cell / tile / operator) in prefix sums; they run on a branch
 //     stream that forks from the caller's stream and joins it again;
 //   - all populations on the direct route share ONE P2P launch with a block per
@@ -287,8 +287,9 @@ int plan_batch(msp_batch *b, const float *sigma, const msp_fgt_params *prm, std:
 // gets everything but its descriptor pointer.  Host synchronisations allowed.
 int prepare_fgt(msp_batch *b, const std::vector<PopPlan> &plans, const float *w, const uint8_t *is_target,
                 float *u_out, std::vector<FgtPop> &fp, DevBuf &foff, DevBuf &franges, DevBuf &stamps,
-                FgtBatchPlan &bp) {
+                FgtBatchPlan &bp, FgtLayouts &layouts) {
     fp.clear();
+    layouts.clear();
     std::vector<int64_t> ops_off{0}, pw_off{0}, grid_off{0}, tile_off[3] = {{0}, {0}, {0}};
     int64_t n_pts = 0;
     int p = 0;
@@ -325,6 +326,12 @@ int prepare_fgt(msp_batch *b, const std::vector<PopPlan> &plans, const float *w,
     for (const FgtPop &f : fp)
         for (int pass = 0; pass < 3; ++pass)
             tile_off[pass].push_back(tile_off[pass].back() + fgt_pop_tiles(f, p, pass, gemm));
+    for (const FgtPop &f : fp) {
+        uint32_t sig;
+        std::memcpy(&sig, &plans[f.pop].prm.sigma, 4);
+        layouts.emplace_back(f.pop, (uint64_t)sig << 32 | (uint64_t)f.level << 16 | (uint64_t)p << 8 | 4u |
+                                        (gemm ? 2u : 0u) | (split ? 1u : 0u));
+    }
     const int nf = (int)fp.size();
     MSP_TRY(foff.ensure((size_t)6 * (nf + 1) * 8));
     MSP_TRY(franges.ensure((size_t)(n_pts + 1) * sizeof(int4) + 16));
@@ -359,6 +366,16 @@ int prepare_fgt(msp_batch *b, const std::vector<PopPlan> &plans, const float *w,
     return MSP_OK;
 }
 
+// What a plan keeps in its populations' grids and tables, made anew where it was not made
+// yet or the other call's plan has since put another layout there.
+int lay_out(msp_batch *b, const FgtBatchPlan &bp, const FgtLayouts &layouts, bool anew, hipStream_t s) {
+    for (const auto &l : layouts) anew = anew || b->pops[l.first]->batch_layout != l.second;
+    if (!anew) return MSP_OK;
+    MSP_TRY(fgt_batch_lay_out(bp, s));
+    for (const auto &l : layouts) b->pops[l.first]->batch_layout = l.second;
+    return MSP_OK;
+}
+
 // The populations in the order of the direct-route launches: the longest lists first.
 std::vector<int> largest_first(const msp_batch *b) {
     std::vector<int> o(b->npop);
@@ -377,11 +394,12 @@ int prepare_batch(msp_batch *b, const std::vector<PopPlan> &plans, const float *
     // earlier work on s may still read the descriptors about to be replaced
     MSP_HIP(hipStreamSynchronize(s));
     std::vector<FgtPop> fp;
-    MSP_TRY(prepare_fgt(b, plans, w, is_target, u_out, fp, b->foff, b->franges, b->stamps, b->fplan));
+    MSP_TRY(prepare_fgt(b, plans, w, is_target, u_out, fp, b->foff, b->franges, b->stamps, b->fplan, b->flayout));
     MSP_TRY(b->fdesc.ensure((fp.size() + 1) * sizeof(FgtPop)));
     if (!fp.empty()) {
         MSP_HIP(hipMemcpy(b->fdesc.p, fp.data(), fp.size() * sizeof(FgtPop), hipMemcpyHostToDevice));
         b->fplan.pops = b->fdesc.as<FgtPop>();
+        MSP_TRY(lay_out(b, b->fplan, b->flayout, true, s));
     }
     for (int k : largest_first(b)) {
         msp_tree *t = b->pops[k].get();
@@ -450,7 +468,7 @@ int enqueue_forward(msp_batch *b, const std::vector<PopPlan> &plans, const float
     MSP_HIP(hipEventRecord(b->fork, s));
     MSP_HIP(hipStreamWaitEvent(b->side[0], b->fork, 0));
     MSP_TRY(fgt_batch_forward(b->fplan, b->side[0]));
-    if (b->fplan.npop > 0) launches += 8;
+    if (b->fplan.npop > 0) launches += 6;
     (void)stamps;
     const int nd = b->n_direct;
     if (nd > 0) {
@@ -540,6 +558,7 @@ int batch_forward(msp_batch *b, const float *w, const uint8_t *is_target, const 
     append_bytes(key, sigma, sizeof(float) * b->npop);
     append_bytes(key, b->route.data(), sizeof(int32_t) * b->route.size());
     if (use_graph && b->exec && key == b->key && state_signature(b) == b->fsig) {
+        MSP_TRY(lay_out(b, b->fplan, b->flayout, false, s));
         MSP_HIP(hipGraphLaunch(b->exec, s));
         return MSP_OK;
     }
@@ -599,7 +618,8 @@ int prepare_backward(msp_batch *b, const std::vector<PopPlan> &plans, const floa
     }
     // expansion route: one plan, two descriptor sets
     std::vector<FgtPop> fp;
-    MSP_TRY(prepare_fgt(b, plans, w, nullptr, nullptr, fp, b->bw_foff, b->bw_franges, b->bw_stamps, b->bw_plan[0]));
+    MSP_TRY(prepare_fgt(b, plans, w, nullptr, nullptr, fp, b->bw_foff, b->bw_franges, b->bw_stamps, b->bw_plan[0],
+                        b->bw_layout));
     const size_t nf = fp.size();
     for (FgtPop &f : fp) f.rec = b->pops[f.pop]->bwd.as<float>();
     std::vector<FgtPop> both(fp);
@@ -613,6 +633,7 @@ int prepare_backward(msp_batch *b, const std::vector<PopPlan> &plans, const floa
         MSP_HIP(hipMemcpy(b->bw_fdesc.p, both.data(), both.size() * sizeof(FgtPop), hipMemcpyHostToDevice));
         b->bw_plan[0].pops = b->bw_fdesc.as<FgtPop>();
         b->bw_plan[1].pops = b->bw_fdesc.as<FgtPop>() + nf;
+        MSP_TRY(lay_out(b, b->bw_plan[0], b->bw_layout, true, s));   // one for both: the same trees
     }
     // direct route
     std::vector<GradDesc> gd;
@@ -737,6 +758,7 @@ int batch_backward(msp_batch *b, const float *w, const uint8_t *is_target, const
     append_bytes(key, sigma, sizeof(float) * b->npop);
     append_bytes(key, b->route.data(), sizeof(int32_t) * b->route.size());
     if (use_graph && b->bexec && key == b->bkey && state_signature(b) == b->bsig) {
+        MSP_TRY(lay_out(b, b->bw_plan[0], b->bw_layout, false, s));
         MSP_HIP(hipGraphLaunch(b->bexec, s));
         return MSP_OK;
     }

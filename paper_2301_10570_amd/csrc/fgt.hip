@@ -1959,14 +1959,11 @@ __device__ inline int find_pop(const int64_t *off, int npop, int64_t x) {
     return lo;
 }
 
-// The batched expansion kernels run beside the persistent P2P, whose wavefronts are
-// older and keep the vector units busy: at equal priority the few wavefronts of a
-// latency-bound kernel like k_bcells got hardly an issue slot (1.7 ms beside the P2P of
-// 256 populations, 0.1 ms alone).
+// The batched expansion passes run beside the P2P, which keeps the vector units busy: a
+// pass's wavefronts, the longer of the two chains of launches, issue first.
 __device__ inline void ahead_of_p2p() { __builtin_amdgcn_s_setprio(3); }
 
 __global__ void k_bops(FgtBatchPlan bp) {
-    ahead_of_p2p();
     const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (g >= bp.n_ops) return;
     const int k = find_pop(bp.ops_off, bp.npop, g);
@@ -1974,20 +1971,15 @@ __global__ void k_bops(FgtBatchPlan bp) {
     m2l_ops_one(bp.p, f.G[0], f.G[1], f.G[2], f.step, f.opsx, f.opsy, f.opsz, (int)(g - bp.ops_off[k]));
 }
 
-// zero moment grids (cells without points are never written by the P2M), clear
-// the cell counters and the timestamps.  Each population's grid is cleared
-// in 16-byte stores by all threads (grids start at allocation boundaries).
+// zero moment grids (cells without points are never written by the P2M) and the cell
+// counters.  Each population's grid is cleared in 16-byte stores by all threads (grids
+// start at allocation boundaries).
 __global__ void k_bclear(FgtBatchPlan bp) {
-    ahead_of_p2p();
     const int64_t g0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t nth = (int64_t)gridDim.x * blockDim.x;
     if (g0 == 0) {
         bp.ncells[0] = 0;
         bp.ncells[1] = 0;
-    }
-    if (g0 < bp.npop) {
-        bp.stamps[2 * bp.pops[g0].pop] = ~0ull;
-        bp.stamps[2 * bp.pops[g0].pop + 1] = 0ull;
     }
     for (int k = 0; k < bp.npop; ++k) {
         float *A = bp.pops[k].A;
@@ -1997,6 +1989,13 @@ __global__ void k_bclear(FgtBatchPlan bp) {
         for (int64_t g = g0; g < n4; g += nth) A4[g] = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int64_t g = 4 * n4 + g0; g < n; g += nth) A[g] = 0.f;
     }
+}
+
+__global__ void k_bstamps(FgtBatchPlan bp) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= bp.npop) return;
+    bp.stamps[2 * bp.pops[k].pop] = ~0ull;
+    bp.stamps[2 * bp.pops[k].pop + 1] = 0ull;
 }
 
 // Occupied cells of every population.  A window is 64 consecutive points (key
@@ -2010,7 +2009,6 @@ __global__ void k_bclear(FgtBatchPlan bp) {
 // system).
 constexpr int kCellWin = 16;
 __global__ void __launch_bounds__(256) k_bcells(FgtBatchPlan bp, int cmax) {
-    ahead_of_p2p();
     const int lane = threadIdx.x & 63;
     const int64_t w0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kCellWin;
     if (w0 >= bp.n_pw) return;   // whole wavefronts
@@ -2720,18 +2718,28 @@ int batch_p2m_l2p_p(const FgtBatchPlan &bp, bool l2p, hipStream_t s) {
 
 }  // namespace
 
-namespace {
-// operator tables, cleared grids, the cell list, P2M and the three M2L passes
-int fgt_batch_expand(const FgtBatchPlan &bp, hipStream_t s) {
+// What the passes need of the populations' trees and sigmas alone, made when the plan is
+// made and not by every call: operator tables, zeros in the cells without points (no pass
+// writes them), the list of the other cells.  On 256 populations of 1,024 to 65,536 points
+// these were 230 of a call's 1,600 us of expansion kernels.
+int fgt_batch_lay_out(const FgtBatchPlan &bp, hipStream_t s) {
+    if (bp.npop == 0) return MSP_OK;
     hipLaunchKernelGGL(k_bops, dim3(grid_for(bp.n_ops, 64)), dim3(64), 0, s, bp);
     MSP_CHECK_LAUNCH();
     const int64_t fill_threads = bp.n_grid / 4 < (int64_t)bp.cus * 2048 ? bp.n_grid / 4 + 1 : (int64_t)bp.cus * 2048;
-    hipLaunchKernelGGL(k_bclear, dim3(grid_for(fill_threads > bp.npop ? fill_threads : bp.npop, kBlock)),
-                       dim3(kBlock), 0, s, bp);
+    hipLaunchKernelGGL(k_bclear, dim3(grid_for(fill_threads, kBlock)), dim3(kBlock), 0, s, bp);
     MSP_CHECK_LAUNCH();
     const int64_t cell_waves = (bp.n_pw + kCellWin - 1) / kCellWin;
     hipLaunchKernelGGL(k_bcells, dim3((unsigned)((cell_waves + 3) / 4)), dim3(256), 0, s, bp,
                        bp.p <= 8 ? kSmallCell : 0);
+    MSP_CHECK_LAUNCH();
+    return MSP_OK;
+}
+
+namespace {
+// cleared timestamps, P2M and the three M2L passes
+int fgt_batch_expand(const FgtBatchPlan &bp, hipStream_t s) {
+    hipLaunchKernelGGL(k_bstamps, dim3(grid_for(bp.npop, 64)), dim3(64), 0, s, bp);
     MSP_CHECK_LAUNCH();
     MSP_TRY(batch_p2m_l2p_p(bp, false, s));
     for (int pass = 0; pass < 3; ++pass) {
@@ -2791,7 +2799,7 @@ int fgt_pop_prepare(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, F
     MSP_TRY(t->gridA.ensure(gbytes));
     MSP_TRY(t->gridB.ensure(gbytes));
     MSP_TRY(t->ops.ensure(obytes));
-    t->ops_valid = false;   // the batched pass writes the tables itself
+    t->ops_valid = false;   // the batch writes the tables itself
     t->grid_bytes_valid = (int64_t)gbytes;
     f->keys = t->keys.as<uint64_t>();
     f->ps = t->ps.as<float4>();

@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <memory>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/mspfmm.h"
@@ -231,6 +232,8 @@ struct msp_tree {
     msp::DevBuf bwd;   // backward scratch: records, target weights (input and key order), reductions
     // expansion grids and translation operators
     msp::DevBuf gridA, gridB, ops;
+    // what a batch last laid out in gridA and ops (0: nothing): see FgtLayout
+    uint64_t batch_layout = 0;
     bool ops_valid = false;     // M2L operator tables in ops match ops_sig (p, grid, cell / sigma)
     uint64_t ops_sig[5] = {};
     int64_t grid_bytes_valid = 0;
@@ -315,6 +318,10 @@ struct FgtBatchPlan {
     size_t gemm_lds;   // dynamic LDS of the GEMM tiles (largest population)
 };
 
+// The layouts a plan needs in its populations' grids and tables: (population, layout),
+// a layout naming sigma, level, p and the kind of grid.
+using FgtLayouts = std::vector<std::pair<int, uint64_t>>;
+
 }  // namespace msp
 
 // A batch of independent populations (batch.hip).
@@ -339,6 +346,7 @@ struct msp_batch {
     // expansion-route populations: descriptors, offsets, range list, launch plan
     msp::DevBuf fdesc, foff, franges;
     msp::FgtBatchPlan fplan{};
+    msp::FgtLayouts flayout, bw_layout;
     // branch stream for the expansion-route populations (forked from the caller's stream)
     static constexpr int kBranches = 1;
     hipStream_t side[kBranches] = {};
@@ -448,6 +456,7 @@ int64_t fgt_pop_tiles(const FgtPop &f, int p, int pass, bool gemm);
 size_t fgt_pop_gemm_lds(const FgtPop &f, int p, bool split = false);
 // LDS of the split tile with the whole operator table (its limit is the batch's)
 size_t fgt_pop_split_whole(const FgtPop &f);
+int fgt_batch_lay_out(const FgtBatchPlan &bp, hipStream_t s);
 int fgt_batch_forward(const FgtBatchPlan &bp, hipStream_t s);
 // value, gradient and (want_lap) Laplacian of every population's field at all its
 // points, into f.rec + i * stride + slot (key order i)

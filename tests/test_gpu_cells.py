@@ -85,3 +85,47 @@ def test_padded_translation_tiles(p, m2l):
     assert np.abs(C - Cv).max() <= (1e-5 if m2l == "mfma" else 2e-4) * np.abs(Cv).max()
     assert rel_err(u[tgt], v[tgt]).max() <= (1e-5 if m2l == "mfma" else 5e-5)
     tree.close()
+
+
+def test_batch_layouts_alternate():
+    """Calls of one batch with other sigmas, orders and tiles in turn, replayed: each finds the
+    tables and cleared cells of its own plan.  The expansions are summed in one order, so a
+    call's bits are those of a batch of its own."""
+    import torch
+    import paper_2301_10570_amd as msp
+    rng = np.random.default_rng(77)
+    sizes = [9000, 40, 7000, 12000]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n = int(off[-1])
+    pts = (rng.random((n, 3)) * np.repeat([1.0, 0.3, 0.5, 1.0], sizes)[:, None] * 900.0).astype(np.float32)
+    pts[:3000] = pts[:3000] * 0.2   # cells without points, and full ones
+    x = [torch.from_numpy(np.ascontiguousarray(pts[:, k])).cuda() for k in range(3)]
+    w = torch.from_numpy(rng.integers(0, 4, n).astype(np.float32)).cuda()
+    g = torch.from_numpy(rng.random(n).astype(np.float32)).cuda()
+    sig = [np.full(4, s, dtype=np.float32) for s in (150.0, 260.0)]
+    calls = [(0, 8, "mfma"), (1, 8, "mfma"), (1, 6, "mfma"), (0, 8, "bf16x3")]
+
+    def run(b, call, back):
+        s, p, m2l = calls[call]
+        if back:
+            r = b.backward(w, g, sig[s], p=p, route="fgt", m2l=m2l, out=outs.setdefault((id(b), call), None),
+                           use_graph=True)
+            outs[(id(b), call)] = r
+            return [r["w"].clone(), r["pos"][1].clone(), r["sigma"].clone()]
+        u = us.setdefault((id(b), call), torch.empty(n, device="cuda"))
+        return [b.forward(w, sig[s], p=p, route="fgt", m2l=m2l, out=u, use_graph=True).clone()]
+
+    outs, us, own = {}, {}, {}
+    for call in range(len(calls)):
+        for back in (False, True):
+            b = msp.Batch().build(*x, off)
+            own[call, back] = run(b, call, back)
+            torch.cuda.synchronize()
+            b.close()
+    b = msp.Batch().build(*x, off)
+    for call, back in [(0, False), (1, True), (0, False), (1, True), (1, True), (2, False), (1, True), (2, False),
+                       (3, True), (2, False), (3, True), (0, False), (0, True), (0, False), (3, True), (0, False)]:
+        print(f"call {calls[call]} backward={back}", flush=True)
+        for got, want in zip(run(b, call, back), own[call, back]):
+            torch.testing.assert_close(got, want, rtol=0, atol=0)
+    b.close()
