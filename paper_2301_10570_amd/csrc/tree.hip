@@ -559,11 +559,25 @@ __global__ void k_level_scan(uint32_t *blkcnt, int nblk, uint32_t *total) {
     if (threadIdx.x == 0) total[blockIdx.x] = tot;
 }
 
-__global__ void k_level_offsets(const uint32_t *total, int64_t *level_off) {
-    if (threadIdx.x != 0) return;
-    int64_t run = 0;
-    for (int l = 0; l <= kDepth; ++l) { level_off[l] = run; run += total[l]; }
-    level_off[kDepth + 1] = run;
+// The level offsets from the levels' totals, for the device and (page-locked) for the
+// host, whose one readback of the build also holds the box and the flags.  One wavefront.
+// one: the totals are the counts of the only tile, whose own offsets are then 0.
+constexpr size_t kRbBox = kMaxLevels * 8;
+__global__ void __launch_bounds__(64) k_level_offsets(uint32_t *total, int one, int64_t *level_off, const float *box,
+                                                      char *host) {
+    const int l = threadIdx.x;
+    int64_t run = l <= kDepth ? (int64_t)total[l] : 0;
+    const int64_t mine = run;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t t = __shfl_up(run, o, 64);
+        if (l >= o) run += t;
+    }
+    if (l <= kDepth + 1) {
+        level_off[l] = run - mine;
+        reinterpret_cast<int64_t *>(host)[l] = run - mine;
+        if (one && l <= kDepth) total[l] = 0;
+    }
+    if (l < 10) reinterpret_cast<float *>(host + kRbBox)[l] = box[l];   // box (8 floats), flags
 }
 
 // Parent of every node: the last node one level up whose first point is at or
@@ -690,6 +704,116 @@ __global__ void __launch_bounds__(kBlock) k_seg_sort(const uint64_t *kin, const 
     kout[o] = key;
     vout[o] = val;
     ps[o] = pin[val];
+}
+
+// Small inputs (n <= kSmallMax): the bounding box and the keys in one block, then the
+// sort by counting: a point's place is the number of points with a smaller (key, index),
+// n^2 comparisons spread over the chip, two instructions each.  The fourteen launches of
+// the general path, each a few microseconds of latency for a handful of points, took
+// 55 us for 1,000 points and 61 us for 5,003; these two take 13 us and 25 us.  (A bitonic
+// sort in the first block's LDS took 20 us and 86 us.)  The line: at 8,000 points a whole
+// direct evaluation with its build takes 134 us, 167 us with the general path; four times
+// the comparisons at 16,000 would cost what they save.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallMax = 8192;
+__global__ void __launch_bounds__(kSmallThreads) k_small_keys(const float *x, const float *y, const float *z,
+                                                              const float *w, int n, float *box, int *flags,
+                                                              uint64_t *key, float4 *pin) {
+    constexpr int PER = kSmallMax / kSmallThreads, WAVES = kSmallThreads / 64;
+    __shared__ float red[6][WAVES];
+    __shared__ int bad;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) bad = 0;
+    float4 q[PER];
+    float r[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    bool finite = true;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = u * kSmallThreads + tid;
+        q[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i < n) q[u] = make_float4(x[i], y[i], z[i], w ? w[i] : 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (u * kSmallThreads + tid >= n) continue;
+        const float c[3] = {q[u].x, q[u].y, q[u].z};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (!isfinite(c[k])) {
+                finite = false;
+                continue;
+            }
+            r[k] = fminf(r[k], c[k]);
+            r[3 + k] = fmaxf(r[3 + k], c[k]);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            r[k] = fminf(r[k], __shfl_xor(r[k], o, 64));
+            r[3 + k] = fmaxf(r[3 + k], __shfl_xor(r[3 + k], o, 64));
+        }
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) red[k][wave] = r[k];
+    __syncthreads();
+    if (!finite) bad = 1;
+    float b[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        b[k] = red[k][lane & (WAVES - 1)];
+#pragma unroll
+        for (int o = WAVES / 2; o > 0; o >>= 1) {
+            const float v = __shfl_xor(b[k], o, 64);
+            b[k] = k < 3 ? fminf(b[k], v) : fmaxf(b[k], v);
+        }
+    }
+    double lo[3], side, scale;
+    root_cube(b, lo, side, scale);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = u * kSmallThreads + tid;
+        if (i >= n) continue;
+        key[i] = morton3(quantise(q[u].x, lo[0], scale), quantise(q[u].y, lo[1], scale), quantise(q[u].z, lo[2], scale));
+        pin[i] = q[u];
+    }
+    __syncthreads();
+    if (tid == 0) {
+        flags[0] = bad;   // a non-finite coordinate
+        flags[1] = 0;     // no run is too long here
+#pragma unroll
+        for (int k = 0; k < 6; ++k) box[k] = b[k];
+    }
+}
+
+// A block places 64 points, its sixteen wavefronts count over a sixteenth of the keys each.
+__global__ void __launch_bounds__(kSmallThreads) k_small_rank(const uint64_t *__restrict__ key, int n, uint64_t *kout,
+                                                              int32_t *vout, const float4 *pin, float4 *ps) {
+    constexpr int WAVES = kSmallThreads / 64;
+    __shared__ int part[WAVES][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i0 = blockIdx.x * 64, i = i0 + lane;
+    const uint64_t mine = key[i < n ? i : n - 1];
+    const int per = (n + WAVES - 1) / WAVES, j0 = wave * per, j1 = j0 + per < n ? j0 + per : n;
+    int before = 0;
+    // keys of points before this block's count when equal, those after it do not
+    const int a = j1 < i0 ? j1 : i0, b = j0 > i0 + 64 ? j0 : i0 + 64;
+    int j = j0;
+#pragma unroll 8
+    for (; j < a; ++j) before += key[j] <= mine;
+    for (; j < j1 && j < b; ++j) before += key[j] < mine || (key[j] == mine && j < i);
+#pragma unroll 8
+    for (; j < j1; ++j) before += key[j] < mine;
+    part[wave][lane] = before;
+    __syncthreads();
+    if (wave != 0 || i >= n) return;
+    int o = 0;
+#pragma unroll
+    for (int q = 0; q < WAVES; ++q) o += part[q][lane];
+    kout[o] = mine;
+    vout[o] = i;
+    ps[o] = pin[i];
 }
 
 __global__ void k_inverse_perm(const int32_t *perm, int64_t n, int32_t *iperm) {
@@ -892,9 +1016,9 @@ int build_tree(msp_tree *t, const float *x, const float *y, const float *z, int6
         MSP_TRY(t->bbox.ensure(kBboxBytes));
         float *part = t->bbox.as<float>();
         float *out = part + parts * 6;
-        int *bad = bbox_flags(t);
-        MSP_HIP(hipMemsetAsync(bad, 0, 2 * sizeof(int), s));   // non-finite flag, sort-run overflow
-        {
+        if (n > kSmallMax) {
+            int *bad = bbox_flags(t);
+            MSP_HIP(hipMemsetAsync(bad, 0, 2 * sizeof(int), s));   // non-finite flag, sort-run overflow
             PhaseScope ps(&t->timing, PH_BBOX, s);
             hipLaunchKernelGGL(k_bbox_partial, dim3(parts), dim3(kBlock), 0, s, x, y, z, n, part, bad);
             MSP_CHECK_LAUNCH();
@@ -939,6 +1063,18 @@ int build_tree(msp_tree *t, const float *x, const float *y, const float *z, int6
     uint32_t *blkcnt = t->blkcnt.as<uint32_t>();
     uint32_t *ltot = blkcnt + (size_t)kMaxLevels * nblk;
     auto keys_and_sort = [&](bool full) -> int {
+        if (n <= kSmallMax) {
+            PhaseScope ps(&t->timing, PH_SORT, s);
+            hipLaunchKernelGGL(k_small_keys, dim3(1), dim3(kSmallThreads), 0, s, x, y, z, w, (int)n,
+                               t->bbox.as<float>() + kBboxParts * 6, bbox_flags(t), t->keys2.as<uint64_t>(),
+                               t->pin.as<float4>());
+            MSP_CHECK_LAUNCH();
+            hipLaunchKernelGGL(k_small_rank, dim3((unsigned)((n + 63) / 64)), dim3(kSmallThreads), 0, s,
+                               t->keys2.as<uint64_t>(), (int)n, t->keys.as<uint64_t>(), t->perm.as<int32_t>(),
+                               t->pin.as<float4>(), t->ps.as<float4>());
+            MSP_CHECK_LAUNCH();
+            return MSP_OK;
+        }
         {
             PhaseScope ps(&t->timing, PH_KEYS, s);
             hipLaunchKernelGGL(k_morton, dim3(nblk), dim3(kBlock), 0, s, x, y, z, w, n,
@@ -971,23 +1107,21 @@ int build_tree(msp_tree *t, const float *x, const float *y, const float *z, int6
                                t->llev.as<uint8_t>(), blkcnt, nblk);
             MSP_CHECK_LAUNCH();
         }
-        hipLaunchKernelGGL(k_level_scan, dim3(kDepth + 1), dim3(kBlock), 0, s, blkcnt, nblk, ltot);
-        MSP_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_level_offsets, dim3(1), dim3(64), 0, s, ltot, t->d_level_off.as<int64_t>());
+        if (nblk > 1) {
+            hipLaunchKernelGGL(k_level_scan, dim3(kDepth + 1), dim3(kBlock), 0, s, blkcnt, nblk, ltot);
+            MSP_CHECK_LAUNCH();
+        }
+        MSP_TRY(t->build_stage.ensure(kRbBox + 8 * sizeof(float) + 2 * sizeof(int)));
+        hipLaunchKernelGGL(k_level_offsets, dim3(1), dim3(64), 0, s, nblk > 1 ? ltot : blkcnt, nblk > 1 ? 0 : 1,
+                           t->d_level_off.as<int64_t>(), t->bbox.as<float>() + kBboxParts * 6,
+                           static_cast<char *>(t->build_stage.p));
         MSP_CHECK_LAUNCH();
         return MSP_OK;
     };
-    // one readback per build: level offsets, then the box and the two flags
-    // (non-finite input, sort run overflow), into page-locked memory
-    constexpr size_t kRbBox = kMaxLevels * 8;
+    // one readback per build, written by the last kernel of levels()
     auto readback = [&]() -> int {
-        MSP_TRY(t->build_stage.ensure(kRbBox + 8 * sizeof(float) + 2 * sizeof(int)));
-        char *h = static_cast<char *>(t->build_stage.p);
-        MSP_HIP(hipMemcpyAsync(h, t->d_level_off.p, kMaxLevels * 8, hipMemcpyDeviceToHost, s));
-        MSP_HIP(hipMemcpyAsync(h + kRbBox, t->bbox.as<float>() + kBboxParts * 6, 8 * sizeof(float) + 2 * sizeof(int),
-                               hipMemcpyDeviceToHost, s));
         MSP_HIP(hipStreamSynchronize(s));
-        std::memcpy(t->level_off, h, kMaxLevels * 8);
+        std::memcpy(t->level_off, t->build_stage.p, kMaxLevels * 8);
         return MSP_OK;
     };
     // a weighted build (handle memory) also counts the sources before each position,

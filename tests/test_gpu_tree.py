@@ -77,6 +77,31 @@ def test_tree_full_slab():
     _compare(wl.x, wl.y, wl.z)
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 1000, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 5003, 8191,
+                               8192, 8193])
+def test_small_build(n):
+    """The small build at its edges and past its end: points that repeat (ties
+    by index), one far outlier, a weighted build; exact."""
+    rng = np.random.default_rng(n)
+    p = np.round(rng.random((n, 3)) * 23.0).astype(np.float32)
+    p[n // 3:] += (rng.random((n - n // 3, 3)) * 1e-3).astype(np.float32)
+    p[rng.permutation(n)[:1]] = [1e4, -3e3, 0.25]
+    x, y, z = (np.ascontiguousarray(p[:, k]) for k in range(3))
+    print(f"small build n={n}", flush=True)
+    _compare(x, y, z, leaf_max=5)
+    import torch
+    import paper_2301_10570_amd as msp
+    w = rng.random(n).astype(np.float32)
+    tree = msp.Tree()
+    tree.build(*(torch.from_numpy(v).cuda() for v in (x, y, z)), leaf_max=5, w=torch.from_numpy(w).cuda())
+    _check_records(tree, x, y, z, octree.build(x, y, z, leaf_max=5).perm, w)
+    bad = torch.from_numpy(x.copy()).cuda()
+    bad[n // 2] = float("nan")
+    with pytest.raises(msp.MspError):
+        tree.build(bad, *(torch.from_numpy(v).cuda() for v in (y, z)))
+    tree.close()
+
+
 def test_weighted_build_records():
     """A weighted build carries the weights into key order with the positions."""
     import torch
