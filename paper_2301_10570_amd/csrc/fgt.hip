@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int6
                                                       int level, int Gx, int Gy, int Gz, double lox, double loy, double loz,
                                                       double cell, double inv_sigma, float *A, float4 *stage) {
     __shared__ float pw[kBlock * kPowStr];
-    __shared__ float red[kBlock / 64][512];
+    float (*red)[512] = reinterpret_cast<float (*)[512]>(pw);   // used when the cell's powers are not
     // one cell per block, or every gridDim.x-th one in grids of mostly empty cells (32,768
     // cells, 8% with points: 238 us with a search in every block, 52 us)
     for (int64_t g = blockIdx.x; g < (int64_t)Gx * Gy * Gz; g += gridDim.x) {
@@ -380,19 +380,22 @@ __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int6
     }
     const double cx = lox + (kx + 0.5) * cell, cy = loy + (ky + 0.5) * cell, cz = loz + (kz + 0.5) * cell;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    float4 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
+    // the next chunk's point and weight as they lie in memory, and with w the indices of
+    // the chunk after it: nothing waits for them before they are used a chunk later (points
+    // past the cell: its last one, with weight 0)
+    float4 nxt;
+    float nw = 0.f;
+    int32_t pj = 0;
+    auto clip = [&](int64_t j) { return j < end ? j : end - 1; };
     auto fetch = [&](int64_t c0) {
-        const int64_t j = c0 + tid;
-        nxt = make_float4(0.f, 0.f, 0.f, 0.f);   // past the cell: zero weight
-        if (j < end) {
-            const float4 q = ps[j];
-            const float wv = w ? w[perm[j]] : q.w;   // NULL: the weights are staged in the records
-            // the weight in key order, for later calls (whole records: full-line writes)
-            if (stage) stage[j] = make_float4(q.x, q.y, q.z, wv);
-            nxt = make_float4(((q.x - (float)cx) * (float)inv_sigma), ((q.y - (float)cy) * (float)inv_sigma),
-                              ((q.z - (float)cz) * (float)inv_sigma), wv);
+        const int64_t j = clip(c0 + tid);
+        nxt = ps[j];
+        if (w) {   // NULL: the weights are staged in the records
+            nw = w[pj];
+            pj = perm[clip(j + kBlock)];
         }
     };
+    if (w) pj = perm[clip(start + tid)];
     // this lane's operand slots: row m = (ax, ay_lo), column n = (ay_hi within the tile, az)
     const int m = lane & 15, kq = lane >> 4;
     const int ax = m >> 1, aylo = m & 1;
@@ -405,16 +408,22 @@ __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int6
     for (int64_t c0 = start; c0 < end; c0 += kBlock) {
         wave_sync();
         {
+            const bool in = c0 + tid < end;
+            const float wv = w ? nw : nxt.w;
+            // the weight in key order, for later calls (whole records: full-line writes)
+            if (stage && in) stage[c0 + tid] = make_float4(nxt.x, nxt.y, nxt.z, wv);
+            const float X = (nxt.x - (float)cx) * (float)inv_sigma, Y = (nxt.y - (float)cy) * (float)inv_sigma,
+                        Z = (nxt.z - (float)cz) * (float)inv_sigma;
             float *r = pw + tid * kPowStr;
-            float xp = 1.f, yp = 1.f, wz = nxt.w;
+            float xp = 1.f, yp = 1.f, wz = in ? wv : 0.f;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 r[k] = xp;
                 r[8 + k] = yp;
                 r[16 + k] = wz;
-                xp *= nxt.x;
-                yp *= nxt.y;
-                wz *= nxt.z;
+                xp *= X;
+                yp *= Y;
+                wz *= Z;
             }
         }
         wave_sync();
@@ -445,6 +454,7 @@ __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int6
         }
     }
     // D[4 kq + i][n16] of both tiles -> red[wave][(az * 8 + ay) * 8 + ax]
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int mm = 4 * kq + i, axo = mm >> 1, aylo_o = mm & 1;
@@ -1279,8 +1289,8 @@ __device__ inline int64_t run_end(const uint64_t *keys, int64_t i, int64_t e, in
 // a coefficient read from LDS serves NPT chains: with four the vector units bound it
 // (2 p^3 flops a point), but few points then make few wavefronts.  One block per cell
 // left the chip to the fullest cells: 262,144 points in 64 blobs (32,768 cells, 2,600
-// with points, up to 5,000 in one) 198 us, 35 us here; 2,097,152 points in 512 cells
-// 86 us, 60 us here; 4,194,304 points in 1,024 cells 87 us, 89 us here.
+// with points, up to 5,000 in one) at p = 8 198 us, 35 us in this form; 2,097,152 points
+// in 512 cells 86 us, 60 us.  p = 8 has its own, k_l2p_mfma8.
 template <int P, int NPT>
 __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n, const float4 *ps,
                                                 const int32_t *perm, const CellTable cells, int level,
@@ -1400,6 +1410,126 @@ __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n,
             }
             s0 = e;
         }
+    }
+}
+
+// The same for p = 8 on the matrix cores, which bound it (64 instructions of 32 cycles for
+// 64 points, the sums over ax): a wavefront takes runs of 64 points in four groups of 16.
+// v_mfma_f32_16x16x4f32 with the coefficients as operand A (row m of tile t: az = m / 4 +
+// 4 (t / 2), ay = m % 4 + 4 (t % 2); held in eight registers per lane, no LDS) and the
+// powers of X as operand B leaves lane l = 16 kq + n of a group with the sums over ax of
+// point n for az = kq and kq + 4 and every ay: two Horner chains in Y, and the four kq
+// added across the lanes.  DENSE: cells' ends from the table (or a search) and one key a
+// cell, otherwise from the lanes' own keys.  Horner in the vector unit (k_l2p), then here:
+// 262,144 points in 2,600 cells 35 us, 19 us; 2,097,152 points in 512 cells 58 us, 44 us;
+// 4,194,304 points in 1,024 cells 87 us, 73 us, where the sums' scattered 4-byte stores bound
+// it.
+template <bool DENSE>
+__global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int64_t n, const float4 *ps,
+                                                      const int32_t *perm, const CellTable cells, int level,
+                                                      int Gx, int Gy, int Gz, double lox, double loy, double loz,
+                                                      double cell, double inv_sigma, const float *C, int chunks,
+                                                      float *u_out) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n16 = lane & 15, kq = lane >> 4, sh = 3 * (kDepth - level);
+    const int64_t Rx = (int64_t)Gx * 8, Ry = (int64_t)Gy * 8;
+    int64_t i0 = (blockIdx.x * (int64_t)(kBlock / 64) + wave) * 64 * chunks;
+    const int64_t iend = i0 + (int64_t)chunks * 64 < n ? i0 + (int64_t)chunks * 64 : n;
+    float4 qn[4];   // point n16 of each group (four lanes read the same record)
+    int32_t jn = 0;
+    uint64_t kn = 0;
+    auto fetch = [&](int64_t c0) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int64_t i = c0 + 16 * g + n16;
+            qn[g] = ps[i < n ? i : n - 1];
+        }
+        const int64_t i = c0 + lane < n ? c0 + lane : n - 1;
+        jn = perm[i];
+        if constexpr (!DENSE) kn = keys[i] >> sh;
+    };
+    if (i0 < iend) fetch(i0);
+    const float is = (float)inv_sigma;
+    float a[8];
+    float cx = 0.f, cy = 0.f, cz = 0.f;
+    uint64_t staged = ~0ull;   // the cell whose coefficients a holds
+    int64_t cend = -1;         // DENSE: its end
+    for (; i0 < iend; i0 += 64) {
+        const int64_t i1 = i0 + 64 < iend ? i0 + 64 : iend;
+        float4 q[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) q[g] = qn[g];
+        const int32_t jo = jn;
+        const uint64_t mine = kn;
+        if (i1 < iend) fetch(i1);
+        float u = 0.f;
+        for (int64_t s0 = i0; s0 < i1;) {
+            uint64_t m;
+            int64_t e;
+            if constexpr (DENSE) {
+                m = s0 < cend ? staged : keys[s0] >> sh;
+            } else {
+                const int l = (int)(s0 - i0);
+                m = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), l) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)mine, l);
+            }
+            if (m != staged) {
+                const int kx = (int)compact3(m >> 2), ky = (int)compact3(m >> 1), kz = (int)compact3(m);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int az = (n16 >> 2) + 4 * (t >> 1), ay = (n16 & 3) + 4 * (t & 1);
+                    const float *row = C + (((int64_t)kz * 8 + az) * Ry + (int64_t)ky * 8 + ay) * Rx + (int64_t)kx * 8;
+                    a[2 * t] = row[kq];
+                    a[2 * t + 1] = row[kq + 4];
+                }
+                cx = (float)(lox + (kx + 0.5) * cell);
+                cy = (float)(loy + (ky + 0.5) * cell);
+                cz = (float)(loz + (kz + 0.5) * cell);
+                staged = m;
+            }
+            if constexpr (DENSE) {
+                // past the end that is known (a search ends at the run's end): look again; the
+                // cell holds point s0, so its end lies past s0
+                if (s0 >= cend) {
+                    const int kx = (int)compact3(m >> 2), ky = (int)compact3(m >> 1), kz = (int)compact3(m);
+                    cend = cells.at ? (int64_t)cells.at[((int64_t)kz * Gy + ky) * Gx + kx].z : run_end(keys, s0, i1, sh);
+                }
+                e = cend < i1 ? cend : i1;
+            } else e = s0 + __popcll(__ballot(mine == m && i0 + lane >= s0 && i0 + lane < i1));
+            const int g0 = __builtin_amdgcn_readfirstlane((int)(s0 - i0) >> 4),
+                      g1 = __builtin_amdgcn_readfirstlane((int)(e - 1 - i0) >> 4);
+            float v[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                v[g] = 0.f;
+                if (g < g0 || g > g1) continue;
+                const float X = (q[g].x - cx) * is, Y = (q[g].y - cy) * is, Z = (q[g].z - cz) * is;
+                const float X2 = X * X, Z2 = Z * Z, Z4 = Z2 * Z2;
+                const float b0 = (kq & 1 ? X : 1.f) * (kq & 2 ? X2 : 1.f), b1 = b0 * (X2 * X2);
+                f32x4 d[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * t], b0, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * t + 1], b1, d[t], 0, 0, 0);
+                }
+                float lo = d[1][3], hi = d[3][3];
+#pragma unroll
+                for (int r = 6; r >= 0; --r) {
+                    lo = fmaf(lo, Y, d[r >> 2][r & 3]);
+                    hi = fmaf(hi, Y, d[2 + (r >> 2)][r & 3]);
+                }
+                v[g] = (kq & 1 ? Z : 1.f) * (kq & 2 ? Z2 : 1.f) * fmaf(hi, Z4, lo);
+            }
+            // the four kq of a point, halving the lanes and the groups together: lane 16 g + n
+            // gets point n of group g
+            const bool h2 = (kq & 2) != 0, h1 = (kq & 1) != 0;
+            const float r0 = (h2 ? v[2] : v[0]) + __shfl_xor(h2 ? v[0] : v[2], 32, 64);
+            const float r1 = (h2 ? v[3] : v[1]) + __shfl_xor(h2 ? v[1] : v[3], 32, 64);
+            const float r = (h1 ? r1 : r0) + __shfl_xor(h1 ? r0 : r1, 16, 64);
+            if (i0 + lane >= s0 && i0 + lane < e) u = r;
+            s0 = e;
+        }
+        if (i0 + lane < i1) u_out[jo] = u;
     }
 }
 
@@ -1874,8 +2004,8 @@ int launch_p2m_l2p(msp_tree *t, const FgtPlan &pl, double inv_sigma, bool l2p, c
                            t->geo.lo[2], pl.cell, inv_sigma, A, ga.stage ? t->ps.as<float4>() : nullptr);
     } else {
         // every point's sum straight to input order, flags and self term afterwards; four
-        // points per lane once that still makes sixteen wavefronts per compute unit, then
-        // more runs per wavefront while it does
+        // points per lane (p = 8: dense cells) once that still makes sixteen wavefronts per
+        // compute unit, then more runs per wavefront while it does
         const int bw = P <= 12 ? kBlock / 64 : 1;
         auto launch = [&](auto kern, int npt) {
             const int64_t most = t->n / (64 * npt * 4096);
@@ -1885,7 +2015,9 @@ int launch_p2m_l2p(msp_tree *t, const FgtPlan &pl, double inv_sigma, bool l2p, c
                                pl.level, pl.G[0], pl.G[1], pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell,
                                inv_sigma, C, chunks, ga.u_out);
         };
-        if (t->n >= 4 * 64 * 4096) launch(k_l2p<P, 4>, 4);
+        const bool many = t->n >= 4 * 64 * 4096;
+        if constexpr (P == 8) launch(many ? k_l2p_mfma8<true> : k_l2p_mfma8<false>, 1);
+        else if (many) launch(k_l2p<P, 4>, 4);
         else launch(k_l2p<P, 1>, 1);
         // (the target flags and the self term follow in fgt_forward_grid)
     }

@@ -291,7 +291,7 @@ k_node_moments(int64_t v0, int64_t v1, int level, const int32_t *nfirst, const i
     constexpr int RP = (P2 + 63) / 64;                  // (ay, az) rows per lane
     constexpr bool MX = P == 8;                         // P2M on the matrix cores
     constexpr bool ILP = P == 1 || P == 2 || P == 4;
-    constexpr int STR = MX ? 24 : ILP ? 4 : 3 * P + 1;  // staged floats per point
+    constexpr int STR = MX ? 25 : ILP ? 4 : 3 * P + 1;  // staged floats per point
     constexpr int PR = P + 1;                           // padded row of a child block
     // about 4.5 KB of shift buffers, so that the wave's LDS stays near 8 KB and four
     // waves fit on each SIMD
@@ -366,32 +366,35 @@ k_node_moments(int64_t v0, int64_t v1, int level, const int32_t *nfirst, const i
             const int ax = mr >> 1, aylo = mr & 1, azc = mr & 7, ayh = mr >> 3;
             f32x4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
             int owner = 0;
-            float4 nxt = make_float4(0.f, 0.f, 0.f, 0.f);
+            // the next chunk's point as it lies in memory: nothing waits for it before it is
+            // staged (past the list: a point of the node, with weight 0)
+            float4 nxt;
             auto fetch = [&](int32_t c0) {
                 const int32_t j = c0 + lane;
-                nxt = make_float4(0.f, 0.f, 0.f, 0.f);   // past the list: weight 0
+                int32_t i = nf;
                 if (j < total) {
                     while (part_end[owner] <= j) ++owner;
-                    const float4 q = ps[part_first[owner] + j];
-                    nxt = make_float4(((q.x - (float)cx) * (float)inv_sigma), ((q.y - (float)cy) * (float)inv_sigma),
-                                      ((q.z - (float)cz) * (float)inv_sigma), q.w);
+                    i = part_first[owner] + j;
                 }
+                nxt = ps[i];
             };
             __syncthreads();   // part_first / part_end written above
             fetch(0);
             for (int32_t c0 = 0; c0 < total; c0 += 64) {
                 __syncthreads();
                 {
+                    const float X = (nxt.x - (float)cx) * (float)inv_sigma, Y = (nxt.y - (float)cy) * (float)inv_sigma,
+                                Z = (nxt.z - (float)cz) * (float)inv_sigma;
                     float *r = pts + lane * STR;
-                    float xp = 1.f, yp = 1.f, wz = nxt.w;
+                    float xp = 1.f, yp = 1.f, wz = c0 + lane < total ? nxt.w : 0.f;
 #pragma unroll
                     for (int k = 0; k < 8; ++k) {
                         r[k] = xp;
                         r[8 + k] = yp;
                         r[16 + k] = wz;
-                        xp *= nxt.x;
-                        yp *= nxt.y;
-                        wz *= nxt.z;
+                        xp *= X;
+                        yp *= Y;
+                        wz *= Z;
                     }
                 }
                 __syncthreads();

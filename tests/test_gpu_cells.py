@@ -87,6 +87,28 @@ def test_padded_translation_tiles(p, m2l):
     tree.close()
 
 
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 48, 63, 64, 65, 257, 5001, 1048575, 1048577])
+def test_l2p_runs(n):
+    """The L2P at p = 8 on runs that end inside a group of 16 or of 64 points, cells of one
+    point and of thousands, keys per lane and cells from the table: small cells (half a cell
+    is 0.05 sigma), so that the series' tails are far below the rounding of 64 float32 terms,
+    2e-6."""
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(n, extent=(300.0, 300.0, 300.0), sigma=200.0, seed=906 + n)
+    wl.w[:] = np.maximum(wl.w, 1)
+    if n > 4:   # a cell that holds many
+        for v in (wl.x, wl.y, wl.z):
+            v[n // 2:n // 2 + n // 4] = np.float32(150.5) + np.float32(0.01) * v[n // 2:n // 2 + n // 4]
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    print(f"l2p runs n={n}", flush=True)
+    u = tree.forward(d["w"], None, sigma=wl.sigma, p=8, level=4, route="fgt").cpu().numpy()
+    pick = np.arange(n) if n < 300 else np.random.default_rng(n).permutation(n)[:100]
+    ref = oracle.attraction(wl, pick)
+    assert rel_err(u[pick], ref).max() <= 2e-6
+    tree.close()
+
+
 def test_batch_layouts_alternate():
     """Calls of one batch with other sigmas, orders and tiles in turn, replayed: each finds the
     tables and cleared cells of its own plan.  The expansions are summed in one order, so a
