@@ -2091,10 +2091,6 @@ __device__ inline int find_pop(const int64_t *off, int npop, int64_t x) {
     return lo;
 }
 
-// The batched expansion passes run beside the P2P, which keeps the vector units busy: a
-// pass's wavefronts, the longer of the two chains of launches, issue first.
-__device__ inline void ahead_of_p2p() { __builtin_amdgcn_s_setprio(3); }
-
 __global__ void k_bops(FgtBatchPlan bp) {
     const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (g >= bp.n_ops) return;
@@ -2506,7 +2502,6 @@ __device__ void p2m_cells_group(const FgtBatchPlan &bp, int64_t r0, int64_t nsma
 // wavefront (four wavefronts per block, each on its own cells).
 template <int P>
 __global__ void __launch_bounds__(256) k_bp2m(FgtBatchPlan bp) {
-    ahead_of_p2p();
     __shared__ float4 stage[4][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t wid = (int64_t)blockIdx.x * 4 + wave, nw = (int64_t)gridDim.x * 4;
@@ -2527,7 +2522,6 @@ __global__ void __launch_bounds__(256) k_bp2m(FgtBatchPlan bp) {
 }
 
 __global__ void __launch_bounds__(64) k_bm2l(FgtBatchPlan bp, int pass) {
-    ahead_of_p2p();
     const int64_t g = blockIdx.x;
     const int k = find_pop(bp.tile_off[pass], bp.npop, g);
     const FgtPop &f = bp.pops[k];
@@ -2546,7 +2540,6 @@ __global__ void __launch_bounds__(64) k_bm2l(FgtBatchPlan bp, int pass) {
 // x pass from the cell-major moments, z pass into the cell-major Taylor grid
 template <int PASS>
 __global__ void __launch_bounds__(256) k_bm2l_gemm(FgtBatchPlan bp) {
-    ahead_of_p2p();
     extern __shared__ float sm[];
     const int64_t g = blockIdx.x;
     const int k = find_pop(bp.tile_off[PASS], bp.npop, g);
@@ -2774,7 +2767,6 @@ __device__ void l2p_cells_group(const FgtBatchPlan &bp, int64_t r0, int64_t nsma
 // wavefront (four wavefronts per block, each on its own cells).
 template <int P>
 __global__ void __launch_bounds__(256) k_bl2p(FgtBatchPlan bp) {
-    ahead_of_p2p();
     constexpr int SC = P * (P * P + 4) > 256 ? P * (P * P + 4) : 256;   // slice buffer, or 64 float4
     __shared__ __align__(16) float sC[4][SC];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -2800,7 +2792,6 @@ __global__ void __launch_bounds__(256) k_bl2p(FgtBatchPlan bp) {
 // population's records f.rec + i * stride + slot (key order i).
 template <int P>
 __global__ void __launch_bounds__(64) k_bl2p_grad(FgtBatchPlan bp, int stride, int slot, int want_lap) {
-    ahead_of_p2p();
     constexpr int P3 = P * P * P;
     __shared__ float sC[P3];
     const int lane = threadIdx.x;
