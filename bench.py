@@ -42,7 +42,7 @@ def m2p_flops(p):        # Hermite rows (3 p recurrence steps) and the p^3 contr
 # phase -> kernel it times (one kernel per launch of the phase)
 KERNEL_OF_PHASE = {"sort_scatter": "k_rs_scatter", "sort_hist": "k_rs_hist", "sort_runs": "k_seg_sort",
                    "p2m": "k_p2m_mfma8",
-                   "l2p": "k_l2p", "m2l_x": "k_m2l_gemm", "m2l_y": "k_m2l_gemm",
+                   "l2p": "k_l2p_mfma8", "m2l_x": "k_m2l_gemm", "m2l_y": "k_m2l_gemm",
                    "m2l_z": "k_m2l_gemm", "morton": "k_morton", "stage": "k_stage",
                    "partner": "k_partner", "partner_direct": "k_partner_direct",
                    "partner_wave": "k_partner_wave",
@@ -60,7 +60,8 @@ def _algorithmic(phase, ctx):
         # p = 8: moments as a matrix-core product (k_p2m_mfma8)
         return ("mfma" if p == 8 else "alu"), "TFLOP/s", 2.0 * p3 * ns
     if phase == "l2p":
-        return "alu", "TFLOP/s", 2.0 * p3 * nt
+        # p = 8: the sums over ax as a matrix-core product (k_l2p_mfma8)
+        return ("mfma" if p == 8 else "alu"), "TFLOP/s", 2.0 * p3 * nt
     if phase in ("m2l_x", "m2l_y", "m2l_z"):
         G = ctx["grid"]
         k = {"m2l_x": 0, "m2l_y": 1, "m2l_z": 2}[phase]
