@@ -629,6 +629,7 @@ __device__ inline void split_bf16(const float *src, int stride, bf16x8 &hi, bf16
 // offset, row and column) and sweeps the r columns in 16-wide MFMA tiles
 // (v_mfma_f32_16x16x4f32, same lane layout as above).  LDS: RT x (U + 1) floats of
 // In and (2G - 1) p^2 floats of T (dynamic).
+constexpr size_t kTileLds = 64 * 1024;   // LDS that a tile may take
 constexpr int kOpStr = 80;   // floats of an 8 x 8 operator block in LDS (p = 8)
 // The largest cell offset that a tile of two-cell column blocks meets (p = 8).
 __host__ __device__ inline int m2l_reach(int G, int band) { return band < G - 2 ? band + 1 : G - 1; }
@@ -3147,9 +3148,12 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
     if (!t->gridA.fixed) {
         int band[3];
         for (int k = 0; k < 3; ++k) band[k] = m2l_band(p, step, pl.G[k]);
-        // cells of few points on average: many may be empty
-        const bool sparse = p == 8 && !valu && !bf16x3 && ncell >= 4096 && t->n < 64 * ncell &&
-                            pl.G[0] <= 64 && pl.G[1] <= 64 && pl.G[2] <= 64;
+        // cells of few points on average: many may be empty.  Every pass has to run on the
+        // banded tile: the passes for tiles that do not fit in LDS read all cells of a row,
+        // also those that a masked pass before them has left unwritten
+        bool sparse = p == 8 && !valu && !bf16x3 && ncell >= 4096 && t->n < 64 * ncell;
+        for (int k = 0; k < 3; ++k)
+            sparse = sparse && pl.G[k] <= 64 && m2l_gemm_lds(8 * pl.G[k], pl.G[k], 8, 16, band[k]) <= kTileLds;
         MSP_TRY(cell_tables(t, pl, sparse ? band : nullptr, masks, s));
         ga.cells = CellTable{t->cell_pts.as<int4>(), t->cell_gen};
         ga.sparse = sparse;

@@ -151,3 +151,32 @@ def test_batch_layouts_alternate():
         for got, want in zip(run(b, call, back), own[call, back]):
             torch.testing.assert_close(got, want, rtol=0, atol=0)
     b.close()
+
+
+@pytest.mark.parametrize("extent", [(240.0, 640.0, 80.0), (640.0, 240.0, 80.0), (240.0, 80.0, 640.0)])
+def test_masks_where_a_tile_may_not_fit(extent):
+    """Cells far smaller than sigma along 64 cells: nearly every pair of cells translates, so
+    the tile of that axis takes more LDS than those of the others.  Whatever passes run, none
+    reads what a pass that skips cells has not written: every grid entry is NaN beforehand."""
+    import torch
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(2000, extent=(1.0, 1.0, 1.0), sigma=125.0, seed=907)
+    half = wl.n // 2
+    for v, e in zip((wl.x, wl.y, wl.z), extent):     # clusters at opposite ends of the grid
+        v[:] = v * np.float32(0.1 * e)
+        v[half:] += np.float32(0.9 * e)
+        v[0], v[-1] = 0.0, e
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    kw = dict(sigma=wl.sigma, p=8, level=6, route="fgt")
+    print(f"masks extent {extent} grid {tree.plan(**kw)['grid']}", flush=True)
+    ws = torch.empty(tree.forward_query(**kw), dtype=torch.uint8, device="cuda")
+    ref = tree.forward_ws(d["w"], ws, d["tgt"], **kw).cpu().numpy()
+    tree.forward(torch.full_like(d["w"], float("nan")), d["tgt"], m2l="valu", **kw)   # (writes all of the grids)
+    for rep in range(2):
+        u = tree.forward(d["w"], d["tgt"], **kw).cpu().numpy()
+        np.testing.assert_array_equal(u, ref)
+    tgt = np.nonzero(wl.a > 0)[0]
+    sel = tgt[synth.sample_indices(tgt.size, 64, seed=908)]
+    assert rel_err(u[sel], oracle.attraction(wl, sel)).max() <= 1e-4
+    tree.close()
