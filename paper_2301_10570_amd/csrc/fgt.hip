@@ -2044,7 +2044,8 @@ template <int P>
 int launch_l2p_grad(msp_tree *t, const FgtPlan &pl, double inv_sigma, const float *C, float *out,
                     int stride, int want_lap, hipStream_t s) {
     const int64_t ncell = (int64_t)pl.G[0] * pl.G[1] * pl.G[2];
-    const CellTable cells{t->cell_level == pl.level ? t->cell_pts.as<int4>() : nullptr, t->cell_gen};
+    const bool made = t->cell_level == pl.level && !t->gridA.fixed && !capturing(s);
+    const CellTable cells{made ? t->cell_pts.as<int4>() : nullptr, t->cell_gen};
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k_l2p_grad<P>), dim3((unsigned)ncell), dim3(kBlock), 0, s,
                        t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), cells, pl.level, pl.G[0], pl.G[1],
                        pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell, inv_sigma, C, out,
@@ -3143,9 +3144,11 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
     const bool valu = (prm->flags & MSP_M2L_VALU) != 0;
     const bool bf16x3 = (prm->flags & MSP_M2L_BF16X3) != 0;
     PassMask masks[3];
-    // (the calls that run in a caller's workspace search for the cells: their memory was
-    // counted without the table)
-    if (!t->gridA.fixed) {
+    // The calls that run in a caller's workspace search for the cells: their memory was
+    // counted without the table.  So do calls that are recorded into a graph, whose replays
+    // may follow another build or level: with a table of other points the cells would come
+    // out empty and the L2P, which goes from a cell's end to the next, might not end.
+    if (!t->gridA.fixed && !capturing(s)) {
         int band[3];
         for (int k = 0; k < 3; ++k) band[k] = m2l_band(p, step, pl.G[k]);
         // cells of few points on average: many may be empty.  Every pass has to run on the

@@ -531,6 +531,18 @@ inline unsigned grid_for(int64_t n, int block) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
+// Whether `s` is recording into a caller's graph.  What such a call launches runs when the
+// graph is replayed, at times the handle does not see: a table that it made must not be
+// noted as made, and a table that an eager call made may be another one by then.
+inline bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 }  // namespace msp
 
 // ---------------------------------------------------------------------------------------

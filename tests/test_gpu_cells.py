@@ -180,3 +180,42 @@ def test_masks_where_a_tile_may_not_fit(extent):
     sel = tgt[synth.sample_indices(tgt.size, 64, seed=908)]
     assert rel_err(u[sel], oracle.attraction(wl, sel)).max() <= 1e-4
     tree.close()
+
+
+@pytest.mark.parametrize("kind,n,p", [("blobs", 16384, 8), ("box", 1048576 + 77, 8), ("box", 1048576 + 77, 6),
+                                      ("box", 30011, 10)])
+def test_recorded_call_and_the_table(kind, n, p):
+    """A forward recorded into a caller's graph finds its cells at each replay: the eager call
+    after the recording makes its own table, and a replay after another build (other points in
+    the same box and buffers) gives the sums of those points."""
+    import torch
+    import paper_2301_10570_amd as msp
+    wl = _make(kind, n)
+    d = to_dev(wl)
+    g = torch.Generator().manual_seed(n)
+    other = d["x"][torch.randperm(wl.n, generator=g).cuda()].contiguous()   # the same extent
+    kw = dict(sigma=wl.sigma, p=p, route="fgt")
+    print(f"recorded {kind} n={wl.n} p={p}", flush=True)
+    tree = msp.Tree().build(other, d["y"], d["z"])
+    ref_other = tree.forward(d["w"], d["tgt"], **kw).cpu().numpy()
+    tree.build(d["x"], d["y"], d["z"])
+    ref = tree.forward(d["w"], d["tgt"], **kw).cpu().numpy()
+    tree.build(other, d["y"], d["z"])
+    tree.build(d["x"], d["y"], d["z"])
+    out = torch.zeros_like(d["w"])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tree.forward(d["w"], d["tgt"], out=out, **kw)
+    np.testing.assert_array_equal(tree.forward(d["w"], d["tgt"], **kw).cpu().numpy(), ref)
+    for rep in range(2):
+        out.zero_()
+        graph.replay()
+        np.testing.assert_array_equal(out.cpu().numpy(), ref)
+    tree.build(other, d["y"], d["z"])
+    for rep in range(2):
+        out.zero_()
+        graph.replay()
+        np.testing.assert_array_equal(out.cpu().numpy(), ref_other)
+        np.testing.assert_array_equal(tree.forward(d["w"], d["tgt"], **kw).cpu().numpy(), ref_other)
+    tree.close()
