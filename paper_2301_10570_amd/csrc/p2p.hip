@@ -267,10 +267,16 @@ int direct_route_lists(msp_tree *t, const msp_fgt_params *prm, hipStream_t s) {
     if (t->n == 0) return MSP_OK;
     if (t->lists_valid && t->list_sigma == prm->sigma && t->list_cutoff == prm->cutoff_sigmas) return MSP_OK;
     const int64_t nn = t->n_nodes;
+    // The lists of a recorded call exist only after a replay: they are not noted as made.
+    // Without their lengths (which msp_fgt_forward_query counts) the call is refused.
+    const bool recorded = capturing(s);
+    if (recorded && !(t->counts_valid && t->list_sigma == prm->sigma && t->list_cutoff == prm->cutoff_sigmas))
+        return fail(MSP_EHIP, "the interaction lists of sigma %g are not there and cannot be counted in a call that is "
+                    "recorded into a graph", (double)prm->sigma);
     if (nn <= kRowNodes) {
         PhaseScope ps(&t->timing, PH_LISTS, s);
         t->lists_valid = false;
-        t->counts_valid = false;   // the offsets of compact lists are not written here
+        t->counts_valid = recorded;   // the offsets of compact lists are not written here
         MSP_TRY(t->list_cnt.ensure(nn * 4));
         MSP_TRY(t->list_idx.ensure(nn * nn * 4));
         MSP_TRY(walk_lists(t, prm, nn, t->list_cnt.as<int32_t>(), t->list_idx.as<int32_t>(), s));
@@ -282,7 +288,7 @@ int direct_route_lists(msp_tree *t, const msp_fgt_params *prm, hipStream_t s) {
         MSP_TRY(direct_route_fill(t, prm, s));
         t->list_stride = 0;
     }
-    t->lists_valid = true;
+    t->lists_valid = !recorded;
     return MSP_OK;
 }
 

@@ -150,3 +150,43 @@ def test_all_pairs(nt, ns):
     pick = np.unique(np.concatenate([np.arange(min(nt, 70)), np.arange(max(0, nt - 70), nt)]))
     assert rel_err(u[pick], oracle.gauss_sum(t[pick], s, w, 80.0)).max() <= 1e-5
     assert np.all(np.isfinite(u)) and np.all(u > 0)
+
+
+@pytest.mark.parametrize("n", [300, 5003, 40000])
+def test_lists_are_not_made_in_a_recorded_call(n):
+    """A direct-route call whose lists are not there yet is refused while it is recorded, and
+    leaves the handle as it was; with their lengths counted (the query) or the lists there it
+    is recorded, and neither it nor the eager calls between its replays take the other's."""
+    import torch
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(n, extent=(900.0, 900.0, 700.0), sigma=60.0, seed=4100 + n)
+    d = to_dev(wl)
+    kw = dict(sigma=wl.sigma, route="direct")
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    print(f"recorded direct call n={n} nodes={tree.info()['n_nodes']}", flush=True)
+    ref = tree.forward(d["w"], d["tgt"], **kw).cpu().numpy()
+    out = torch.zeros_like(d["w"])
+    tree.build(d["x"], d["y"], d["z"])       # the buffers are there, the lists are not
+    torch.cuda.synchronize()
+    empty = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(empty):
+        out.fill_(1.0)
+        with pytest.raises(msp.MspError):
+            tree.forward(d["w"], d["tgt"], out=out, **kw)
+    for counted in (True, False):
+        if counted:
+            tree.forward_query(**kw)
+        else:
+            np.testing.assert_array_equal(tree.forward(d["w"], d["tgt"], **kw).cpu().numpy(), ref)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            tree.forward(d["w"], d["tgt"], out=out, **kw)
+        for rep in range(3):
+            if rep or not counted:
+                np.testing.assert_array_equal(tree.forward(d["w"], d["tgt"], **kw).cpu().numpy(), ref)
+            out.zero_()
+            graph.replay()
+            np.testing.assert_array_equal(out.cpu().numpy(), ref)
+        tree.build(d["x"], d["y"], d["z"])
+    tree.close()
