@@ -4,16 +4,16 @@
 // NW wavefronts share one target leaf (sh is private to each wave).  The list is cut
 // into windows of at most 64 entries, about sixteen of them (p2p_window), which go round
 // the waves; the source points of a window form one sequence, staged in LDS in chunks of
-// 128.  Sums of at most 32 terms are float32 and are added in float64, so the result does
-// not depend on how many waves share the leaf (the order of the float64 additions moves
-// it by 2^-53).  exp(-d^2/sigma^2) is evaluated as exp2(-d^2) of coordinates from the
+// 128.  At most 32 terms are added one after another in float32, and in the matrix form
+// sixteen such sums in pairs; the rest is float64, so the result does not depend on how many
+// waves share the leaf (the order of the float64 additions moves it by 2^-53).  exp(-d^2/sigma^2) is evaluated as exp2(-d^2) of coordinates from the
 // leaf centre scaled by k_scale = sqrt(log2(e)) / sigma.
 //
 // Two forms, by the size of the leaf against sigma (see kMatrixReach):
-//   p2p_block_matrix   exp2(-d^2) = exp2(-t^2) exp2(2 t.s) exp2(-s^2): the products t.s of
-//       16 targets and 16 sources come from one matrix instruction, the other two factors
-//       are one value per target and per source, and a pair costs one exponential and
-//       one multiply-add on the vector unit in place of eight instructions.
+//   p2p_block_matrix   exp2(-d^2) = exp2(-t^2) exp2(2 t.s - s^2): the exponents 2 t.s - s^2 of
+//       16 targets and 16 sources come from one matrix instruction, the other factor is one
+//       value per target, and a pair costs one exponential and one multiply-add on the
+//       vector unit in place of eight instructions.
 //   p2p_block_vector   the differences themselves.  T = 1, 2 or 4 targets per lane (nt up
 //       to 9, 18, 64), the lanes in G = floor(64 / ceil(nt / T)) groups, each taking
 //       every G-th source: nine tenths of the lanes' targets are there (one target per
@@ -341,6 +341,13 @@ __device__ inline double exp2_near(double x) {
     return ldexp(e, (int)n);
 }
 
+// exp2(-t^2) of point i of the leaf about ct
+__device__ inline double target_factor(const LeafSet &L, int32_t i, const float *ct) {
+    const float4 q = ld_global4(L.ps, i);
+    const double x = (q.x - ct[0]) * L.k_scale, y = (q.y - ct[1]) * L.k_scale, z = (q.z - ct[2]) * L.k_scale;
+    return exp2_near(-(x * x + y * y + z * z));
+}
+
 template <int CTRL>
 __device__ inline float dpp(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
@@ -348,9 +355,10 @@ __device__ inline float dpp(float v) {
 
 // The same by matrix products, M = ceil(nt / 16) tiles of 16 targets; the sums lack the
 // factors exp2(-t^2).  Lane l holds of a tile (v_mfma_f32_16x16x4f32): operand A target
-// l % 16, operand B source l % 16, both their component l / 16; result source l % 16 and
-// targets 4 (l / 16) .. + 3.  The fourth component takes what of a far source's s^2 would
-// underflow: its weight carries exp2(-min(s^2, 100)), the product -(s^2 - 100).
+// l % 16, operand B source l % 16, both their component l / 16, the fourth being -1 and
+// s^2; result source l % 16 and targets 4 (l / 16) .. + 3.  2 t.s - s^2 = t^2 - d^2 is at
+// most kMatrixReach^2 and never underflows before -d^2 does, so a weight keeps its range
+// (up to 2^127; see p2p_leaf).
 template <int NW, int M>
 __device__ inline double p2p_block_matrix(const LeafSet &L, const int32_t *lst, int len, const float ct[3], int32_t tf,
                                           int nt, int wave, P2PShared &sh) {
@@ -372,9 +380,8 @@ __device__ inline double p2p_block_matrix(const LeafSet &L, const int32_t *lst, 
         for (int h = 0; h < kP2PChunk / 64; ++h) {
             const float x = (nxt[h].x - ct[0]) * L.k_scale, y = (nxt[h].y - ct[1]) * L.k_scale,
                         z = (nxt[h].z - ct[2]) * L.k_scale;
-            const float s2 = fmaf(x, x, fmaf(y, y, z * z)), near = fminf(s2, 100.f);
-            sh.sp[64 * h + lane] = make_float4(x, y, z, s2 - near);
-            sh.sw[64 * h + lane] = nid[h] < 0 ? 0.f : nxt[h].w * __builtin_amdgcn_exp2f(-near);
+            sh.sp[64 * h + lane] = make_float4(x, y, z, fmaf(x, x, fmaf(y, y, z * z)));
+            sh.sw[64 * h + lane] = nid[h] < 0 ? 0.f : nxt[h].w;
         }
     };
     auto use = [&](int left, bool own, bool flush) {
@@ -443,17 +450,23 @@ __device__ inline void p2p_leaf(const LeafSet &L, const LeafTask &t, int wave, P
     sh.sid[kP2PChunk + lane] = kNoTarget;
     for (int t0 = 0; t0 < tn; t0 += 64) {
         const int nt = __builtin_amdgcn_readfirstlane(tn - t0 < 64 ? tn - t0 : 64);
-        double s;
+        double s = 0.0;
 #define MSP_P2P(F, K) F<NW, K>(L, lst, len, ct, tf + t0, nt, wave, sh)
+        bool again = false;
         if (matrix) {
             if (nt <= 16) s = MSP_P2P(p2p_block_matrix, 1);
             else if (nt <= 32) s = MSP_P2P(p2p_block_matrix, 2);
             else if (nt <= 48) s = MSP_P2P(p2p_block_matrix, 3);
             else s = MSP_P2P(p2p_block_matrix, 4);
-        } else {
+            // w exp2(t^2 - d^2) of weights beyond 2^127 / 2 leaves float32 where w exp2(-d^2) does
+            // not: these by differences
+            again = __ballot(lane < nt && !(fabs(s) <= 3.4028234663852886e38)) != 0;
+        }
+        if (!matrix || again) {
             if (nt <= 9) s = MSP_P2P(p2p_block_vector, 1);
             else if (nt <= 18) s = MSP_P2P(p2p_block_vector, 2);
             else s = MSP_P2P(p2p_block_vector, 4);
+            if (again && lane < nt) s /= target_factor(L, tf + t0 + lane, ct);
         }
 #undef MSP_P2P
         if constexpr (NW > 1) {
@@ -468,11 +481,7 @@ __device__ inline void p2p_leaf(const LeafSet &L, const LeafTask &t, int wave, P
         }
         if (wave == 0 && lane < nt) {
             const int32_t ti = tf + t0 + lane;
-            if (matrix) {
-                const float4 q = ld_global4(L.ps, ti);
-                const double x = (q.x - ct[0]) * L.k_scale, y = (q.y - ct[1]) * L.k_scale, z = (q.z - ct[2]) * L.k_scale;
-                s *= exp2_near(-(x * x + y * y + z * z));
-            }
+            if (matrix) s *= target_factor(L, ti, ct);
             L.usort[ti] = ld_global(L.tflag, ti) ? (float)s : 0.f;
         }
         if constexpr (NW > 1) __syncthreads();   // red is free again

@@ -190,3 +190,31 @@ def test_lists_are_not_made_in_a_recorded_call(n):
             np.testing.assert_array_equal(out.cpu().numpy(), ref)
         tree.build(d["x"], d["y"], d["z"])
     tree.close()
+
+
+def test_leaf_sums_take_weights_of_any_size():
+    """Leaves small against sigma (scaled reach 0.95): weights of 2^-50 at 8.6 scaled units, whose
+    terms of 2^-124 are normal numbers while the weight times exp2(-s^2) is not, and one of 3e38
+    beside its targets, whose sum is finite while w exp2(2 t.s - s^2) is not.  Tolerances: the
+    rounding of coordinates of 9.5 units, twice in d^2 = 74, and of s^2, 5e-5 of a far sum; 2e-6
+    of a near one."""
+    import paper_2301_10570_amd as msp
+    rng = np.random.default_rng(50)
+    near = 195.0 + 4.0 * rng.random((12, 3))          # towards the far corner of cell 3 of 32
+    far = 420.0 + 10.0 * rng.random((9, 3))           # the middle of cell 8
+    pts = np.concatenate([[[0.0] * 3], near, far, [[1599.99] * 3]]).astype(np.float32)
+    tree = msp.build_tree(*(_T(pts[:, k]) for k in range(3)), leaf_max=8, max_depth=5)
+    sigma, kw = 54.75, dict(sigma=54.75, route="direct", cutoff_sigmas=0.0)
+    pick = np.arange(1, 13)
+    w = np.zeros(len(pts), dtype=np.float32)
+    w[13:22] = rng.integers(1, 4, 9) * np.float32(2.0 ** -50)
+    u = tree.forward(_T(w), None, **kw).cpu().numpy()[pick]
+    ref = oracle.gauss_sum(pts[pick], pts, w, sigma)
+    print("far", rel_err(u, ref).max(), flush=True)
+    assert ref.min() > 2.0 ** -126 and rel_err(u, ref).max() <= 5e-5
+    w[:] = 0.0
+    w[5] = 3e38
+    u = tree.forward(_T(w), None, **kw).cpu().numpy()[pick]
+    ref = oracle.gauss_sum(pts[pick], pts, w, sigma)
+    assert np.all(np.isfinite(u)) and rel_err(u, ref).max() <= 2e-6
+    tree.close()
