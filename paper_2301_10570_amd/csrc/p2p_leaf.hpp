@@ -323,13 +323,14 @@ __device__ inline double p2p_block_vector(const LeafSet &L, const int32_t *lst, 
     return s;
 }
 
-// Largest scaled distance of a target from its leaf's centre for the matrix form.  Its
-// error grows with the size of 2 t.s against d^2.  Measured against float64 over leaves
-// of 10 and 40 points, root mean square (largest) relative error of a sum, vector form ->
-// matrix form: reach 1: 3.6e-8 (8.5e-8) -> 3.5e-8 (7.2e-8); 1.5: 4.2e-8 (1.1e-7) ->
-// 4.2e-8 (1.2e-7); 2: 4.8e-8 (1.2e-7) -> 4.7e-8 (1.9e-7); 3: 6.5e-8 (2.7e-7) -> 8.8e-8
-// (3.4e-7).
-constexpr float kMatrixReach = 1.5f;
+// Largest scaled distance of a target from its leaf's centre for the matrix form, whose
+// error grows with the size of 2 t.s and s^2 against d^2.  Measured against float64 over
+// 512 leaves of 10 and 40 points, root mean square (largest) relative error of a sum, the
+// compensated float32 sums of differences that this replaced -> matrix form: reach 0.3:
+// 6.6e-8 (2.0e-7) -> 5.6e-8 (1.5e-7); 0.6: 8.1e-8 (2.3e-7) -> 7.6e-8 (2.3e-7); 1: 8.3e-8
+// (3.2e-7) -> 7.9e-8 (2.4e-7); 1.2: 9.2e-8 (3.8e-7) -> 9.1e-8 (2.9e-7), at 10 points 9.0e-8
+// -> 9.1e-8; 1.5 at 10 points: 1.14e-7 -> 1.19e-7.  At 1 no figure is larger.
+constexpr float kMatrixReach = 1.f;
 
 // 2^x for a small x (|x| below 127; to 1e-11): the nearest whole power, and the Taylor
 // series of the rest's exponential.
