@@ -388,8 +388,7 @@ int msp_partner_descent(msp_tree *t, const float *w, const float *a, const msp_f
 
 /* Copy an internal buffer, for pass-level checks.
  *   which 0: Hermite moment grid after P2M of the last expansion-route forward call
- *   which 1: Taylor grid after M2L of that call (in grids of 4,096 cells and more with
- *     fewer than 64 points a cell, cells without points may be left unspecified)
+ *   which 1: Taylor grid after M2L of that call
  *     layout of both: float32 [kz][az][ky][ay][kx][ax], with (kx,ky,kz) the cell's
  *     lattice coordinates inside the grid reported by msp_fgt_plan and (ax,ay,az)
  *     the coefficient multi-index (p values each);

@@ -554,6 +554,7 @@ int msp_fgt_debug_buffer(msp_tree *t, int32_t which, void *dst, size_t dst_bytes
     }
     if (!dst) return MSP_OK;
     if (dst_bytes < *bytes) return fail(MSP_EINVAL, "destination holds %zu bytes, need %zu", dst_bytes, *bytes);
+    if (which == 1) MSP_TRY(complete_taylor(t, (hipStream_t)stream));
     MSP_HIP(hipMemcpyAsync(dst, src, *bytes, hipMemcpyDeviceToDevice, (hipStream_t)stream));
     return MSP_OK;
 }

@@ -3103,6 +3103,103 @@ static int cell_tables(msp_tree *t, const FgtPlan &pl, const int *band, PassMask
     return MSP_OK;
 }
 
+// The translation: gridA (moments) to gridB (Taylor coefficients), by way of gridB and the
+// third grid.  masks: all of them or none; forward: a forward sum's (see pad below).
+static int translate(msp_tree *t, int p, const int (&G)[3], double step, uint32_t flags, const int (&band)[3],
+                     const PassMask (&masks)[3], bool forward, hipStream_t s) {
+    const bool valu = (flags & MSP_M2L_VALU) != 0, bf16x3 = (flags & MSP_M2L_BF16X3) != 0;
+    float *A = t->gridA.as<float>(), *B = t->gridB.as<float>(), *Tmp = t->ops.as<float>();
+    float *opsx = Tmp + (size_t)G[0] * G[1] * G[2] * p * p * p;
+    float *opsy = opsx + (size_t)(2 * G[0] - 1) * p * p;
+    float *opsz = opsy + (size_t)(2 * G[1] - 1) * p * p;
+    // three passes: contract x (In [Uz][Uy][Ux]), then y, then z
+    const int64_t Ux = (int64_t)G[0] * p, Uy = (int64_t)G[1] * p, Uz = (int64_t)G[2] * p;
+    struct Pass { const float *in; float *out; int64_t R; int G; const float *T; int64_t U; };
+    const Pass passes[3] = {{A, B, Uz * Uy, G[0], opsx, Ux},
+                            {B, Tmp, Ux * Uz, G[1], opsy, Uy},
+                            {Tmp, B, Uy * Ux, G[2], opsz, Uz}};
+    for (int k = 0; k < 3; ++k) {
+        const Pass &ps = passes[k];
+        const PassMask &pm = masks[k];
+        PhaseScope sc(&t->timing, PH_M2L_X + k, s);
+        if (valu) {
+            dim3 grid((unsigned)((ps.R + TR - 1) / TR), (unsigned)((ps.U + TV - 1) / TV));
+            hipLaunchKernelGGL(k_m2l_pass, grid, dim3(kBlock), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
+        } else if (bf16x3) {
+            // rows per block: enough blocks to fill the chip, at most 64, and fewer
+            // when the tile would not fit in LDS
+            int RT = 64;
+            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds_split(ps.G, RT, band[k]) > 64 * 1024))
+                RT >>= 1;
+            const size_t lds = m2l_gemm_lds_split(ps.G, RT, band[k]);
+            // p < 8 in forward sums: the tile's sums run in another order than those of the
+            // 32 x 32 tiles, whose bits the gradients keep.  (1,792 cells at p = 6: 378
+            // wavefronts that rebuilt their operands per K step took 73 us for the three
+            // passes, 17 us here.)
+            if ((p == 8 || (p < 8 && forward)) && lds <= 64 * 1024) {
+                // column groups as in the float32 passes below
+                const int64_t rows = (ps.R + RT - 1) / RT;
+                const int ngroup = ((8 * ps.G + 15) / 16 + 3) / 4;
+                const int64_t want = (1024 + rows - 1) / rows;
+                const dim3 grid((unsigned)rows, (unsigned)(want < ngroup ? want : ngroup));
+                if (RT == 64)
+                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k]);
+                else if (RT == 32)
+                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k]);
+                else
+                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k]);
+            } else {
+                dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
+                hipLaunchKernelGGL(k_m2l_pass_bf16x3, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
+            }
+        } else {
+            // rows per block: enough blocks to fill the chip, at most 64, and fewer
+            // when the tile would not fit in LDS
+            // p < 8 in forward sums: eight terms per cell (the tile for any p sums in another
+            // order, whose bits the gradients keep)
+            const int pad = p < 8 && forward ? 1 : 0;
+            const int Ut = pad ? 8 * ps.G : (int)ps.U;
+            int RT = 64;
+            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds(Ut, ps.G, p, RT, band[k]) > 64 * 1024))
+                RT >>= 1;
+            const size_t lds = m2l_gemm_lds(Ut, ps.G, p, RT, band[k]);
+            if (lds <= 64 * 1024) {
+                // column groups of four 16-wide blocks, one per wavefront, as the grid's y,
+                // only while the row tiles alone make fewer than 1024 blocks (every group
+                // stages the whole input rows)
+                const int64_t rows = (ps.R + RT - 1) / RT;
+                const int ngroup = ((Ut + 15) / 16 + 3) / 4;
+                const int64_t want = (1024 + rows - 1) / rows;
+                const int cg = want < ngroup ? (int)want : ngroup;
+                const dim3 grid((unsigned)rows, (unsigned)cg);
+                if (RT == 64)
+                    hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
+                else if (RT == 32)
+                    hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
+                else
+                    hipLaunchKernelGGL(k_m2l_gemm<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
+            } else {
+                dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
+                hipLaunchKernelGGL(k_m2l_pass_mfma, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
+            }
+        }
+        MSP_CHECK_LAUNCH();
+    }
+    return MSP_OK;
+}
+
+// The whole Taylor grid of the last call, for msp_fgt_debug_buffer: with masks it computed the
+// cells that are read.
+int complete_taylor(msp_tree *t, hipStream_t s) {
+    if (!t->taylor_partial) return MSP_OK;
+    int band[3];
+    for (int k = 0; k < 3; ++k) band[k] = m2l_band(8, t->taylor_step, t->taylor_G[k]);
+    const PassMask all[3];
+    MSP_TRY(translate(t, 8, t->taylor_G, t->taylor_step, 0, band, all, true, s));
+    t->taylor_partial = false;
+    return MSP_OK;
+}
+
 int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, const float *w,
                      const uint8_t *is_target, float *u_out, hipStream_t s) {
     const bool staged = (prm->flags & MSP_WEIGHTS_STAGED) != 0;
@@ -3144,13 +3241,13 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
     const bool valu = (prm->flags & MSP_M2L_VALU) != 0;
     const bool bf16x3 = (prm->flags & MSP_M2L_BF16X3) != 0;
     PassMask masks[3];
+    int band[3] = {0, 0, 0};
+    for (int k = 0; k < 3 && !valu; ++k) band[k] = m2l_band(p, step, pl.G[k]);
     // The calls that run in a caller's workspace search for the cells: their memory was
     // counted without the table.  So do calls that are recorded into a graph, whose replays
     // may follow another build or level: with a table of other points the cells would come
     // out empty and the L2P, which goes from a cell's end to the next, might not end.
     if (!t->gridA.fixed && !capturing(s)) {
-        int band[3];
-        for (int k = 0; k < 3; ++k) band[k] = m2l_band(p, step, pl.G[k]);
         // cells of few points on average: many may be empty.  Every pass has to run on the
         // banded tile: the passes for tiles that do not fit in LDS read all cells of a row,
         // also those that a masked pass before them has left unwritten
@@ -3165,80 +3262,11 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
         PhaseScope ps(&t->timing, PH_P2M, s);
         MSP_TRY(dispatch_p2m_l2p(t, pl, inv_sigma, false, nullptr, A, ga, s));
     }
-    // three passes: contract x (In [Uz][Uy][Ux]), then y, then z
-    const int64_t Ux = (int64_t)pl.G[0] * p, Uy = (int64_t)pl.G[1] * p, Uz = (int64_t)pl.G[2] * p;
-    struct Pass { const float *in; float *out; int64_t R; int G; const float *T; int64_t U; };
-    const Pass passes[3] = {{A, B, Uz * Uy, pl.G[0], opsx, Ux},
-                            {B, Tmp, Ux * Uz, pl.G[1], opsy, Uy},
-                            {Tmp, B, Uy * Ux, pl.G[2], opsz, Uz}};
-    for (int k = 0; k < 3; ++k) {
-        const Pass &ps = passes[k];
-        const PassMask &pm = masks[k];
-        PhaseScope sc(&t->timing, PH_M2L_X + k, s);
-        if (valu) {
-            dim3 grid((unsigned)((ps.R + TR - 1) / TR), (unsigned)((ps.U + TV - 1) / TV));
-            hipLaunchKernelGGL(k_m2l_pass, grid, dim3(kBlock), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
-        } else if (bf16x3) {
-            // rows per block: enough blocks to fill the chip, at most 64, and fewer
-            // when the tile would not fit in LDS
-            const int band = m2l_band(p, step, ps.G);
-            int RT = 64;
-            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds_split(ps.G, RT, band) > 64 * 1024))
-                RT >>= 1;
-            const size_t lds = m2l_gemm_lds_split(ps.G, RT, band);
-            // p < 8 in forward sums: the tile's sums run in another order than those of the
-            // 32 x 32 tiles, whose bits the gradients keep.  (1,792 cells at p = 6: 378
-            // wavefronts that rebuilt their operands per K step took 73 us for the three
-            // passes, 17 us here.)
-            if ((p == 8 || (p < 8 && u_out)) && lds <= 64 * 1024) {
-                // column groups as in the float32 passes below
-                const int64_t rows = (ps.R + RT - 1) / RT;
-                const int ngroup = ((8 * ps.G + 15) / 16 + 3) / 4;
-                const int64_t want = (1024 + rows - 1) / rows;
-                const dim3 grid((unsigned)rows, (unsigned)(want < ngroup ? want : ngroup));
-                if (RT == 64)
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
-                else if (RT == 32)
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
-                else
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band);
-            } else {
-                dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
-                hipLaunchKernelGGL(k_m2l_pass_bf16x3, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
-            }
-        } else {
-            // rows per block: enough blocks to fill the chip, at most 64, and fewer
-            // when the tile would not fit in LDS
-            const int band = m2l_band(p, step, ps.G);
-            // p < 8 in forward sums: eight terms per cell (the tile for any p sums in another
-            // order, whose bits the gradients keep)
-            const int pad = p < 8 && u_out ? 1 : 0;
-            const int Ut = pad ? 8 * ps.G : (int)ps.U;
-            int RT = 64;
-            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds(Ut, ps.G, p, RT, band) > 64 * 1024))
-                RT >>= 1;
-            const size_t lds = m2l_gemm_lds(Ut, ps.G, p, RT, band);
-            if (lds <= 64 * 1024) {
-                // column groups of four 16-wide blocks, one per wavefront, as the grid's y,
-                // only while the row tiles alone make fewer than 1024 blocks (every group
-                // stages the whole input rows)
-                const int64_t rows = (ps.R + RT - 1) / RT;
-                const int ngroup = ((Ut + 15) / 16 + 3) / 4;
-                const int64_t want = (1024 + rows - 1) / rows;
-                const int cg = want < ngroup ? (int)want : ngroup;
-                const dim3 grid((unsigned)rows, (unsigned)cg);
-                if (RT == 64)
-                    hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm, pad);
-                else if (RT == 32)
-                    hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm, pad);
-                else
-                    hipLaunchKernelGGL(k_m2l_gemm<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band, pm, pad);
-            } else {
-                dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
-                hipLaunchKernelGGL(k_m2l_pass_mfma, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
-            }
-        }
-        MSP_CHECK_LAUNCH();
+    MSP_TRY(translate(t, p, pl.G, step, prm->flags, band, masks, u_out != nullptr, s));
+    if (!t->gridA.fixed) {
+        t->taylor_partial = masks[0].in != nullptr;
+        std::copy(pl.G, pl.G + 3, t->taylor_G);
+        t->taylor_step = step;
     }
     if (!u_out) return MSP_OK;   // callers that evaluate the Taylor grid themselves
     {

@@ -237,6 +237,10 @@ struct msp_tree {
     bool ops_valid = false;     // M2L operator tables in ops match ops_sig (p, grid, cell / sigma)
     uint64_t ops_sig[5] = {};
     int64_t grid_bytes_valid = 0;
+    // the last call computed only part of gridB (see complete_taylor): its grid and cell / sigma
+    bool taylor_partial = false;
+    int taylor_G[3] = {};
+    double taylor_step = 0.0;
     // point range of every cell of the expansion level, and which rows of cells the
     // translation passes need (kept until the next build)
     msp::DevBuf cell_pts, cell_mask;
@@ -466,6 +470,7 @@ int plan_fgt(const msp_tree *t, const msp_fgt_params *prm, FgtPlan *plan);
 // operator tables
 void fgt_grid_bytes(const FgtPlan &pl, size_t *grid, size_t *ops);
 double rho_max_for_p(int p);
+int complete_taylor(msp_tree *t, hipStream_t s);
 int stage_inputs(msp_tree *t, const float *w, const uint8_t *is_target, hipStream_t s);
 int fgt_forward_grid(msp_tree *t, const FgtPlan &plan, const msp_fgt_params *prm, const float *w,
                      const uint8_t *is_target, float *u_out, hipStream_t s);

@@ -219,3 +219,26 @@ def test_recorded_call_and_the_table(kind, n, p):
         np.testing.assert_array_equal(out.cpu().numpy(), ref_other)
         np.testing.assert_array_equal(tree.forward(d["w"], d["tgt"], **kw).cpu().numpy(), ref_other)
     tree.close()
+
+
+@pytest.mark.parametrize("kind,n", [("blobs", 16384), ("corners", 5000)])
+def test_debug_buffers_hold_whole_grids(kind, n):
+    """The Taylor grid that the debug buffer gives after a call that skipped empty cells: every
+    cell, as the vector passes have it (1e-5 of the largest), and the moments untouched by it."""
+    import torch
+    import paper_2301_10570_amd as msp
+    wl = _make(kind, n)
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    kw = dict(sigma=wl.sigma, p=8, route="fgt")
+    print(f"debug buffers {kind} n={wl.n} grid {tree.plan(**kw)['grid']}", flush=True)
+    tree.forward(d["w"], d["tgt"], m2l="valu", **kw)
+    Av, Cv = (tree.debug_buffer(k).cpu().numpy() for k in (0, 1))
+    tree.forward(torch.full_like(d["w"], float("nan")), d["tgt"], m2l="valu", **kw)   # (writes all of the grids)
+    for rep in range(2):
+        tree.forward(d["w"], d["tgt"], **kw)
+        A, C = (tree.debug_buffer(k).cpu().numpy() for k in (0, 1))
+        np.testing.assert_array_equal(A, Av)
+        assert np.abs(C - Cv).max() <= 1e-5 * np.abs(Cv).max()
+        np.testing.assert_array_equal(tree.debug_buffer(1).cpu().numpy(), C)
+    tree.close()
