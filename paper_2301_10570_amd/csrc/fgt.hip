@@ -3153,12 +3153,15 @@ static int translate(msp_tree *t, int p, const int (&G)[3], double step, uint32_
                 hipLaunchKernelGGL(k_m2l_pass_bf16x3, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
             }
         } else {
+            // p = 5 to 7 in forward sums: the tile of eight terms per cell where it fits (64 x 64 x
+            // 13 cells, the x pass: p = 7 536 -> 204 us, 6 259 -> 162, 5 135 -> 121; below five the
+            // zeros cost more than they save: 4 55 -> 82, 3 26 -> 48).  The tile for any p sums in
+            // another order, whose bits the gradients keep
+            const int pad =
+                forward && p >= 5 && p < 8 && m2l_gemm_lds(8 * ps.G, ps.G, p, 16, band[k]) <= kTileLds ? 1 : 0;
+            const int Ut = pad ? 8 * ps.G : (int)ps.U;
             // rows per block: enough blocks to fill the chip, at most 64, and fewer
             // when the tile would not fit in LDS
-            // p < 8 in forward sums: eight terms per cell (the tile for any p sums in another
-            // order, whose bits the gradients keep)
-            const int pad = p < 8 && forward ? 1 : 0;
-            const int Ut = pad ? 8 * ps.G : (int)ps.U;
             int RT = 64;
             while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds(Ut, ps.G, p, RT, band[k]) > 64 * 1024))
                 RT >>= 1;

@@ -242,3 +242,30 @@ def test_debug_buffers_hold_whole_grids(kind, n):
         assert np.abs(C - Cv).max() <= 1e-5 * np.abs(Cv).max()
         np.testing.assert_array_equal(tree.debug_buffer(1).cpu().numpy(), C)
     tree.close()
+
+
+@pytest.mark.parametrize("p,extent", [(1, (1275.0, 1275.0, 75.0)), (3, (1275.0, 1275.0, 75.0)),
+                                      (4, (1275.0, 1275.0, 75.0)), (5, (1175.0, 1275.0, 75.0)),
+                                      (4, (300.0, 1275.0, 75.0)), (7, (1175.0, 1275.0, 75.0))])
+def test_whole_rows_where_the_padded_tile_does_not_serve(p, extent):
+    """Grids up to 128 cells wide: the tile of p terms per cell where the padded one is too large
+    or (p below five) does more work, in forward sums as in gradients: the same Taylor grid from
+    the same weights; and the vector passes to 1e-5."""
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(20000, extent=extent, sigma=96.0, seed=909)
+    for k, v in enumerate((wl.x, wl.y, wl.z)):
+        v[0], v[-1] = 0.0, extent[k] + (4.9 if k == 1 else 0.0)
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    kw = dict(sigma=wl.sigma, p=p, level=7, route="fgt")
+    print(f"wide grid p={p} {tree.plan(**kw)['grid']}", flush=True)
+    u = tree.forward(d["w"], None, **kw).cpu().numpy()
+    C = tree.debug_buffer(1).cpu().numpy()
+    v = tree.forward(d["w"], None, m2l="valu", **kw).cpu().numpy()
+    Cv = tree.debug_buffer(1).cpu().numpy()
+    assert np.abs(C - Cv).max() <= 1e-5 * np.abs(Cv).max()
+    assert rel_err(u, v).max() <= 1e-5
+    if p != 7:
+        tree.backward(d["w"], d["w"], None, want=("w",), **kw)    # the field of the same weights
+        np.testing.assert_array_equal(tree.debug_buffer(1).cpu().numpy(), C)
+    tree.close()
