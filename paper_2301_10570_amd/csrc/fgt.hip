@@ -630,14 +630,16 @@ __device__ inline void split_bf16(const float *src, int stride, bf16x8 &hi, bf16
 // (v_mfma_f32_16x16x4f32, same lane layout as above).  LDS: RT x (U + 1) floats of
 // In and (2G - 1) p^2 floats of T (dynamic).
 constexpr size_t kTileLds = 64 * 1024;   // LDS that a tile may take
-constexpr int kOpStr = 80;   // floats of an 8 x 8 operator block in LDS (p = 8)
+// floats of an 8 x 8 operator block in LDS (p = 8): apart by a quarter of the banks, or
+// without a gap where only that fits (57 cells and more that nearly all reach each other)
+constexpr int kOpStr = 80, kOpPacked = 64;
 // The largest cell offset that a tile of two-cell column blocks meets (p = 8).
 __host__ __device__ inline int m2l_reach(int G, int band) { return band < G - 2 ? band + 1 : G - 1; }
-__host__ __device__ inline size_t m2l_gemm_lds(int U, int G, int p, int RT, int band) {
+__host__ __device__ inline size_t m2l_gemm_lds(int U, int G, int p, int RT, int band, int ostr = kOpStr) {
     // input rows, operator table, and (cell-major modes) row bases and column offsets;
     // p = 8, or p < 8 with eight terms per cell (U = 8 G)
     if (U == 8 * G)
-        return ((size_t)RT * (U + 2) + (size_t)(2 * m2l_reach(G, band) + 1) * kOpStr) * 4 + (size_t)RT * 8;
+        return ((size_t)RT * (U + 2) + (size_t)(2 * m2l_reach(G, band) + 1) * ostr) * 4 + (size_t)RT * 8;
     const size_t nT = (size_t)(2 * G - 1) * p * p;
     return ((size_t)RT * (U + 1) + nT + (nT & 1)) * 4 + (size_t)RT * 8 + (size_t)U * 4;
 }
@@ -869,7 +871,7 @@ __device__ inline uint64_t rows_mask(const uint64_t *m, int glo, int64_t r0, int
 // served together read 32 banks; with rows padded by one and blocks untransposed the
 // operand reads took four times as long and bound the pass as much as the matrix cores
 // did.
-template <int RT, int MODE, bool PAD>
+template <int RT, int MODE, bool PAD, int OS = kOpStr>
 __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int p, int G, const float *T, int64_t r0,
                                float *sm, int Ga, int band, PassMask pm) {
     constexpr int NR = RT / 16;   // 16-wide column tiles per block
@@ -905,7 +907,7 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int p, in
         for (int k = 0; k < 4; ++k) {
             const int e = e0 + 256 * k;   // block e / 16, target term (e / 2) % 8, source terms 4 (e % 2) ..
             if (e >= nT4) continue;
-            float *d = sT + (e >> 4) * kOpStr + (e & 1) * 32 + ((e >> 1) & 7);
+            float *d = sT + (e >> 4) * OS + (e & 1) * 32 + ((e >> 1) & 7);
             d[0] = t[k].x;
             d[8] = t[k].y;
             d[16] = t[k].z;
@@ -914,7 +916,7 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int p, in
     }
     // U = 8 G: rows in 16-byte chunks, which never straddle a cell
     const int U4 = U / 4;
-    int64_t *rowbase = reinterpret_cast<int64_t *>(sT + nop * kOpStr);
+    int64_t *rowbase = reinterpret_cast<int64_t *>(sT + nop * OS);
     if constexpr (MODE != 0) {
         for (int rr = threadIdx.x; rr < RT; rr += 256) {
             const int64_t r = r0 + rr;
@@ -992,10 +994,10 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int p, in
 #pragma unroll
         for (int j = 0; j < NR; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         // source cells within `band` of this column block's two cells (those beyond are
-        // negligible); entry of term 4 h + q of cell s: base - 80 s + 32 h
+        // negligible); entry of term 4 h + q of cell s: base - OS s + 32 h
         const int s_lo = 2 * vc - band > 0 ? 2 * vc - band : 0;
         const int s_hi = 2 * vc + 1 + band < G - 1 ? 2 * vc + 1 + band : G - 1;
-        const int base = has ? (tv + ob) * kOpStr + q * 8 + b : 0;
+        const int base = has ? (tv + ob) * OS + q * 8 + b : 0;
         const float *bcol = sIn + (lane & 15) * UP + q;
         auto round = [&](const int (&sc)[NC], int cnt) {
             float a[2 * NC];
@@ -1003,7 +1005,7 @@ __device__ void m2l_gemm_tile8(const float *In, float *Out, int64_t R, int p, in
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const float t = sT[has ? base - kOpStr * sc[c] + 32 * h : 0];
+                    const float t = sT[has ? base - OS * sc[c] + 32 * h : 0];
                     a[2 * c + h] = has && c < cnt ? t : 0.f;
                 }
 #pragma unroll
@@ -1187,6 +1189,13 @@ __global__ void __launch_bounds__(256) k_m2l_gemm(const float *In, float *Out, i
     if (p == 8) m2l_gemm_tile<RT, 0, 8>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band, pm);
     else if (pad) m2l_gemm_tile8<RT, 0, true>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band, PassMask{});
     else m2l_gemm_tile<RT>(In, Out, R, p, G, T, (int64_t)blockIdx.x * RT, sm, 0, band);
+}
+
+// The same for p = 8 with packed operator blocks.
+__global__ void __launch_bounds__(256) k_m2l_gemm_packed(const float *In, float *Out, int64_t R, int G, const float *T,
+                                                         int band, PassMask pm) {
+    extern __shared__ float sm[];
+    m2l_gemm_tile8<16, 0, false, kOpPacked>(In, Out, R, 8, G, T, (int64_t)blockIdx.x * 16, sm, 0, band, pm);
 }
 
 // The whole-K tile with split bfloat16 products (p <= 8).
@@ -3165,8 +3174,10 @@ static int translate(msp_tree *t, int p, const int (&G)[3], double step, uint32_
             int RT = 64;
             while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds(Ut, ps.G, p, RT, band[k]) > 64 * 1024))
                 RT >>= 1;
-            const size_t lds = m2l_gemm_lds(Ut, ps.G, p, RT, band[k]);
-            if (lds <= 64 * 1024) {
+            size_t lds = m2l_gemm_lds(Ut, ps.G, p, RT, band[k]);
+            const bool packed = p == 8 && lds > kTileLds;
+            if (packed) lds = m2l_gemm_lds(Ut, ps.G, p, RT, band[k], kOpPacked);
+            if (lds <= kTileLds) {
                 // column groups of four 16-wide blocks, one per wavefront, as the grid's y,
                 // only while the row tiles alone make fewer than 1024 blocks (every group
                 // stages the whole input rows)
@@ -3175,7 +3186,10 @@ static int translate(msp_tree *t, int p, const int (&G)[3], double step, uint32_
                 const int64_t want = (1024 + rows - 1) / rows;
                 const int cg = want < ngroup ? (int)want : ngroup;
                 const dim3 grid((unsigned)rows, (unsigned)cg);
-                if (RT == 64)
+                if (packed)   // (RT = 16)
+                    hipLaunchKernelGGL(k_m2l_gemm_packed, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, ps.G, ps.T,
+                                       band[k], pm);
+                else if (RT == 64)
                     hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
                 else if (RT == 32)
                     hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
@@ -3256,7 +3270,7 @@ int fgt_forward_grid(msp_tree *t, const FgtPlan &pl, const msp_fgt_params *prm, 
         // also those that a masked pass before them has left unwritten
         bool sparse = p == 8 && !valu && !bf16x3 && ncell >= 4096 && t->n < 64 * ncell;
         for (int k = 0; k < 3; ++k)
-            sparse = sparse && pl.G[k] <= 64 && m2l_gemm_lds(8 * pl.G[k], pl.G[k], 8, 16, band[k]) <= kTileLds;
+            sparse = sparse && pl.G[k] <= 64 && m2l_gemm_lds(8 * pl.G[k], pl.G[k], 8, 16, band[k], kOpPacked) <= kTileLds;
         MSP_TRY(cell_tables(t, pl, sparse ? band : nullptr, masks, s));
         ga.cells = CellTable{t->cell_pts.as<int4>(), t->cell_gen};
         ga.sparse = sparse;

@@ -269,3 +269,27 @@ def test_whole_rows_where_the_padded_tile_does_not_serve(p, extent):
         tree.backward(d["w"], d["w"], None, want=("w",), **kw)    # the field of the same weights
         np.testing.assert_array_equal(tree.debug_buffer(1).cpu().numpy(), C)
     tree.close()
+
+
+@pytest.mark.parametrize("extent", [(560.0, 635.0, 35.0), (570.0, 635.0, 35.0), (620.0, 635.0, 35.0), (35.0, 635.0, 630.0)])
+def test_wide_rows_that_reach_each_other(extent):
+    """p = 8 on 56 to 64 cells an axis that all translate into each other: operator blocks apart
+    in LDS, or packed where only that fits; against the vector passes, 1e-5."""
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(60000, extent=extent, sigma=200.0, seed=910)
+    for k, v in enumerate((wl.x, wl.y, wl.z)):
+        v[0], v[-1] = 0.0, extent[k] - 0.1 + (5.0 if k == 1 else 0.0)
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    kw = dict(sigma=wl.sigma, p=8, level=6, route="fgt")
+    print(f"wide rows {tree.plan(**kw)['grid']}", flush=True)
+    tree.forward(d["w"], None, **kw)
+    tree.set_timing(True)
+    u = tree.forward(d["w"], None, **kw).cpu().numpy()
+    print({k: round(1e3 * v[0], 1) for k, v in tree.timing().items() if "m2l" in k}, flush=True)
+    C = tree.debug_buffer(1).cpu().numpy()
+    v = tree.forward(d["w"], None, m2l="valu", **kw).cpu().numpy()
+    Cv = tree.debug_buffer(1).cpu().numpy()
+    assert np.abs(C - Cv).max() <= 1e-5 * np.abs(Cv).max()
+    assert rel_err(u, v).max() <= 1e-5
+    tree.close()
