@@ -1293,29 +1293,31 @@ __device__ inline int64_t run_end(const uint64_t *keys, int64_t i, int64_t e, in
 }
 
 // Taylor series of the cells at their points (Horner in x, then y, then z), every
-// point's sum to input order.  A wavefront takes `chunks` runs of 64 NPT consecutive
-// points in key order (the next run's records loaded while one is evaluated), cell by
-// cell (usually one), with the cell's coefficients in LDS; NPT points per lane, so that
+// point's sum to input order.  A wavefront takes `chunks` runs of 64 NPT (SHORT: of
+// short_run) consecutive points in key order (the next run's records loaded while one is evaluated),
+// cell by cell (usually one), with the cell's coefficients in LDS; NPT points per lane, so that
 // a coefficient read from LDS serves NPT chains: with four the vector units bound it
 // (2 p^3 flops a point), but few points then make few wavefronts.  One block per cell
 // left the chip to the fullest cells: 262,144 points in 64 blobs (32,768 cells, 2,600
 // with points, up to 5,000 in one) at p = 8 198 us, 35 us in this form; 2,097,152 points
-// in 512 cells 86 us, 60 us.  p = 8 has its own, k_l2p_mfma8.
-template <int P, int NPT>
+// in 512 cells 86 us, 60 us.  p = 8 has its own, k_l2p_mfma8, and above it a block per cell is
+// faster, k_l2p_cells.
+template <int P, int NPT, bool SHORT>
 __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n, const float4 *ps,
                                                 const int32_t *perm, const CellTable cells, int level,
                                                 int Gx, int Gy, int Gz, double lox, double loy, double loz,
-                                                double cell, double inv_sigma, const float *C, int chunks,
+                                                double cell, double inv_sigma, const float *C, int short_run, int chunks,
                                                 float *u_out) {
-    constexpr int P3 = P * P * P, NW = P <= 12 ? kBlock / 64 : 1;   // (LDS of large p: launched with one wave)
-    constexpr int CPL = (P3 + 63) / 64;                             // coefficients per lane
+    const int run = SHORT ? short_run : 64 * NPT;
+    constexpr int P3 = P * P * P, NW = kBlock / 64;
+    constexpr int CPL = (P3 + 63) / 64;   // coefficients per lane
     __shared__ __align__(16) float coef[NW][P3];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float *sC = coef[wave];
     const int sh = 3 * (kDepth - level);
     const int64_t Rx = (int64_t)Gx * P, Ry = (int64_t)Gy * P;
-    int64_t i0 = (blockIdx.x * (int64_t)(blockDim.x >> 6) + wave) * (64 * NPT) * chunks;
-    const int64_t iend = i0 + (int64_t)chunks * (64 * NPT) < n ? i0 + (int64_t)chunks * (64 * NPT) : n;
+    int64_t i0 = (blockIdx.x * (int64_t)(blockDim.x >> 6) + wave) * run * chunks;
+    const int64_t iend = i0 + (int64_t)chunks * run < n ? i0 + (int64_t)chunks * run : n;
     float4 qn[NPT];
     int32_t jn[NPT];
     auto fetch = [&](int64_t c0) {
@@ -1328,8 +1330,8 @@ __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n,
     };
     if (i0 < iend) fetch(i0);
     uint64_t staged = ~0ull;   // the cell whose coefficients LDS holds
-    for (; i0 < iend; i0 += 64 * NPT) {
-        const int64_t i1 = i0 + 64 * NPT < iend ? i0 + 64 * NPT : iend;
+    for (; i0 < iend; i0 += run) {
+        const int64_t i1 = i0 + run < iend ? i0 + run : iend;
         float4 q[NPT];
         int32_t jo[NPT];
 #pragma unroll
@@ -1423,8 +1425,74 @@ __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n,
     }
 }
 
+// The same for p > 8 with a block per cell: the block shares the cell's p^3 coefficients, which
+// the runs' wavefronts each load for themselves, and a thread takes four points at a time, so
+// that a coefficient read from LDS serves four chains.  In runs, then here: 1,000 points in
+// 512 cells, p = 12: 430 us, 40 us; 1,000,000 in 1,024, p = 10: 73 us, 46 us; p = 13: 584 us,
+// 104 us; 262,144 in 2,600 of 31,744, p = 9: 126 us, 72 us.
+template <int P>
+__global__ void __launch_bounds__(kBlock) k_l2p_cells(const uint64_t *keys, int64_t n, const float4 *ps,
+                                                      const int32_t *perm, const CellTable cells, int level,
+                                                      int Gx, int Gy, int Gz, double lox, double loy, double loz,
+                                                      double cell, double inv_sigma, const float *C, float *u_out) {
+    constexpr int P3 = P * P * P, NPT = 4;
+    __shared__ float sC[P3];
+    const int64_t g = blockIdx.x;
+    const int kx = (int)(g % Gx), ky = (int)((g / Gx) % Gy), kz = (int)(g / ((int64_t)Gx * Gy));
+    int64_t start, end;
+    cell_points(cells, g, keys, n, level, kx, ky, kz, start, end);
+    if (start == end) return;
+    const int64_t Rx = (int64_t)Gx * P, Ry = (int64_t)Gy * P;
+    for (int e = threadIdx.x; e < P3; e += kBlock) {
+        const int ax = e % P, ay = (e / P) % P, az = e / (P * P);
+        sC[e] = C[(((int64_t)kz * P + az) * Ry + (int64_t)ky * P + ay) * Rx + (int64_t)kx * P + ax];
+    }
+    __syncthreads();
+    const float cx = (float)(lox + (kx + 0.5) * cell), cy = (float)(loy + (ky + 0.5) * cell),
+                cz = (float)(loz + (kz + 0.5) * cell);
+    for (int64_t i0 = start + threadIdx.x; i0 < end; i0 += NPT * kBlock) {
+        float X[NPT], Y[NPT], Z[NPT], uz[NPT];
+        int32_t jo[NPT];
+#pragma unroll
+        for (int u = 0; u < NPT; ++u) {
+            const int64_t i = i0 + (int64_t)u * kBlock < end ? i0 + (int64_t)u * kBlock : i0;
+            const float4 q = ps[i];
+            X[u] = (q.x - cx) * (float)inv_sigma;
+            Y[u] = (q.y - cy) * (float)inv_sigma;
+            Z[u] = (q.z - cz) * (float)inv_sigma;
+            jo[u] = perm[i];
+            uz[u] = 0.f;
+        }
+        for (int az = P - 1; az >= 0; --az) {
+            float uy[NPT];
+#pragma unroll
+            for (int u = 0; u < NPT; ++u) uy[u] = 0.f;
+#pragma unroll
+            for (int ay = P - 1; ay >= 0; --ay) {
+                const float *c = sC + (az * P + ay) * P;
+                float ux[NPT];
+#pragma unroll
+                for (int u = 0; u < NPT; ++u) ux[u] = c[P - 1];
+#pragma unroll
+                for (int ax = P - 2; ax >= 0; --ax) {
+                    const float cv = c[ax];
+#pragma unroll
+                    for (int u = 0; u < NPT; ++u) ux[u] = fmaf(ux[u], X[u], cv);
+                }
+#pragma unroll
+                for (int u = 0; u < NPT; ++u) uy[u] = fmaf(uy[u], Y[u], ux[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < NPT; ++u) uz[u] = fmaf(uz[u], Z[u], uy[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < NPT; ++u)
+            if (i0 + (int64_t)u * kBlock < end) u_out[jo[u]] = uz[u];
+    }
+}
+
 // The same for p = 8 on the matrix cores, which bound it (64 instructions of 32 cycles for
-// 64 points, the sums over ax): a wavefront takes runs of 64 points in four groups of 16.
+// 64 points, the sums over ax): a wavefront takes runs of up to 64 points in four groups of 16.
 // v_mfma_f32_16x16x4f32 with the coefficients as operand A (row m of tile t: az = m / 4 +
 // 4 (t / 2), ay = m % 4 + 4 (t % 2); held in eight registers per lane, no LDS) and the
 // powers of X as operand B leaves lane l = 16 kq + n of a group with the sums over ax of
@@ -1434,17 +1502,18 @@ __global__ void __launch_bounds__(kBlock) k_l2p(const uint64_t *keys, int64_t n,
 // 262,144 points in 2,600 cells 35 us, 19 us; 2,097,152 points in 512 cells 58 us, 44 us;
 // 4,194,304 points in 1,024 cells 87 us, 73 us, where the sums' scattered 4-byte stores bound
 // it.
-template <bool DENSE>
+template <bool DENSE, bool SHORT>
 __global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int64_t n, const float4 *ps,
                                                       const int32_t *perm, const CellTable cells, int level,
                                                       int Gx, int Gy, int Gz, double lox, double loy, double loz,
-                                                      double cell, double inv_sigma, const float *C, int chunks,
+                                                      double cell, double inv_sigma, const float *C, int short_run, int chunks,
                                                       float *u_out) {
+    const int run = SHORT ? short_run : 64;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n16 = lane & 15, kq = lane >> 4, sh = 3 * (kDepth - level);
     const int64_t Rx = (int64_t)Gx * 8, Ry = (int64_t)Gy * 8;
-    int64_t i0 = (blockIdx.x * (int64_t)(kBlock / 64) + wave) * 64 * chunks;
-    const int64_t iend = i0 + (int64_t)chunks * 64 < n ? i0 + (int64_t)chunks * 64 : n;
+    int64_t i0 = (blockIdx.x * (int64_t)(kBlock / 64) + wave) * run * chunks;
+    const int64_t iend = i0 + (int64_t)chunks * run < n ? i0 + (int64_t)chunks * run : n;
     float4 qn[4];   // point n16 of each group (four lanes read the same record)
     int32_t jn = 0;
     uint64_t kn = 0;
@@ -1464,8 +1533,8 @@ __global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int6
     float cx = 0.f, cy = 0.f, cz = 0.f;
     uint64_t staged = ~0ull;   // the cell whose coefficients a holds
     int64_t cend = -1;         // DENSE: its end
-    for (; i0 < iend; i0 += 64) {
-        const int64_t i1 = i0 + 64 < iend ? i0 + 64 : iend;
+    for (; i0 < iend; i0 += run) {
+        const int64_t i1 = i0 + run < iend ? i0 + run : iend;
         float4 q[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) q[g] = qn[g];
@@ -2013,22 +2082,33 @@ int launch_p2m_l2p(msp_tree *t, const FgtPlan &pl, double inv_sigma, bool l2p, c
                            ga.w_gather, ga.cells, pl.level, pl.G[0], pl.G[1], pl.G[2], t->geo.lo[0], t->geo.lo[1],
                            t->geo.lo[2], pl.cell, inv_sigma, A, ga.stage ? t->ps.as<float4>() : nullptr);
     } else {
-        // every point's sum straight to input order, flags and self term afterwards; four
-        // points per lane (p = 8: dense cells) once that still makes sixteen wavefronts per
-        // compute unit, then more runs per wavefront while it does
-        const int bw = P <= 12 ? kBlock / 64 : 1;
-        auto launch = [&](auto kern, int npt) {
-            const int64_t most = t->n / (64 * npt * 4096);
-            const int chunks = most < 1 ? 1 : most > 4 ? 4 : (int)most;
-            hipLaunchKernelGGL(kern, dim3(grid_for(t->n, 64 * npt * bw * chunks)), dim3(64 * bw), 0, s,
-                               t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), t->perm.as<int32_t>(), ga.cells,
-                               pl.level, pl.G[0], pl.G[1], pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell,
-                               inv_sigma, C, chunks, ga.u_out);
-        };
-        const bool many = t->n >= 4 * 64 * 4096;
-        if constexpr (P == 8) launch(many ? k_l2p_mfma8<true> : k_l2p_mfma8<false>, 1);
-        else if (many) launch(k_l2p<P, 4>, 4);
-        else launch(k_l2p<P, 1>, 1);
+        // every point's sum straight to input order, flags and self term afterwards
+        if constexpr (P > 8) {
+            hipLaunchKernelGGL(k_l2p_cells<P>, dim3((unsigned)ncell), dim3(kBlock), 0, s, t->keys.as<uint64_t>(),
+                               t->n, t->ps.as<float4>(), t->perm.as<int32_t>(), ga.cells, pl.level, pl.G[0], pl.G[1],
+                               pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell, inv_sigma, C, ga.u_out);
+        } else {
+            // four points per lane (p = 8: dense cells) once that still makes sixteen wavefronts
+            // per compute unit, then more runs per wavefront while it does; shorter runs while a
+            // wavefront's cells, one after another, would be the launch (1,000 points in 4,096
+            // cells: 58 us in runs of 64, 9 us in runs of 4; 100,000: 13 us in runs of 64, 14 in
+            // 32)
+            auto launch = [&](auto kern, int npt) {
+                const int64_t most = t->n / (64 * npt * 4096);
+                const int chunks = most < 1 ? 1 : most > 4 ? 4 : (int)most;
+                int run = 64 * npt;
+                while (npt == 1 && run > 4 && t->n < (int64_t)1536 * run) run >>= 1;
+                hipLaunchKernelGGL(kern, dim3(grid_for(t->n, run * (kBlock / 64) * chunks)), dim3(kBlock), 0, s,
+                                   t->keys.as<uint64_t>(), t->n, t->ps.as<float4>(), t->perm.as<int32_t>(), ga.cells,
+                                   pl.level, pl.G[0], pl.G[1], pl.G[2], t->geo.lo[0], t->geo.lo[1], t->geo.lo[2],
+                                   pl.cell, inv_sigma, C, run, chunks, ga.u_out);
+            };
+            const bool many = t->n >= 4 * 64 * 4096, few = t->n < 1536 * 64;
+            if constexpr (P == 8)
+                launch(many ? k_l2p_mfma8<true, false> : few ? k_l2p_mfma8<false, true> : k_l2p_mfma8<false, false>, 1);
+            else if (many) launch(k_l2p<P, 4, false>, 4);
+            else launch(few ? k_l2p<P, 1, true> : k_l2p<P, 1, false>, 1);
+        }
         // (the target flags and the self term follow in fgt_forward_grid)
     }
     MSP_CHECK_LAUNCH();

@@ -293,3 +293,51 @@ def test_wide_rows_that_reach_each_other(extent):
     assert np.abs(C - Cv).max() <= 1e-5 * np.abs(Cv).max()
     assert rel_err(u, v).max() <= 1e-5
     tree.close()
+
+
+@pytest.mark.parametrize("n,p", [(1, 9), (65, 9), (700, 9), (30011, 11), (4000, 12), (700, 13), (20000, 16)])
+def test_l2p_by_cells(n, p):
+    """Orders above eight, a block per cell: cells of one point, of more than a block's 1,024, and
+    none; the bits of the same call in a workspace, and the float32 sums' rounding, 2e-6."""
+    import torch
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(n, extent=(400.0, 300.0, 200.0), sigma=200.0, seed=920 + n)
+    wl.w[:] = np.maximum(wl.w, 1)
+    if n > 4000:   # a cell that holds many
+        for v in (wl.x, wl.y, wl.z):
+            v[n // 2:n // 2 + 1500] = np.float32(150.5) + np.float32(0.01) * v[n // 2:n // 2 + 1500]
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    kw = dict(sigma=wl.sigma, p=p, level=4, route="fgt")
+    print(f"l2p by cells n={n} p={p}", flush=True)
+    u = tree.forward(d["w"], d["tgt"], **kw).cpu().numpy()
+    ws = torch.empty(tree.forward_query(**kw), dtype=torch.uint8, device="cuda")
+    np.testing.assert_array_equal(tree.forward_ws(d["w"], ws, d["tgt"], **kw).cpu().numpy(), u)
+    tgt = np.nonzero(wl.a > 0)[0]
+    pick = tgt[:100]
+    assert np.all(u[wl.a <= 0] == 0) and (pick.size == 0 or rel_err(u[pick], oracle.attraction(wl, pick)).max() <= 2e-6)
+    tree.close()
+
+
+@pytest.mark.parametrize("n", [6143, 6144, 12287, 49152, 98303, 98304])
+@pytest.mark.parametrize("p", [5, 8])
+def test_l2p_run_lengths(n, p):
+    """Either side of the point counts where a wavefront's run halves, cells across runs: the bits
+    of the workspace call, which searches the cells, and the series' bar at that cell size (half
+    a cell is some 0.16 sigma), 1e-4."""
+    import torch
+    import paper_2301_10570_amd as msp
+    wl = synth.blobs(n // 256 + 1, 256, extent=3000.0, std=60.0, sigma=340.0, seed=930 + n)
+    for k in ("x", "y", "z", "w", "a"):
+        setattr(wl, k, getattr(wl, k)[:n].copy())
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    kw = dict(sigma=wl.sigma, p=p, level=5, route="fgt")
+    print(f"l2p run lengths n={n} p={p}", flush=True)
+    u = tree.forward(d["w"], None, **kw).cpu().numpy()
+    ws = torch.empty(tree.forward_query(**kw), dtype=torch.uint8, device="cuda")
+    np.testing.assert_array_equal(tree.forward_ws(d["w"], ws, None, **kw).cpu().numpy(), u)
+    pick = np.random.default_rng(n).permutation(n)[:60]
+    ref = oracle.attraction(wl, pick)
+    assert rel_err(u[pick], ref).max() <= 1e-4
+    tree.close()
