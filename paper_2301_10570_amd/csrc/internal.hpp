@@ -490,7 +490,9 @@ int scatter_output(msp_tree *t, float *u_out, uint32_t flags, bool subtract_self
 int direct_route(msp_tree *t, const msp_fgt_params *prm, hipStream_t s, bool lists_ready = false);
 // the lists of prm into the handle's list_idx (list_stride says how they lie)
 int direct_route_lists(msp_tree *t, const msp_fgt_params *prm, hipStream_t s);
-// wavefronts per target leaf (1, 4, 8 or 16) in the passes over a tree of n_nodes nodes
+// wavefronts per target leaf (1, 4, 8 or 16) in the passes over a tree of n_nodes nodes: one
+// beyond kSharedNodes
+constexpr int64_t kSharedNodes = 4096;
 int p2p_waves(int64_t n_nodes);
 // per-leaf list lengths and offsets for prm's sigma and cutoff (one host
 // synchronisation when they change), and the compact list entries into t->list_idx

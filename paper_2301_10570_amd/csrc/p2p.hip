@@ -133,9 +133,10 @@ __global__ void __launch_bounds__(1024) k_scan_i32_to_i64(const int32_t *cnt, in
 }
 
 // NW wavefronts per target leaf (non-leaf nodes return at once): a block per node, or
-// for NW = 1 four nodes per block.
+// for NW = 1 four nodes per block, held to 80 registers: with short lists the pass waits for
+// loads (150,000 points in leaves of up to 8, lists of 30: 90 us with 112 registers, 75 us).
 template <int NW>
-__global__ void __launch_bounds__(NW == 1 ? 256 : NW * 64, 4) k_p2p(LeafSet ls) {
+__global__ void __launch_bounds__(NW == 1 ? 256 : NW * 64, NW == 1 ? 6 : 4) k_p2p(LeafSet ls) {
     constexpr int W = NW == 1 ? 4 : NW;
     __shared__ P2PShared sh[W];
     __shared__ double red[NW > 1 ? NW : 1][64];
@@ -297,7 +298,7 @@ int p2p_waves(int64_t n_nodes) {
     // slots; 16 (the largest block) below 1024 nodes.  4,096 points (300 leaves, lists
     // of 45 chunks) took 220 us on one wavefront per leaf and take 24 us on 16.
     int nw = 16;
-    while (nw > 1 && n_nodes * nw > 16384) nw >>= 1;
+    while (nw > 1 && n_nodes * nw > 4 * kSharedNodes) nw >>= 1;
     return nw >= 4 ? nw : 1;
 }
 

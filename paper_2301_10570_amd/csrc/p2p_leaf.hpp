@@ -186,10 +186,14 @@ __device__ inline int32_t window_point(const ListWindow &win, int start, int c, 
 }
 
 // Entries per window of a list of len: sixteen windows for the sixteen wavefronts that
-// may share a leaf, of 8 to 64 entries.
-__device__ inline int p2p_window(int len) {
+// may share a leaf, of 8 to 64 entries.  Trees of more leaves than the chip has wavefront
+// slots have a wavefront per leaf, for which windows of 8 are so many more chains of
+// dependent loads: 64 entries (40,000 points in leaves of one, lists of some 30: 81 us with
+// 64 before the leaves were shared, 254 us with 8).  The rule looks at the tree alone, so that
+// a batch's launch, which always shares, cuts a list as the tree's own call does.
+__device__ inline int p2p_window(int len, int64_t n_nodes) {
     const int w = (len + 15) >> 4;
-    return w < 8 ? 8 : (w > 64 ? 64 : w);
+    return n_nodes > kSharedNodes ? 64 : w < 8 ? 8 : (w > 64 ? 64 : w);
 }
 
 // The wave's walk over its windows and their chunks: stage(nxt, nid, own) puts a chunk's
@@ -203,7 +207,7 @@ __device__ inline void p2p_sources(const LeafSet &L, const int32_t *lst, int len
                                    P2PShared &sh, Stage stage, Use use) {
     constexpr int PER = kP2PChunk / 64;
     const int lane = threadIdx.x & 63;
-    const int W = __builtin_amdgcn_readfirstlane(p2p_window(len));
+    const int W = __builtin_amdgcn_readfirstlane(p2p_window(len, L.n_nodes));
     for (int w0 = wave * W; w0 < len; w0 += NW * W) {
         int start;
         const int tot = load_window(lst, w0, len - w0 < W ? len - w0 : W, L.n_nodes, L.nfirst, L.ncount, lane, sh.win,

@@ -241,3 +241,26 @@ def test_leaf_sums_on_either_side_of_the_matrix_form(reach, bar):
     rms = np.sqrt(np.mean(e2))
     print(f"reach {reach} rms {rms:.3e}", flush=True)
     assert rms <= bar
+
+
+@pytest.mark.parametrize("sigma,exclude", [(12.0, False), (40.0, True), (160.0, False), (1000.0, False)])
+def test_one_wavefront_per_leaf(sigma, exclude):
+    """A tree of more than 4,096 nodes: a wavefront per leaf over windows of 64 list entries, lists
+    shorter and longer than one window; the batch's four wavefronts per leaf cut them alike."""
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(6000, extent=(800.0, 800.0, 800.0), sigma=sigma, seed=4200)
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"], leaf_max=1)
+    assert tree.info()["n_nodes"] > 4096
+    print(f"one wavefront per leaf sigma={sigma} nodes={tree.info()['n_nodes']}", flush=True)
+    u = tree.forward(d["w"], None, sigma=sigma, route="direct", exclude_self=exclude).cpu().numpy()
+    pick = np.random.default_rng(5).permutation(wl.n)[:500]
+    ref = oracle.attraction(wl, pick, exclude_self=exclude)
+    far = wl.w.astype(np.float64).sum() * np.exp(-4.5 ** 2)
+    assert np.all(np.abs(u[pick] - ref) <= 1e-5 * np.abs(ref) + far)
+    b = msp.Batch().build(d["x"], d["y"], d["z"], np.array([0, wl.n], dtype=np.int64),
+                          leaf_max=np.array([1], dtype=np.int32))
+    ub = b.forward(d["w"], np.array([sigma], dtype=np.float32), route="direct", exclude_self=exclude).cpu().numpy()
+    np.testing.assert_array_equal(ub, u)
+    b.close()
+    tree.close()
