@@ -36,7 +36,8 @@ __global__ void k_stage_both(const float *w, const float *gt, const int32_t *per
 template <int NW, bool TWO>
 __global__ void __launch_bounds__(NW * 64, NW > 1 ? 4 : 6) k_p2p_grad(GradLeafSet L, const float *g2, int stride, int want_lap) {
     __shared__ GradShared sh[NW];
-    __shared__ GradBlock bk;
+    __shared__ GradBlock own;
+    GradBlock &bk = NW > 1 ? own : *reinterpret_cast<GradBlock *>(sh[0].src);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const LeafTask t = uniform_copy(leaf_task(L, (int64_t)blockIdx.x, 0));
     if (t.count > 0) p2p_grad_leaf<NW, TWO>(L, g2, t, stride, want_lap, wave, sh[wave], bk);

@@ -35,13 +35,15 @@ struct GradShared {
     ListWindow win;
 };
 
-// What the wavefronts of a leaf share: the ordered running sums and whose turn it is to
-// add to them, and the other sums.
+// What the wavefronts of a leaf share: the ordered running sums in float32, those in
+// float64, and whose turn it is to add to either.
 struct GradBlock {
     float run[3][64];
     double sum[6][64];
-    int turn;
+    int turn, turn64;
 };
+// A wavefront alone needs them when its sources are done: in the place of those.
+static_assert(sizeof(GradBlock) <= sizeof(float4) * 256, "the sums fit where the sources were");
 
 // A scalar whose uses stay where they are: the slots' addresses, kept in registers across
 // the units, would spill.
@@ -63,8 +65,9 @@ __device__ inline int not_hoisted(int x) {
 // wavefront evaluates units of at most 16 sources a group (the chunk, or a part of it
 // where G < 4), keeps the weights, exp and r^2 of every pair in registers, and adds them
 // when its turn comes: four instructions a pair in the chain in place of some 25, and no
-// load.  The
-// gradients are float32 per unit and float64 over the units.  5,003 points, both fields:
+// load.  The gradients are float32 per unit and float64 over the units, added in the units'
+// order too, in a turn of its own behind the first: a leaf's records have the same bits
+// however many wavefronts share it.  5,003 points, both fields:
 // 162 us with a wavefront per kind of sum, 72 us with eight per leaf; 48 populations of
 // 1,024 to 32,768 points: 1.61 ms with a wavefront per leaf, whose largest leaves were the
 // launch's tail, 1.0 ms with four.
@@ -72,12 +75,12 @@ template <int NW, bool TWO>
 __device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, const LeafTask &t, int stride, int want_lap,
                                      int wave, GradShared &sh, GradBlock &bk) {
     const int lane = threadIdx.x & 63, len = t.len;
-#pragma unroll
-    for (int c = 64; c < 256; c += 64) {
-        sh.src[c + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-        sh.sg[c + lane] = 0.f;
-    }
     for (int t0 = 0; t0 < t.count; t0 += 64) {
+#pragma unroll
+        for (int c = 64; c < 256; c += 64) {
+            sh.src[c + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+            sh.sg[c + lane] = 0.f;
+        }
         const int nt = __builtin_amdgcn_readfirstlane(t.count - t0 < 64 ? t.count - t0 : 64);
         const int G = __builtin_amdgcn_readfirstlane(64 / nt);
         // lane / nt as a multiply by ceil(2^16 / nt): exact for lane < 64, nt <= 64
@@ -92,7 +95,9 @@ __device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, cons
         if constexpr (NW > 1) {
             if (wave == 0) {
                 bk.run[0][lane] = bk.run[1][lane] = bk.run[2][lane] = 0.f;
-                if (lane == 0) bk.turn = 0;
+#pragma unroll
+                for (int c = 0; c < 6; ++c) bk.sum[c][lane] = 0.0;
+                if (lane == 0) bk.turn = bk.turn64 = 0;
             }
             __syncthreads();
         }
@@ -161,15 +166,12 @@ __device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, cons
                         }
                     }
                 }
-                total[0] += (double)px;
-                total[1] += (double)py;
-                total[2] += (double)pz;
-                if constexpr (TWO) {
-                    total[3] += (double)qx;
-                    total[4] += (double)qy;
-                    total[5] += (double)qz;
+                const float part[6] = {px, py, pz, qx, qy, qz};
+                if constexpr (NW == 1) {
+#pragma unroll
+                    for (int c = 0; c < (TWO ? 6 : 3); ++c) total[c] += (double)part[c];
+                    continue;
                 }
-                if constexpr (NW == 1) continue;
                 // (the weights again, before the turn: they need not be live above)
                 float wt[16], gw[16];
 #pragma unroll
@@ -203,23 +205,25 @@ __device__ inline void p2p_grad_leaf(const GradLeafSet &L, const float *g2, cons
                 bk.run[1][lane] = sr;
                 if constexpr (TWO) bk.run[2][lane] = gu;
                 __hip_atomic_store(&bk.turn, before + mine + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                while (__hip_atomic_load(&bk.turn64, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != before + mine)
+                    __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+                for (int c = 0; c < (TWO ? 6 : 3); ++c) bk.sum[c][lane] += (double)part[c];
+                __hip_atomic_store(&bk.turn64, before + mine + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             mine -= units;
             before += units;
         }
-        // the other sums, wave by wave
-        for (int q = 0; q < NW; ++q) {
-            if (wave == q) {
+        if constexpr (NW > 1) {
+            __syncthreads();
+        } else {
+            wave_sync();   // the sources are no longer read
 #pragma unroll
-                for (int c = 0; c < (TWO ? 6 : 3); ++c) bk.sum[c][lane] = (q > 0 ? bk.sum[c][lane] : 0.0) + total[c];
-                if constexpr (NW == 1) {
-                    bk.run[0][lane] = su;
-                    bk.run[1][lane] = sr;
-                    bk.run[2][lane] = gu;
-                }
-            }
-            if constexpr (NW > 1) __syncthreads();
-            else wave_sync();
+            for (int c = 0; c < (TWO ? 6 : 3); ++c) bk.sum[c][lane] = total[c];
+            bk.run[0][lane] = su;
+            bk.run[1][lane] = sr;
+            bk.run[2][lane] = gu;
+            wave_sync();
         }
         if (wave == 0 && grp == 0 && a < nt) {
             float r[3] = {0.f, 0.f, 0.f};

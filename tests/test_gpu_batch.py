@@ -337,3 +337,35 @@ def test_batch_pair_count(pops):
     with pytest.raises(msp.MspError):
         b.pair_count()
     b.close()
+
+
+@pytest.mark.parametrize("npop,n", [(3, 800), (2, 5000)])
+def test_batch_gradients_have_the_bits_of_the_trees(npop, n):
+    """Four wavefronts share a leaf (in the tree's own call
+    eight, or one beyond 4,096 nodes): the sums of a leaf run in one order whichever it is."""
+    import torch
+    import paper_2301_10570_amd as msp
+    rng = np.random.default_rng(npop)
+    sizes = np.full(npop, n) - np.arange(npop) % 7
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    T = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    pts = (rng.random((int(off[-1]), 3)) * 700.0).astype(np.float32)
+    x = [T(pts[:, k]) for k in range(3)]
+    w = T(rng.integers(0, 4, len(pts)).astype(np.float32))
+    g = T((rng.random(len(pts)) + 0.5).astype(np.float32))
+    tg = T((rng.random(len(pts)) < 0.8).astype(np.uint8))
+    sig = np.full(npop, 60.0, dtype=np.float32)
+    leaf = np.where(np.arange(npop) % 3 == 2, 20, 1 if n == 5000 else 64).astype(np.int32)
+    print(f"batch gradients {npop} x {n}", flush=True)
+    b = msp.Batch().build(*x, off, leaf_max=leaf)
+    got = b.backward(w, g, sig, is_target=tg, route="direct")
+    for k in range(npop):
+        c = slice(int(off[k]), int(off[k + 1]))
+        tree = msp.Tree().build(*(v[c].contiguous() for v in x), leaf_max=int(leaf[k]))
+        ref = tree.backward(w[c].contiguous(), g[c].contiguous(), tg[c].contiguous(), sigma=60.0, route="direct")
+        assert torch.equal(got["w"][c], ref["w"]), k
+        for a in range(3):
+            assert torch.equal(got["pos"][a][c], ref["pos"][a]), (k, a)
+        assert got["sigma"][k].item() == ref["sigma"].item(), k
+        tree.close()
+    b.close()
