@@ -186,20 +186,23 @@ __global__ void k_bw_stage(const GradDesc *desc, const int64_t *pt_off, int nd, 
     D.g2[i] = gt[j];
 }
 
-// P2P with derivatives of both fields over the nodes of every direct-route population:
-// a block of four wavefronts per node, as in the forward's launch.  Three wavefronts per
-// SIMD: held to 128 registers (four) a call on 48 populations took 1.59 ms, 1.56 ms here.
-__global__ void __launch_bounds__(256, 3) k_batch_p2p_grad(const GradDesc *desc, const LeafTask *tasks, int64_t n,
-                                                           int want_lap) {
-    __shared__ GradShared sh[4];
-    __shared__ GradBlock bk;
+// P2P with derivatives of both fields over the nodes of every direct-route population: a
+// block of NW wavefronts per node, 4 or (see prepare_backward) 1: held to 128 registers, and
+// alone to 80 (64 populations of 1,000 to 30,000 points: 4.54 ms, 4.69 with five wavefronts
+// per SIMD, 4.96 with seven).
+template <int NW>
+__global__ void __launch_bounds__(NW * 64, NW == 1 ? 6 : 4) k_batch_p2p_grad(const GradDesc *desc, const LeafTask *tasks,
+                                                                             int64_t n, int want_lap) {
+    __shared__ GradShared sh[NW];
+    __shared__ GradBlock own;
+    GradBlock &bk = NW > 1 ? own : *reinterpret_cast<GradBlock *>(sh[0].src);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int64_t item = blockIdx.x; item < n; item += gridDim.x) {
         const LeafTask t = uniform_copy(tasks[item]);
         if (t.count == 0) continue;
         const GradLeafSet L = uniform_copy(desc[t.owner].L);
         const float *g2 = uniform_copy(desc[t.owner].g2);
-        p2p_grad_leaf<4, true>(L, g2, t, kRec, want_lap, wave, sh[wave], bk);
+        p2p_grad_leaf<NW, true>(L, g2, t, kRec, want_lap, wave, sh[wave], bk);
     }
 }
 
@@ -636,7 +639,21 @@ int prepare_backward(msp_batch *b, const std::vector<PopPlan> &plans, const floa
         b->bw_plan[1].pops = b->bw_fdesc.as<FgtPop>() + nf;
         MSP_TRY(lay_out(b, b->bw_plan[0], b->bw_layout, true, s));   // one for both: the same trees
     }
-    // direct route
+    // direct route.  Four wavefronts share a leaf where one leaf's list would be the launch:
+    // where the pairs of all leaves, as the plans estimate them, are fewer than 1.5 times the
+    // longest list on every lane of the chip; else the ordered sums are a cost without a use.
+    // Four, then one, us a call: 48 populations of 1,024 to 32,768 points (pairs / longest
+    // list 80,000) 1,101, 1,289; 4 of 30,000 to 40,000 (92,000) 2,791, 4,232; 128 of 1,024
+    // to 32,768 (136,000) 2,661, 2,333; 256 of 1,024 to 65,536 (427,000) 8,842, 6,597; 16 of
+    // 20,000 to 60,000 (304,000) 14,327, 10,616.
+    double pairs = 0.0, longest = 0.0;
+    for (int k = 0; k < b->npop; ++k) {
+        const double n = (double)b->pops[k]->n;
+        if (plans[k].pl.route == MSP_ROUTE_FGT || n == 0) continue;
+        pairs += plans[k].pl.direct_cost / 8.0;
+        longest = std::max(longest, plans[k].pl.direct_cost / (8.0 * n));
+    }
+    b->bw_share = pairs < 1.5 * 256.0 * b->cus * longest;
     std::vector<GradDesc> gd;
     std::vector<int64_t> poff{0}, ioff{0};
     for (int k : largest_first(b)) {
@@ -719,8 +736,13 @@ int enqueue_backward(msp_batch *b, const float *w, const uint8_t *is_target, con
                            b->bw_pt_off.as<int64_t>(), nd, w, gt);
         MSP_CHECK_LAUNCH();
         if (b->bw_items > 0) {
-            hipLaunchKernelGGL(k_batch_p2p_grad, dim3(item_grid(b->bw_items)), dim3(256), 0, s, desc,
-                               b->bw_tasks.as<LeafTask>(), b->bw_items, grad_sigma ? 1 : 0);
+            const dim3 grid(item_grid(b->bw_items));
+            if (b->bw_share)
+                hipLaunchKernelGGL(k_batch_p2p_grad<4>, grid, dim3(256), 0, s, desc, b->bw_tasks.as<LeafTask>(),
+                                   b->bw_items, grad_sigma ? 1 : 0);
+            else
+                hipLaunchKernelGGL(k_batch_p2p_grad<1>, grid, dim3(64), 0, s, desc, b->bw_tasks.as<LeafTask>(),
+                                   b->bw_items, grad_sigma ? 1 : 0);
             MSP_CHECK_LAUNCH();
         }
     }

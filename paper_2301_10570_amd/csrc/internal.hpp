@@ -361,6 +361,7 @@ struct msp_batch {
         bw_comb, bw_boff, bw_partial, bw_gt;
     msp::FgtBatchPlan bw_plan[2]{};
     int32_t bw_nd = 0;
+    bool bw_share = true;   // wavefronts share a leaf in the backward's P2P launch
     int64_t bw_points = 0, bw_items = 0, bw_nblk = 0;
     // branch stream of the backward's expansion-route populations
     hipStream_t bside = nullptr;

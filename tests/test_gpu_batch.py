@@ -339,10 +339,10 @@ def test_batch_pair_count(pops):
     b.close()
 
 
-@pytest.mark.parametrize("npop,n", [(3, 800), (2, 5000)])
+@pytest.mark.parametrize("npop,n", [(150, 800), (3, 800), (2, 5000)])
 def test_batch_gradients_have_the_bits_of_the_trees(npop, n):
-    """Four wavefronts share a leaf (in the tree's own call
-    eight, or one beyond 4,096 nodes): the sums of a leaf run in one order whichever it is."""
+    """Enough leaves to fill the chip run on a wavefront each, fewer share four (the tree's own call
+    has eight, or one beyond 4,096 nodes): the sums of a leaf run in one order whichever it is."""
     import torch
     import paper_2301_10570_amd as msp
     rng = np.random.default_rng(npop)
