@@ -340,11 +340,8 @@ __device__ inline bool pair_by_series(const BoxArgs &g, int32_t vs, int32_t vc, 
     return g.nlevel[vs] >= g.level && g.nlevel[vc] >= g.level && na > kC2 && nd > kC1 &&
            dx * dx + dy * dy + dz * dz <= kBoxAdmitR * kBoxAdmitR;
 }
-__device__ inline bool pair_is_large(const BoxArgs &g, int32_t s, int32_t c) {
-    const int32_t vs = g.box_node[s], vc = g.box_node[c];
-    return g.ncount[vc] > kSmallBox ||
-           pair_by_series(g, vs, vc, g.box_na[s], g.box_nd[c], g.box_geo[s], g.box_geo[c]);
-}
+// (the expansions need more than kC1 dendrites, so the dendrite box's points alone decide)
+static_assert(kSmallBox <= kC1, "a pair by the expansions is a large one");
 
 // a box's pairs and large pairs into the two columns that are scanned into offsets
 __device__ inline void put_counts(const BoxArgs &g, int64_t s, int64_t *cnt, int64_t n, int64_t nl) {
@@ -380,7 +377,7 @@ __global__ void __launch_bounds__(256) k_box_lists(BoxArgs g, int64_t *cnt) {
             const int32_t bu = g.node_box[u];
             if (bu >= 0) {
                 if (g.box_nd[bu] > 0) {
-                    const bool big = pair_is_large(g, (int32_t)s, bu);
+                    const bool big = g.ncount[u] > kSmallBox;
                     if (!cnt) {
                         g.pair_s[base + n] = (int32_t)s;
                         g.pair_c[base + n] = bu;
@@ -421,7 +418,7 @@ __global__ void __launch_bounds__(256) k_box_lists_all(BoxArgs g, int64_t *cnt) 
                 ok = gx * gx + gy * gy + gz * gz <= g.cut * g.cut;
             }
             const uint64_t mask = __ballot(ok);
-            const bool big = ok && pair_is_large(g, (int32_t)s, (int32_t)c);
+            const bool big = ok && g.ncount[g.box_node[c]] > kSmallBox;
             const uint64_t bigs = __ballot(big);
             if (!cnt && ok) {
                 const int64_t pos = base + n + __popcll(mask & below);
@@ -648,7 +645,7 @@ __global__ void __launch_bounds__(kPairWaves * 64, 6) k_box_pairs_small(BoxArgs 
                 const int32_t vc = g.box_node[c];
                 const double4 gc = g.box_geo[c];
                 nc = g.ncount[vc];
-                mine = nc <= kSmallBox && !pair_by_series(g, vs, vc, na, g.box_nd[c], gs, gc);
+                mine = nc <= kSmallBox;
                 if (mine) {
                     fc = g.nfirst[vc];
                     gap2 = pair_gap2(gs, gc);
