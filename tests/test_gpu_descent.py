@@ -285,3 +285,29 @@ def test_box_pairs_by_size(n, leaf_max, sigma, cutoff):
     oreq, mmin = _oracle_run(od, 8)
     if mmin >= TIE:
         assert g == oreq
+
+
+@pytest.mark.parametrize("n,leaf_max,sigma", [(3000, 700, 60.0), (2600, 90, 40.0), (2000, 30, 50.0), (1300, 8, 90.0)])
+def test_steps_in_leaves_of_every_size(n, leaf_max, sigma):
+    """Step by step on the oracle's frontier, leaves of up to 700 candidates (one round of 64 and
+    several, lanes that share a leaf's tasks or not): every choice that is not within TIE of a
+    boundary is the oracle's, and every request of a step."""
+    wl = synth.uniform_box(n, extent=(420.0, 400.0, 380.0), sigma=sigma, seed=60 + n)
+    tree, od, w, a = _setup(wl, leaf_max)
+    print(f"descent steps, {n} neurons, leaf_max {leaf_max}", flush=True)
+    S, T = np.array([0]), np.array([0])
+    total, flips, reqs = 0, 0, 0
+    for step in range(60):
+        if S.size == 0:
+            break
+        S2, T2, req = tree.descent_step(w, a, S, T, step, 8, sigma, cutoff_sigmas=0.0)
+        onxt, oreq, dec = od.step(list(zip(S.tolist(), T.tolist())), step, 8)
+        assert sorted(map(tuple, req.tolist())) == sorted(oreq)
+        diff = len(set(_pairs(S2, T2)) ^ set(onxt)) // 2
+        near = sum(1 for _, _, m in dec if m < TIE)
+        assert diff <= near, (step, diff, near, len(dec))
+        total, flips, reqs = total + len(dec), flips + diff, reqs + len(oreq)
+        S = np.array([s for s, _ in onxt], np.int64)
+        T = np.array([t for _, t in onxt], np.int64)
+    assert S.size == 0 and reqs > 0.4 * np.count_nonzero(wl.a > 0) and flips < 0.05 * total
+    print(f"  {total} choices, {flips} near-tie flips, {reqs} requests")
