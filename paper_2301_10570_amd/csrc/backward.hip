@@ -34,7 +34,8 @@ __global__ void k_stage_both(const float *w, const float *gt, const int32_t *per
 
 // P2P with derivatives, NW wavefronts per target leaf.
 template <int NW, bool TWO>
-__global__ void __launch_bounds__(NW * 64, NW > 1 ? 4 : 6) k_p2p_grad(GradLeafSet L, const float *g2, int stride, int want_lap) {
+__global__ void __launch_bounds__(NW * 64, NW > 1 ? 4 : 6)
+k_p2p_grad(GradLeafSet L, const float *g2, int stride, int want_lap) {
     __shared__ GradShared sh[NW];
     __shared__ GradBlock own;
     GradBlock &bk = NW > 1 ? own : *reinterpret_cast<GradBlock *>(sh[0].src);

@@ -923,7 +923,7 @@ __global__ void __launch_bounds__(256) k_desc_choose(const int64_t *nunit, const
                 sv[wave][lane] = x;
                 wave_sync();
                 if (lane < nc)
-    #pragma unroll 2
+#pragma unroll 2
                     for (int q = 0; q < G; ++q) v += sv[wave][q * nc + lane];
             } else if (lane < m) {
                 v = unit_value(U, k0 + lane, 0, 1, du, ta, crng);
@@ -1548,7 +1548,10 @@ int scan_cols(const int64_t *count, int64_t stride, int64_t *data, int64_t *bsum
     return MSP_OK;
 }
 
-inline int64_t scan_blocks(int64_t stride) { return (stride + kScanBlock - 1) / kScanBlock > 0 ? (stride + kScanBlock - 1) / kScanBlock : 1; }
+inline int64_t scan_blocks(int64_t stride) {
+    const int64_t nb = (stride + kScanBlock - 1) / kScanBlock;
+    return nb > 0 ? nb : 1;
+}
 
 template <class T>
 int to_host(std::vector<T> &v, const void *dev, int64_t count) {
@@ -1569,8 +1572,8 @@ struct Descent {
 
 // Staged weights and node moments, a in key order with its prefix counts, the
 // inverse permutation, and the box table with every box pair's attraction.
-// Synchronises `s` (the numbers of axons and boxes, of pairs).  No box pairs (box_level -1) when p is beyond kBoxPMax, when the root
-// is a leaf, or, without a cutoff, when the axon boxes times the dendrite boxes
+// Synchronises `s` (the numbers of axons and boxes, of pairs).  No box pairs (box_level
+// -1) when p is beyond kBoxPMax, when the root is a leaf, or, without a cutoff, when the axon boxes times the dendrite boxes
 // exceed kBoxPairsNoCutoff.
 int desc_setup(Descent &D, msp_tree *t, const float *w, const float *a, const msp_fgt_params *prm, hipStream_t s) {
     D.t = t;

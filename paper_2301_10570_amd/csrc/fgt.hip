@@ -368,112 +368,114 @@ __global__ void __launch_bounds__(kBlock) k_p2m_mfma8(const uint64_t *keys, int6
     // one cell per block, or every gridDim.x-th one in grids of mostly empty cells (32,768
     // cells, 8% with points: 238 us with a search in every block, 52 us)
     for (int64_t g = blockIdx.x; g < (int64_t)Gx * Gy * Gz; g += gridDim.x) {
-    const int kx = (int)(g % Gx), ky = (int)((g / Gx) % Gy), kz = (int)(g / ((int64_t)Gx * Gy));
-    int64_t start, end;
-    cell_points(cells, g, keys, n, level, kx, ky, kz, start, end);
-    if (start == end) {   // no points: zeros, 16 bytes a thread
-        const int e = threadIdx.x;
-        if (e < 128)
-            *reinterpret_cast<float4 *>(A + (((int64_t)kz * 8 + (e >> 4)) * Gy * 8 + (int64_t)ky * 8 + ((e >> 1) & 7)) *
-                                                Gx * 8 + (int64_t)kx * 8 + 4 * (e & 1)) = make_float4(0.f, 0.f, 0.f, 0.f);
-        continue;
-    }
-    const double cx = lox + (kx + 0.5) * cell, cy = loy + (ky + 0.5) * cell, cz = loz + (kz + 0.5) * cell;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    // the next chunk's point and weight as they lie in memory, and with w the indices of
-    // the chunk after it: nothing waits for them before they are used a chunk later (points
-    // past the cell: its last one, with weight 0)
-    float4 nxt;
-    float nw = 0.f;
-    int32_t pj = 0;
-    auto clip = [&](int64_t j) { return j < end ? j : end - 1; };
-    auto fetch = [&](int64_t c0) {
-        const int64_t j = clip(c0 + tid);
-        nxt = ps[j];
-        if (w) {   // NULL: the weights are staged in the records
-            nw = w[pj];
-            pj = perm[clip(j + kBlock)];
+        const int kx = (int)(g % Gx), ky = (int)((g / Gx) % Gy), kz = (int)(g / ((int64_t)Gx * Gy));
+        int64_t start, end;
+        cell_points(cells, g, keys, n, level, kx, ky, kz, start, end);
+        if (start == end) {   // no points: zeros, 16 bytes a thread
+            const int e = threadIdx.x;
+            if (e < 128)
+                *reinterpret_cast<float4 *>(
+                    A + (((int64_t)kz * 8 + (e >> 4)) * Gy * 8 + (int64_t)ky * 8 + ((e >> 1) & 7)) * Gx * 8 +
+                    (int64_t)kx * 8 + 4 * (e & 1)) = make_float4(0.f, 0.f, 0.f, 0.f);
+            continue;
         }
-    };
-    if (w) pj = perm[clip(start + tid)];
-    // this lane's operand slots: row m = (ax, ay_lo), column n = (ay_hi within the tile, az)
-    const int m = lane & 15, kq = lane >> 4;
-    const int ax = m >> 1, aylo = m & 1;
-    const int n16 = lane & 15, azc = n16 & 7, ayh0 = n16 >> 3;
-    f32x4 acc0 = f32x4{0.f, 0.f, 0.f, 0.f}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-    fetch(start);
-    // each wavefront stages and reads only its own 64 rows (thread tid writes row
-    // tid, wavefront w reads rows 64 w .. 64 w + 63), so the waves synchronise
-    // only with themselves
-    for (int64_t c0 = start; c0 < end; c0 += kBlock) {
-        wave_sync();
-        {
-            const bool in = c0 + tid < end;
-            const float wv = w ? nw : nxt.w;
-            // the weight in key order, for later calls (whole records: full-line writes)
-            if (stage && in) stage[c0 + tid] = make_float4(nxt.x, nxt.y, nxt.z, wv);
-            const float X = (nxt.x - (float)cx) * (float)inv_sigma, Y = (nxt.y - (float)cy) * (float)inv_sigma,
-                        Z = (nxt.z - (float)cz) * (float)inv_sigma;
-            float *r = pw + tid * kPowStr;
-            float xp = 1.f, yp = 1.f, wz = in ? wv : 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                r[k] = xp;
-                r[8 + k] = yp;
-                r[16 + k] = wz;
-                xp *= X;
-                yp *= Y;
-                wz *= Z;
+        const double cx = lox + (kx + 0.5) * cell, cy = loy + (ky + 0.5) * cell, cz = loz + (kz + 0.5) * cell;
+        const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+        // the next chunk's point and weight as they lie in memory, and with w the indices of
+        // the chunk after it: nothing waits for them before they are used a chunk later (points
+        // past the cell: its last one, with weight 0)
+        float4 nxt;
+        float nw = 0.f;
+        int32_t pj = 0;
+        auto clip = [&](int64_t j) { return j < end ? j : end - 1; };
+        auto fetch = [&](int64_t c0) {
+            const int64_t j = clip(c0 + tid);
+            nxt = ps[j];
+            if (w) {   // NULL: the weights are staged in the records
+                nw = w[pj];
+                pj = perm[clip(j + kBlock)];
             }
-        }
-        wave_sync();
-        if (c0 + kBlock < end) fetch(c0 + kBlock);
-        const int cnt = end - c0 < kBlock ? (int)(end - c0) : kBlock;
-        const int w0 = __builtin_amdgcn_readfirstlane(wid) * 64;
-        if (w0 < cnt) {
-            // rows past the cell weigh 0, so the steps go in groups of eight (a
-            // wave-uniform count): all operands of a group are read from LDS
-            // before its products
-            const int steps = ((cnt - w0 < 64 ? cnt - w0 : 64) + 3) / 4;
-            for (int s0 = 0; s0 < steps; s0 += 8) {
-                float av[8], b0v[8], b1v[8];
+        };
+        if (w) pj = perm[clip(start + tid)];
+        // this lane's operand slots: row m = (ax, ay_lo), column n = (ay_hi within the tile, az)
+        const int m = lane & 15, kq = lane >> 4;
+        const int ax = m >> 1, aylo = m & 1;
+        const int n16 = lane & 15, azc = n16 & 7, ayh0 = n16 >> 3;
+        f32x4 acc0 = f32x4{0.f, 0.f, 0.f, 0.f}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+        fetch(start);
+        // each wavefront stages and reads only its own 64 rows (thread tid writes row
+        // tid, wavefront w reads rows 64 w .. 64 w + 63), so the waves synchronise
+        // only with themselves
+        for (int64_t c0 = start; c0 < end; c0 += kBlock) {
+            wave_sync();
+            {
+                const bool in = c0 + tid < end;
+                const float wv = w ? nw : nxt.w;
+                // the weight in key order, for later calls (whole records: full-line writes)
+                if (stage && in) stage[c0 + tid] = make_float4(nxt.x, nxt.y, nxt.z, wv);
+                const float X = (nxt.x - (float)cx) * (float)inv_sigma, Y = (nxt.y - (float)cy) * (float)inv_sigma,
+                            Z = (nxt.z - (float)cz) * (float)inv_sigma;
+                float *r = pw + tid * kPowStr;
+                float xp = 1.f, yp = 1.f, wz = in ? wv : 0.f;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const float *r = pw + (w0 + 4 * (s0 + u) + kq) * kPowStr;
-                    av[u] = r[ax] * r[8 + aylo];
-                    b0v[u] = r[8 + 2 * ayh0] * r[16 + azc];
-                    b1v[u] = r[8 + 2 * (ayh0 + 2)] * r[16 + azc];
-                }
-                __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the products
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], b0v[u], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], b1v[u], acc1, 0, 0, 0);
+                for (int k = 0; k < 8; ++k) {
+                    r[k] = xp;
+                    r[8 + k] = yp;
+                    r[16 + k] = wz;
+                    xp *= X;
+                    yp *= Y;
+                    wz *= Z;
                 }
             }
+            wave_sync();
+            if (c0 + kBlock < end) fetch(c0 + kBlock);
+            const int cnt = end - c0 < kBlock ? (int)(end - c0) : kBlock;
+            const int w0 = __builtin_amdgcn_readfirstlane(wid) * 64;
+            if (w0 < cnt) {
+                // rows past the cell weigh 0, so the steps go in groups of eight (a
+                // wave-uniform count): all operands of a group are read from LDS
+                // before its products
+                const int steps = ((cnt - w0 < 64 ? cnt - w0 : 64) + 3) / 4;
+                for (int s0 = 0; s0 < steps; s0 += 8) {
+                    float av[8], b0v[8], b1v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const float *r = pw + (w0 + 4 * (s0 + u) + kq) * kPowStr;
+                        av[u] = r[ax] * r[8 + aylo];
+                        b0v[u] = r[8 + 2 * ayh0] * r[16 + azc];
+                        b1v[u] = r[8 + 2 * (ayh0 + 2)] * r[16 + azc];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the products
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], b0v[u], acc0, 0, 0, 0);
+                        acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], b1v[u], acc1, 0, 0, 0);
+                    }
+                }
+            }
         }
-    }
-    // D[4 kq + i][n16] of both tiles -> red[wave][(az * 8 + ay) * 8 + ax]
-    __syncthreads();
+        // D[4 kq + i][n16] of both tiles -> red[wave][(az * 8 + ay) * 8 + ax]
+        __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int mm = 4 * kq + i, axo = mm >> 1, aylo_o = mm & 1;
-        red[wid][(azc * 8 + 2 * ayh0 + aylo_o) * 8 + axo] = acc0[i];
-        red[wid][(azc * 8 + 2 * (ayh0 + 2) + aylo_o) * 8 + axo] = acc1[i];
-    }
-    __syncthreads();
-    const int64_t Rx = (int64_t)Gx * 8, Ry = (int64_t)Gy * 8;
-    for (int e = tid; e < 512; e += kBlock) {
-        float sum = 0.f;
+        for (int i = 0; i < 4; ++i) {
+            const int mm = 4 * kq + i, axo = mm >> 1, aylo_o = mm & 1;
+            red[wid][(azc * 8 + 2 * ayh0 + aylo_o) * 8 + axo] = acc0[i];
+            red[wid][(azc * 8 + 2 * (ayh0 + 2) + aylo_o) * 8 + axo] = acc1[i];
+        }
+        __syncthreads();
+        const int64_t Rx = (int64_t)Gx * 8, Ry = (int64_t)Gy * 8;
+        for (int e = tid; e < 512; e += kBlock) {
+            float sum = 0.f;
 #pragma unroll
-        for (int q = 0; q < kBlock / 64; ++q) sum += red[q][e];
-        const int ex = e & 7, ey = (e >> 3) & 7, ez = e >> 6;
-        float f = 1.f;
-        for (int k = 2; k <= ex; ++k) f *= (float)k;
-        for (int k = 2; k <= ey; ++k) f *= (float)k;
-        for (int k = 2; k <= ez; ++k) f *= (float)k;
-        A[(((int64_t)kz * 8 + ez) * Ry + (int64_t)ky * 8 + ey) * Rx + (int64_t)kx * 8 + ex] = sum / f;
-    }    __syncthreads();   // red and pw may be written again
+            for (int q = 0; q < kBlock / 64; ++q) sum += red[q][e];
+            const int ex = e & 7, ey = (e >> 3) & 7, ez = e >> 6;
+            float f = 1.f;
+            for (int k = 2; k <= ex; ++k) f *= (float)k;
+            for (int k = 2; k <= ey; ++k) f *= (float)k;
+            for (int k = 2; k <= ez; ++k) f *= (float)k;
+            A[(((int64_t)kz * 8 + ez) * Ry + (int64_t)ky * 8 + ey) * Rx + (int64_t)kx * 8 + ex] = sum / f;
+        }
+        __syncthreads();   // red and pw may be written again
     }
 }
 
@@ -1506,8 +1508,8 @@ template <bool DENSE, bool SHORT>
 __global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int64_t n, const float4 *ps,
                                                       const int32_t *perm, const CellTable cells, int level,
                                                       int Gx, int Gy, int Gz, double lox, double loy, double loz,
-                                                      double cell, double inv_sigma, const float *C, int short_run, int chunks,
-                                                      float *u_out) {
+                                                      double cell, double inv_sigma, const float *C, int short_run,
+                                                      int chunks, float *u_out) {
     const int run = SHORT ? short_run : 64;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n16 = lane & 15, kq = lane >> 4, sh = 3 * (kDepth - level);
@@ -2073,7 +2075,8 @@ int launch_p2m_l2p(msp_tree *t, const FgtPlan &pl, double inv_sigma, bool l2p, c
     if (!l2p && P == 8) {
         hipLaunchKernelGGL(k_p2m_mfma8, dim3((unsigned)(ga.sparse && ncell > 8192 ? 8192 : ncell)), dim3(kBlock), 0, s,
                            t->keys.as<uint64_t>(), t->n,
-                           t->ps.as<float4>(), t->perm.as<int32_t>(), ga.w_gather, ga.cells, pl.level, pl.G[0], pl.G[1], pl.G[2],
+                           t->ps.as<float4>(), t->perm.as<int32_t>(), ga.w_gather, ga.cells, pl.level, pl.G[0],
+                           pl.G[1], pl.G[2],
                            t->geo.lo[0], t->geo.lo[1], t->geo.lo[2], pl.cell, inv_sigma, A,
                            ga.stage ? t->ps.as<float4>() : nullptr);
     } else if (!l2p) {
@@ -3054,7 +3057,8 @@ int64_t fgt_pop_tiles(const FgtPop &f, int p, int pass, bool gemm) {
 size_t fgt_pop_gemm_lds(const FgtPop &f, int p, bool split) {
     size_t m = 0;
     for (int k = 0; k < 3; ++k) {
-        const size_t l = split ? m2l_gemm_lds_split(f.G[k], 32, f.band[k]) : m2l_gemm_lds(f.G[k] * p, f.G[k], p, 32, f.band[k]);
+        const size_t l = split ? m2l_gemm_lds_split(f.G[k], 32, f.band[k])
+                               : m2l_gemm_lds(f.G[k] * p, f.G[k], p, 32, f.band[k]);
         m = l > m ? l : m;
     }
     return m;
@@ -3218,25 +3222,23 @@ static int translate(msp_tree *t, int p, const int (&G)[3], double step, uint32_
             // rows per block: enough blocks to fill the chip, at most 64, and fewer
             // when the tile would not fit in LDS
             int RT = 64;
-            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds_split(ps.G, RT, band[k]) > 64 * 1024))
+            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds_split(ps.G, RT, band[k]) > kTileLds))
                 RT >>= 1;
             const size_t lds = m2l_gemm_lds_split(ps.G, RT, band[k]);
             // p < 8 in forward sums: the tile's sums run in another order than those of the
             // 32 x 32 tiles, whose bits the gradients keep.  (1,792 cells at p = 6: 378
             // wavefronts that rebuilt their operands per K step took 73 us for the three
             // passes, 17 us here.)
-            if ((p == 8 || (p < 8 && forward)) && lds <= 64 * 1024) {
+            if ((p == 8 || (p < 8 && forward)) && lds <= kTileLds) {
                 // column groups as in the float32 passes below
                 const int64_t rows = (ps.R + RT - 1) / RT;
                 const int ngroup = ((8 * ps.G + 15) / 16 + 3) / 4;
                 const int64_t want = (1024 + rows - 1) / rows;
                 const dim3 grid((unsigned)rows, (unsigned)(want < ngroup ? want : ngroup));
-                if (RT == 64)
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k]);
-                else if (RT == 32)
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k]);
-                else
-                    hipLaunchKernelGGL(k_m2l_gemm_bf16x3<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k]);
+                hipLaunchKernelGGL(RT == 64   ? k_m2l_gemm_bf16x3<64>
+                                   : RT == 32 ? k_m2l_gemm_bf16x3<32>
+                                              : k_m2l_gemm_bf16x3<16>,
+                                   grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k]);
             } else {
                 dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
                 hipLaunchKernelGGL(k_m2l_pass_bf16x3, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);
@@ -3252,7 +3254,7 @@ static int translate(msp_tree *t, int p, const int (&G)[3], double step, uint32_
             // rows per block: enough blocks to fill the chip, at most 64, and fewer
             // when the tile would not fit in LDS
             int RT = 64;
-            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds(Ut, ps.G, p, RT, band[k]) > 64 * 1024))
+            while (RT > 16 && ((ps.R + RT - 1) / RT < 1024 || m2l_gemm_lds(Ut, ps.G, p, RT, band[k]) > kTileLds))
                 RT >>= 1;
             size_t lds = m2l_gemm_lds(Ut, ps.G, p, RT, band[k]);
             const bool packed = p == 8 && lds > kTileLds;
@@ -3269,12 +3271,9 @@ static int translate(msp_tree *t, int p, const int (&G)[3], double step, uint32_
                 if (packed)   // (RT = 16)
                     hipLaunchKernelGGL(k_m2l_gemm_packed, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, ps.G, ps.T,
                                        band[k], pm);
-                else if (RT == 64)
-                    hipLaunchKernelGGL(k_m2l_gemm<64>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
-                else if (RT == 32)
-                    hipLaunchKernelGGL(k_m2l_gemm<32>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
                 else
-                    hipLaunchKernelGGL(k_m2l_gemm<16>, grid, dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
+                    hipLaunchKernelGGL(RT == 64 ? k_m2l_gemm<64> : RT == 32 ? k_m2l_gemm<32> : k_m2l_gemm<16>, grid,
+                                       dim3(256), lds, s, ps.in, ps.out, ps.R, p, ps.G, ps.T, band[k], pm, pad);
             } else {
                 dim3 grid((unsigned)((ps.R + MT - 1) / MT), (unsigned)((ps.U + MT - 1) / MT));
                 hipLaunchKernelGGL(k_m2l_pass_mfma, grid, dim3(64), 0, s, ps.in, ps.out, ps.R, p, ps.G, ps.T);

@@ -2,12 +2,13 @@
 // single-tree direct route and the batched kernel.
 //
 // NW wavefronts share one target leaf (sh is private to each wave).  The list is cut
-// into windows of at most 64 entries, about sixteen of them (p2p_window), which go round
-// the waves; the source points of a window form one sequence, staged in LDS in chunks of
-// 128.  At most 32 terms are added one after another in float32, and in the matrix form
-// sixteen such sums in pairs; the rest is float64, so the result does not depend on how many
-// waves share the leaf (the order of the float64 additions moves it by 2^-53).  exp(-d^2/sigma^2) is evaluated as exp2(-d^2) of coordinates from the
-// leaf centre scaled by k_scale = sqrt(log2(e)) / sigma.
+// into windows of at most 64 entries (p2p_window), which go round the waves; the source
+// points of a window form one sequence, staged in LDS in chunks of 128.  At most 32 terms
+// are added one after another in float32, and in the matrix form sixteen such sums in
+// pairs; the rest is float64, so the result does not depend on how many waves share the
+// leaf (the order of the float64 additions moves it by 2^-53).  exp(-d^2/sigma^2) is
+// evaluated as exp2(-d^2) of coordinates from the leaf centre scaled by k_scale =
+// sqrt(log2(e)) / sigma.
 //
 // Two forms, by the size of the leaf against sigma (see kMatrixReach):
 //   p2p_block_matrix   exp2(-d^2) = exp2(-t^2) exp2(2 t.s - s^2): the exponents 2 t.s - s^2 of

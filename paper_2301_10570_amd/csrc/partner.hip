@@ -1843,7 +1843,8 @@ int launch_direct(msp_tree *t, const QuerySet &q, hipStream_t s) {
         // as there are neurons with axons, most steps use few), the wavefronts go round
         const bool many = q.nq > 65536;
         const unsigned blocks = grid_for(many ? 65536 : q.nq, 4);
-        hipLaunchKernelGGL(many ? k_partner_wave<true> : k_partner_wave<false>, dim3(blocks), dim3(256), 0, s, q.nq, q.nq_dev, q.target_idx,
+        hipLaunchKernelGGL(many ? k_partner_wave<true> : k_partner_wave<false>, dim3(blocks), dim3(256), 0, s, q.nq,
+                           q.nq_dev, q.target_idx,
                            q.node_id, q.uniforms, t->n, t->n_nodes, q.qpos, t->nlevel.as<int32_t>(),
                            t->nfirst.as<int32_t>(), t->ncount.as<int32_t>(), t->nfchild.as<int32_t>(),
                            t->nnchild.as<int32_t>(), t->nix.as<int32_t>(), t->niy.as<int32_t>(),
