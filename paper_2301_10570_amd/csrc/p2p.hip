@@ -330,14 +330,18 @@ int direct_all_pairs(const float *tx, const float *ty, const float *tz, int64_t 
                      float *u, hipStream_t s) {
     if (nt == 0) return MSP_OK;
     const float neg_c = (float)(-1.4426950408889634 / ((double)sigma * sigma));
-    // targets per block: 64 once they make four blocks per compute unit, fewer below
-    // (down to 2: 200 targets are then still 100 blocks), so that few targets against
-    // many sources spread over the chip
+    // Targets per block.  More of them share a source read from LDS, fewer spread few targets
+    // over the chip.  Against 262,144 sources, us with 2, 8, 32, 64 targets per block:
+    // 1,024 targets 142, 157, 587, 1,143; 2,048 266, 164, 585, 1,149; 8,192 1,013, 572, 594,
+    // 1,142; 12,288 1,508, 844, 1,033, 1,162; 16,384 2,000, 1,114, 1,041, 1,164; 32,768 3,983,
+    // 2,203, 1,940, 2,007; 65,536 7,886, 4,365, 3,714, 3,683.  The lines lie where the next
+    // size has made one round of two blocks per compute unit (32: 16,384) or wins (8 and
+    // 64); the same against 20,000 sources.
 #define MSP_DIRECT(T) hipLaunchKernelGGL(k_direct<T>, dim3(grid_for(nt, T)), dim3(kDirWaves * 64), 0, s, tx, ty, \
                                          tz, nt, sx, sy, sz, w, ns, neg_c, u)
     if (nt >= 64 * 1024) MSP_DIRECT(64);
     else if (nt >= 32 * 512) MSP_DIRECT(32);
-    else if (nt >= 8 * 512) MSP_DIRECT(8);
+    else if (nt >= 1280) MSP_DIRECT(8);
     else MSP_DIRECT(2);
 #undef MSP_DIRECT
     MSP_CHECK_LAUNCH();

@@ -264,3 +264,15 @@ def test_one_wavefront_per_leaf(sigma, exclude):
     np.testing.assert_array_equal(ub, u)
     b.close()
     tree.close()
+
+
+@pytest.mark.parametrize("nt,ns", [(1279, 300), (1280, 300), (1281, 4097)])
+def test_all_pairs_where_eight_targets_share_a_block(nt, ns):
+    import paper_2301_10570_amd as msp
+    print(f"all-pairs sum {nt} x {ns}", flush=True)
+    rng = np.random.default_rng(nt + ns)
+    t = rng.random((nt, 3)).astype(np.float32) * 300
+    s = rng.random((ns, 3)).astype(np.float32) * 300
+    w = rng.random(ns).astype(np.float32) + 0.1
+    u = msp.direct_sum(*(_T(t[:, k]) for k in range(3)), *(_T(s[:, k]) for k in range(3)), _T(w), 80.0).cpu().numpy()
+    assert rel_err(u, oracle.gauss_sum(t, s, w, 80.0)).max() <= 1e-5
