@@ -1499,7 +1499,10 @@ __global__ void __launch_bounds__(kBlock) k_l2p_cells(const uint64_t *keys, int6
 // 4 (t / 2), ay = m % 4 + 4 (t % 2); held in eight registers per lane, no LDS) and the
 // powers of X as operand B leaves lane l = 16 kq + n of a group with the sums over ax of
 // point n for az = kq and kq + 4 and every ay: two Horner chains in Y, and the four kq
-// added across the lanes.  DENSE: cells' ends from the table (or a search) and one key a
+// added across the lanes.  The products run from the highest power
+// down and the coefficient of 1 is added to the finished sum: root mean square rounding of a
+// sum 2.8e-8, by Horner in multiply-adds 4.6e-8 (rising powers, the coefficient among them,
+// 8.1e-8).  DENSE: cells' ends from the table (or a search) and one key a
 // cell, otherwise from the lanes' own keys.  Horner in the vector unit (k_l2p), then here:
 // 262,144 points in 2,600 cells 35 us, 19 us; 2,097,152 points in 512 cells 58 us, 44 us;
 // 4,194,304 points in 1,024 cells 87 us, 73 us, where the sums' scattered 4-byte stores bound
@@ -1532,7 +1535,7 @@ __global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int6
     if (i0 < iend) fetch(i0);
     const float is = (float)inv_sigma;
     float a[8];
-    float cx = 0.f, cy = 0.f, cz = 0.f;
+    float cx = 0.f, cy = 0.f, cz = 0.f, c000 = 0.f;
     uint64_t staged = ~0ull;   // the cell whose coefficients a holds
     int64_t cend = -1;         // DENSE: its end
     for (; i0 < iend; i0 += run) {
@@ -1560,9 +1563,12 @@ __global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int6
                 for (int t = 0; t < 4; ++t) {
                     const int az = (n16 >> 2) + 4 * (t >> 1), ay = (n16 & 3) + 4 * (t & 1);
                     const float *row = C + (((int64_t)kz * 8 + az) * Ry + (int64_t)ky * 8 + ay) * Rx + (int64_t)kx * 8;
-                    a[2 * t] = row[kq];
-                    a[2 * t + 1] = row[kq + 4];
+                    a[2 * t] = row[7 - kq];
+                    a[2 * t + 1] = row[3 - kq];
                 }
+                // the coefficient of 1 is added last: the other sums' rounding is that of the rest
+                c000 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a[1]), 48));
+                if (lane == 48) a[1] = 0.f;
                 cx = (float)(lox + (kx + 0.5) * cell);
                 cy = (float)(loy + (ky + 0.5) * cell);
                 cz = (float)(loz + (kz + 0.5) * cell);
@@ -1586,12 +1592,12 @@ __global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int6
                 if (g < g0 || g > g1) continue;
                 const float X = (q[g].x - cx) * is, Y = (q[g].y - cy) * is, Z = (q[g].z - cz) * is;
                 const float X2 = X * X, Z2 = Z * Z, Z4 = Z2 * Z2;
-                const float b0 = (kq & 1 ? X : 1.f) * (kq & 2 ? X2 : 1.f), b1 = b0 * (X2 * X2);
+                const float b0 = (kq & 1 ? 1.f : X) * (kq & 2 ? 1.f : X2), b1 = b0 * (X2 * X2);
                 f32x4 d[4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * t], b0, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * t + 1], b1, d[t], 0, 0, 0);
+                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * t], b1, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2 * t + 1], b0, d[t], 0, 0, 0);
                 }
                 float lo = d[1][3], hi = d[3][3];
 #pragma unroll
@@ -1607,7 +1613,7 @@ __global__ void __launch_bounds__(kBlock) k_l2p_mfma8(const uint64_t *keys, int6
             const float r0 = (h2 ? v[2] : v[0]) + __shfl_xor(h2 ? v[0] : v[2], 32, 64);
             const float r1 = (h2 ? v[3] : v[1]) + __shfl_xor(h2 ? v[1] : v[3], 32, 64);
             const float r = (h1 ? r1 : r0) + __shfl_xor(h1 ? r0 : r1, 16, 64);
-            if (i0 + lane >= s0 && i0 + lane < e) u = r;
+            if (i0 + lane >= s0 && i0 + lane < e) u = c000 + r;
             s0 = e;
         }
         if (i0 + lane < i1) u_out[jo] = u;

@@ -341,3 +341,43 @@ def test_l2p_run_lengths(n, p):
     ref = oracle.attraction(wl, pick)
     assert rel_err(u[pick], ref).max() <= 1e-4
     tree.close()
+
+
+@pytest.mark.parametrize("n,sigma", [(30011, 150.0), (1048576 + 77, 110.0)])
+def test_l2p_rounds_no_more_than_horner(n, sigma):
+    """The series at p = 8 from the Taylor grid itself, against float64 at the same float32 local
+    coordinates: the root mean square rounding of the sums is at most that of a Horner evaluation
+    in float32 multiply-adds (a float64 step rounded to float32)."""
+    import paper_2301_10570_amd as msp
+    wl = synth.uniform_box(n, extent=(1500.0, 900.0, 400.0), sigma=sigma, seed=940)
+    wl.w[:] = np.maximum(wl.w, 1)
+    d = to_dev(wl)
+    tree = msp.build_tree(d["x"], d["y"], d["z"])
+    kw = dict(sigma=wl.sigma, p=8, route="fgt")
+    plan, info = tree.plan(**kw), tree.info()
+    G, cell = plan["grid"], info["side"] / 2.0 ** plan["level"]
+    u = tree.forward(d["w"], None, **kw).cpu().numpy()
+    C = tree.debug_buffer(1).cpu().numpy().reshape(G[2], 8, G[1], 8, G[0], 8)
+    pick = np.random.default_rng(n).permutation(n)[:20000]
+    pos = np.stack([wl.x, wl.y, wl.z], 1)[pick]
+    k = np.minimum(((pos.astype(np.float64) - info["lo"]) / cell).astype(int), np.array(G) - 1)
+    c32 = (np.array(info["lo"]) + (k + 0.5) * cell).astype(np.float32)
+    t = (pos - c32) * np.float32(1.0 / wl.sigma)
+    keep = np.abs(t).max(1) < 0.4999 * cell / wl.sigma       # (the key decides on a cell's faces)
+    t, k, got = t[keep].astype(np.float64), k[keep], u[pick][keep]
+    co = C[k[:, 2], :, k[:, 1], :, k[:, 0], :].astype(np.float64)      # [point][az][ay][ax]
+    powers = [t[:, a, None] ** np.arange(8) for a in range(3)]
+    exact = np.matmul(np.matmul(np.matmul(co, powers[0][:, None, :, None])[..., 0], powers[1][:, :, None])[..., 0][:, None, :],
+                      powers[2][:, :, None])[:, 0, 0]
+    f32 = lambda a: a.astype(np.float32).astype(np.float64)
+    h = co
+    for a in range(3):                                       # x, then y, then z
+        x = t[:, a].reshape((-1,) + (1,) * (h.ndim - 2))
+        acc = h[..., 7]
+        for q in range(6, -1, -1):
+            acc = f32(acc * x + h[..., q])
+        h = acc
+    rms = [float(np.sqrt(np.mean(((v - exact) / exact) ** 2))) for v in (got.astype(np.float64), h)]
+    print(f"l2p rounding n={n} rho {plan['rho']:.2f}: kernel {rms[0]:.2e}, Horner {rms[1]:.2e}", flush=True)
+    assert rms[0] <= rms[1]
+    tree.close()
