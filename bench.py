@@ -305,7 +305,7 @@ def _batch_bench(args, dev, oracle_threads):
     """256 independent populations (sizes log-uniform in [1024, 65536], sigma
     log-uniform in [50, 300] um, each in its own 1 mm cube): autotuned leaf size
     and route per population, the forward as one captured hipGraph (all
-    direct-route populations in one persistent launch), per-population latency
+    direct-route populations in one launch), per-population latency
     from device timestamps, forward + backward, and accuracy on sampled targets."""
     import numpy as np
     import torch

@@ -239,7 +239,9 @@ int msp_fgt_plan(msp_tree *t, const msp_fgt_params *prm, msp_fgt_info *info);
  * the expansion level by M2M and L2L shifts (msp_fgt_info.fine_terms).  Direct route: Eq. (8) summed over all
  * source leaves within the cutoff of each target leaf.  The direct route
  * synchronises `stream` once when its interaction lists are (re)built, in trees of
- * more than 2,048 nodes. */
+ * more than 2,048 nodes.  Under stream capture it cannot: such a call is refused
+ * with MSP_EHIP unless the lengths of its lists are known, from an earlier call
+ * with this sigma and cutoff or from msp_fgt_forward_query. */
 int msp_fgt_forward(msp_tree *t, const float *w, const uint8_t *is_target,
                     const msp_fgt_params *prm, float *u_out, void *stream);
 

@@ -25,8 +25,10 @@ import sys
 
 
 def short_name(name: str) -> str:
-    m = re.search(r"(k_[A-Za-z0-9_]+(<\d+>)?|__amd_rocclr_\w+|\w*elementwise_kernel\w*)", name)
-    return m.group(1) if m else name[:48]
+    m = re.search(r"(k_[A-Za-z0-9_]+(<[\w ,:()]*>)?|__amd_rocclr_\w+|\w*elementwise_kernel\w*)", name)
+    if not m:
+        return name[:48]
+    return m.group(1).replace("msp::(anonymous namespace)::", "")
 
 
 def stats(path: str, command: str) -> str:
@@ -160,7 +162,7 @@ def main():
     c = sub.add_parser("util")
     c.add_argument("csv")
     c.add_argument("--command", required=True)
-    c.add_argument("--kernels", required=True, help="comma-separated short kernel names")
+    c.add_argument("--kernels", required=True, help="comma-separated kernel names without template arguments")
     args = ap.parse_args()
     if args.what == "util":
         sys.stdout.write(util(args.csv, args.command, args.kernels.split(",")))
