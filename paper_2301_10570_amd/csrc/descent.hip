@@ -606,8 +606,8 @@ __device__ inline int stage_axons(const BoxArgs &g, int32_t fs, int32_t ns, int3
 // added by a segmented scan.  A window holds 64 pairs, 16 when s has many axons (its
 // windows are the longest to run).  With one block per pair, most of the time went to
 // starting 1.4 million wavefronts that each set up two boxes for some hundred terms
-// (64 blobs of 4,096 neurons, 3.2e9 terms: 3.89 ms; 0.70 ms here for 0.8e9 of them and
-// 1.28 ms below for the others).
+// (64 blobs of 4,096 neurons, 3.2e9 terms: 3.89 ms; 0.56 ms here for 0.8e9 of them and
+// 1.09 ms below for the others).
 constexpr int kPairWaves = 4, kAxTile = 512, kPairBlocks = 4;
 __global__ void __launch_bounds__(kPairWaves * 64, 6) k_box_pairs_small(BoxArgs g) {
     __shared__ float4 ax[kAxTile];
